@@ -16,19 +16,27 @@
 //   * the columns after the super-block: one GEMM per super-block, outside this kernel, from the
 //     -E and V this kernel leaves behind in the GEMM's operand format.
 //
-// Who holds what.  The super-block is eight blocks of 128 columns; wave w holds blocks w and w + 4, each as
+// Who holds what.  The super-block is eight blocks of 128 columns and wave w of the workgroup's eight holds block w, as
 // four 32-column pieces of two 32 x 32 MFMA accumulator tiles (rows 0-31 and 32-63) of the TRANSPOSED
 // product  W^T += [U; P]^T [-E | V]^T :  lane l, register v of a tile holds row l % 32 of the tile,
 // column 8 (v / 4) + 4 (l / 32) + v % 4 of the piece.  v_permlane32_swap of the registers of the two
-// tiles turns that into "one row per lane" for the sequential steps.
-// While block b is worked on, the wave that holds it (the owner) runs the column steps of its eight
-// sub-blocks and updates the rest of the block; the other three waves have no sequential work in
-// that time: they apply each sub-block's update to the later blocks they hold, under the owner's next
-// column steps.  One workgroup barrier per sub-block publishes its -E and V.
-// The pieces are kept in a fixed place: the owner moves its pieces down by one when a piece is
-// finished and its second block into the first one's registers when the block is finished, so every
-// register index in the code is static.
+// tiles turns that into "one row per lane" for the sequential steps, and turns -E and V of a sub-block back into
+// MFMA operands without a trip through LDS.
+//
+// A wave's life has three parts.  Updater: its block lies after the one being worked on; it applies every sub-block's
+// update to its four pieces, the left operands fetched into registers one sub-block ahead.  Owner: it runs the column
+// steps of its eight sub-blocks; between two of them it only updates the rest of its own block.  Finished: as one of two helpers it
+// fetches for the owner what that needs next (diagonal pieces of U and P, left operands) and writes the owner's results
+// to memory from LDS.  One workgroup barrier per sub-block publishes its -E and V.
+//
+// What bounds it: the chain of column steps.  A sub-block costs the owner ~16 x 120 clocks of column steps, 16 swaps, the
+// publication of its -E and V and 12 MFMAs per 32 columns of its block that are left; the other waves' MFMAs (at most
+// 96 per SIMD and sub-block) and the loads of their left operands (112 KB per sub-block at first) hide behind that.
+// Measured, 1024 columns of 4096 rows (64 workgroups): 149 us alone, 170-180 beside a far update; with four waves of two
+// blocks each, where the owner also updated its second block, read U and P from LDS in the column steps and stored its
+// results itself, it took 290.
 #include "common.h"
+#include <utility>
 
 namespace gptaq {
 
@@ -91,20 +99,22 @@ __global__ __launch_bounds__(256) void near_operands_kernel(const float* U, cons
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Left operands of a sub-block's update, staged per wave: piece (32 columns) x {U hi, U lo, P hi, P lo} x 1 KB,
-// written by global -> LDS loads one sub-block ahead of their use and read back by the lane that requested them.
-constexpr int kSbPieces = 8;                     // per wave: 2 blocks x 4 pieces
-constexpr int kSbStage = kSbPieces * 4 * 1024;
-static_assert(kSbBlocks == 8, "two blocks per wave, four waves");
+constexpr int kSbWaves = 8;                      // one 128-column block each
+constexpr int kSbDiagLd = 20;                    // padded row of a staged 16 x 16 piece, in floats
+static_assert(kSbBlocks == kSbWaves, "one block per wave");
 struct SbShared {
-  // operands [-E | V]^T of a sub-block's update, in MFMA fragment order: [buffer][term][hi/lo][row half][k chunk][row]
-  u32x4 frag[2][2][2][2][2][32];
-  float Ud[2][kSub][kSub], Pd[2][kSub][kSub];     // diagonal pieces of U and P (fp32), double-buffered
-  float dinv[2][kSub];                            // 1 / U_jj
+  // operands [-E | V]^T of a sub-block's update in MFMA fragment order: [buffer][-E hi, -E lo, V hi, V lo][row half][lane]
+  u32x4 frag[2][4][2][64];
+  // left operands for the owner's own pieces: [buffer][piece][U hi, U lo, P hi, P lo], 1 KB each
+  u32x4 left[3][4][4][64];
+  float x[2][64][kSbDiagLd];                     // W^ of a sub-block, a row per row
+  u32x4 codes[2][64];
+  float Ud[2][kSub][kSbDiagLd], Pd[2][kSub][kSbDiagLd];     // diagonal pieces of U and P, transposed: [column][step]
+  float dinv[2][kSub];                           // 1 / U_jj
 };
 
 // 1 KB per wavefront from global memory straight into LDS: lane l's 16 bytes land at lds + 16 l.
-__device__ __forceinline__ void sb_load_lds(const uint16_t* src, unsigned char* lds) {
+__device__ __forceinline__ void sb_load_lds(const uint16_t* src, void* lds) {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                    (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
 }
@@ -118,75 +128,109 @@ __device__ __forceinline__ void sb_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// Where this wave's pieces are while sub-block x is worked on.
-struct SbGeo {
-  int b, r, half, owner;      // block of the sub-block, finished pieces of that block, first/second half of a piece, owning wave
-  int cur0;                   // block in slot 0 (the wave's first block until it has finished it, then its second)
-  bool two;                   // slot 1 still holds the second block
-  uint32_t active;            // bit 4 s + i: piece i of slot s takes the update of sub-block x
-};
-__device__ __forceinline__ SbGeo sb_geo(int x, int wave, int sbw, int nev, int terms) {
-  SbGeo g;
-  const int eb = x & 7;
-  g.b = x >> 3; g.r = eb >> 1; g.half = eb & 1; g.owner = g.b & 3;
-  g.cur0 = g.b > wave ? wave + 4 : wave;
-  g.two = g.b <= wave;
-  g.active = 0;
-  if (terms != 0 && x + 1 < nev) {
-    // pieces of block B that exist (the super-block may be narrower than 1024 columns)
-    auto pieces_in = [&](int B) { return max(0, min(4, (sbw - 128 * B + 31) >> 5)); };
-    uint32_t m0;
-    if (g.cur0 == g.b) {
-      // the block being worked on: its first g.r pieces are finished and have made room, so piece i is the block's
-      // piece i + g.r; the piece the sub-block lies in takes the update of its second half only
-      const int cnt = pieces_in(g.b) - g.r;
-      m0 = cnt > 0 ? ((1u << cnt) - 1u) & ~(uint32_t)g.half : 0u;
-    } else {
-      m0 = g.cur0 > g.b ? (1u << pieces_in(g.cur0)) - 1u : 0u;
-    }
-    const uint32_t m1 = g.two ? (1u << pieces_in(wave + 4)) - 1u : 0u;     // (wave + 4 > b whenever slot 1 is in use)
-    g.active = m0 | (m1 << 4);
-  }
-  return g;
+// w += (lane C of each group of 16 lanes of s) * e: the 16 entries of a row of U (or P) sit in the 16 lanes of s, so a
+// column step needs neither LDS reads nor a register per entry.  s must not have been written by the two instructions
+// before (the compiler does not look into the asm): see sb_pin.
+template <int C> __device__ __forceinline__ void sb_fmac_lane(float& w, float s, float e) {
+  asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(w) : "v"(s), "v"(e), "n"(C));
 }
-// first super-block column of piece i of slot s
-__device__ __forceinline__ int sb_piece_col(const SbGeo& g, int wave, int s, int i) {
-  const int B = s == 0 ? g.cur0 : wave + 4;
-  return 128 * B + 32 * (B == g.b ? i + g.r : i);
+template <int C> __device__ __forceinline__ float sb_mul_lane(float s, float e) {
+  float r;
+  asm("v_mul_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(s), "v"(e), "n"(C));
+  return r;
+}
+__device__ __forceinline__ void sb_pin(float (&s)[kSub]) {
+  asm volatile("s_nop 1" : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7]),
+               "+v"(s[8]), "+v"(s[9]), "+v"(s[10]), "+v"(s[11]), "+v"(s[12]), "+v"(s[13]), "+v"(s[14]), "+v"(s[15]));
 }
 
+// two fp32 -> bf16 pair (round to nearest even) and what the rounding left over
+__device__ __forceinline__ u32x2 sb_split2(float a, float b) {
+  typedef __attribute__((ext_vector_type(2))) float f32x2;
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+  const uint32_t hi = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+  const float ra = a - __uint_as_float(hi << 16), rb = b - __uint_as_float(hi & 0xffff0000u);
+  return u32x2{hi, __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{ra, rb}), bf16x2))};
+}
+
+// registers 8 HALF .. 8 HALF + 7 of a piece's two tiles -> the 16 columns of the sub-block, one row per lane
 template <int HALF>
-__device__ __forceinline__ void sb_extract(const f32x16 (&acc)[2][4][2], float (&w)[kSub]) {
-  // registers 8 HALF .. 8 HALF + 7 of the current piece's two tiles -> the 16 columns of the sub-block, one row per lane
+__device__ __forceinline__ void sb_extract(const f32x16 (&t)[2], float (&w)[kSub]) {
 #pragma unroll
   for (int vv = 0; vv < 8; ++vv) {
-    const float a0 = acc[0][0][0][8 * HALF + vv];
-    const float a1 = acc[0][0][1][8 * HALF + vv];
-    const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a0), __float_as_uint(a1), false, false);
+    const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(t[0][8 * HALF + vv]), __float_as_uint(t[1][8 * HALF + vv]),
+                                                     false, false);
     const int c = 8 * (vv >> 2) + (vv & 3);
     w[c] = __uint_as_float(r[0]);          // lanes 0-31: tile 0, lanes 32-63: tile 1, columns of lane half 0
     w[c + 4] = __uint_as_float(r[1]);      // the columns lane half 1 held
   }
 }
 
+// t += left operands (U hi, U lo, P hi, P lo of 32 columns) x fragments (-E hi, -E lo, V hi, V lo): three products per term
+__device__ __forceinline__ void sb_piece_update(f32x16 (&t)[2], const u32x4 (&left)[4], const u32x4 (&fr)[4][2], bool useE, bool useP) {
+#pragma unroll
+  for (int tm = 0; tm < 2; ++tm) {
+    if (!(tm ? useP : useE)) continue;
+    const bf16x8 ah = __builtin_bit_cast(bf16x8, left[2 * tm]), al = __builtin_bit_cast(bf16x8, left[2 * tm + 1]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int rh = 0; rh < 2; ++rh)
+        t[rh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q == 2 ? al : ah, __builtin_bit_cast(bf16x8, fr[2 * tm + (q == 1)][rh]), t[rh], 0, 0, 0);
+  }
+}
+
+// The grid of a row whose range is [lo, hi] (the lanes of a row agree), its reciprocal, and its place in the outputs.
+struct SbGrid { float sc, zr, isc; };
+
+// One column step (lines 7-10 of Algorithm 1), one row per lane, and those after it.
+template <int J>
+__device__ __forceinline__ void sb_steps(float (&w)[kSub], const float (&u)[kSub], const float (&p)[kSub], float dreg, const SbGrid& g,
+                                         float dlo, float dhi, float e_prev, float v_prev, u32x4 (&pk)[4][2], u32x4& cw) {
+  if constexpr (J < kSub) {
+    const float v = w[J];
+    // code - zero = clamp(rint(v / scale), -zero, maxq - zero): the same integers as clamp(rint(.) + zero, 0, maxq)
+    // - zero, with a shorter dependency chain in front of the updates (one median instead of add, max, min, sub)
+    const float d = __builtin_amdgcn_fmed3f(rintf(v * g.isc), dlo, dhi);
+    const float x = g.sc * d;
+    const float e1 = sb_mul_lane<J>(dreg, x - v);          // -E_J
+    w[J] = x;
+    cw[J >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(d + g.zr, J & 3, cw[J >> 2]);
+    [&]<int... C>(std::integer_sequence<int, C...>) {
+      (sb_fmac_lane<J + 1 + C>(w[J + 1 + C], p[J], v), ...);
+      (sb_fmac_lane<J + 1 + C>(w[J + 1 + C], u[J], e1), ...);
+    }(std::make_integer_sequence<int, kSub - 1 - J>{});
+    if constexpr (J & 1) {
+      const u32x2 pe = sb_split2(e_prev, e1), pv = sb_split2(v_prev, v);
+      pk[0][J >> 3][(J >> 1) & 3] = pe[0];
+      pk[1][J >> 3][(J >> 1) & 3] = pe[1];
+      pk[2][J >> 3][(J >> 1) & 3] = pv[0];
+      pk[3][J >> 3][(J >> 1) & 3] = pv[1];
+    }
+    sb_steps<J + 1>(w, u, p, dreg, g, dlo, dhi, e1, v, pk, cw);
+  }
+}
+
 // FAST: rows of W and of the codes are 16-byte aligned and n is a multiple of 16 (vector loads and stores).
-template <bool FAST>
-__global__ __launch_bounds__(256) void quant_sb_kernel(SbArgs a) {
+// TERMS: the update terms of Eq. 15 that are applied (3: both; a run-time choice would cost branches around every MFMA group,
+// and with them spills).
+template <bool FAST, int TERMS>
+__global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char sb_smem[];
-  SbShared& sh = *reinterpret_cast<SbShared*>(sb_smem + 4 * kSbStage);
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  unsigned char* const stage = sb_smem + wave * kSbStage;           // this wave's staged left operands
+  SbShared& sh = *reinterpret_cast<SbShared*>(sb_smem);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l32 = lane & 31, lh = lane >> 5;
   const int row0 = blockIdx.x * 64;
   const int sbw = a.sbw;                                  // columns of this super-block
   const int nev = (sbw + kSub - 1) / kSub;
-  const bool useE = a.terms & 1, useP = a.terms & 2;
+  constexpr bool useE = TERMS & 1, useP = TERMS & 2, update = TERMS != 0;
+  const uint32_t lane_off = (uint32_t)(l32 * kSub + 8 * lh);       // this lane's 16 bytes of 32 columns x 16 k of a left operand
+  const int first_own = min(8 * wave, nev), last_own = min(8 * wave + 8, nev);
 
   // ---- W -> accumulators.  Out-of-range elements read a clamped (valid) address and are replaced by 0,
   // so the loads need no branches.  Dead inputs were zeroed in W before this kernel.
-  f32x16 acc[2][4][2];
-#pragma unroll
-  for (int s = 0; s < 2; ++s)
+  f32x16 acc[4][2];
+  if (first_own < last_own) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
 #pragma unroll
@@ -195,305 +239,250 @@ __global__ __launch_bounds__(256) void quant_sb_kernel(SbArgs a) {
         const float* src = a.W + (int64_t)min(row, a.m - 1) * a.ldw + a.sb0;
 #pragma unroll
         for (int vq = 0; vq < 4; ++vq) {
-          const int c = 128 * (wave + 4 * s) + 32 * i + 8 * vq + 4 * lh;    // super-block column of element 0
+          const int c = 128 * wave + 32 * i + 8 * vq + 4 * lh;    // super-block column of element 0
           if (FAST) {
             const bool ok = row < a.m && c < sbw;
             const f32x4 x = *reinterpret_cast<const f32x4*>(src + min(c, sbw - 4));
 #pragma unroll
-            for (int q = 0; q < 4; ++q) acc[s][i][rh][4 * vq + q] = ok ? x[q] : 0.f;
+            for (int q = 0; q < 4; ++q) acc[i][rh][4 * vq + q] = ok ? x[q] : 0.f;
           } else {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
               const float x = src[min(c + q, sbw - 1)];
-              acc[s][i][rh][4 * vq + q] = (row < a.m && c + q < sbw) ? x : 0.f;
+              acc[i][rh][4 * vq + q] = (row < a.m && c + q < sbw) ? x : 0.f;
             }
           }
         }
       }
-      __builtin_amdgcn_sched_barrier(0);                  // (all 64 loads in flight at once would need 256 registers)
     }
-
-  // ---- per-row grid (one row per lane); for grouped grids it is renewed by the owner at every group start
-  float sc = 1.f, zr = 0.f, isc = 1.f;
-  if (a.group <= 0) {
-    const int row = row0 + lane;
-    if (row < a.m) { sc = a.scales[row]; zr = a.zeros[row]; }
-    isc = 1.f / sc;
   }
 
-  // diagonal pieces of sub-block x into buffer x & 1: `which` 0 loads U (and 1 / U_jj), 1 loads P
-  auto load_diag = [&](int x, int which) {
+  // ---- the two helpers of sub-block x: wave (block + 7) % 8 fetches, wave (block + 6) % 8 stores
+  // what the owner of sub-block x needs besides its accumulators: the diagonal pieces of U and P (transposed into
+  // buffer x & 1) and the left operands of the update of its own later columns (buffer x % 3)
+  auto fetch_for_owner = [&](int x) {
+    const int b = x >> 3, eb = x & 7;
+    if (update) {
+      for (int i = (eb + 1) >> 1; i < 4; ++i) {
+        const int64_t o = ((int64_t)x * kSbCols + 128 * b + 32 * i) * kSub;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (q < 2 ? useE : useP) sb_load_lds(a.Nop[q] + o + lane_off, &sh.left[x % 3][i][q][0]);
+      }
+    }
     const int j = lane >> 2, c4 = (lane & 3) * 4;
     const int64_t r = (int64_t)a.sb0 + kSub * x + j;
-    const float* S = which ? a.P : a.U;
-    float v[4];
+    float u[4], p[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int64_t c = (int64_t)a.sb0 + kSub * x + c4 + i;
-      const bool on = which ? useP : (useE || c4 + i == j);            // the diagonal of U is always needed
-      v[i] = (on && r < a.n && c < a.n && c4 + i >= j && (which == 0 || c4 + i > j)) ? S[r * a.ldh + c] : 0.f;
+      const bool in = r < a.n && c < a.n;
+      u[i] = (in && c4 + i >= j && (useE || c4 + i == j)) ? a.U[r * a.ldh + c] : 0.f;   // the diagonal of U is always needed
+      p[i] = (in && c4 + i > j && useP) ? a.P[r * a.ldh + c] : 0.f;
     }
-    float* dst = which ? &sh.Pd[x & 1][j][c4] : &sh.Ud[x & 1][j][c4];
-    *reinterpret_cast<f32x4*>(dst) = f32x4{v[0], v[1], v[2], v[3]};
-    if (which == 0 && (j >> 2) == (lane & 3)) {
-      const float d = v[j & 3];
-      sh.dinv[x & 1][j] = d != 0.f ? 1.f / d : 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      sh.Ud[x & 1][c4 + i][j] = u[i];
+      sh.Pd[x & 1][c4 + i][j] = p[i];
+      if (c4 + i == j) sh.dinv[x & 1][j] = u[i] != 0.f ? 1.f / u[i] : 0.f;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the left operands have landed
+  };
+  // results of sub-block x from LDS to memory: W^, codes, and -E and V for the update of the columns after the super-block
+  auto store_results = [&](int x) {
+    const int buf = x & 1, colg = a.sb0 + kSub * x;
+    if (FAST) {
+#pragma unroll
+      for (int it = 0; it < 4; ++it) {
+        const int item = lane + 64 * it, r = item >> 2, q = item & 3;
+        if (row0 + r < a.m)
+          *reinterpret_cast<f32x4*>(a.W + (int64_t)(row0 + r) * a.ldw + colg + 4 * q) = *reinterpret_cast<const f32x4*>(&sh.x[buf][r][4 * q]);
+      }
+      if (row0 + lane < a.m) *reinterpret_cast<u32x4*>(a.codes + (int64_t)(row0 + lane) * a.n + colg) = sh.codes[buf][lane];
+    } else if (row0 + lane < a.m) {
+      const u32x4 cw = sh.codes[buf][lane];
+#pragma unroll
+      for (int c = 0; c < kSub; ++c)
+        if (colg + c < a.n) {
+          a.W[(int64_t)(row0 + lane) * a.ldw + colg + c] = sh.x[buf][lane][c];
+          a.codes[(int64_t)(row0 + lane) * a.n + colg + c] = (uint8_t)(cw[c >> 2] >> (8 * (c & 3)));
+        }
+    }
+    if (a.Eh) {
+#pragma unroll
+      for (int it = 0; it < 2; ++it) {
+        const int item = lane + 64 * it, r = item >> 1, ch = item & 1;
+        if (row0 + r < a.m) {
+          const int64_t o = (int64_t)(row0 + r) * a.ldev + kSub * x + 8 * ch;
+          *reinterpret_cast<u32x4*>(a.Eh + o) = sh.frag[buf][0][r >> 5][32 * ch + (r & 31)];
+          *reinterpret_cast<u32x4*>(a.El + o) = sh.frag[buf][1][r >> 5][32 * ch + (r & 31)];
+          *reinterpret_cast<u32x4*>(a.Vh + o) = sh.frag[buf][2][r >> 5][32 * ch + (r & 31)];
+          *reinterpret_cast<u32x4*>(a.Vl + o) = sh.frag[buf][3][r >> 5][32 * ch + (r & 31)];
+        }
+      }
     }
   };
-
-  // Requests the left operands of sub-block x's update for this wave's pieces: they depend on U and P only, so
-  // they are fetched a whole sub-block ahead (global -> LDS, no registers) and have the column steps' time to land.
-  auto request_left = [&](int x, const SbGeo& g) {
-    const uint32_t lane_off = (uint32_t)(l32 * kSub + 8 * lh);
-    for (uint32_t rest = g.active; rest; rest &= rest - 1) {
-      const int p = __builtin_ctz(rest);
-      const int64_t o = ((int64_t)x * kSbCols + sb_piece_col(g, wave, p >> 2, p & 3)) * kSub + lane_off;
-      unsigned char* dst = stage + p * 4096;
-      if (useE) {
-        sb_load_lds(a.Nop[0] + o, dst);
-        sb_load_lds(a.Nop[1] + o, dst + 1024);
-      }
-      if (useP) {
-        sb_load_lds(a.Nop[2] + o, dst + 2048);
-        sb_load_lds(a.Nop[3] + o, dst + 3072);
-      }
-    }
+  // a helper's part of the time between barrier x - 1 and barrier x (x == nev: after the last one)
+  auto help = [&](int x) {
+    const int b = min(x, nev - 1) >> 3;
+    if (wave == ((b + 7) & 7) && x + 1 < nev) fetch_for_owner(x + 1);
+    if (wave == ((b + 6) & 7) && x >= 1) store_results(x - 1);
   };
-  SbGeo g_next = sb_geo(0, wave, sbw, nev, a.terms);
-  request_left(0, g_next);
-  if (wave == 1) load_diag(0, 0);
-  if (wave == 2) load_diag(0, 1);
+  if (wave == 7) fetch_for_owner(0);
   __syncthreads();
 
-  for (int e = 0; e < nev; ++e) {
-    // (the lane number is re-read every iteration: addresses derived from it are then formed where they are
-    // used instead of occupying registers through the whole loop, which has none to spare)
-    int lane_v = lane;
-    asm volatile("" : "+v"(lane_v));
-    const SbGeo g = g_next;
-    const int buf = e & 1;
-    const int colg = a.sb0 + kSub * e;                    // first column of the sub-block
-    const bool is_owner = wave == g.owner;
+  // ================= updater: sub-blocks before this wave's own
+  int e = 0;
+  if (first_own < last_own && first_own > 0) {
+    // left operands of piece t % 4 of sub-block t / 4, requested two pieces ahead of their use (three register sets would
+    // not fit beside the accumulators; two pieces' MFMAs and the other wave of the SIMD cover an L2 round trip)
+    u32x4 left[2][4];
+    auto load_left = [&](int x, int i, u32x4 (&dst)[4]) {
+      const int64_t o = ((int64_t)x * kSbCols + 128 * wave + 32 * i) * kSub;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (q < 2 ? useE : useP) dst[q] = *reinterpret_cast<const u32x4*>(a.Nop[q] + o + lane_off);
+    };
+    if (update) {
+      load_left(0, 0, left[0]);
+      load_left(0, 1, left[1]);
+    }
+    for (; e < first_own; ++e) {
+      help(e);
+      sb_barrier();
+      if (!update) continue;
+      u32x4 fr[4][2];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int rh = 0; rh < 2; ++rh) fr[q][rh] = sh.frag[e & 1][q][rh][lane];
+      const int nx = min(e + 1, first_own - 1);            // (the last request is a repeat that nobody uses)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        sb_piece_update(acc[i], left[i & 1], fr, useE, useP);
+        load_left(i < 2 ? e : nx, (i + 2) & 3, left[i & 1]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
 
-    // results of the 16 steps (owner only): W^ and the codes, packed one byte each as they are produced
-    float wh[kSub];
-    uint32_t cw[4] = {0u, 0u, 0u, 0u};
-    if (is_owner) {
-      const int row = row0 + lane_v;
+  // ================= owner: the column steps of this wave's eight sub-blocks
+  if (first_own < last_own) {
+    SbGrid g{1.f, 0.f, 1.f};
+    const int row = row0 + lane;
+    if (a.group <= 0) {
+      if (row < a.m) { g.sc = a.scales[row]; g.zr = a.zeros[row]; }
+      g.isc = 1.f / g.sc;
+    }
+    auto new_grid = [&](float lo, float hi, int x) {
+      sb_grid_params(lo, hi, a.maxq, a.sym, g.sc, g.zr);
+      g.isc = 1.f / g.sc;
+      if (row < a.m) {
+        const int64_t o = (int64_t)row * a.G + (a.sb0 + kSub * x) / a.group;
+        a.scales[o] = g.sc;
+        a.zeros[o] = g.zr;
+      }
+    };
+    auto event = [&]<int EB>(std::integral_constant<int, EB>) {
+      constexpr int R = EB >> 1, HALF = EB & 1, NEXT = (EB + 1) >> 1;      // current piece, its half, first piece with columns left
+      const int x = first_own + EB, buf = x & 1;
+      if (x >= last_own) return;
       // ---- group range over the current (error-compensated) weights: the group's pieces are all in this wave
-      if (a.group >= 32 && (kSub * e) % a.group == 0) {
+      if (HALF == 0 && a.group >= 32 && (32 * R) % a.group == 0) {
         float mn[2], mx[2];
 #pragma unroll
         for (int rh = 0; rh < 2; ++rh) {
           float lo = 0.f, hi = 0.f;
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (32 * i < a.group) {
+          for (int i = R; i < 4; ++i)
+            if (32 * (i - R) < a.group) {
 #pragma unroll
-              for (int v = 0; v < 16; ++v) { lo = fminf(lo, acc[0][i][rh][v]); hi = fmaxf(hi, acc[0][i][rh][v]); }
+              for (int v = 0; v < 16; ++v) { lo = fminf(lo, acc[i][rh][v]); hi = fmaxf(hi, acc[i][rh][v]); }
             }
           const u32x2 r0 = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(lo), false, false);
           const u32x2 r1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(hi), __float_as_uint(hi), false, false);
           mn[rh] = fminf(__uint_as_float(r0[0]), __uint_as_float(r0[1]));
           mx[rh] = fmaxf(__uint_as_float(r1[0]), __uint_as_float(r1[1]));
         }
-        sb_grid_params(lh ? mn[1] : mn[0], lh ? mx[1] : mx[0], a.maxq, a.sym, sc, zr);
-        isc = 1.f / sc;
-        if (row < a.m) {
-          const int64_t o = (int64_t)row * a.G + colg / a.group;
-          a.scales[o] = sc;
-          a.zeros[o] = zr;
+        new_grid(lh ? mn[1] : mn[0], lh ? mx[1] : mx[0], x);
+      }
+      float w[kSub], u[kSub], p[kSub];
+      {
+        const float* ud = sh.Ud[buf][lane & 15];
+        const float* pd = sh.Pd[buf][lane & 15];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 a4 = *reinterpret_cast<const f32x4*>(ud + 4 * q), b4 = *reinterpret_cast<const f32x4*>(pd + 4 * q);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) { u[4 * q + k] = a4[k]; p[4 * q + k] = b4[k]; }
         }
       }
-      // ================= the 16 column steps of this sub-block (lines 7-10), one row per lane
-      float w[kSub];
-      if (g.half) sb_extract<1>(acc, w); else sb_extract<0>(acc, w);
-      uint32_t peh[8], pel[8], pvh[8], pvl[8];             // -E and V as bf16 hi + lo pairs (operands of the updates)
+      float dreg = sh.dinv[buf][lane & 15];
+      sb_extract<HALF>(acc[R], w);
       if (a.group == kSub) {                               // the group is this sub-block: its grid comes from the registers
         float mn = 0.f, mx = 0.f;
 #pragma unroll
         for (int c = 0; c < kSub; ++c) { mn = fminf(mn, w[c]); mx = fmaxf(mx, w[c]); }
-        sb_grid_params(mn, mx, a.maxq, a.sym, sc, zr);
-        isc = 1.f / sc;
-        if (row < a.m) {
-          const int64_t o = (int64_t)row * a.G + colg / a.group;
-          a.scales[o] = sc;
-          a.zeros[o] = zr;
-        }
+        new_grid(mn, mx, x);
       }
-      const float* Ud = &sh.Ud[buf][0][0];
-      const float* Pd = &sh.Pd[buf][0][0];
-      // the pieces of row j of U and P right of the diagonal (and 1 / U_jj), fetched two steps ahead of their use: a
-      // wait for "everything but the latest reads" then never waits for reads that have only just been issued
-      f32x4 ub[3][4], pb[3][4];
-      float db[3];
-      auto fetch = [&](int j) {
+      sb_pin(u);
+      sb_pin(p);
+      asm volatile("s_nop 1" : "+v"(dreg));
+      u32x4 pk[4][2];                                      // -E hi, -E lo, V hi, V lo: 16 columns as two chunks of eight
+      u32x4 cw = {0u, 0u, 0u, 0u};                         // the codes, one byte each
+      sb_steps<0>(w, u, p, dreg, g, -g.zr, a.maxq - g.zr, 0.f, 0.f, pk, cw);
+      // one row and two chunks of eight columns per lane -> one chunk and a row of each half per lane (an MFMA operand)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (4 * q + 3 > j) {
-            ub[j % 3][q] = *reinterpret_cast<const f32x4*>(Ud + j * kSub + 4 * q);
-            pb[j % 3][q] = *reinterpret_cast<const f32x4*>(Pd + j * kSub + 4 * q);
-          }
-        db[j % 3] = sh.dinv[buf][j];
-      };
-      fetch(0);
-      fetch(1);
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int j = 0; j < kSub; ++j) {
-        if (j + 2 < kSub) fetch(j + 2);
-        const f32x4(&uc)[4] = ub[j % 3];
-        const f32x4(&pc)[4] = pb[j % 3];
-        const float dj = db[j % 3];
-        const float v = w[j];
-        // code - zero = clamp(rint(v / scale), -zero, maxq - zero): the same integers as clamp(rint(.) + zero, 0, maxq)
-        // - zero, with a shorter dependency chain in front of the updates (one median instead of add, max, min, sub)
-        const float d = __builtin_amdgcn_fmed3f(rintf(v * isc), -zr, a.maxq - zr);
-        const float x = sc * d;
-        const float e1 = (x - v) * dj;                    // -E_j
-        wh[j] = x;
-        cw[j >> 2] |= (uint32_t)(d + zr) << (8 * (j & 3));
-        {
-          const uint32_t h1 = sb_bf16_rne(e1), l1 = sb_bf16_rne(e1 - sb_bf16_f32((uint16_t)h1));
-          const uint32_t h2 = sb_bf16_rne(v), l2 = sb_bf16_rne(v - sb_bf16_f32((uint16_t)h2));
-          if (j & 1) { peh[j >> 1] |= h1 << 16; pel[j >> 1] |= l1 << 16; pvh[j >> 1] |= h2 << 16; pvl[j >> 1] |= l2 << 16; }
-          else { peh[j >> 1] = h1; pel[j >> 1] = l1; pvh[j >> 1] = h2; pvl[j >> 1] = l2; }
+        for (int k = 0; k < 4; ++k) {
+          const u32x2 r = __builtin_amdgcn_permlane32_swap(pk[q][0][k], pk[q][1][k], false, false);
+          pk[q][0][k] = r[0];
+          pk[q][1][k] = r[1];
         }
 #pragma unroll
-        for (int c = j + 1; c < kSub; ++c) w[c] = fmaf(e1, uc[c >> 2][c & 3], fmaf(v, pc[c >> 2][c & 3], w[c]));
-      }
-      {
-        const int rh = lane >> 5;
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int ch = 0; ch < 2; ++ch) {
-          sh.frag[buf][0][0][rh][ch][l32] = u32x4{peh[4 * ch], peh[4 * ch + 1], peh[4 * ch + 2], peh[4 * ch + 3]};
-          sh.frag[buf][0][1][rh][ch][l32] = u32x4{pel[4 * ch], pel[4 * ch + 1], pel[4 * ch + 2], pel[4 * ch + 3]};
-          sh.frag[buf][1][0][rh][ch][l32] = u32x4{pvh[4 * ch], pvh[4 * ch + 1], pvh[4 * ch + 2], pvh[4 * ch + 3]};
-          sh.frag[buf][1][1][rh][ch][l32] = u32x4{pvl[4 * ch], pvl[4 * ch + 1], pvl[4 * ch + 2], pvl[4 * ch + 3]};
-        }
-      }
+        for (int rh = 0; rh < 2; ++rh) sh.frag[buf][q][rh][lane] = pk[q][rh];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) *reinterpret_cast<f32x4*>(&sh.x[buf][lane][4 * q]) = f32x4{w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]};
+      sh.codes[buf][lane] = cw;
       sb_barrier();
-    } else {
-      // the waves that hold later blocks fetch the next sub-block's diagonal pieces while they wait
-      if (e + 1 < nev) {
-        if (wave == ((g.owner + 1) & 3)) load_diag(e + 1, 0);
-        if (wave == ((g.owner + 2) & 3)) load_diag(e + 1, 1);
-      }
-      sb_barrier();
-    }
-
-    // ================= every wave: this sub-block's update of its own later columns (Eq. 18 inside the super-block)
-    if (g.active) {
-      bf16x8 fe[2][2], fv[2][2];                          // [hi/lo][row half]
+      if (update) {
+        // the columns of this block that are left, the next sub-block's piece first
 #pragma unroll
-      for (int hl = 0; hl < 2; ++hl)
+        for (int i = R; i < 4; ++i) {
+          if (i < NEXT) continue;
+          u32x4 left[4];
 #pragma unroll
-        for (int rh = 0; rh < 2; ++rh) {
-          fe[hl][rh] = __builtin_bit_cast(bf16x8, sh.frag[buf][0][hl][rh][lh][l32]);
-          fv[hl][rh] = __builtin_bit_cast(bf16x8, sh.frag[buf][1][hl][rh][lh][l32]);
-        }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // the staged left operands (requested a sub-block ago) have landed
-      const unsigned char* mine = stage + lane_v * 16;
-      // one piece at a time, the next piece's operands read from LDS under this piece's MFMAs
-      u32x4 cur[4];
-      auto read_left = [&](int p, u32x4 (&dst)[4]) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (q < 2 ? useE : useP) dst[q] = *reinterpret_cast<const u32x4*>(mine + p * 4096 + q * 1024);
-      };
-      read_left(__builtin_ctz(g.active), cur);
-#pragma unroll
-      for (int p = 0; p < kSbPieces; ++p) {
-        if ((g.active >> p) & 1u) {
-          u32x4 nxt[4];
-          const uint32_t rest = g.active >> (p + 1);
-          if (rest) read_left(p + 1 + __builtin_ctz(rest), nxt);
-          if (p == 0 && is_owner) {
-            // the piece the sub-block lies in: the sub-block's own columns (its first half) take no update
+          for (int q = 0; q < 4; ++q) left[q] = sh.left[x % 3][i][q][lane];
+          if (HALF == 0 && i == R) {
+            // the sub-block's own columns, the first half of its piece, take no update
             const bool keep = l32 >= kSub;
-            const u32x4 z = {0u, 0u, 0u, 0u};
 #pragma unroll
-            for (int q = 0; q < 4; ++q) cur[q] = keep ? cur[q] : z;
+            for (int q = 0; q < 4; ++q) left[q] = keep ? left[q] : u32x4{0u, 0u, 0u, 0u};
           }
-          f32x16(&t)[2] = acc[p >> 2][p & 3];
-          if (useE) {
-            const bf16x8 ah = __builtin_bit_cast(bf16x8, cur[0]), al = __builtin_bit_cast(bf16x8, cur[1]);
-#pragma unroll
-            for (int rh = 0; rh < 2; ++rh) {
-              t[rh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, fe[0][rh], t[rh], 0, 0, 0);
-              t[rh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, fe[1][rh], t[rh], 0, 0, 0);
-              t[rh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, fe[0][rh], t[rh], 0, 0, 0);
-            }
-          }
-          if (useP) {
-            const bf16x8 ah = __builtin_bit_cast(bf16x8, cur[2]), al = __builtin_bit_cast(bf16x8, cur[3]);
-#pragma unroll
-            for (int rh = 0; rh < 2; ++rh) {
-              t[rh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, fv[0][rh], t[rh], 0, 0, 0);
-              t[rh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, fv[1][rh], t[rh], 0, 0, 0);
-              t[rh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, fv[0][rh], t[rh], 0, 0, 0);
-            }
-          }
-#pragma unroll
-          for (int q = 0; q < 4; ++q) cur[q] = nxt[q];
-          __builtin_amdgcn_sched_barrier(0);
+          sb_piece_update(acc[i], left, pk, useE, useP);
         }
       }
-    }
-    // the owner keeps its pieces in a fixed place: a finished piece makes room for the next, a finished block for
-    // the wave's second block
-    if (is_owner) {
-      if ((e & 7) == 7) {
-        if (g.two) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int rh = 0; rh < 2; ++rh) acc[0][i][rh] = acc[1][i][rh];
-        }
-      } else if (g.half) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-          for (int rh = 0; rh < 2; ++rh) acc[0][i][rh] = acc[0][i + 1][rh];
-      }
-    }
-    // the staging area is free again (its reads have returned): request the next sub-block's operands, then let
-    // this sub-block's results leave for memory
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    g_next = sb_geo(e + 1, wave, sbw, nev, a.terms);
-    request_left(e + 1, g_next);
-    if (is_owner) {
-      const int row = row0 + lane_v;
-      if (row < a.m) {
-        float* wdst = a.W + (int64_t)row * a.ldw + colg;
-        uint8_t* cdst = a.codes + (int64_t)row * a.n + colg;
-        if (FAST) {
-#pragma unroll
-          for (int c4 = 0; c4 < kSub; c4 += 4)
-            *reinterpret_cast<f32x4*>(wdst + c4) = f32x4{wh[c4], wh[c4 + 1], wh[c4 + 2], wh[c4 + 3]};
-          *reinterpret_cast<u32x4*>(cdst) = u32x4{cw[0], cw[1], cw[2], cw[3]};
-        } else {
-#pragma unroll
-          for (int c = 0; c < kSub; ++c)
-            if (colg + c < a.n) { wdst[c] = wh[c]; cdst[c] = (uint8_t)(cw[c >> 2] >> (8 * (c & 3))); }
-        }
-      }
-    }
-    if (a.Eh && wave == ((g.owner + 3) & 3)) {
-      // -E and V for the update of the columns after the super-block: copied to memory from the LDS fragments by
-      // a wave that has nothing else to do now (they stay valid until the sub-block after next is published)
-#pragma unroll
-      for (int it = 0; it < 2; ++it) {
-        const int item = lane_v + 64 * it, r = item >> 1, ch = item & 1;
-        if (row0 + r < a.m) {
-          const int64_t o = (int64_t)(row0 + r) * a.ldev + kSub * e + 8 * ch;
-          *reinterpret_cast<u32x4*>(a.Eh + o) = sh.frag[buf][0][0][r >> 5][ch][r & 31];
-          *reinterpret_cast<u32x4*>(a.El + o) = sh.frag[buf][0][1][r >> 5][ch][r & 31];
-          *reinterpret_cast<u32x4*>(a.Vh + o) = sh.frag[buf][1][0][r >> 5][ch][r & 31];
-          *reinterpret_cast<u32x4*>(a.Vl + o) = sh.frag[buf][1][1][r >> 5][ch][r & 31];
-        }
-      }
-    }
+    };
+    event(std::integral_constant<int, 0>{});
+    event(std::integral_constant<int, 1>{});
+    event(std::integral_constant<int, 2>{});
+    event(std::integral_constant<int, 3>{});
+    event(std::integral_constant<int, 4>{});
+    event(std::integral_constant<int, 5>{});
+    event(std::integral_constant<int, 6>{});
+    event(std::integral_constant<int, 7>{});
+    e = last_own;
   }
+
+  // ================= finished
+  for (; e < nev; ++e) {
+    help(e);
+    sb_barrier();
+  }
+  help(nev);
 }
 
 hipError_t launch_near_operands(const float* U, const float* P, int64_t ldh, int n, int sb0, int sbw, uint16_t* const* N4,
@@ -504,17 +493,23 @@ hipError_t launch_near_operands(const float* U, const float* P, int64_t ldh, int
   return hipGetLastError();
 }
 
-hipError_t launch_quant_sb(const SbArgs& a, hipStream_t s) {
-  constexpr int lds = 4 * kSbStage + (int)sizeof(SbShared);
-  static LdsLimitOnce fast_once, slow_once;
-  hipError_t e = fast_once.ensure(reinterpret_cast<const void*>(&quant_sb_kernel<true>), lds);
-  if (e == hipSuccess) e = slow_once.ensure(reinterpret_cast<const void*>(&quant_sb_kernel<false>), lds);
+template <bool FAST, int TERMS>
+static hipError_t launch_quant_sb_as(const SbArgs& a, hipStream_t s) {
+  constexpr int lds = (int)sizeof(SbShared);
+  static LdsLimitOnce once;                      // per instantiation
+  const hipError_t e = once.ensure(reinterpret_cast<const void*>(&quant_sb_kernel<FAST, TERMS>), lds);
   if (e != hipSuccess) return e;
-  if (a.fast_rows)
-    hipLaunchKernelGGL(quant_sb_kernel<true>, dim3((a.m + 63) / 64), dim3(256), lds, s, a);
-  else
-    hipLaunchKernelGGL(quant_sb_kernel<false>, dim3((a.m + 63) / 64), dim3(256), lds, s, a);
+  hipLaunchKernelGGL((quant_sb_kernel<FAST, TERMS>), dim3((a.m + 63) / 64), dim3(64 * kSbWaves), lds, s, a);
   return hipGetLastError();
+}
+
+hipError_t launch_quant_sb(const SbArgs& a, hipStream_t s) {
+  switch (a.terms) {
+    case 3: return a.fast_rows ? launch_quant_sb_as<true, 3>(a, s) : launch_quant_sb_as<false, 3>(a, s);
+    case 2: return a.fast_rows ? launch_quant_sb_as<true, 2>(a, s) : launch_quant_sb_as<false, 2>(a, s);
+    case 1: return a.fast_rows ? launch_quant_sb_as<true, 1>(a, s) : launch_quant_sb_as<false, 1>(a, s);
+    default: return a.fast_rows ? launch_quant_sb_as<true, 0>(a, s) : launch_quant_sb_as<false, 0>(a, s);
+  }
 }
 
 }  // namespace gptaq
