@@ -1,0 +1,345 @@
+// The fp64 part of the factor sweep (Algorithm 1, line 3): one 256-column outer block OB at a time,
+//   block_factor_kernel : F_OB,OB = V V^T, V upper triangular, in one workgroup;
+//   block_panel_kernel  : V_I,OB = F_I,OB V_OB,OB^-T for the rows I above OB, and U_OB,OB = V_OB,OB^-1, written as the digit
+//                         operands of the rank-256 products (gemm_i8s.hip).
+//
+// Both count indices of the block from its end, r -> 255 - r, which turns the factorisation "from the last column to the
+// first" into the usual one: S = V V^T with V lower triangular, columns 0, 1, ... (S, V, W = V^-1 below are in this order;
+// where the matrix ends the block is filled up with the identity, which then comes first and couples to nothing).
+//
+// A 16 x 16 tile of fp64 is held by a wavefront as lane l, register v: row l % 16, column 4 (l / 16) + v.  That is at once
+// (columns c and rows of the contraction counted in the order 4 (l / 16) + v)
+//   * the B operand of four v_mfma_f64_16x16x4 (contraction over the tile's columns), and
+//   * their result, when the A operand's lane l carries row perm(l % 16) of its tile, perm(4 v + g) = 4 g + v,
+// so  T_ab^T -= X_b X_a^T  and  X_a^T = W_k T_ak^T  chain from accumulator to operand without a shuffle.  In memory and
+// LDS a tile is two runs of 64 x 16 bytes: registers 0, 1 of every lane, then 2, 3.
+//
+// What bounds them: the factorisation is a chain of 256 column steps (each a reciprocal, its Newton steps and an update,
+// ~100 clocks) on one CU beside 680 tile products of 256 clocks on three of its SIMDs; the panel kernel is a chain of 16 tile
+// columns.  An f64 MFMA (64 clocks for 1024 products) is no faster than v_fma_f64, but its operands are one register a lane,
+// where fp64 FMAs on 64 x 64 tiles were bound by their LDS reads and by solves of one wavefront.  Measured per block of 256
+// columns: factorisation 152 -> 62 us, panel 50 -> 17 us (n = 4096) with the digits (8 us) and the inverse (a kernel of 46 us
+// on the other chain) in it.  gptaq_prepare 4.41 -> 2.42 ms at n = 4096, 22.5 -> 19.4 at n = 11008.
+#include "common.h"
+#include "i8_digits.h"
+#include <utility>
+
+namespace gptaq {
+
+typedef __attribute__((ext_vector_type(2))) double f64x2;
+typedef __attribute__((ext_vector_type(4))) double f64x4;
+
+namespace {
+constexpr int NT = kFactorBlock / 16;             // tiles per side of the block
+constexpr int TILE = 256;                         // doubles of a tile
+
+__device__ __forceinline__ f64x4 load_tile(const double* t, int lane) {
+  const f64x2 a = *reinterpret_cast<const f64x2*>(t + 2 * lane), b = *reinterpret_cast<const f64x2*>(t + 128 + 2 * lane);
+  return f64x4{a[0], a[1], b[0], b[1]};
+}
+__device__ __forceinline__ void store_tile(double* t, int lane, f64x4 x) {
+  *reinterpret_cast<f64x2*>(t + 2 * lane) = f64x2{x[0], x[1]};
+  *reinterpret_cast<f64x2*>(t + 128 + 2 * lane) = f64x2{x[2], x[3]};
+}
+// lane whose part of a stored tile is the A operand of lane l
+__device__ __forceinline__ int operand_lane(int lane) { return (lane & 48) | (4 * (lane & 3)) | ((lane >> 2) & 3); }
+
+// c + (A tile) x (B tile), contraction over both tiles' 16 columns
+__device__ __forceinline__ f64x4 tile_product(f64x4 a, f64x4 b, f64x4 c) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], b[s], c, 0, 0, 0);
+  return c;
+}
+
+// LDS-only barrier: the stores to memory of a step need not have arrived
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// acc += (lane C of each group of 16 lanes of s) * e.  The compiler does not look into the asm: s must not have been written by
+// the two instructions before (row_value below waits; every later use is behind a chain of results of that one).
+template <int C> __device__ __forceinline__ void fmac_lane(double& acc, double s, double e) {
+  asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(s), "v"(e), "n"(C));
+}
+template <int C> __device__ __forceinline__ double row_value(double s) {      // lane C of each group of 16 lanes
+  double r;
+  asm("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=v"(r) : "v"(s), "n"(C));
+  return r;
+}
+
+// hardware estimates + Newton steps (about 1 ulp; no correctly rounded quotient is needed)
+__device__ __forceinline__ double recip(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+
+struct FactorShared {
+  double x[NT][TILE];        // V_ak of the current tile column k
+  double diag[TILE];         // tile (k, k) before its factorisation, entry (row, column) at 16 column + row
+  double w[TILE];            // W_kk, as a stored tile
+};
+
+// ---- the 16 x 16 factorisation, one wavefront.  Every group of 16 lanes holds the whole symmetric tile, lane r row r in
+// registers s[0..15]; a step needs the pivot column in every lane, and by symmetry lane c's s[j] is S[c][j]: a broadcast inside
+// the group of 16 (DPP) delivers it as an operand of the product.  f: rows of the identity taken through the same steps, which
+// makes them the rows of V^-T.
+template <int J>
+__device__ __forceinline__ void factor_steps(double (&s)[16], double (&f)[16], double& piv, int r, int32_t* info, int last_index) {
+  if constexpr (J < 16) {
+    const double p = row_value<J>(s[J]);
+    const bool bad = !(p > 0.0);
+    if (bad && (threadIdx.x & 63) == 0) atomicCAS(info, 0, last_index - J);
+    piv = r == J ? p : piv;
+    const double q = bad ? 0.0 : -recip(p);
+    const double ns = s[J] * q, nf = f[J] * q;
+    [&]<int... C>(std::integer_sequence<int, C...>) {
+      (fmac_lane<J + 1 + C>(s[J + 1 + C], s[J], ns), ...);
+      (fmac_lane<J + 1 + C>(f[J + 1 + C], s[J], nf), ...);
+    }(std::make_integer_sequence<int, 15 - J>{});
+    factor_steps<J + 1>(s, f, piv, r, info, last_index);
+  }
+}
+
+__device__ __forceinline__ void factor_diag(FactorShared& sh, int32_t* info, int last_index) {
+  const int lane = threadIdx.x & 63, r = lane & 15;
+  double s[16], f[16];
+#pragma unroll
+  for (int c = 0; c < 16; ++c) {
+    s[c] = sh.diag[16 * c + r];
+    f[c] = c == r ? 1.0 : 0.0;
+  }
+  double piv = 1.0;
+  factor_steps<0>(s, f, piv, r, info, last_index);
+  // column c of V and row c of W are scaled by 1 / sqrt(pivot c)
+  double rs = piv > 0.0 ? 1.0 / sqrt(piv) : 1.0;
+  asm volatile("s_nop 1" : "+v"(rs));
+  double w[16];
+  [&]<int... C>(std::integer_sequence<int, C...>) {
+    ((w[C] = 0.0, fmac_lane<C>(w[C], rs, f[C])), ...);
+  }(std::make_integer_sequence<int, 16>{});
+  // w[c] of lane i is W[c][i]: tile position of (row c, column i)
+  if (lane < 16) {
+    double* dst = sh.w + (((r >> 1) & 1) * 128 + (r >> 2) * 32 + (r & 1));
+#pragma unroll
+    for (int c = 0; c < 16; ++c) dst[2 * c] = w[c];
+  }
+}
+
+// ---- the tile rows.  Wavefront 0 factors the diagonal tiles and has its SIMD to itself but for wavefront 4, which moves results
+// to memory: an f64 MFMA holds the pipe that f64 VALU instructions need for 64 clocks, and the chain of column steps must not
+// wait for it.  The other six hold the tiles (a, 0 .. a) of these rows a, a SIMD's two about as many as another's at every step:
+__host__ __device__ constexpr int tile_row(int w, int i) {
+  constexpr int8_t rows[8][4] = {{-1, -1, -1, -1}, {15, 4, 3, -1}, {14, 5, 2, -1}, {13, 6, 1, 0},
+                                 {-1, -1, -1, -1}, {10, 9, -1, -1}, {11, 8, -1, -1}, {12, 7, -1, -1}};
+  return rows[w][i];
+}
+__host__ __device__ constexpr int tile_rows(int w) { int n = 0; while (n < 4 && tile_row(w, n) >= 0) ++n; return n; }
+__host__ __device__ constexpr int tile_base(int w, int i) { int b = 0; for (int q = 0; q < i; ++q) b += tile_row(w, q) + 1; return b; }
+
+template <int W>
+__device__ __forceinline__ void factor_rows(const BlockFactor& a, FactorShared& sh) {
+  constexpr int NR = tile_rows(W);
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, ol = operand_lane(lane);
+  f64x4 t[tile_base(W, NR)];
+#pragma unroll
+  for (int i = 0; i < NR; ++i)
+#pragma unroll
+    for (int b = 0; b <= tile_row(W, i); ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int row = 16 * tile_row(W, i) + r, col = 16 * b + 4 * g + v;       // counted from the end
+        const int fi = a.o0 + kFactorBlock - 1 - max(row, col), fj = a.o0 + kFactorBlock - 1 - min(row, col);
+        t[tile_base(W, i) + b][v] = fj < a.n ? a.F[(int64_t)fi * a.ldf + fj] : (fi == fj ? 1.0 : 0.0);
+      }
+  auto put_diag = [&](const f64x4& d) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sh.diag[16 * (4 * g + v) + r] = d[v];
+  };
+#pragma unroll
+  for (int i = 0; i < NR; ++i)
+    if (tile_row(W, i) == 0) put_diag(t[tile_base(W, i)]);
+  lds_barrier();
+#pragma clang loop unroll(full)
+  for (int k = 0; k < NT; ++k) {
+    lds_barrier();                                             // W_kk is in LDS; every wavefront is done with column k - 1
+    if (k == NT - 1) break;
+    f64x4 nx[NR];
+    const f64x4 wk = load_tile(sh.w, ol);
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+      if (tile_row(W, i) > k) {
+        const f64x4 x = tile_product(wk, t[tile_base(W, i) + k], f64x4{0.0, 0.0, 0.0, 0.0});
+        store_tile(sh.x[tile_row(W, i)], lane, x);
+        nx[i] = -x;
+      }
+    lds_barrier();                                             // column k of V is in LDS
+    // the diagonal tile that the next factorisation waits for; meanwhile each other wavefront updates one of its tiles
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+      if (tile_row(W, i) == k + 1) {
+        f64x4& d = t[tile_base(W, i) + k + 1];
+        d = tile_product(load_tile(sh.x[k + 1], ol), nx[i], d);
+        put_diag(d);
+      }
+    const bool owner = tile_row(W, 0) == k + 1 || (NR > 1 && tile_row(W, 1) == k + 1) || (NR > 2 && tile_row(W, 2) == k + 1);
+    const bool first_done = !owner && tile_row(W, 0) > k + 1;
+    if (first_done) {
+      f64x4& d = t[tile_base(W, 0) + k + 1];
+      d = tile_product(load_tile(sh.x[k + 1], ol), nx[0], d);
+    }
+    lds_barrier();
+#pragma unroll
+    for (int b = k + 1; b < NT; ++b) {
+      if (b > tile_row(W, 0)) continue;
+      const f64x4 xb = load_tile(sh.x[b], ol);
+#pragma unroll
+      for (int i = 0; i < NR; ++i)
+        if (tile_row(W, i) >= b && !(b == k + 1 && (tile_row(W, i) == k + 1 || (i == 0 && first_done)))) {
+          f64x4& d = t[tile_base(W, i) + b];
+          d = tile_product(xb, nx[i], d);
+        }
+    }
+  }
+}
+
+__global__ __launch_bounds__(512) void block_factor_kernel(BlockFactor a) {
+  __shared__ __attribute__((aligned(16))) FactorShared sh;
+  const int lane = threadIdx.x & 63;
+  switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
+    case 0:
+      lds_barrier();                                           // tile (0, 0) is in LDS
+      for (int k = 0; k < NT; ++k) {
+        factor_diag(sh, a.info, a.o0 + kFactorBlock - 16 * k);
+        lds_barrier();
+        if (k == NT - 1) break;
+        lds_barrier();
+        lds_barrier();
+      }
+      break;
+    case 4:
+      lds_barrier();
+      for (int k = 0; k < NT; ++k) {
+        lds_barrier();
+        double* col = a.V + (int64_t)k * NT * TILE;
+        store_tile(col + k * TILE, lane, load_tile(sh.w, lane));
+        if (k == NT - 1) break;
+        lds_barrier();
+        lds_barrier();
+        for (int i = k + 1; i < NT; ++i) store_tile(col + i * TILE, lane, load_tile(sh.x[i], lane));
+      }
+      break;
+    case 1: factor_rows<1>(a, sh); break;
+    case 2: factor_rows<2>(a, sh); break;
+    case 3: factor_rows<3>(a, sh); break;
+    case 5: factor_rows<5>(a, sh); break;
+    case 6: factor_rows<6>(a, sh); break;
+    default: factor_rows<7>(a, sh); break;
+  }
+}
+
+// ---- the rows above the block, and the inverse.  One workgroup per 16 rows; wavefront w holds tile columns w, w + 4, ...
+// Step k: their owner turns tile column k into V_ik = F_ik W_kk^T and publishes it in LDS; all update their later columns.
+// Workgroups 0 .. 15 take 16 rows of the identity through the same steps, which makes them rows of V^-T, i.e. columns of
+// U_OB,OB.  The digit operands keep the matrix's own order of columns: k = 255 - (column counted from the end).
+__global__ __launch_bounds__(256) void block_panel_kernel(BlockPanel a) {
+  __shared__ __attribute__((aligned(16))) double xs[2][TILE];
+  __shared__ double rowmax[4][16];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 15, g = lane >> 4, ol = operand_lane(lane);
+  const bool inverse = blockIdx.x < NT;
+  const int row0 = inverse ? 16 * (int)blockIdx.x : 16 * ((int)blockIdx.x - NT);
+  f64x4 t[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int col = 16 * (wave + 4 * q) + 4 * g + v, fj = a.o0 + kFactorBlock - 1 - col;
+      if (inverse) t[q][v] = col == row0 + r ? 1.0 : 0.0;
+      else t[q][v] = fj < a.n ? a.F[(int64_t)(row0 + r) * a.ldf + fj] : 0.0;
+    }
+  auto tile_of = [&](int k, int b) { return a.V + ((int64_t)k * NT + b) * TILE; };
+  // left operands of a step, fetched during the step before: W_kk for its owner, V_bk of the wavefront's later columns b
+  f64x4 wk, vb[4], wn, vn[4];
+  auto fetch = [&](int k, f64x4& w, f64x4 (&v)[4]) {
+    if (k >= NT) return;
+    if (wave == (k & 3)) w = load_tile(tile_of(k, k), ol);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (4 * q + 3 > k) v[q] = load_tile(tile_of(k, max(wave + 4 * q, k)), ol);
+  };
+  fetch(0, wk, vb);
+#pragma clang loop unroll(full)
+  for (int k = 0; k < NT; ++k) {
+    fetch(k + 1, wn, vn);
+    const int q0 = k >> 2;
+    if (wave == (k & 3)) {
+      t[q0] = tile_product(wk, t[q0], f64x4{0.0, 0.0, 0.0, 0.0});
+      store_tile(xs[k & 1], lane, -t[q0]);
+    }
+    if (k == NT - 1) break;
+    lds_barrier();
+    const f64x4 nx = load_tile(xs[k & 1], lane);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (4 * q + 3 > k && wave + 4 * q > k) t[q] = tile_product(vb[q], nx, t[q]);
+    wk = wn;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) vb[q] = vn[q];
+  }
+  // ---- digits: one scale per row, the row's 256 entries are in the four wavefronts
+  double mx = 0.0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) mx = fmax(mx, fabs(t[q][v]));
+  mx = fmax(mx, __shfl_xor(mx, 16, 64));
+  mx = fmax(mx, __shfl_xor(mx, 32, 64));
+  if (lane < 16) rowmax[wave][lane] = mx;
+  lds_barrier();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) mx = fmax(mx, rowmax[q][r]);
+  const int e = digit_exponent(mx);
+  const double sc = digit_scale(e);
+  const I8Operand& o = inverse ? a.Ucol : a.Vs;
+  const int row = inverse ? kFactorBlock - 1 - (row0 + r) : row0 + r;      // row of the operand
+  if (wave == 0 && g == 0) o.scale[row] = e - 26;
+  const int line = (row >> 3) & 3;
+  uint8_t* slab = o.planes + (int64_t)(row >> 5) * 1024 + 256 * line;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint32_t w[kI8Planes];
+    pack_digits(digits_of(t[q][3], sc), digits_of(t[q][2], sc), digits_of(t[q][1], sc), digits_of(t[q][0], sc), w);
+    const int k0 = kFactorBlock - 4 - (16 * (wave + 4 * q) + 4 * g);       // k of the last of the lane's four columns
+    const int slot = ((row & 7) << 1) | (((k0 >> 4) & 1) ^ (line & 1));
+    uint8_t* dst = slab + (int64_t)(k0 >> 5) * o.chunk_stride() + slot * 16 + (k0 & 15);
+#pragma unroll
+    for (int i = 0; i < kI8Planes; ++i) *reinterpret_cast<uint32_t*>(dst + (int64_t)i * o.plane_stride()) = w[i];
+  }
+  if (inverse) {
+    const int j = kFactorBlock - 1 - (row0 + r);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = kFactorBlock - 1 - (16 * (wave + 4 * q) + 4 * g + v);
+        a.Uob[(int64_t)i * kFactorBlock + j] = t[q][v];
+        if (i <= j && a.o0 + j < a.n) a.F[(int64_t)(a.o0 + i) * a.ldf + a.o0 + j] = t[q][v];
+      }
+  }
+}
+}  // namespace
+
+hipError_t launch_block_factor(const BlockFactor& a, hipStream_t s) {
+  hipLaunchKernelGGL(block_factor_kernel, dim3(1), dim3(512), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_block_panel(const BlockPanel& a, hipStream_t s) {
+  hipLaunchKernelGGL(block_panel_kernel, dim3((unsigned)(NT + a.o0 / 16)), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace gptaq

@@ -75,8 +75,8 @@ struct I8Operand {
   uint8_t* planes;
   int32_t* scale;
   int64_t rows_pad;
-  int64_t chunk_stride() const { return rows_pad * 32; }
-  int64_t plane_stride() const { return rows_pad * kI8MaxK; }
+  __host__ __device__ int64_t chunk_stride() const { return rows_pad * 32; }
+  __host__ __device__ int64_t plane_stride() const { return rows_pad * kI8MaxK; }
   static size_t plane_bytes(int64_t rows_pad) { return (size_t)kI8Planes * rows_pad * kI8MaxK; }
 };
 struct I8Gemm {
@@ -92,6 +92,25 @@ hipError_t launch_slice_i8(const double* src, int64_t sr, int64_t sk, int R, int
 // of 128 and 64); upper_only skips the tiles entirely below the diagonal of C.
 hipError_t launch_gemm_i8s(const I8Operand& A, int a_row0, const I8Operand& B, int b_row0, double* C, int64_t ldc, int M,
                            int N, int K, double alpha, int beta, int upper_only, hipStream_t s);
+
+// The fp64 part of the factor sweep, one outer block of kFactorBlock columns [o0, o0 + kFactorBlock) at a time (o0 a multiple of
+// it; the block may reach past n).  V holds the block's factor as 16 x 16 tiles, (k, a) at (16 k + a) * 256 doubles.
+constexpr int kFactorBlock = 256;
+constexpr size_t kFactorTileBytes = (size_t)kFactorBlock * kFactorBlock * 8;
+struct BlockFactor {
+  const double* F; int64_t ldf; int n, o0;
+  int32_t* info;                     // set to 1 + index of the first pivot that is not positive, unless set already
+  double* V;
+};
+struct BlockPanel {
+  double* F; int64_t ldf; int n, o0;
+  const double* V;
+  I8Operand Vs;                      // out: digits of V_I,OB, rows I = 0 .. o0 - 1
+  I8Operand Ucol;                    // out: digits of the columns of U_OB,OB
+  double* Uob;                       // out: U_OB,OB, kFactorBlock x kFactorBlock, zeros below the diagonal; the upper part also to F
+};
+hipError_t launch_block_factor(const BlockFactor& a, hipStream_t s);
+hipError_t launch_block_panel(const BlockPanel& a, hipStream_t s);
 
 // Column loop + in-super-block updates of a whole super-block in one launch (quantize_sb.hip).
 constexpr int kSbCols = 1024;       // columns per super-block

@@ -33,3 +33,21 @@ def test_column_loop_at_the_edges_of_its_blocks(bits, group, m, n, terms):
     got = PU.gpu_quantize(W, dev(U32), dev(P32) if terms & 2 else None, bits, group, False, 128, terms=terms)
     PU.check_against_oracle(W, U32.astype(np.float64), P32.astype(np.float64), got, bits, group, False,
                             label=f"edge W{bits} g{group} {m}x{n} terms {terms}", terms=terms)
+
+
+# Sizes around the 16-column tiles and the 256-column outer blocks of the factorisation: a block of identity padding and one
+# column, part of a tile, whole tiles, one column into the next block, three blocks with a ragged first one.
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 47, 240, 241, 255, 257, 273, 528, 767])
+def test_factor_and_inverse_at_tile_edges(n):
+    k = max(64, 4 * n)
+    Xb, Xtb = synth.make_activations(k, n, 11, f"factor{n}", min(2, n - 1), 20.0)
+    H, A = O.accumulate(Xb, Xtb)
+    U, P, _ = O.prepare(H, A, 0.01)
+    Hd, Ad = dev(np.triu(H)), dev(A)
+    _, info = PU.gpu_prepare(Hd, Ad, 0.01)
+    assert info.cpu().tolist() == [0, 0]
+    # U: one rounding to fp32 of a result exact to ~1e-12, from an H rounded to fp32 (2^-24 each, condition number ~1e2);
+    # P: products of bf16 hi + lo splits (2^-17 per operand)
+    assert PU.rel_fro(Hd.cpu().numpy(), U) <= 1e-6
+    if n > 1:
+        assert PU.rel_fro(Ad.cpu().numpy(), P) <= 5e-5
