@@ -18,8 +18,9 @@
 // ~100 clocks) on one CU beside 680 tile products of 256 clocks on three of its SIMDs; the panel kernel is a chain of 16 tile
 // columns.  An f64 MFMA (64 clocks for 1024 products) is no faster than v_fma_f64, but its operands are one register a lane,
 // where fp64 FMAs on 64 x 64 tiles were bound by their LDS reads and by solves of one wavefront.  Measured per block of 256
-// columns: factorisation 152 -> 62 us, panel 50 -> 17 us (n = 4096) with the digits (8 us) and the inverse (a kernel of 46 us
-// on the other chain) in it.  gptaq_prepare 4.41 -> 2.42 ms at n = 4096, 22.5 -> 19.4 at n = 11008.
+// columns: factorisation 152 -> 47 us (110K clocks: the first half bound by the MFMAs, the second by the column steps, 3.0K clocks
+// per tile), panel 50 -> 17 us (n = 4096) with the digits (8 us) and the inverse (a kernel of 46 us
+// on the other chain) in it.  gptaq_prepare 4.41 -> 2.37 ms at n = 4096, 22.5 -> 19.4 at n = 11008.
 #include "common.h"
 #include "i8_digits.h"
 #include <utility>
@@ -44,6 +45,14 @@ __device__ __forceinline__ void store_tile(double* t, int lane, f64x4 x) {
 // lane whose part of a stored tile is the A operand of lane l
 __device__ __forceinline__ int operand_lane(int lane) { return (lane & 48) | (4 * (lane & 3)) | ((lane >> 2) & 3); }
 
+// F[row][col + 3 .. col] (four columns, counted from the end), 0 past column n.  The addresses are clamped instead of predicated:
+// a branch per entry would wait for every load before the next one is sent.  col % 4 == 0; ldf is a multiple of 16.
+__device__ __forceinline__ f64x4 load_row4(const double* F, int64_t ldf, int n, int row, int col) {
+  const double* p = F + (int64_t)min(row, n - 1) * ldf + (col < ldf ? col : 0);
+  const f64x2 a = *reinterpret_cast<const f64x2*>(p), b = *reinterpret_cast<const f64x2*>(p + 2);
+  return f64x4{col + 3 < n ? b[1] : 0.0, col + 2 < n ? b[0] : 0.0, col + 1 < n ? a[1] : 0.0, col < n ? a[0] : 0.0};
+}
+
 // c + (A tile) x (B tile), contraction over both tiles' 16 columns
 __device__ __forceinline__ f64x4 tile_product(f64x4 a, f64x4 b, f64x4 c) {
 #pragma unroll
@@ -51,11 +60,22 @@ __device__ __forceinline__ f64x4 tile_product(f64x4 a, f64x4 b, f64x4 c) {
   return c;
 }
 
-// LDS-only barrier: the stores to memory of a step need not have arrived
+// LDS-only barrier: the stores to memory of a step need not have arrived.  The products of a step stay in front of it (the
+// compiler is free to move them past, into the time of the next step's first, critical ones: 6 us of 60).
 __device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// LDS written by some lanes of a wavefront becomes readable by its others: the hardware keeps a wavefront's accesses in order,
+// the compiler does behind a fence
+__device__ __forceinline__ void wave_publish() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // acc += (lane C of each group of 16 lanes of s) * e.  The compiler does not look into the asm: s must not have been written by
@@ -69,11 +89,10 @@ template <int C> __device__ __forceinline__ double row_value(double s) {      //
   return r;
 }
 
-// hardware estimates + Newton steps (about 1 ulp; no correctly rounded quotient is needed)
-__device__ __forceinline__ double recip(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(fma(-x, r, 1.0), r, r);
-  return fma(fma(-x, r, 1.0), r, r);
+// hardware estimate (about 26 bits) and one step of third order (about 1 ulp)
+__device__ __forceinline__ double rsqrt_of(double x) {
+  const double r = __builtin_amdgcn_rsq(x), e = fma(-x * r, r, 1.0);          // (1 - e)^(-1/2) = 1 + e / 2 + 3 e^2 / 8 + ...
+  return fma(r * e, fma(e, 0.375, 0.5), r);
 }
 
 struct FactorShared {
@@ -86,20 +105,48 @@ struct FactorShared {
 // registers s[0..15]; a step needs the pivot column in every lane, and by symmetry lane c's s[j] is S[c][j]: a broadcast inside
 // the group of 16 (DPP) delivers it as an operand of the product.  f: rows of the identity taken through the same steps, which
 // makes them the rows of V^-T.
+// The updates of step J, s[J+1..15] and then f[J+1..15], in one list: all but the first are independent work for the time the
+// next pivot's broadcast and reciprocal take (the compiler's own order left a third of the chain uncovered).
+template <int J, int FROM, int TO>
+__device__ __forceinline__ void step_updates(double (&s)[16], double (&f)[16], double ns, double nf) {
+  constexpr int N = 2 * (15 - J), END = TO < N ? TO : N;
+  if constexpr (FROM < END) {
+    constexpr int C = FROM < 15 - J ? J + 1 + FROM : 2 * J - 14 + FROM;
+    if constexpr (FROM < 15 - J) fmac_lane<C>(s[C], s[J], ns); else fmac_lane<C>(f[C], s[J], nf);
+    step_updates<J, FROM + 1, TO>(s, f, ns, nf);
+  }
+}
+// q: 1 / pivot J, or 0 if that is not positive
 template <int J>
-__device__ __forceinline__ void factor_steps(double (&s)[16], double (&f)[16], double& piv, int r, int32_t* info, int last_index) {
-  if constexpr (J < 16) {
-    const double p = row_value<J>(s[J]);
-    const bool bad = !(p > 0.0);
-    if (bad && (threadIdx.x & 63) == 0) atomicCAS(info, 0, last_index - J);
-    piv = r == J ? p : piv;
-    const double q = bad ? 0.0 : -recip(p);
-    const double ns = s[J] * q, nf = f[J] * q;
-    [&]<int... C>(std::integer_sequence<int, C...>) {
-      (fmac_lane<J + 1 + C>(s[J + 1 + C], s[J], ns), ...);
-      (fmac_lane<J + 1 + C>(f[J + 1 + C], s[J], nf), ...);
-    }(std::make_integer_sequence<int, 15 - J>{});
-    factor_steps<J + 1>(s, f, piv, r, info, last_index);
+__device__ __forceinline__ void factor_steps(double (&s)[16], double (&f)[16], double& piv, double q, int r) {
+  if constexpr (J < 15) {
+    const double ns = -(s[J] * q);
+    step_updates<J, 0, 1>(s, f, ns, 0.0);
+    __builtin_amdgcn_sched_barrier(0);
+    const double nf = -(f[J] * q);
+    step_updates<J, 1, 3>(s, f, ns, nf);
+    __builtin_amdgcn_sched_barrier(0);
+    const double p = row_value<J + 1>(s[J + 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    step_updates<J, 3, 5>(s, f, ns, nf);
+    __builtin_amdgcn_sched_barrier(0);
+    const double x = __builtin_amdgcn_rcp(p);
+    __builtin_amdgcn_sched_barrier(0);
+    piv = r == J + 1 ? p : piv;
+    step_updates<J, 5, 8>(s, f, ns, nf);
+    const double x0 = p > 0.0 ? x : 0.0;
+    __builtin_amdgcn_sched_barrier(0);
+    const double e = fma(-p, x0, 1.0);
+    __builtin_amdgcn_sched_barrier(0);
+    step_updates<J, 8, 9>(s, f, ns, nf);
+    __builtin_amdgcn_sched_barrier(0);
+    const double e2 = fma(e, e, e);
+    __builtin_amdgcn_sched_barrier(0);
+    step_updates<J, 9, 10>(s, f, ns, nf);
+    __builtin_amdgcn_sched_barrier(0);
+    const double qn = fma(e2, x0, x0);           // the estimate's 26 bits and one step of third order: about 1 ulp
+    step_updates<J, 10, 32>(s, f, ns, nf);
+    factor_steps<J + 1>(s, f, piv, qn, r);
   }
 }
 
@@ -111,10 +158,13 @@ __device__ __forceinline__ void factor_diag(FactorShared& sh, int32_t* info, int
     s[c] = sh.diag[16 * c + r];
     f[c] = c == r ? 1.0 : 0.0;
   }
-  double piv = 1.0;
-  factor_steps<0>(s, f, piv, r, info, last_index);
+  double piv = row_value<0>(s[0]);                            // of lane r: pivot r, once its step is reached
+  const double x0 = piv > 0.0 ? __builtin_amdgcn_rcp(piv) : 0.0, e = fma(-piv, x0, 1.0);
+  factor_steps<0>(s, f, piv, fma(fma(e, e, e), x0, x0), r);
+  const uint64_t bad = __ballot(!(piv > 0.0)) & 0xffff;       // the first pivot in the order of the factorisation is reported
+  if (bad && lane == 0) atomicCAS(info, 0, last_index - __builtin_ctzll(bad));
   // column c of V and row c of W are scaled by 1 / sqrt(pivot c)
-  double rs = piv > 0.0 ? 1.0 / sqrt(piv) : 1.0;
+  double rs = piv > 0.0 ? rsqrt_of(piv) : 1.0;
   asm volatile("s_nop 1" : "+v"(rs));
   double w[16];
   [&]<int... C>(std::integer_sequence<int, C...>) {
@@ -144,16 +194,30 @@ __device__ __forceinline__ void factor_rows(const BlockFactor& a, FactorShared& 
   constexpr int NR = tile_rows(W);
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, ol = operand_lane(lane);
   f64x4 t[tile_base(W, NR)];
+  // A CU takes ~14 bytes per clock of what other CUs have just written, 20K clocks for the whole block: so only two tile columns
+  // are waited for at the start, and the others are requested kAhead columns ahead of their first update (step 0)
+  constexpr int kAhead = 4;
+  const int last = a.o0 + kFactorBlock - 1;
+  auto load_column = [&](int b) {
 #pragma unroll
-  for (int i = 0; i < NR; ++i)
+    for (int i = NR - 1; i >= 0; --i) {
+      if (b > tile_row(W, i)) continue;
+      const int row = 16 * tile_row(W, i) + r;
+      f64x4& d = t[tile_base(W, i) + b];
+      if (b < tile_row(W, i)) {
+        d = load_row4(a.F, a.ldf, a.n, last - row, last - 3 - 16 * b - 4 * g);
+      } else {
 #pragma unroll
-    for (int b = 0; b <= tile_row(W, i); ++b)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int row = 16 * tile_row(W, i) + r, col = 16 * b + 4 * g + v;       // counted from the end
-        const int fi = a.o0 + kFactorBlock - 1 - max(row, col), fj = a.o0 + kFactorBlock - 1 - min(row, col);
-        t[tile_base(W, i) + b][v] = fj < a.n ? a.F[(int64_t)fi * a.ldf + fj] : (fi == fj ? 1.0 : 0.0);
+        for (int v = 0; v < 4; ++v) {                                            // both halves from the upper triangle of F
+          const int col = 16 * b + 4 * g + v, fi = last - max(row, col), fj = last - min(row, col);
+          const double x = a.F[(int64_t)min(fi, a.n - 1) * a.ldf + min(fj, a.n - 1)];
+          d[v] = fj < a.n ? x : (fi == fj ? 1.0 : 0.0);
+        }
       }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  load_column(0);
   auto put_diag = [&](const f64x4& d) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) sh.diag[16 * (4 * g + v) + r] = d[v];
@@ -162,42 +226,43 @@ __device__ __forceinline__ void factor_rows(const BlockFactor& a, FactorShared& 
   for (int i = 0; i < NR; ++i)
     if (tile_row(W, i) == 0) put_diag(t[tile_base(W, i)]);
   lds_barrier();
+#pragma unroll
+  for (int b = 1; b <= kAhead; ++b) load_column(b);
 #pragma clang loop unroll(full)
   for (int k = 0; k < NT; ++k) {
     lds_barrier();                                             // W_kk is in LDS; every wavefront is done with column k - 1
     if (k == NT - 1) break;
     f64x4 nx[NR];
     const f64x4 wk = load_tile(sh.w, ol);
-#pragma unroll
-    for (int i = 0; i < NR; ++i)
-      if (tile_row(W, i) > k) {
-        const f64x4 x = tile_product(wk, t[tile_base(W, i) + k], f64x4{0.0, 0.0, 0.0, 0.0});
-        store_tile(sh.x[tile_row(W, i)], lane, x);
-        nx[i] = -x;
-      }
-    lds_barrier();                                             // column k of V is in LDS
-    // the diagonal tile that the next factorisation waits for; meanwhile each other wavefront updates one of its tiles
+    auto column = [&](int i) {                                 // V_ak of the wavefront's i-th row
+      const f64x4 x = tile_product(wk, t[tile_base(W, i) + k], f64x4{0.0, 0.0, 0.0, 0.0});
+      store_tile(sh.x[tile_row(W, i)], lane, x);
+      nx[i] = -x;
+    };
+    // the diagonal tile that the next factorisation waits for comes first
 #pragma unroll
     for (int i = 0; i < NR; ++i)
       if (tile_row(W, i) == k + 1) {
+        __builtin_amdgcn_s_setprio(2);
+        column(i);
+        wave_publish();
         f64x4& d = t[tile_base(W, i) + k + 1];
         d = tile_product(load_tile(sh.x[k + 1], ol), nx[i], d);
         put_diag(d);
+        __builtin_amdgcn_s_setprio(0);
       }
-    const bool owner = tile_row(W, 0) == k + 1 || (NR > 1 && tile_row(W, 1) == k + 1) || (NR > 2 && tile_row(W, 2) == k + 1);
-    const bool first_done = !owner && tile_row(W, 0) > k + 1;
-    if (first_done) {
-      f64x4& d = t[tile_base(W, 0) + k + 1];
-      d = tile_product(load_tile(sh.x[k + 1], ol), nx[0], d);
-    }
-    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+      if (tile_row(W, i) > k + 1) column(i);
+    lds_barrier();                                             // column k of V and the next diagonal tile are in LDS
 #pragma unroll
     for (int b = k + 1; b < NT; ++b) {
       if (b > tile_row(W, 0)) continue;
+      if (k == 0 && b + kAhead < NT) load_column(b + kAhead);
       const f64x4 xb = load_tile(sh.x[b], ol);
 #pragma unroll
       for (int i = 0; i < NR; ++i)
-        if (tile_row(W, i) >= b && !(b == k + 1 && (tile_row(W, i) == k + 1 || (i == 0 && first_done)))) {
+        if (tile_row(W, i) >= b && tile_row(W, i) > k + 1) {
           f64x4& d = t[tile_base(W, i) + b];
           d = tile_product(xb, nx[i], d);
         }
@@ -216,7 +281,6 @@ __global__ __launch_bounds__(512) void block_factor_kernel(BlockFactor a) {
         lds_barrier();
         if (k == NT - 1) break;
         lds_barrier();
-        lds_barrier();
       }
       break;
     case 4:
@@ -226,7 +290,6 @@ __global__ __launch_bounds__(512) void block_factor_kernel(BlockFactor a) {
         double* col = a.V + (int64_t)k * NT * TILE;
         store_tile(col + k * TILE, lane, load_tile(sh.w, lane));
         if (k == NT - 1) break;
-        lds_barrier();
         lds_barrier();
         for (int i = k + 1; i < NT; ++i) store_tile(col + i * TILE, lane, load_tile(sh.x[i], lane));
       }
@@ -256,10 +319,14 @@ __global__ __launch_bounds__(256) void block_panel_kernel(BlockPanel a) {
   for (int q = 0; q < 4; ++q)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int col = 16 * (wave + 4 * q) + 4 * g + v, fj = a.o0 + kFactorBlock - 1 - col;
-      if (inverse) t[q][v] = col == row0 + r ? 1.0 : 0.0;
-      else t[q][v] = fj < a.n ? a.F[(int64_t)(row0 + r) * a.ldf + fj] : 0.0;
+      const int col = 16 * (wave + 4 * q) + 4 * g + v;
+      t[q][v] = col == row0 + r ? 1.0 : 0.0;
     }
+  if (!inverse) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      t[q] = load_row4(a.F, a.ldf, a.n, row0 + r, a.o0 + kFactorBlock - 4 - 16 * (wave + 4 * q) - 4 * g);
+  }
   auto tile_of = [&](int k, int b) { return a.V + ((int64_t)k * NT + b) * TILE; };
   // left operands of a step, fetched during the step before: W_kk for its owner, V_bk of the wavefront's later columns b
   f64x4 wk, vb[4], wn, vn[4];
