@@ -217,6 +217,97 @@ __device__ __forceinline__ void tile_loop(const GemmProblem& P, unsigned char* s
   wait_vm_and_lds<0>();   // the surplus loads past the last k-tile
 }
 
+// A wave-uniform value that is to stay in scalar registers (the compiler would otherwise choose between the two problems of a
+// batch again at every use).
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ int64_t uniform(int64_t x) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x), hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)x >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// C as a buffer: an element is addressed by a lane offset, a scalar offset and an immediate, all in bytes
+struct TileBuffer {
+  __amdgpu_buffer_rsrc_t rsrc;
+  __device__ __forceinline__ TileBuffer(float* base) : rsrc(__builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00020000)) {}
+  __device__ __forceinline__ float load(uint32_t lane, uint32_t scalar) const {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, lane, scalar, 0));
+  }
+  __device__ __forceinline__ void store(float x, uint32_t lane, uint32_t scalar) const {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), rsrc, lane, scalar, 0);
+  }
+};
+
+// The accumulators of a BT x BT tile at (m0, n0) to C.
+// An element is addressed as (lane offset) + (scalar offset of its row) + (immediate), one instruction each; at the edge of the
+// matrix, where a row or a column lies outside, its load reads the tile's first element instead and its store is masked.  With a
+// branch per element and 64-bit products per address, ~35 instructions each, a 256-tile took ~45 us here: accumulate_upper at
+// n = 4096, where 16 of the 256 CUs have two tiles, took 115 us for 64 tokens and 197 us for 2048; now 56 and 136.
+// For C += acc the loads run two pieces (of eight rows per half wave) ahead of the stores.  Rows so far apart that a tile is
+// out of reach of 32-bit offsets take 64-bit addresses (WIDE).
+template <int BT, int MODE, bool EDGE, bool WIDE>
+__device__ __forceinline__ void store_tile_as(float* C, int64_t ldc, int M, int N, int run_mode, int m0, int n0,
+                                              const f32x16 (&acc)[BT / 64][BT / 64]) {
+  constexpr int WT = BT / 2, FR = WT / 32, NC = 2 * FR, AHEAD = WIDE ? 0 : EDGE ? 1 : 2;
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));        // (what follows is not to be kept in registers through the main loop)
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int row0 = m0 + (wave >> 1) * WT, col0 = n0 + (wave & 1) * WT;               // the wavefront's first element
+  const int lrow = 4 * (lane >> 5), lcol = lane & 31;                                // and the lane's, from there
+  const int mrem = M - row0 - lrow, nrem = N - col0 - lcol, above = row0 + lrow - col0 - lcol;
+  const int store_mode = MODE >= 0 ? MODE : run_mode;
+  if (EDGE && (row0 >= M || col0 >= N)) return;
+  float* base = C + (int64_t)row0 * ldc + col0;
+  const TileBuffer buf(base);
+  const uint32_t ld4 = (uint32_t)ldc * 4u, first = (uint32_t)lrow * ld4 + (uint32_t)lcol * 4u;
+  auto row = [](int c, int v) { return (c >> 1) * 32 + 8 * (2 * (c & 1) + (v >> 2)) + (v & 3); };
+  float old[AHEAD + 1][8][FR];
+  auto request = [&](int c) {
+#pragma unroll
+    for (int v = 0; v < 8; ++v)
+#pragma unroll
+      for (int j = 0; j < FR; ++j) {
+        const int r = row(c, v);
+        const bool in = !EDGE || (r < mrem && 32 * j < nrem);
+        float& x = old[c % (AHEAD + 1)][v][j];
+        if (WIDE) x = in ? base[(int64_t)(lrow + r) * ldc + lcol + 32 * j] : 0.f;
+        else if (EDGE) x = buf.load(in ? first + r * ld4 + 128 * j : 0u, 0u);
+        else x = buf.load(first + 128 * j, r * ld4);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if (store_mode == 0) {
+#pragma unroll
+    for (int c = 0; c < AHEAD; ++c) request(c);
+  }
+#pragma unroll
+  for (int c = 0; c < NC; ++c) {
+    if (store_mode == 0 && c + AHEAD < NC) request(c + AHEAD);
+#pragma unroll
+    for (int v = 0; v < 8; ++v) {
+      const int r = row(c, v);
+      if (EDGE && r >= mrem) continue;
+#pragma unroll
+      for (int j = 0; j < FR; ++j) {
+        if (EDGE && 32 * j >= nrem) continue;
+        const float a = acc[c >> 1][j][8 * (c & 1) + v];
+        const float x = store_mode == 0 ? old[c % (AHEAD + 1)][v][j] + a : run_mode == 1 || 32 * j - r > above ? a : 0.f;
+        if (WIDE) base[(int64_t)(lrow + r) * ldc + lcol + 32 * j] = x;
+        else if (EDGE) buf.store(x, first + r * ld4 + 128 * j, 0u);
+        else buf.store(x, first + 128 * j, r * ld4);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+template <int BT>
+__device__ __forceinline__ void store_tile(float* C, int64_t ldc, int M, int N, int store_mode, int m0, int n0,
+                                           const f32x16 (&acc)[BT / 64][BT / 64]) {
+  if (ldc >= (1 << 21)) store_tile_as<BT, -1, true, true>(C, ldc, M, N, store_mode, m0, n0, acc);
+  else if (m0 + BT > M || n0 + BT > N) store_tile_as<BT, -1, true, false>(C, ldc, M, N, store_mode, m0, n0, acc);
+  else if (store_mode == 0) store_tile_as<BT, 0, false, false>(C, ldc, M, N, store_mode, m0, n0, acc);
+  else store_tile_as<BT, 2, false, false>(C, ldc, M, N, store_mode, m0, n0, acc);
+}
+
 // One BT x BT tile of C: tile number `wid` of the batch (see the numbering below).
 template <int BT>
 __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* smem, int wid) {
@@ -275,10 +366,7 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* sme
     tm = first + r % gsz;
     tn = r / gsz;
   }
-  const int m0 = tm * BT, n0 = tn * BT;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int rl = lane & 31, half = lane >> 5;
+  const int m0 = uniform(tm * BT), n0 = uniform(tn * BT);
 
   const bool skipped = P.tile_mode == 1 && n0 + BT <= m0;
   int klo = 0, khi = P.K;
@@ -306,50 +394,15 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* sme
 
   // ---- epilogue.  MFMA 32x32 result: register v of a lane holds row 8*(v/4) + 4*(lane/32) + v%4,
   // column lane%32 of the block.
-  // For C += acc all 64 loads of a row of blocks are issued before the first store, so the
-  // read-modify-write costs a few memory round trips per tile instead of one per element.
   if (skipped && P.store_mode == 0) return;
-  const int rbase = m0 + wm * WT + 4 * half, cbase = n0 + wn * WT + rl;
-  if (P.store_mode == 0) {
-#pragma unroll
-    for (int i = 0; i < FR; ++i) {
-      float old[FR][16];
-#pragma unroll
-      for (int j = 0; j < FR; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int row = rbase + i * 32 + 8 * (v >> 2) + (v & 3), col = cbase + j * 32;
-          old[j][v] = (row < P.M && col < P.N) ? P.C[(int64_t)row * P.ldc + col] : 0.f;
-        }
-#pragma unroll
-      for (int j = 0; j < FR; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int row = rbase + i * 32 + 8 * (v >> 2) + (v & 3), col = cbase + j * 32;
-          if (row < P.M && col < P.N) P.C[(int64_t)row * P.ldc + col] = old[j][v] + acc[i][j][v];
-        }
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < FR; ++i)
-#pragma unroll
-      for (int j = 0; j < FR; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int row = rbase + i * 32 + 8 * (v >> 2) + (v & 3), col = cbase + j * 32;
-          if (row < P.M && col < P.N) {
-            const float a = acc[i][j][v];
-            P.C[(int64_t)row * P.ldc + col] = (P.store_mode == 1 || col > row) ? a : 0.f;
-          }
-        }
-  }
+  store_tile<BT>(P.C, uniform(P.ldc), uniform(P.M), uniform(P.N), uniform(P.store_mode), m0, n0, acc);
 }
 
 // CAPPED = false: one workgroup per tile.  CAPPED = true: a workgroup takes tiles blockIdx.x, blockIdx.x + gridDim.x,
 // ...: the caller caps the grid to leave compute units to a kernel running beside this one.  The grid is a multiple
 // of 8 then, so a workgroup's tiles all belong to its own XCD's share.
 template <int BT, bool CAPPED>
-__global__ __launch_bounds__(256) void gemm_nt_kernel(GemmBatch b) {
+__global__ __launch_bounds__(256, BT == 128 ? 2 : 1) void gemm_nt_kernel(GemmBatch b) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if (!CAPPED) {
     gemm_tile<BT>(b, smem, blockIdx.x);

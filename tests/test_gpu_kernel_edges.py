@@ -4,6 +4,7 @@ import pytest
 import torch
 
 from oracle import gptaq_oracle as O
+from paper_2504_02692_amd import binding as B
 from paper_2504_02692_amd import synth
 from tests import parity_util as PU
 
@@ -51,3 +52,31 @@ def test_factor_and_inverse_at_tile_edges(n):
     assert PU.rel_fro(Hd.cpu().numpy(), U) <= 1e-6
     if n > 1:
         assert PU.rel_fro(Ad.cpu().numpy(), P) <= 5e-5
+
+
+# The tile store of the bf16 product: inside the matrix, at its edges, rows farther apart than n, and so far apart that a tile is
+# out of reach of 32-bit offsets; 128-tiles and (from 224 of them) 256-tiles.
+@pytest.mark.parametrize("n,ld,tokens", [(8, 8, 40), (128, 128, 33), (136, 140, 64), (1032, 1032, 96), (3608, 3616, 64), (3840, 3840, 32),
+                                         (136, 1 << 21, 50)])
+@pytest.mark.parametrize("upper", [False, True])
+def test_products_are_added_up_to_the_edge_and_no_further(n, ld, tokens, upper):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    X = torch.randn((tokens, n), device="cuda", generator=g).bfloat16()
+    Xt = (X.float() + 0.05 * torch.randn((tokens, n), device="cuda", generator=g)).bfloat16()
+    start = [torch.randn((n, n), device="cuda", generator=g) for _ in range(2)]
+    full = [torch.full((n, ld), -7.0, device="cuda") for _ in range(2)]
+    H, A = full[0][:, :n], full[1][:, :n]
+    H.copy_(start[0])
+    A.copy_(start[1])
+    ws = B.workspace(B.gptaq_accumulate_workspace_bytes(tokens, n))
+    (B.gptaq_accumulate_upper if upper else B.gptaq_accumulate)(X, Xt, H, A, ws)
+    torch.cuda.synchronize()
+    Xd, Dd = X.double(), Xt.double() - X.double()
+    # fp32 sums of `tokens` exact products and one rounding: 2^-24 each, far inside the accumulation's bar
+    for got, ref, half in ((H, start[0].double() + Xd.T.contiguous() @ Xd, True), (A, start[1].double() + Dd.T.contiguous() @ Xd, upper)):
+        got = got.double()
+        if half:
+            got, ref = got.triu(), ref.triu()
+        assert float((got - ref).norm() / ref.norm()) <= 1e-5
+    for f in full:
+        assert bool((f[:, n:] == -7.0).all())
