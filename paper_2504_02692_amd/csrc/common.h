@@ -124,6 +124,7 @@ struct SbArgs {
   float* scales; float* zeros; uint8_t* codes;
   uint16_t *Eh, *El, *Vh, *Vl;       // -E and V of the super-block as bf16 hi/lo, row stride ldev (NULL: not wanted)
   int64_t ldev;
+  int clip_grid, clip_steps;         // clip-range search of every group (0 steps: plain min-max; groups only)
   int fast_rows;                     // rows of W and of codes may be stored 16 bytes at a time
 };
 // N4: four buffers of (kSbCols / 16) * kSbCols * 16 bf16 each.

@@ -441,7 +441,7 @@ __global__ __launch_bounds__(256) void zero_dead_columns_kernel(float* W, int64_
 static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const float* U, const float* P, int64_t ldh,
                              const uint8_t* dead, int bits, int group, int sym, uint8_t* codes, float* scales,
                              float* zeros, uint16_t* const* buf, uint16_t* const* farop, hipStream_t s, int terms,
-                             bool may_use_helper = true, bool make_farop = true) {
+                             int mse_grid, int mse_steps, bool may_use_helper = true, bool make_farop = true) {
   constexpr int64_t LDE = kSbCols;               // row stride of the -E / V buffers and of the far right operands
   if (dead) {
     hipLaunchKernelGGL(zero_dead_columns_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, s, W, ldw, (int)m, (int)n, dead);
@@ -456,10 +456,11 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
   a.G = group > 0 ? (int)(n / group) : 1;
   a.scales = scales; a.zeros = zeros; a.codes = codes;
   a.ldev = LDE;
+  a.clip_grid = mse_grid; a.clip_steps = group > 0 ? mse_steps : 0;
   a.fast_rows = (ldw % 4 == 0) && (((uintptr_t)W & 15) == 0) && (n % 16 == 0) && (((uintptr_t)codes & 15) == 0);
   if (group <= 0) {
     hipLaunchKernelGGL(row_params_kernel, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, W, ldw, (int)m, (int)n,
-                       (const uint8_t*)nullptr, a.maxq, sym, 0, 0, scales, zeros);
+                       (const uint8_t*)nullptr, a.maxq, sym, mse_grid, mse_steps, scales, zeros);
     GPTAQ_LAUNCH_CHECK();
   }
   const int nsb = (int)((n + kSbCols - 1) / kSbCols);
@@ -589,9 +590,9 @@ static int quantize_layer_impl(float* W, int64_t m, int64_t n, int64_t ldw, cons
   uint16_t* buf[24];
   for (int i = 0; i < 24; ++i) buf[i] = (uint16_t*)(base + L.off[i]);
 
-  // The super-block kernel takes groups that tile its 16/32/128-column pieces; the clip-range search and other
-  // group sizes go through the block-by-block kernels below.
-  if (mse_steps == 0 && (group <= 0 || group == 16 || group == 32 || group == 64 || group == 128)) {
+  // The super-block kernel takes groups that tile its 16/32/128-column pieces; other group sizes go through the
+  // block-by-block kernels below.
+  if (group <= 0 || group == 16 || group == 32 || group == 64 || group == 128) {
     // Rows are independent (Step 1).  A tall matrix goes through as two row halves on two streams: the super-block
     // kernel of one half, whose length is a chain of column steps whatever the number of rows, then runs beside the
     // far update of the other half instead of leaving the chip to it alone (and 344 workgroups of 64 rows no
@@ -622,16 +623,17 @@ static int quantize_layer_impl(float* W, int64_t m, int64_t n, int64_t ldw, cons
       for (int i = 0; i < 4; ++i) bufB[i] = buf[i] + mA * kSbCols;          // its rows of the -E / V buffers
       for (int i = 4; i < 12; ++i) bufB[i] = buf[12 + i];                  // operands of its own
       const int rcB = quantize_layer_sb(W + mA * ldw, mB, n, ldw, U, P, ldh, dead, bits, group, sym, codes + mA * n,
-                                        scales + mA * G, zeros + mA * G, bufB, farop, side->stream, terms, false, false);
+                                        scales + mA * G, zeros + mA * G, bufB, farop, side->stream, terms, mse_grid, mse_steps, false, false);
       const int rcA = quantize_layer_sb(W, mA, n, ldw, U, P, ldh, dead, bits, group, sym, codes, scales, zeros, buf, farop,
-                                        s, terms, false, false);
+                                        s, terms, mse_grid, mse_steps, false, false);
       // the helper stream is behind the caller's stream when the call returns, error or not
       const hipError_t keep = (hipError_t)gptaq_last_hip_error();
       if (hipEventRecord(ev_join, side->stream) == hipSuccess) hipStreamWaitEvent(s, ev_join, 0);
       if (rcA != GPTAQ_OK || rcB != GPTAQ_OK) set_last_hip_error(keep);
       return rcA != GPTAQ_OK ? rcA : rcB;
     }
-    return quantize_layer_sb(W, m, n, ldw, U, P, ldh, dead, bits, group, sym, codes, scales, zeros, buf, farop, s, terms);
+    return quantize_layer_sb(W, m, n, ldw, U, P, ldh, dead, bits, group, sym, codes, scales, zeros, buf, farop, s, terms,
+                             mse_grid, mse_steps);
   }
 
   QuantArgs a;

@@ -54,12 +54,18 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // Uniform affine min-max grid with 0 inside the range; the few operations per group are done in fp64 so
 // that the fp32 scale is the correctly rounded (xmax - xmin) / maxq.
-__device__ __forceinline__ void sb_grid_params(float xmin, float xmax, float maxq, int sym, float& scale, float& zero) {
+__device__ __forceinline__ double sb_grid_params(float xmin, float xmax, float maxq, int sym, float& scale, float& zero) {
   double lo = fmin((double)xmin, 0.0), hi = fmax((double)xmax, 0.0);
   if (sym) { hi = fmax(fabs(lo), hi); lo = -hi; }
   if (lo == 0.0 && hi == 0.0) { lo = -1.0; hi = 1.0; }
-  scale = (float)((hi - lo) / (double)maxq);
+  const double base = (hi - lo) / (double)maxq;
+  scale = (float)base;
   zero = sym ? (maxq + 1.f) * 0.5f : (float)rint(-lo / (double)scale);
+  return base;
+}
+// scale of candidate i of the clip-range search
+__device__ __forceinline__ float sb_clip_scale(double base, int i, int grid) {
+  return (float)((1.0 - (double)i / (double)grid) * base);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -111,6 +117,19 @@ struct SbShared {
   u32x4 codes[2][64];
   float Ud[2][kSub][kSbDiagLd], Pd[2][kSub][kSbDiagLd];     // diagonal pieces of U and P, transposed: [column][step]
   float dinv[2][kSub];                           // 1 / U_jj
+};
+
+// Clip-range search of a group of the current weights (Section 5.1; candidates p = 1 - i / grid of the min-max range, the smallest sum of squared errors wins, the
+// earlier one on ties).  The owner stages the group's weights, one row per lane, and all eight wavefronts search: each takes
+// every eighth candidate, so no sum crosses lanes.  Bound by its five instructions per weight and candidate: ~20 us per 128
+// columns and 80 candidates of 64 rows, whatever the number of workgroups.  (With one row per wavefront, two columns per
+// lane and a reduction over the lanes for each candidate, in a launch per 128 columns, a 4096 x 4096 layer took 3.61 ms; 1.64.)
+struct SbClip {
+  float w[128][64];                              // [column of the group][row]
+  double base[64];                               // full scale of the row's group, not yet rounded
+  float zero[64];
+  float err[kSbWaves][64];                       // the best of a wavefront's candidates
+  int cand[kSbWaves][64];
 };
 
 // 1 KB per wavefront from global memory straight into LDS: lane l's 16 bytes land at lds + 16 l.
@@ -214,10 +233,12 @@ __device__ __forceinline__ void sb_steps(float (&w)[kSub], const float (&u)[kSub
 // FAST: rows of W and of the codes are 16-byte aligned and n is a multiple of 16 (vector loads and stores).
 // TERMS: the update terms of Eq. 15 that are applied (3: both; a run-time choice would cost branches around every MFMA group,
 // and with them spills).
-template <bool FAST, int TERMS>
+// CLIP: the range of every group is searched (groups only; per-channel ranges come with the call).
+template <bool FAST, int TERMS, bool CLIP>
 __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char sb_smem[];
   SbShared& sh = *reinterpret_cast<SbShared*>(sb_smem);
+  SbClip& cl = *reinterpret_cast<SbClip*>(sb_smem + sizeof(SbShared));      // (with CLIP only)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l32 = lane & 31, lh = lane >> 5;
   const int row0 = blockIdx.x * 64;
@@ -331,6 +352,43 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
   if (wave == 7) fetch_for_owner(0);
   __syncthreads();
 
+  // this wavefront's part of the search for the group that starts at sub-block x; all wavefronts come here at the same x
+  auto search = [&]() {
+    constexpr int NC = 10;                                // candidates at a time: a weight is read once for all of them
+    sb_barrier();
+    const double base = cl.base[lane];
+    const float dlo = -cl.zero[lane], dhi = a.maxq + dlo;
+    float best = __builtin_inff();
+    int cand = 0;
+    for (int i0 = wave; i0 < a.clip_steps; i0 += NC * kSbWaves) {
+      float sc[NC], isc[NC], err[NC];
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        sc[k] = sb_clip_scale(base, min(i0 + k * kSbWaves, a.clip_steps - 1), a.clip_grid);
+        isc[k] = 1.f / sc[k];
+        err[k] = 0.f;
+      }
+#pragma unroll 4
+      for (int c = 0; c < a.group; ++c) {
+        const float x = cl.w[c][lane];
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+          const float d = fmaf(sc[k], __builtin_amdgcn_fmed3f(rintf(x * isc[k]), dlo, dhi), -x);
+          err[k] = fmaf(d, d, err[k]);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        const int i = i0 + k * kSbWaves;
+        if (i < a.clip_steps && err[k] < best) { best = err[k]; cand = i; }
+      }
+    }
+    cl.err[wave][lane] = best;
+    cl.cand[wave][lane] = cand;
+    sb_barrier();
+  };
+  auto group_starts = [&](int x) { return CLIP && (kSub * (x & 7)) % a.group == 0; };
+
   // ================= updater: sub-blocks before this wave's own
   int e = 0;
   if (first_own < last_own && first_own > 0) {
@@ -348,6 +406,7 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
       load_left(0, 1, left[1]);
     }
     for (; e < first_own; ++e) {
+      if (group_starts(e)) search();
       help(e);
       sb_barrier();
       if (!update) continue;
@@ -374,8 +433,22 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
       if (row < a.m) { g.sc = a.scales[row]; g.zr = a.zeros[row]; }
       g.isc = 1.f / g.sc;
     }
-    auto new_grid = [&](float lo, float hi, int x) {
-      sb_grid_params(lo, hi, a.maxq, a.sym, g.sc, g.zr);
+    auto new_grid = [&](float lo, float hi, int x) {      // (with CLIP the group's weights have been staged)
+      const double base = sb_grid_params(lo, hi, a.maxq, a.sym, g.sc, g.zr);
+      if (CLIP) {
+        cl.base[lane] = base;
+        cl.zero[lane] = g.zr;
+        search();
+        float best = __builtin_inff();
+        int cand = -1;
+#pragma unroll
+        for (int q = 0; q < kSbWaves; ++q) {
+          const float err = cl.err[q][lane];
+          const int i = cl.cand[q][lane];
+          if (err < best || (err == best && i < cand)) { best = err; cand = i; }
+        }
+        if (cand >= 0) g.sc = sb_clip_scale(base, cand, a.clip_grid);
+      }
       g.isc = 1.f / g.sc;
       if (row < a.m) {
         const int64_t o = (int64_t)row * a.G + (a.sb0 + kSub * x) / a.group;
@@ -404,6 +477,16 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
           mn[rh] = fminf(__uint_as_float(r0[0]), __uint_as_float(r0[1]));
           mx[rh] = fmaxf(__uint_as_float(r1[0]), __uint_as_float(r1[1]));
         }
+        if (CLIP) {
+#pragma unroll
+          for (int i = R; i < 4; ++i)
+            if (32 * (i - R) < a.group) {
+#pragma unroll
+              for (int rh = 0; rh < 2; ++rh)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) cl.w[32 * (i - R) + 8 * (v >> 2) + 4 * lh + (v & 3)][32 * rh + l32] = acc[i][rh][v];
+            }
+        }
         new_grid(lh ? mn[1] : mn[0], lh ? mx[1] : mx[0], x);
       }
       float w[kSub], u[kSub], p[kSub];
@@ -422,7 +505,11 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
       if (a.group == kSub) {                               // the group is this sub-block: its grid comes from the registers
         float mn = 0.f, mx = 0.f;
 #pragma unroll
-        for (int c = 0; c < kSub; ++c) { mn = fminf(mn, w[c]); mx = fmaxf(mx, w[c]); }
+        for (int c = 0; c < kSub; ++c) {
+          mn = fminf(mn, w[c]);
+          mx = fmaxf(mx, w[c]);
+          if (CLIP) cl.w[c][lane] = w[c];
+        }
         new_grid(mn, mx, x);
       }
       sb_pin(u);
@@ -479,6 +566,7 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
 
   // ================= finished
   for (; e < nev; ++e) {
+    if (group_starts(e)) search();
     help(e);
     sb_barrier();
   }
@@ -493,22 +581,28 @@ hipError_t launch_near_operands(const float* U, const float* P, int64_t ldh, int
   return hipGetLastError();
 }
 
-template <bool FAST, int TERMS>
+template <bool FAST, int TERMS, bool CLIP>
 static hipError_t launch_quant_sb_as(const SbArgs& a, hipStream_t s) {
-  constexpr int lds = (int)sizeof(SbShared);
+  constexpr int lds = (int)(sizeof(SbShared) + (CLIP ? sizeof(SbClip) : 0));
   static LdsLimitOnce once;                      // per instantiation
-  const hipError_t e = once.ensure(reinterpret_cast<const void*>(&quant_sb_kernel<FAST, TERMS>), lds);
+  const hipError_t e = once.ensure(reinterpret_cast<const void*>(&quant_sb_kernel<FAST, TERMS, CLIP>), lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((quant_sb_kernel<FAST, TERMS>), dim3((a.m + 63) / 64), dim3(64 * kSbWaves), lds, s, a);
+  hipLaunchKernelGGL((quant_sb_kernel<FAST, TERMS, CLIP>), dim3((a.m + 63) / 64), dim3(64 * kSbWaves), lds, s, a);
   return hipGetLastError();
+}
+
+template <int TERMS>
+static hipError_t launch_quant_sb_terms(const SbArgs& a, hipStream_t s) {
+  if (a.clip_steps > 0) return a.fast_rows ? launch_quant_sb_as<true, TERMS, true>(a, s) : launch_quant_sb_as<false, TERMS, true>(a, s);
+  return a.fast_rows ? launch_quant_sb_as<true, TERMS, false>(a, s) : launch_quant_sb_as<false, TERMS, false>(a, s);
 }
 
 hipError_t launch_quant_sb(const SbArgs& a, hipStream_t s) {
   switch (a.terms) {
-    case 3: return a.fast_rows ? launch_quant_sb_as<true, 3>(a, s) : launch_quant_sb_as<false, 3>(a, s);
-    case 2: return a.fast_rows ? launch_quant_sb_as<true, 2>(a, s) : launch_quant_sb_as<false, 2>(a, s);
-    case 1: return a.fast_rows ? launch_quant_sb_as<true, 1>(a, s) : launch_quant_sb_as<false, 1>(a, s);
-    default: return a.fast_rows ? launch_quant_sb_as<true, 0>(a, s) : launch_quant_sb_as<false, 0>(a, s);
+    case 3: return launch_quant_sb_terms<3>(a, s);
+    case 2: return launch_quant_sb_terms<2>(a, s);
+    case 1: return launch_quant_sb_terms<1>(a, s);
+    default: return launch_quant_sb_terms<0>(a, s);
   }
 }
 

@@ -80,3 +80,20 @@ def test_products_are_added_up_to_the_edge_and_no_further(n, ld, tokens, upper):
         assert float((got - ref).norm() / ref.norm()) <= 1e-5
     for f in full:
         assert bool((f[:, n:] == -7.0).all())
+
+
+# The clip-range search inside the super-block kernel: every group size it takes, one candidate, fewer candidates than wavefronts,
+# a full batch of ten per wavefront and one more, a last block cut short, a second super-block, rows that take no vector stores;
+# and per-channel ranges, searched before the column loop.
+@pytest.mark.parametrize("group,m,n,grid,steps", [(16, 65, 144, 100, 80), (32, 64, 160, 8, 1), (64, 130, 192, 10, 7), (128, 63, 1152, 100, 81),
+                                                  (128, 1, 128, 100, 100), (0, 66, 130, 100, 80)])
+def test_clip_search_in_the_column_loop(group, m, n, grid, steps):
+    k = max(256, n + n // 2)
+    Xb, Xtb = synth.make_activations(k, n, 37, "clip", 2, 20.0)
+    H, A = O.accumulate(Xb, Xtb)
+    U, P, _ = O.prepare(H, A, 0.01)
+    U32, P32 = U.astype(np.float32), P.astype(np.float32)
+    W = synth.make_weights(m, n, 37, f"clip{m}x{n}")
+    got = PU.gpu_quantize(W, dev(U32), dev(P32), 4, group, False, 128, mse=(grid, steps))
+    PU.check_against_oracle(W, U32.astype(np.float64), P32.astype(np.float64), got, 4, group, False,
+                            label=f"clip g{group} {m}x{n} {steps}/{grid}", mse=(grid, steps))
