@@ -74,14 +74,27 @@ __device__ __forceinline__ uint16_t bf16_rne(float f) {
 }
 __device__ __forceinline__ float bf16_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
+// The two products of Theorem 4.2 only read the operand blocks of kSplitBlock^2 on and above the diagonal (their tiles start
+// and their k ranges begin at multiples of a tile edge that divides it), so the others are not written: a third of
+// extract_U_kernel's bytes and two thirds of split_rows_kernel's.
+constexpr int kSplitBlock = 256;
+
 // U (fp32, upper, zeros below) from F; its bf16 hi/lo split row-major (Uh, Ul) and
-// transposed (Uth, Utl), all zero-padded to np x np.   grid (np/64, np/64), 256 threads.
+// transposed (Uth, Utl), zero-padded to np x np.   grid (np/64, np/64), 256 threads.
 __global__ __launch_bounds__(256) void extract_U_kernel(const double* F, int64_t ldf, int n, float* U, int64_t ldu,
                                                         uint16_t* Uh, uint16_t* Ul, uint16_t* Uth, uint16_t* Utl,
                                                         int64_t np) {
   __shared__ uint16_t th[64][66], tl[64][66];
   const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
   const int c = threadIdx.x & 63, rb = threadIdx.x >> 6;
+  if (c0 / kSplitBlock < r0 / kSplitBlock) {
+    for (int p = 0; p < 16; ++p) {
+      const int gr = r0 + rb + 4 * p, gc = c0 + c;
+      if (gr < n && gc < n) U[(int64_t)gr * ldu + gc] = 0.f;
+    }
+    return;
+  }
+#pragma unroll 4
   for (int p = 0; p < 16; ++p) {
     const int r = rb + 4 * p, gr = r0 + r, gc = c0 + c;
     float u = 0.f;
@@ -112,7 +125,7 @@ __global__ __launch_bounds__(256) void extract_U_kernel(const double* F, int64_t
 __global__ __launch_bounds__(256) void split_rows_kernel(const float* A, int64_t lda, int n, const uint8_t* zero_rows,
                                                          uint16_t* Ah, uint16_t* Al, int64_t np, int32_t* info) {
   const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x, r = blockIdx.y;
-  if (c >= np) return;
+  if (c >= np || c / kSplitBlock < r / kSplitBlock) return;
   float v = 0.f;
   if (r < n && c < n && c > r && !(zero_rows && zero_rows[r])) v = A[r * lda + c];
   if (info && !__builtin_isfinite(v)) atomicMin(info, -(1 + (int)r));
@@ -183,6 +196,8 @@ extern "C" int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, floa
   const int64_t ldf = round_up(n, 16);
   uint16_t* bb[6];
   for (int i = 0; i < 6; ++i) bb[i] = (uint16_t*)(base + L.off_b[i]);
+  const int64_t np = L.np;
+  uint16_t *Uh = bb[0], *Ul = bb[1], *Uth = bb[2], *Utl = bb[3], *Ah = bb[4], *Al = bb[5];
   const int ni = (int)n;
 
   hipLaunchKernelGGL(diag_stats_kernel, dim3(1), dim3(1024), 0, s, H, ldh, ni, damp, deadbuf, lam, info);
@@ -213,6 +228,10 @@ extern "C" int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, floa
     hipEvent_t ev_fork = side->events[3 * nob];
     chk(hipEventRecord(ev_fork, s));                          // the helper stream starts behind build_F
     chk(hipStreamWaitEvent(sb, ev_fork, 0));
+    // dXXT (dead rows zeroed) split for the products at the end: it depends on nothing here and runs beside the first block
+    hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)((np + 255) / 256), (unsigned)np), dim3(256), 0, sb, dXXT, ldh, ni,
+                       deadbuf, Ah, Al, np, info);
+    chk(hipGetLastError());
     for (int ob = nob - 1; ob >= 0 && ok; --ob) {
       const int o0 = ob * NBO, o1 = (int)(n < o0 + NBO ? n : o0 + NBO), wo = o1 - o0;
       const I8Operand &Vs = sl[ob & 1], &Ucol = sl[3 + (ob & 1)];
@@ -260,16 +279,10 @@ extern "C" int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, floa
       return GPTAQ_ELAUNCH;
     }
   }
-  // U -> H (fp32) and the bf16 splits; dXXT (dead rows zeroed) split.
-  const int64_t np = L.np;
-  uint16_t *Uh = bb[0], *Ul = bb[1], *Uth = bb[2], *Utl = bb[3], *Ah = bb[4], *Al = bb[5];
+  // U -> H (fp32) and the bf16 splits.
   hipLaunchKernelGGL(extract_U_kernel, dim3((unsigned)(np / 64), (unsigned)(np / 64)), dim3(256), 0, s, F, ldf, ni, H,
                      ldh, Uh, Ul, Uth, Utl, np);
   GPTAQ_LAUNCH_CHECK();
-  hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)((np + 255) / 256), (unsigned)np), dim3(256), 0, s, dXXT, ldh,
-                     ni, deadbuf, Ah, Al, np, info);
-  GPTAQ_LAUNCH_CHECK();
-
   // The K ranges of these two products are triangular, so tiles differ in length by the whole of K: the tile list is
   // dealt to the XCDs four tiles at a time (`deal`), not in contiguous runs (n = 11008: 2.8 -> 1.2 ms per product), and
   // while 256-tiles make a single round, the longest one sets the time and 128-tiles balance better (n = 4096)
