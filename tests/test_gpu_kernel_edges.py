@@ -97,3 +97,11 @@ def test_clip_search_in_the_column_loop(group, m, n, grid, steps):
     got = PU.gpu_quantize(W, dev(U32), dev(P32), 4, group, False, 128, mse=(grid, steps))
     PU.check_against_oracle(W, U32.astype(np.float64), P32.astype(np.float64), got, 4, group, False,
                             label=f"clip g{group} {m}x{n} {steps}/{grid}", mse=(grid, steps))
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1023, 1025, 2100])
+def test_ranking_of_the_diagonal(n):
+    """64 inputs per workgroup, 1024 compared at a time; many equal entries."""
+    d = np.random.default_rng(n).integers(0, 40, n).astype(np.float32)
+    perm = B.gptaq_act_order(dev(np.diag(d)))
+    assert np.array_equal(perm.cpu().numpy(), O.act_order_permutation(np.diag(d)))
