@@ -105,3 +105,20 @@ def test_ranking_of_the_diagonal(n):
     d = np.random.default_rng(n).integers(0, 40, n).astype(np.float32)
     perm = B.gptaq_act_order(dev(np.diag(d)))
     assert np.array_equal(perm.cpu().numpy(), O.act_order_permutation(np.diag(d)))
+
+
+# Rows of 16-byte pieces (one, as many as the lanes keep, one more, a third round) and rows that are not; levels up to 16 bits.
+@pytest.mark.parametrize("n", [8, 7, 2048, 2056, 2500, 4104])
+@pytest.mark.parametrize("bits,clip", [(4, 0.9), (2, 1.0), (8, 0.3), (16, 0.9)])
+def test_activation_quantiser_rows(n, bits, clip):
+    Xb, _ = synth.make_activations(9, n, 13, "rows", 1, 20.0)
+    Xb = Xb.copy()
+    Xb[3] = 0                                    # an empty range
+    Xb[4] = (Xb[4] & 0x807f) | (0x01 << 7)       # a range whose scale is a denormal number without a reciprocal
+    Xb[5] = (Xb[5] & 0x807f) | (0xf0 << 7)       # a scale whose reciprocal is one
+    X = PU.to_dev_bf16(Xb)
+    got = B.gptaq_fake_quant_activations(X, bits, clip).contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
+    ref, _, hints = O.fake_quant_activations(Xb, bits, clip, hint_bits=got, tau=PU.tau_for(bits))
+    # (near-ties of x / scale in fp64; the library decides by the sign of an exact residual)
+    assert hints <= max(2, PU.MAX_HINT_FRAC * got.size)
+    assert np.array_equal(ref, got)
