@@ -278,19 +278,29 @@ __global__ __launch_bounds__(64 * NW) void quant_block_kernel(QuantArgs a) {
 __device__ __forceinline__ void split_transpose_rows_tile(const float* S, int64_t ldh, int n, int sb0, int blocksize,
                                                           int chunk, int c_begin, int c_end, uint16_t* oh, uint16_t* ol,
                                                           int64_t ldo) {
-  __shared__ uint16_t th[64][QB + 2], tl[64][QB + 2];
+  __shared__ __attribute__((aligned(4))) uint16_t th[64][QB + 2], tl[64][QB + 2];
   const int i0 = sb0 + chunk * blocksize;
   const int bw = min(blocksize, n - i0);
   const int j0 = blockIdx.x * 64;
   const int c = threadIdx.x & 63, kq = threadIdx.x >> 6;
   const int col = c_begin + j0 + c;
-  for (int p = 0; p < QB / 4; ++p) {
-    const int kk = kq + 4 * p;
-    float v = 0.f;
-    if (kk < bw && col < c_end) v = S[(int64_t)(i0 + kk) * ldh + col];
-    const uint16_t h = q_bf16_rne(v);
-    th[c][kk] = h;
-    tl[c][kk] = q_bf16_rne(v - q_bf16_f32(h));
+  // (all 32 loads of a thread in flight at once, from clamped addresses: a branch around each waits for it)
+  float v[QB / 4];
+  const float* src = S + min(col, n - 1);
+#pragma unroll
+  for (int p = 0; p < QB / 4; ++p) v[p] = src[(int64_t)min(i0 + 8 * (p >> 1) + 2 * kq + (p & 1), n - 1) * ldh];
+#pragma unroll
+  for (int p = 0; p < QB / 4; p += 2) {
+    const int kk = 4 * p + 2 * kq;                       // two consecutive k, a dword of each output
+    uint16_t h[2], l[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const float x = kk + q < bw && col < c_end ? v[p + q] : 0.f;
+      h[q] = q_bf16_rne(x);
+      l[q] = q_bf16_rne(x - q_bf16_f32(h[q]));
+    }
+    *reinterpret_cast<uint32_t*>(&th[c][kk]) = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
+    *reinterpret_cast<uint32_t*>(&tl[c][kk]) = (uint32_t)l[0] | ((uint32_t)l[1] << 16);
   }
   __syncthreads();
   // 64 rows x 128 bf16 = 64 x 64 dwords; thread t writes dword (t & 63) of rows (t >> 6) + 4p
@@ -479,10 +489,12 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
   }
   bool ok = true;
   auto chk = [&](hipError_t e) { if (e != hipSuccess && ok) { ok = false; set_last_hip_error(e); } };
-  if (make_farop && terms != 0 && nsb >= 2) {
+  auto make_far_operands = [&]() {
     // right operands of every far update: rows of U and P of each super-block, the columns after it, transposed to
     // (column x K) and split into bf16 hi + lo; a GEMM reads whole tiles of rows, hence the zero rows past n.  With two
-    // chains the pass runs on the helper stream, beside the first super-block.
+    // chains the pass runs on the helper stream beside the first super-block, behind that one's near operands: its many
+    // small workgroups must not be on every CU before the super-block kernel asks for 64 empty ones
+    // (n = 11008: that kernel then took 483 us instead of 180).
     hipStream_t st = s;
     if (two_chains) {
       st = side->stream;
@@ -496,7 +508,8 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
       chk(hipGetLastError());
     }
     if (two_chains) chk(hipEventRecord(side->events[2 * nsb + 2], st));
-  }
+  };
+  const bool far_operands = make_farop && terms != 0 && nsb >= 2;
   auto ev_sbk = [&](int k) { return side->events[2 * k]; };       // super-block k's kernel has finished
   auto ev_far2 = [&](int k) { return side->events[2 * k + 1]; };  // its far2 update has finished
   // W[:, c0:c1] += [-E | V] [U; P][super-block rows, c0:c1]: -E and V from buffer set `set`, the right operands of
@@ -534,6 +547,7 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
       ProfScope ps(kProfTrailSplit, s);
       chk(launch_near_operands(U, (terms & 2) ? P : nullptr, ldh, (int)n, (int)sb0, a.sbw, buf + 8, s));
     }
+    if (k == 0 && far_operands) make_far_operands();
     {
       ProfScope ps(kProfColumnLoop, s);
       chk(launch_quant_sb(a, s));
