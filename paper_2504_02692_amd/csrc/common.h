@@ -122,8 +122,8 @@ struct SbArgs {
   const uint8_t* dead;
   float maxq; int group, sym, G, terms;
   float* scales; float* zeros; uint8_t* codes;
-  uint16_t *Eh, *El, *Vh, *Vl;       // -E and V of the super-block as bf16 hi/lo, row stride ldev (NULL: not wanted)
-  int64_t ldev;
+  uint16_t *Eh, *El, *Vh, *Vl;       // -E and V of the super-block as bf16 hi/lo, k-tile-major (NULL: not wanted): element
+  int64_t evkt;                      // (row, k) at (k / 32) * evkt + 32 * row + k % 32
   int clip_grid, clip_steps;         // clip-range search of every group (0 steps: plain min-max; groups only)
   int fast_rows;                     // rows of W and of codes may be stored 16 bytes at a time
 };

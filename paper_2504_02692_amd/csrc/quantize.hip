@@ -275,6 +275,8 @@ __global__ __launch_bounds__(64 * NW) void quant_block_kernel(QuantArgs a) {
 // sb0 + c * blocksize .. of U and P), the entries in the columns [c_begin, c_end), transposed to
 // (column x K) with the chunk's rows at K offsets 128 c .. 128 c + 127 (zero padded), split into bf16 hi+lo.
 // grid (ceil(padded columns / 64), 2, chunks): blockIdx.y = 0 for U, 1 for P.
+// KTILES: the outputs are k-tile-major (element (r, k) at (k / 32) ldo + 32 r + k % 32), else row-major (r ldo + k).
+template <bool KTILES>
 __device__ __forceinline__ void split_transpose_rows_tile(const float* S, int64_t ldh, int n, int sb0, int blocksize,
                                                           int chunk, int c_begin, int c_end, uint16_t* oh, uint16_t* ol,
                                                           int64_t ldo) {
@@ -303,14 +305,17 @@ __device__ __forceinline__ void split_transpose_rows_tile(const float* S, int64_
     *reinterpret_cast<uint32_t*>(&tl[c][kk]) = (uint32_t)l[0] | ((uint32_t)l[1] << 16);
   }
   __syncthreads();
-  // 64 rows x 128 bf16 = 64 x 64 dwords; thread t writes dword (t & 63) of rows (t >> 6) + 4p
-  const int d = threadIdx.x & 63;
+  // 64 rows x 128 bf16 = 64 x 64 dwords.  Row-major: thread t writes dword (t & 63) of rows (t >> 6) + 4p.  k-tile-major: the
+  // four k-tiles in turn, 64 rows of 16 dwords each in one run.
   for (int p = 0; p < 16; ++p) {
-    const int r = (threadIdx.x >> 6) + 4 * p;
+    const int item = threadIdx.x + 256 * p, r = KTILES ? (item >> 4) & 63 : item >> 6;
+    const int d = KTILES ? (item >> 10) * 16 + (item & 15) : item & 63;
     const uint32_t vh = (uint32_t)th[r][2 * d] | ((uint32_t)th[r][2 * d + 1] << 16);
     const uint32_t vl = (uint32_t)tl[r][2 * d] | ((uint32_t)tl[r][2 * d + 1] << 16);
-    reinterpret_cast<uint32_t*>(oh + (int64_t)(j0 + r) * ldo + chunk * QB)[d] = vh;
-    reinterpret_cast<uint32_t*>(ol + (int64_t)(j0 + r) * ldo + chunk * QB)[d] = vl;
+    const int64_t o = KTILES ? (int64_t)(chunk * (QB / 32) + (d >> 4)) * ldo + (int64_t)(j0 + r) * 32 + 2 * (d & 15)
+                             : (int64_t)(j0 + r) * ldo + chunk * QB + 2 * d;
+    *reinterpret_cast<uint32_t*>(oh + o) = vh;
+    *reinterpret_cast<uint32_t*>(ol + o) = vl;
   }
 }
 
@@ -318,7 +323,7 @@ __global__ __launch_bounds__(256) void split_transpose_rows_kernel(const float* 
                                                                    int sb0, int blocksize, int c_begin, int c_end,
                                                                    uint16_t* Uth, uint16_t* Utl, uint16_t* Pth,
                                                                    uint16_t* Ptl, int64_t ldo) {
-  split_transpose_rows_tile(blockIdx.y ? P : U, ldh, n, sb0, blocksize, blockIdx.z, c_begin, c_end,
+  split_transpose_rows_tile<false>(blockIdx.y ? P : U, ldh, n, sb0, blocksize, blockIdx.z, c_begin, c_end,
                             blockIdx.y ? Pth : Uth, blockIdx.y ? Ptl : Utl, ldo);
 }
 
@@ -331,7 +336,9 @@ __host__ __device__ inline int64_t far_rows(int64_t n, int k) {
 
 // The far right operands of EVERY super-block that has columns after it, in one launch: they depend on U and P only,
 // so nothing of this has to sit between two super-blocks.  Super-block k's operands start at row sum_{i<k} far_rows(i)
-// of the four output arrays (row stride kSbCols); row r of its part holds column (k + 1) * kSbCols + r.
+// of the four output arrays; row r of its part holds column (k + 1) * kSbCols + r.  A part is k-tile-major like -E and V: a
+// 256-row k-tile is one run of 16 KB (row-major, 64 bytes of every 2 KB, it was two half-used lines per row: layers of
+// 4096 x 11008 4.27 -> 3.94 ms, of 22016 x 4096 2.87 -> 2.57).
 // grid (far_rows(0) / 64, 2, 8 * number of such super-blocks): blockIdx.z = 8 k + chunk of 128 rows of the super-block.
 __global__ __launch_bounds__(256) void far_operands_all_kernel(const float* U, const float* P, int64_t ldh, int n,
                                                                uint16_t* Uth, uint16_t* Utl, uint16_t* Pth,
@@ -341,8 +348,8 @@ __global__ __launch_bounds__(256) void far_operands_all_kernel(const float* U, c
   int64_t first = 0;
   for (int i = 0; i < k; ++i) first += far_rows(n, i);
   const int64_t o = first * kSbCols;
-  split_transpose_rows_tile(blockIdx.y ? P : U, ldh, n, k * kSbCols, QB, chunk, (k + 1) * kSbCols, n,
-                            (blockIdx.y ? Pth : Uth) + o, (blockIdx.y ? Ptl : Utl) + o, (int64_t)kSbCols);
+  split_transpose_rows_tile<true>(blockIdx.y ? P : U, ldh, n, k * kSbCols, QB, chunk, (k + 1) * kSbCols, n,
+                                  (blockIdx.y ? Pth : Uth) + o, (blockIdx.y ? Ptl : Utl) + o, far_rows(n, k) * 32);
 }
 
 }  // namespace gptaq
@@ -452,7 +459,7 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
                              const uint8_t* dead, int bits, int group, int sym, uint8_t* codes, float* scales,
                              float* zeros, uint16_t* const* buf, uint16_t* const* farop, hipStream_t s, int terms,
                              int mse_grid, int mse_steps, bool may_use_helper = true, bool make_farop = true) {
-  constexpr int64_t LDE = kSbCols;               // row stride of the -E / V buffers and of the far right operands
+  const int64_t ev_kt = round_up(m, 256) * 32;   // a k-tile of the -E / V buffers, in elements
   if (dead) {
     hipLaunchKernelGGL(zero_dead_columns_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, s, W, ldw, (int)m, (int)n, dead);
     GPTAQ_LAUNCH_CHECK();
@@ -465,7 +472,7 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
   a.maxq = (float)((1 << bits) - 1); a.group = group; a.sym = sym; a.terms = terms;
   a.G = group > 0 ? (int)(n / group) : 1;
   a.scales = scales; a.zeros = zeros; a.codes = codes;
-  a.ldev = LDE;
+  a.evkt = ev_kt;
   a.clip_grid = mse_grid; a.clip_steps = group > 0 ? mse_steps : 0;
   a.fast_rows = (ldw % 4 == 0) && (((uintptr_t)W & 15) == 0) && (n % 16 == 0) && (((uintptr_t)codes & 15) == 0);
   if (group <= 0) {
@@ -519,8 +526,8 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     int64_t first = 0;
     for (int i = 0; i < k; ++i) first += far_rows(n, i);
     const uint16_t* rop[4];
-    for (int i = 0; i < 4; ++i) rop[i] = farop[i] + first * LDE;
-    const int64_t nt = c1 - c0, ro = (c0 - cbase) * LDE;
+    for (int i = 0; i < 4; ++i) rop[i] = farop[i] + first * kSbCols;
+    const int64_t nt = c1 - c0, ro = (c0 - cbase) * 32, far_kt = far_rows(n, k) * 32;
     const int tile = gemm_tile_for(m, nt);
     GemmBatch b{};
     b.nprob = 1; b.tile = tile; b.max_wgs = max_wgs;
@@ -528,8 +535,8 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     g.C = W + c0; g.ldc = ldw; g.M = (int)m; g.N = (int)nt; g.K = kSbCols;
     g.tiles_m = (int)(round_up(m, tile) / tile); g.tiles_n = (int)(round_up(nt, tile) / tile);
     g.kind = 2; g.nterm = 0; g.tile_mode = 0; g.k_mode = 0; g.store_mode = 0;
-    if (terms & 1) g.term[g.nterm++] = {{ev[0], ev[1]}, {rop[0] + ro, rop[1] + ro}, LDE, LDE, 32, 32};
-    if (terms & 2) g.term[g.nterm++] = {{ev[2], ev[3]}, {rop[2] + ro, rop[3] + ro}, LDE, LDE, 32, 32};
+    if (terms & 1) g.term[g.nterm++] = {{ev[0], ev[1]}, {rop[0] + ro, rop[1] + ro}, 32, 32, ev_kt, far_kt};
+    if (terms & 2) g.term[g.nterm++] = {{ev[2], ev[3]}, {rop[2] + ro, rop[3] + ro}, 32, 32, ev_kt, far_kt};
     ProfScope ps(kProfTrailGemm, st);
     chk(launch_gemm(b, st));
   };

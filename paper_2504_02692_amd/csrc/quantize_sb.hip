@@ -334,7 +334,7 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
       for (int it = 0; it < 2; ++it) {
         const int item = lane + 64 * it, r = item >> 1, ch = item & 1;
         if (row0 + r < a.m) {
-          const int64_t o = (int64_t)(row0 + r) * a.ldev + kSub * x + 8 * ch;
+          const int64_t o = (int64_t)(x >> 1) * a.evkt + (int64_t)(row0 + r) * 32 + kSub * (x & 1) + 8 * ch;
           *reinterpret_cast<u32x4*>(a.Eh + o) = sh.frag[buf][0][r >> 5][32 * ch + (r & 31)];
           *reinterpret_cast<u32x4*>(a.El + o) = sh.frag[buf][1][r >> 5][32 * ch + (r & 31)];
           *reinterpret_cast<u32x4*>(a.Vh + o) = sh.frag[buf][2][r >> 5][32 * ch + (r & 31)];
