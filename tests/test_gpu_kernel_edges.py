@@ -36,6 +36,39 @@ def test_column_loop_at_the_edges_of_its_blocks(bits, group, m, n, terms):
                             label=f"edge W{bits} g{group} {m}x{n} terms {terms}", terms=terms)
 
 
+def bf16_rne(x):
+    return torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).bfloat16().float().numpy()
+
+
+# Where the update of a column comes from: the rest of its sub-block's piece, another piece of the same block, another block of
+# the super-block, the product after it.
+@pytest.mark.parametrize("dst", [16, 32, 128, 1024])
+def test_error_operand_carries_the_unrounded_product(dst):
+    """-E = (W^ - v) / U_jj enters the products as bf16 hi + lo, lo the rounding of what hi leaves of (W^ - v) (1 / U_jj) before
+    that product is rounded to fp32.  One column with an error meets one zero weight through a power of two, so the updated
+    weight IS hi + lo, and the range of its group shows every bit of it."""
+    m, n, bits, group, maxq = 4096, dst + 16, 4, 16, 15.0
+    g = np.random.default_rng(dst)
+    W = np.zeros((m, n), np.float32)
+    W[:, 0] = g.uniform(0.1, 0.9, m)
+    W[:, 1] = 1.0                                # the range of the first group
+    U = np.diag(g.uniform(1.0, 2.0, n)).astype(np.float32)
+    U[0, dst] = 0.5
+    got = PU.gpu_quantize(W, dev(U), None, bits, group, False, 128, terms=1)
+    sc, d = got["scales"][:, 0].astype(np.float64), got["codes"][:, 0] - got["zeros"][:, 0].astype(np.float64)
+    v = W[:, 0].astype(np.float64)
+    t = (sc * d - v).astype(np.float32).astype(np.float64)         # (fp64 holds the product and the sum exactly)
+    prod = t * np.float64(np.float32(1) / U[0, 0])                 # exact: 48 bits
+    hi = bf16_rne(prod.astype(np.float32)).astype(np.float64)
+    lo = bf16_rne((prod - hi).astype(np.float32)).astype(np.float64)
+    old = bf16_rne((prod.astype(np.float32) - hi).astype(np.float32)).astype(np.float64)
+    w = 0.5 * (hi + lo)
+    rows = w == w.astype(np.float32)             # where the updated weight is exact: lo is not all but zero
+    assert rows.mean() > 0.9 and (lo != old)[rows].any()           # the inputs tell the two apart
+    want = np.where(w == 0, 2.0 / maxq, np.abs(w) / maxq).astype(np.float32)
+    assert np.array_equal(got["scales"][rows, dst // group], want[rows])
+
+
 # Sizes around the 16-column tiles and the 256-column outer blocks of the factorisation: a block of identity padding and one
 # column, part of a tile, whole tiles, one column into the next block, three blocks with a ragged first one.
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 47, 240, 241, 255, 257, 273, 528, 767])
