@@ -263,7 +263,7 @@ extern "C" int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, floa
       // ---- inverse chain
       chk(hipStreamWaitEvent(sb, ev_factored, 0));
       chk(launch_gemm_i8s(Vs, 0, Vs, 0, F, ldf, c_lo, c_lo, wo, -1.0, 1, 1, sb));
-      chk(hipEventRecord(side->events[2 * nob + ob], sb));
+      if (ob >= 1) chk(hipEventRecord(side->events[2 * nob + ob], sb));
       double* FJ = F + (int64_t)o0 * ldf + o1;                  // block row OB right of the diagonal block
       chk(launch_slice_i8(FJ, 1, ldf, ni - o1, wo, RJs, sb));   // R_OB,J (digits per column of it)
       chk(launch_slice_i8(Uob, NBO, 1, wo, wo, Urow, sb));
@@ -272,21 +272,17 @@ extern "C" int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, floa
       chk(launch_gemm_i8s(Vs, 0, RJs, 0, F + o1, ldf, o0, ni - o1, wo, -1.0, 1, 0, sb));         // R_I,J -= V_I,OB U_OB,J
       chk(launch_gemm_i8s(Vs, 0, Ucol, 0, F + o0, ldf, o0, wo, wo, -1.0, 0, 0, sb));             // R_I,OB = -V_I,OB U_OB,OB
       chk(hipGetLastError());
-      chk(hipEventRecord(ev_inverted, sb));
+      if (ob >= 2) chk(hipEventRecord(ev_inverted, sb));       // (the join is behind the last two)
     }
-    // join: everything after the sweep runs on the caller's stream (blocks 0 and 1 have not been waited for yet)
-    if (ok) {
-      chk(hipStreamWaitEvent(s, side->events[1], 0));
-      if (nob > 1) chk(hipStreamWaitEvent(s, side->events[3], 0));
-    }
-    if (!ok) {
-      // a launch or an event call failed part-way: whatever the helper stream was given so far must still be behind
-      // the caller's stream when the call returns, so the join is made with a fresh record of the helper stream
-      const hipError_t keep = (hipError_t)gptaq_last_hip_error();
-      if (hipEventRecord(ev_fork, sb) == hipSuccess) hipStreamWaitEvent(s, ev_fork, 0);
-      set_last_hip_error(keep);
-      return GPTAQ_ELAUNCH;
-    }
+    // join: everything after the sweep runs on the caller's stream, and whatever the helper stream was given is behind it when
+    // the call returns, also if a launch or an event call failed part-way
+    hipEvent_t ev_join = side->events[3 * nob + 1];
+    const hipError_t keep = (hipError_t)gptaq_last_hip_error();
+    hipError_t joined = hipEventRecord(ev_join, sb);
+    if (joined == hipSuccess) joined = hipStreamWaitEvent(s, ev_join, 0);
+    if (ok) chk(joined);
+    else set_last_hip_error(keep);
+    if (!ok) return GPTAQ_ELAUNCH;
   }
   // U -> H (fp32) and the bf16 splits.
   hipLaunchKernelGGL(extract_U_kernel, dim3((unsigned)(np / 64), (unsigned)(np / 64)), dim3(256), 0, s, F, ldf, ni, H,

@@ -42,9 +42,10 @@ SideStream* side_stream(int nevents) {
   if (!ss.stream && hipStreamCreateWithFlags(&ss.stream, hipStreamNonBlocking) != hipSuccess) return nullptr;
   while ((int)ss.events.size() < nevents) {
     hipEvent_t e;
-    // They order kernels of one device, so the release may stop at the device: a record with the fence to the host's memory in it
-    // held the factor chain of gptaq_prepare up by ~5 us per 256 columns (n = 4096: 2.32 -> 2.18 ms).
-    if (hipEventCreateWithFlags(&e, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess) return nullptr;
+    // The default release.  (hipEventDisableSystemFence leaves it out altogether: that is meant for events that only take times,
+    // and what these order crosses the L2s of eight XCDs.  gptaq_prepare at n = 4096 takes 2.04 ms with it, 2.07 without;
+    // hipEventReleaseToDevice is no faster than the default.)
+    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return nullptr;
     ss.events.push_back(e);
   }
   return &ss;

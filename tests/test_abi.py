@@ -95,3 +95,15 @@ def test_argument_errors_are_reported_before_any_launch(lib):
     assert q(*ok, 4, 0, 0, 256, one, one, one, one, 1 << 30, null) == -3            # blocksize > 128
     assert q(*ok, 4, 0, 0, 128, one, one, one, one, 16, null) == -4
     assert b"workspace" in lib.gptaq_status_string(-4)
+
+
+def test_events_between_the_streams_release_what_they_order():
+    """Results cross from one stream to the other through the L2s of eight XCDs, so an event that orders the two must be recorded
+    with a release.  hipEventDisableSystemFence leaves it out (hip_runtime_api.h: for events that only take times)."""
+    csrc = os.path.join(ROOT, "paper_2504_02692_amd", "csrc")
+    flags = []
+    for f in sorted(os.listdir(csrc)):
+        if f.endswith((".hip", ".h")):
+            code = re.sub(r"//[^\n]*", "", open(os.path.join(csrc, f)).read())
+            flags += re.findall(r"hipEventCreateWithFlags\([^,]*,([^)]*)\)", code)
+    assert [x.strip() for x in flags] == ["hipEventDisableTiming"]
