@@ -79,7 +79,8 @@ __device__ __forceinline__ void wave_publish() {
 }
 
 // acc += (lane C of each group of 16 lanes of s) * e.  The compiler does not look into the asm: s must not have been written by
-// the two instructions before (row_value below waits; every later use is behind a chain of results of that one).
+// the two instructions before (row_value below waits; every later use is behind a chain of results of that one;
+// tests/test_dpp_hazards.py checks the machine code for it).
 template <int C> __device__ __forceinline__ void fmac_lane(double& acc, double s, double e) {
   asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(s), "v"(e), "n"(C));
 }

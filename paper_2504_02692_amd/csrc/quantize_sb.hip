@@ -149,7 +149,7 @@ __device__ __forceinline__ void sb_barrier() {
 
 // w += (lane C of each group of 16 lanes of s) * e: the 16 entries of a row of U (or P) sit in the 16 lanes of s, so a
 // column step needs neither LDS reads nor a register per entry.  s must not have been written by the two instructions
-// before (the compiler does not look into the asm): see sb_pin.
+// before (the compiler does not look into the asm): see sb_pin; tests/test_dpp_hazards.py checks the machine code for it.
 template <int C> __device__ __forceinline__ void sb_fmac_lane(float& w, float s, float e) {
   asm("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(w) : "v"(s), "v"(e), "n"(C));
 }
