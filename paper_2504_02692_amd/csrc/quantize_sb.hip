@@ -119,11 +119,16 @@ struct SbShared {
   float dinv[2][kSub];                           // 1 / U_jj
 };
 
-// Clip-range search of a group of the current weights (Section 5.1; candidates p = 1 - i / grid of the min-max range, the smallest sum of squared errors wins, the
-// earlier one on ties).  The owner stages the group's weights, one row per lane, and all eight wavefronts search: each takes
-// every eighth candidate, so no sum crosses lanes.  Bound by its five instructions per weight and candidate: ~20 us per 128
-// columns and 80 candidates of 64 rows, whatever the number of workgroups.  (With one row per wavefront, two columns per
-// lane and a reduction over the lanes for each candidate, in a launch per 128 columns, a 4096 x 4096 layer took 3.61 ms; 1.64.)
+// Clip-range search of a group of the current weights (Section 5.1; candidates p = 1 - i / grid of the min-max range, the smallest
+// sum of squared errors wins, the earlier one on ties).  The owner stages the group's weights, one row per lane, and all eight
+// wavefronts search: each takes every eighth candidate, so no sum crosses lanes.  Bound by its five instructions per weight and
+// candidate: ~16 us per 128 columns and 80 candidates of 64 rows, whatever the number of workgroups.  (With one row per wavefront,
+// two columns per lane and a reduction over the lanes for each candidate, in a launch per 128 columns, a 4096 x 4096 layer took
+// 3.92 ms; 1.53.)
+// A wavefront sums five candidates at a time, then two, then one, so that the time follows their number: 64 x 1024 in groups of 128
+// with 1 / 8 / 40 / 80 / 100 / 160 candidates 180 / 182 / 238 / 311 / 345 / 456 us.  (Ten at a time, the last ones repeated to fill
+// them up: 279 / 315 / 315 / 314 / 468 / 468, and 128 columns with up to 20 candidates took 1.2 to 1.4 times as long as one launch per 128
+// columns did.)
 struct SbClip {
   float w[128][64];                              // [column of the group][row]
   double base[64];                               // full scale of the row's group, not yet rounded
@@ -366,35 +371,48 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
 
   // this wavefront's part of the search for the group that starts at sub-block x; all wavefronts come here at the same x
   auto search = [&]() {
-    constexpr int NC = 10;                                // candidates at a time: a weight is read once for all of them
     sb_barrier();
     const double base = cl.base[lane];
     const float dlo = -cl.zero[lane], dhi = a.maxq + dlo;
     float best = __builtin_inff();
     int cand = 0;
-    for (int i0 = wave; i0 < a.clip_steps; i0 += NC * kSbWaves) {
-      float sc[NC], isc[NC], err[NC];
+    // K candidates at a time, i, i + kSbWaves, ...: a weight is read from LDS once for all of them
+    auto offer = [&](auto count, int i) {
+      constexpr int K = decltype(count)::value;
+      float sc[K], isc[K], err[K];
 #pragma unroll
-      for (int k = 0; k < NC; ++k) {
-        sc[k] = sb_clip_scale(base, min(i0 + k * kSbWaves, a.clip_steps - 1), a.clip_grid);
+      for (int k = 0; k < K; ++k) {
+        sc[k] = sb_clip_scale(base, i + k * kSbWaves, a.clip_grid);
         isc[k] = 1.f / sc[k];
         err[k] = 0.f;
       }
-#pragma unroll 4
-      for (int c = 0; c < a.group; ++c) {
-        const float x = cl.w[c][lane];
+      // (four weights at a time, the next four requested before the sums of these)
+      float x[4], nx[4];
 #pragma unroll
-        for (int k = 0; k < NC; ++k) {
-          const float d = fmaf(sc[k], __builtin_amdgcn_fmed3f(rintf(x * isc[k]), dlo, dhi), -x);
-          err[k] = fmaf(d, d, err[k]);
-        }
+      for (int q = 0; q < 4; ++q) x[q] = cl.w[q][lane];
+#pragma unroll 2
+      for (int c = 0; c < a.group; c += 4) {
+        const int cn = min(c + 4, a.group - 4);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) nx[q] = cl.w[cn + q][lane];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int k = 0; k < K; ++k) {
+            const float d = fmaf(sc[k], __builtin_amdgcn_fmed3f(rintf(x[q] * isc[k]), dlo, dhi), -x[q]);
+            err[k] = fmaf(d, d, err[k]);
+          }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = nx[q];
       }
 #pragma unroll
-      for (int k = 0; k < NC; ++k) {
-        const int i = i0 + k * kSbWaves;
-        if (i < a.clip_steps && err[k] < best) { best = err[k]; cand = i; }
-      }
-    }
+      for (int k = 0; k < K; ++k)
+        if (err[k] < best) { best = err[k]; cand = i + k * kSbWaves; }
+    };
+    int i = wave;
+    for (; i + 4 * kSbWaves < a.clip_steps; i += 5 * kSbWaves) offer(std::integral_constant<int, 5>{}, i);
+    for (; i + kSbWaves < a.clip_steps; i += 2 * kSbWaves) offer(std::integral_constant<int, 2>{}, i);
+    if (i < a.clip_steps) offer(std::integral_constant<int, 1>{}, i);
     cl.err[wave][lane] = best;
     cl.cand[wave][lane] = cand;
     sb_barrier();

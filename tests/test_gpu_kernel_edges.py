@@ -132,6 +132,31 @@ def test_clip_search_in_the_column_loop(group, m, n, grid, steps):
                             label=f"clip g{group} {m}x{n} {steps}/{grid}", mse=(grid, steps))
 
 
+def test_clip_search_costs_what_its_candidates_cost():
+    """The search is most of the time of a layer with 64 rows and 80 candidates (311 us of 1024 columns; 182 with 8, 345 with 100):
+    eight candidates have to cost visibly less than 80, and 100 no more than a third above them."""
+    m, n = 64, 1024
+    U = dev(np.eye(n))
+    W0 = dev(synth.make_weights(m, n, 5, "cost"))
+    ws = B.workspace(B.gptaq_quantize_workspace_bytes(m, n))
+
+    def best_ms(steps):
+        times = []
+        for _ in range(12):
+            W = W0.clone()
+            begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            begin.record()
+            B.gptaq_quantize_layer(W, U, None, 4, 128, False, 128, ws, terms=1, mse_grid=100, mse_steps=steps)
+            end.record()
+            end.synchronize()
+            times.append(begin.elapsed_time(end))
+        return min(times)
+
+    t8, t80, t100 = best_ms(8), best_ms(80), best_ms(100)
+    print(f"clip search of 64 x 1024: {t8:.3f} ms with 8 candidates, {t80:.3f} with 80, {t100:.3f} with 100")
+    assert t8 <= 0.8 * t80 and t100 <= 1.33 * t80
+
+
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 1023, 1025, 2100])
 def test_ranking_of_the_diagonal(n):
     """64 inputs per workgroup, 1024 compared at a time; many equal entries."""
