@@ -122,13 +122,15 @@ struct SbShared {
 // Clip-range search of a group of the current weights (Section 5.1; candidates p = 1 - i / grid of the min-max range, the smallest
 // sum of squared errors wins, the earlier one on ties).  The owner stages the group's weights, one row per lane, and all eight
 // wavefronts search: each takes every eighth candidate, so no sum crosses lanes.  Bound by its five instructions per weight and
-// candidate: ~16 us per 128 columns and 80 candidates of 64 rows, whatever the number of workgroups.  (With one row per wavefront,
+// candidate: ~17 us per 128 columns and 80 candidates of 64 rows, whatever the number of workgroups.  (With one row per wavefront,
 // two columns per lane and a reduction over the lanes for each candidate, in a launch per 128 columns, a 4096 x 4096 layer took
-// 3.92 ms; 1.53.)
+// 3.92 ms; 1.57.)
+// A sum is a tree over the columns: its error against 64 bits is 4.2e-8 rms, 1.8e-7 at most (20000 groups of 16, 32, 64 or 128 normal
+// weights; one chain of 128 FMAs: 1.7e-7 and 8.8e-7, the reduction over the lanes 4.3e-8 and 1.9e-7).
 // A wavefront sums five candidates at a time, then two, then one, so that the time follows their number: 64 x 1024 in groups of 128
-// with 1 / 8 / 40 / 80 / 100 / 160 candidates 180 / 182 / 238 / 311 / 345 / 456 us.  (Ten at a time, the last ones repeated to fill
-// them up: 279 / 315 / 315 / 314 / 468 / 468, and 128 columns with up to 20 candidates took 1.2 to 1.4 times as long as one launch per 128
-// columns did.)
+// with 1 / 8 / 40 / 80 / 100 / 160 candidates 184 / 189 / 246 / 323 / 361 / 475 us.  (Ten at a time, the last ones repeated to fill
+// them up: 281 / 316 / 316 / 316 / 471 / 471, and 128 columns with up to 20 candidates took 1.2 to 1.4 times as long as one launch per
+// 128 columns did.)
 struct SbClip {
   float w[128][64];                              // [column of the group][row]
   double base[64];                               // full scale of the row's group, not yet rounded
@@ -298,7 +300,14 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
   // ---- the two helpers of sub-block x: wave (block + 7) % 8 fetches, wave (block + 6) % 8 stores
   // what the owner of sub-block x needs besides its accumulators: the diagonal pieces of U and P (transposed into
   // buffer x & 1) and the left operands of the update of its own later columns (buffer x % 3)
+  auto own_lane = [&]() {                                 // (the search leaves no registers for addresses kept between the events)
+    int l = lane;
+    if (CLIP) asm volatile("" : "+v"(l));
+    return l;
+  };
   auto fetch_for_owner = [&](int x) {
+    const int lane = own_lane();
+    const uint32_t lane_off = (uint32_t)((lane & 31) * kSub + 8 * (lane >> 5));
     const int b = x >> 3, eb = x & 7;
     if (update) {
       for (int i = (eb + 1) >> 1; i < 4; ++i) {
@@ -328,6 +337,7 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
   };
   // results of sub-block x from LDS to memory: W^, codes, and -E and V for the update of the columns after the super-block
   auto store_results = [&](int x) {
+    const int lane = own_lane();
     const int buf = x & 1, colg = a.sb0 + kSub * x;
     if (FAST) {
 #pragma unroll
@@ -370,44 +380,79 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
   __syncthreads();
 
   // this wavefront's part of the search for the group that starts at sub-block x; all wavefronts come here at the same x
-  auto search = [&]() {
+  auto search = [&]() __attribute__((always_inline)) {
     sb_barrier();
     const double base = cl.base[lane];
     const float dlo = -cl.zero[lane], dhi = a.maxq + dlo;
     float best = __builtin_inff();
     int cand = 0;
-    // K candidates at a time, i, i + kSbWaves, ...: a weight is read from LDS once for all of them
-    auto offer = [&](auto count, int i) {
+    // K candidates at a time, i, i + kSbWaves, ...: a weight is read from LDS once for all of them.  Four squares are one chain, the
+    // chains of 16 columns are added in pairs, and these sums again, like the digits of a binary counter: held[l] is the sum of the
+    // last 16 << l columns while it has no partner.
+    auto offer = [&](auto count, int i) __attribute__((always_inline)) {
       constexpr int K = decltype(count)::value;
-      float sc[K], isc[K], err[K];
+      float sc[K], isc[K], held[3][K], sum[K];
 #pragma unroll
       for (int k = 0; k < K; ++k) {
         sc[k] = sb_clip_scale(base, i + k * kSbWaves, a.clip_grid);
         isc[k] = 1.f / sc[k];
-        err[k] = 0.f;
       }
-      // (four weights at a time, the next four requested before the sums of these)
+      // (the next four weights are requested before the squares of these)
       float x[4], nx[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) x[q] = cl.w[q][lane];
-#pragma unroll 2
-      for (int c = 0; c < a.group; c += 4) {
-        const int cn = min(c + 4, a.group - 4);
+#pragma clang loop unroll(disable)
+      for (int c = 0; c < a.group; c += kSub) {
+        float half[K];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) nx[q] = cl.w[cn + q][lane];
+        for (int h = 0; h < 4; ++h) {
+          const int cn = min(c + 4 * h + 4, a.group - 4);
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+          for (int q = 0; q < 4; ++q) nx[q] = cl.w[cn + q][lane];
+          float e[K];
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+              const float d = fmaf(sc[k], __builtin_amdgcn_fmed3f(rintf(x[q] * isc[k]), dlo, dhi), -x[q]);
+              e[k] = q == 0 ? d * d : fmaf(d, d, e[k]);
+            }
 #pragma unroll
           for (int k = 0; k < K; ++k) {
-            const float d = fmaf(sc[k], __builtin_amdgcn_fmed3f(rintf(x[q] * isc[k]), dlo, dhi), -x[q]);
-            err[k] = fmaf(d, d, err[k]);
+            if (h == 0) sum[k] = e[k];
+            if (h == 1) sum[k] += e[k];
+            if (h == 2) half[k] = e[k];
+            if (h == 3) sum[k] += half[k] + e[k];
           }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) x[q] = nx[q];
+          for (int q = 0; q < 4; ++q) x[q] = nx[q];
+        }
+        const int done = c / kSub + 1;                       // (1, 2, 4 or 8 in the end: then sum has every pair in it)
+        if (done & 1) {
+#pragma unroll
+          for (int k = 0; k < K; ++k) held[0][k] = sum[k];
+        } else {
+#pragma unroll
+          for (int k = 0; k < K; ++k) sum[k] += held[0][k];
+          if (done & 2) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) held[1][k] = sum[k];
+          } else {
+#pragma unroll
+            for (int k = 0; k < K; ++k) sum[k] += held[1][k];
+            if (done & 4) {
+#pragma unroll
+              for (int k = 0; k < K; ++k) held[2][k] = sum[k];
+            } else {
+#pragma unroll
+              for (int k = 0; k < K; ++k) sum[k] += held[2][k];
+            }
+          }
+        }
       }
 #pragma unroll
       for (int k = 0; k < K; ++k)
-        if (err[k] < best) { best = err[k]; cand = i + k * kSbWaves; }
+        if (sum[k] < best) { best = sum[k]; cand = i + k * kSbWaves; }
     };
     int i = wave;
     for (; i + 4 * kSbWaves < a.clip_steps; i += 5 * kSbWaves) offer(std::integral_constant<int, 5>{}, i);
@@ -463,7 +508,7 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
       if (row < a.m) { g.sc = a.scales[row]; g.zr = a.zeros[row]; }
       g.isc = 1.f / g.sc;
     }
-    auto new_grid = [&](float lo, float hi, int x) {      // (with CLIP the group's weights have been staged)
+    auto new_grid = [&](float lo, float hi, int x) __attribute__((always_inline)) {      // (with CLIP the group's weights have been staged)
       const double base = sb_grid_params(lo, hi, a.maxq, a.sym, g.sc, g.zr);
       if (CLIP) {
         cl.base[lane] = base;
@@ -519,8 +564,8 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
         }
         new_grid(lh ? mn[1] : mn[0], lh ? mx[1] : mx[0], x);
       }
-      float w[kSub], u[kSub], p[kSub];
-      {
+      float w[kSub], u[kSub], p[kSub], dreg;
+      auto load_diag = [&]() {
         const float* ud = sh.Ud[buf][lane & 15];
         const float* pd = sh.Pd[buf][lane & 15];
 #pragma unroll
@@ -529,8 +574,10 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
 #pragma unroll
           for (int k = 0; k < 4; ++k) { u[4 * q + k] = a4[k]; p[4 * q + k] = b4[k]; }
         }
-      }
-      float dreg = sh.dinv[buf][lane & 15];
+        dreg = sh.dinv[buf][lane & 15];
+      };
+      const bool late = CLIP && a.group == kSub;           // (a search in between leaves no registers for them)
+      if (!late) load_diag();
       sb_extract<HALF>(acc[R], w);
       if (a.group == kSub) {                               // the group is this sub-block: its grid comes from the registers
         float mn = 0.f, mx = 0.f;
@@ -542,6 +589,7 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
         }
         new_grid(mn, mx, x);
       }
+      if (late) load_diag();
       sb_pin(u);
       sb_pin(p);
       asm volatile("s_nop 1" : "+v"(dreg));

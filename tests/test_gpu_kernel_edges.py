@@ -132,6 +132,25 @@ def test_clip_search_in_the_column_loop(group, m, n, grid, steps):
                             label=f"clip g{group} {m}x{n} {steps}/{grid}", mse=(grid, steps))
 
 
+# 96: the block-by-block kernel; the others: the super-block kernel.
+@pytest.mark.parametrize("group", [32, 64, 96, 128])
+def test_clip_search_does_not_lose_small_errors_behind_a_large_one(group):
+    """Two candidates, scales 1 and s = 1 - 1/13000.  One weight is 0 under both and leaves 0.49^2; one is 3, exact under the first
+    only, 9/13000^2 off under the second; all others are s: exact under the second, 1/13000^2 = 0.4 units in the last place of 0.49^2
+    off under the first.  The second candidate is better by (group - 11) of those (10 units or more), but a single fp32 sum that meets
+    the large square first drops every one of them.  In sums of four, added in pairs, at most three are next to the large one, and
+    the roundings of the five to seven additions that follow cost half a unit each."""
+    grid = 13000
+    s = np.float32(1.0 - 1.0 / grid)
+    m = group
+    W = np.full((m, group), s, np.float32)
+    for r in range(m):                           # the large square in every position
+        W[r, r] = 0.49
+        W[r, (r + 5) % group] = 3.0
+    got = PU.gpu_quantize(W, dev(np.eye(group)), None, 2, group, False, 96 if group == 96 else 128, terms=0, mse=(grid, 2))
+    assert np.array_equal(got["scales"], np.full((m, 1), s))
+
+
 def test_clip_search_costs_what_its_candidates_cost():
     """The search is most of the time of a layer with 64 rows and 80 candidates (311 us of 1024 columns; 182 with 8, 345 with 100):
     eight candidates have to cost visibly less than 80, and 100 no more than a third above them."""
