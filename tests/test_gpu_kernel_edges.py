@@ -132,6 +132,49 @@ def test_clip_search_in_the_column_loop(group, m, n, grid, steps):
                             label=f"clip g{group} {m}x{n} {steps}/{grid}", mse=(grid, steps))
 
 
+# Group sizes that do not tile the super-block kernel's pieces are searched by the block-by-block kernel: one lane's columns, both of
+# a lane's columns, several super-blocks (8 blocks of 64 columns).
+@pytest.mark.parametrize("group,blocksize,m,n", [(8, 128, 70, 136), (96, 96, 66, 192), (8, 64, 33, 1160), (40, 120, 130, 240)])
+def test_clip_search_in_the_block_kernel(group, blocksize, m, n):
+    k = max(256, n + n // 2)
+    Xb, Xtb = synth.make_activations(k, n, 41, "clipb", 2, 20.0)
+    H, A = O.accumulate(Xb, Xtb)
+    U, P, _ = O.prepare(H, A, 0.01)
+    U32, P32 = U.astype(np.float32), P.astype(np.float32)
+    W = synth.make_weights(m, n, 41, f"clipb{m}x{n}")
+    got = PU.gpu_quantize(W, dev(U32), dev(P32), 4, group, False, blocksize, mse=(100, 80))
+    PU.check_against_oracle(W, U32.astype(np.float64), P32.astype(np.float64), got, 4, group, False,
+                            label=f"clip g{group} blocks of {blocksize} {m}x{n}", mse=(100, 80))
+
+
+@pytest.mark.parametrize("group", [32, 128])
+def test_clip_search_beside_the_far_update(group):
+    """Three super-blocks: the columns after the next one are updated on the helper stream."""
+    m, n = 40, 2304
+    Xb, Xtb = synth.make_activations(3500, n, 43, "clip2", 2, 20.0)
+    H, A = O.accumulate(Xb, Xtb)
+    U, P, _ = O.prepare(H, A, 0.01)
+    U32, P32 = U.astype(np.float32), P.astype(np.float32)
+    W = synth.make_weights(m, n, 43, "clip2")
+    got = PU.gpu_quantize(W, dev(U32), dev(P32), 4, group, False, 128, mse=(100, 80))
+    PU.check_against_oracle(W, U32.astype(np.float64), P32.astype(np.float64), got, 4, group, False,
+                            label=f"clip g{group} {m}x{n}", mse=(100, 80))
+
+
+def test_clip_search_in_two_row_halves_equals_separate_calls():
+    """From 10240 rows on a matrix goes through as two row halves on two streams, each with its own search."""
+    m, n, half = 10500, 1152, 5376
+    Xb, Xtb = synth.make_activations(1800, n, 44, "clip3", 2, 20.0)
+    H, A = O.accumulate(Xb, Xtb)
+    U, P, _ = O.prepare(H, A, 0.01)
+    U32, P32 = dev(U.astype(np.float32)), dev(P.astype(np.float32))
+    W = synth.make_weights(m, n, 44, "clip3")
+    for group in (128, 0):
+        one, a, b = (PU.gpu_quantize(w, U32, P32, 4, group, False, 128, mse=(100, 20)) for w in (W, W[:half], W[half:]))
+        for key in ("codes", "scales", "zeros", "What"):
+            assert np.array_equal(one[key], np.concatenate([a[key], b[key]])), (group, key)
+
+
 # 96: the block-by-block kernel; the others: the super-block kernel.
 @pytest.mark.parametrize("group", [32, 64, 96, 128])
 def test_clip_search_does_not_lose_small_errors_behind_a_large_one(group):
