@@ -242,3 +242,45 @@ def test_activation_quantiser_rows(n, bits, clip):
     # (near-ties of x / scale in fp64; the library decides by the sign of an exact residual)
     assert hints <= max(2, PU.MAX_HINT_FRAC * got.size)
     assert np.array_equal(ref, got)
+
+
+def test_a_solve_can_be_captured():
+    """gptaq_prepare (three outer blocks) and gptaq_quantize_layer (three super-blocks) put work on the helper stream; it joins the
+    caller's stream in front of the end of the call, also in a capture.  Every replay is checked, with other work in between."""
+    m, n = 33, 2064
+    g = torch.Generator(device="cuda").manual_seed(3)
+    X = torch.randn((2 * n, n), device="cuda", generator=g)
+    H0, A0 = X.T.contiguous() @ X, (0.1 * torch.randn((2 * n, n), device="cuda", generator=g)).T.contiguous() @ X
+    W0 = 0.02 * torch.randn((m, n), device="cuda", generator=g)
+    H, A, W = torch.empty_like(H0), torch.empty_like(A0), torch.empty_like(W0)
+    dead, info = torch.empty(n, dtype=torch.uint8, device="cuda"), torch.empty(2, dtype=torch.int32, device="cuda")
+    codes = torch.empty((m, n), dtype=torch.uint8, device="cuda")
+    scales, zeros = torch.empty((m, n // 16), device="cuda"), torch.empty((m, n // 16), device="cuda")
+    wp = B.workspace(B.gptaq_prepare_workspace_bytes(n))
+    wq = B.workspace(B.gptaq_quantize_workspace_bytes(m, n))
+    lib = B.load()
+
+    def solve():
+        H.copy_(H0), A.copy_(A0), W.copy_(W0)
+        s = torch.cuda.current_stream().cuda_stream
+        assert lib.gptaq_prepare(H.data_ptr(), A.data_ptr(), n, n, 0.01, dead.data_ptr(), info.data_ptr(), wp.data_ptr(), wp.numel(), s) == 0
+        assert lib.gptaq_quantize_layer(W.data_ptr(), m, n, n, H.data_ptr(), A.data_ptr(), n, dead.data_ptr(), 4, 16, 0, 128,
+                                        codes.data_ptr(), scales.data_ptr(), zeros.data_ptr(), wq.data_ptr(), wq.numel(), s) == 0
+
+    out = (H, A, W, codes, scales, zeros, info)
+    solve()
+    torch.cuda.synchronize()
+    eager = [t.clone() for t in out]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        solve()
+    for i in range(3):
+        for t in out:
+            t.fill_(i)
+        wp.fill_(255), wq.fill_(255)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(out, eager):
+            assert torch.equal(a, b)
+        solve()
