@@ -119,7 +119,6 @@ struct SbArgs {
   int sb0, sbw;                      // first column and width (<= kSbCols) of the super-block
   const float* U; const float* P; int64_t ldh;
   const uint16_t* Nop[4];            // launch_near_operands output: U hi, U lo, P hi, P lo
-  const uint8_t* dead;
   float maxq; int group, sym, G, terms;
   float* scales; float* zeros; uint8_t* codes;
   uint16_t *Eh, *El, *Vh, *Vl;       // -E and V of the super-block as bf16 hi/lo, k-tile-major (NULL: not wanted): element

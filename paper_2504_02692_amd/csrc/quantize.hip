@@ -84,15 +84,13 @@ struct ClipSearch {
 };
 
 // One wavefront per row: range of the whole (original) row -> one (scale, zero) per row.
-__global__ __launch_bounds__(256) void row_params_kernel(const float* W, int64_t ldw, int m, int n, const uint8_t* dead,
-                                                         float maxq, int sym, int mse_grid, int mse_steps, float* scales,
-                                                         float* zeros) {
+__global__ __launch_bounds__(256) void row_params_kernel(const float* W, int64_t ldw, int m, int n, float maxq, int sym,
+                                                         int mse_grid, int mse_steps, float* scales, float* zeros) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (row >= m) return;
   float mn = 0.f, mx = 0.f;
   for (int c = lane; c < n; c += 64) {
-    float v = W[(int64_t)row * ldw + c];
-    if (dead && dead[c]) v = 0.f;
+    const float v = W[(int64_t)row * ldw + c];
     mn = fminf(mn, v);
     mx = fmaxf(mx, v);
   }
@@ -106,11 +104,7 @@ __global__ __launch_bounds__(256) void row_params_kernel(const float* W, int64_t
     for (int i = 0; i < mse_steps; ++i) {
       const float si = cs.scale_of(i, mse_grid), isi = 1.f / si;
       float e = 0.f;
-      for (int c = lane; c < n; c += 64) {
-        float v = W[(int64_t)row * ldw + c];
-        if (dead && dead[c]) v = 0.f;
-        e += cs.err_of(v, si, isi);
-      }
+      for (int c = lane; c < n; c += 64) e += cs.err_of(W[(int64_t)row * ldw + c], si, isi);
       cs.offer(wave_sum(e), si);
     }
     sc = cs.best_scale;
@@ -167,15 +161,12 @@ __global__ __launch_bounds__(64 * NW) void quant_block_kernel(QuantArgs a) {
     w0[r] = ok && col0 ? a.W[(int64_t)row * a.ldw + i0 + lane] : 0.f;
     w1[r] = ok && col1 ? a.W[(int64_t)row * a.ldw + i0 + 64 + lane] : 0.f;
     v0[r] = v1[r] = 0.f;
-    sc[r] = 1.f; zr[r] = 0.f;
-    if (a.group <= 0 && ok) { sc[r] = a.scales[row]; zr[r] = a.zeros[row]; }
-    isc[r] = 1.f / sc[r];
-    ms0[r] = ms1[r] = sc[r];
-    mz0[r] = mz1[r] = zr[r];
+    sc[r] = isc[r] = ms0[r] = ms1[r] = 1.f;
+    zr[r] = mz0[r] = mz1[r] = 0.f;
   }
   __syncthreads();
 
-  int next_group = a.group > 0 ? 0 : bw;                  // i0 is a multiple of the group size
+  int next_group = 0;                                     // i0 is a multiple of the group size
   auto group_start = [&](int j) {
     const int jend = j + a.group;
     const bool in0 = lane >= j && lane < jend, in1 = lane + 64 >= j && lane + 64 < jend;
@@ -468,7 +459,6 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
   a.W = W; a.ldw = ldw; a.m = (int)m; a.n = (int)n;
   a.U = U; a.P = (terms & 2) ? P : U; a.ldh = ldh;
   for (int i = 0; i < 4; ++i) a.Nop[i] = buf[8 + i];
-  a.dead = dead;
   a.maxq = (float)((1 << bits) - 1); a.group = group; a.sym = sym; a.terms = terms;
   a.G = group > 0 ? (int)(n / group) : 1;
   a.scales = scales; a.zeros = zeros; a.codes = codes;
@@ -477,7 +467,7 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
   a.fast_rows = (ldw % 4 == 0) && (((uintptr_t)W & 15) == 0) && (n % 16 == 0) && (((uintptr_t)codes & 15) == 0);
   if (group <= 0) {
     hipLaunchKernelGGL(row_params_kernel, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, W, ldw, (int)m, (int)n,
-                       (const uint8_t*)nullptr, a.maxq, sym, mse_grid, mse_steps, scales, zeros);
+                       a.maxq, sym, mse_grid, mse_steps, scales, zeros);
     GPTAQ_LAUNCH_CHECK();
   }
   const int nsb = (int)((n + kSbCols - 1) / kSbCols);
@@ -661,15 +651,10 @@ static int quantize_layer_impl(float* W, int64_t m, int64_t n, int64_t ldw, cons
   a.W = W; a.ldw = ldw; a.m = (int)m; a.n = (int)n;
   a.U = U; a.P = P; a.ldh = ldh; a.dead = dead;
   a.maxq = (float)((1 << bits) - 1); a.group = group; a.sym = sym; a.terms = terms; a.mse_grid = mse_grid; a.mse_steps = mse_steps;
-  a.G = group > 0 ? (int)(n / group) : 1;
+  a.G = (int)(n / group);
   a.scales = scales; a.zeros = zeros; a.codes = codes;
   a.Eh = buf[0]; a.El = buf[1]; a.Vh = buf[2]; a.Vl = buf[3]; a.ldev = KS;
 
-  if (group <= 0) {
-    hipLaunchKernelGGL(row_params_kernel, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, W, ldw, (int)m, (int)n, dead,
-                       a.maxq, sym, mse_grid, mse_steps, scales, zeros);
-    GPTAQ_LAUNCH_CHECK();
-  }
   // Two-level lazy batching (a re-association of the sums of Eq. 18): a block's update reaches the rest
   // of its super-block at once ("near", K = one block), and the columns after the super-block once per
   // super-block ("far", K = SB blocks), which cuts the passes over W of the flat schedule by SB.
