@@ -151,6 +151,12 @@ __device__ __forceinline__ void factor_steps(double (&s)[16], double (&f)[16], d
   }
 }
 
+// w[c] = f[c] * (lane c of each group of 16 lanes of s)
+template <int... C>
+__device__ __forceinline__ void scale_by_lane(double (&w)[16], double s, const double (&f)[16], std::integer_sequence<int, C...>) {
+  ((w[C] = 0.0, fmac_lane<C>(w[C], s, f[C])), ...);
+}
+
 __device__ __forceinline__ void factor_diag(FactorShared& sh, int32_t* info, int last_index) {
   const int lane = threadIdx.x & 63, r = lane & 15;
   double s[16], f[16];
@@ -168,9 +174,7 @@ __device__ __forceinline__ void factor_diag(FactorShared& sh, int32_t* info, int
   double rs = piv > 0.0 ? rsqrt_of(piv) : 1.0;
   asm volatile("s_nop 1" : "+v"(rs));
   double w[16];
-  [&]<int... C>(std::integer_sequence<int, C...>) {
-    ((w[C] = 0.0, fmac_lane<C>(w[C], rs, f[C])), ...);
-  }(std::make_integer_sequence<int, 16>{});
+  scale_by_lane(w, rs, f, std::make_integer_sequence<int, 16>{});
   // w[c] of lane i is W[c][i]: tile position of (row c, column i)
   if (lane < 16) {
     double* dst = sh.w + (((r >> 1) & 1) * 128 + (r >> 2) * 32 + (r & 1));

@@ -42,7 +42,6 @@ namespace gptaq {
 
 constexpr int kSbBlocks = kSbCols / 128;       // 128-column blocks per super-block
 constexpr int kSub = 16;                       // columns per sub-block
-constexpr int kSbEvents = kSbCols / kSub;      // sub-blocks per super-block
 
 __device__ __forceinline__ uint16_t sb_bf16_rne(float f) {
   __bf16 b = (__bf16)f;
@@ -221,6 +220,12 @@ __device__ __forceinline__ void sb_piece_update(f32x16 (&t)[2], const u32x4 (&le
 // The grid of a row whose range is [lo, hi] (the lanes of a row agree), its reciprocal, and its place in the outputs.
 struct SbGrid { float sc, zr, isc; };
 
+// w[J + 1 ..] += (a row of U or P, from its column J + 1 on) * e
+template <int J, int... C>
+__device__ __forceinline__ void sb_row_update(float (&w)[kSub], float s, float e, std::integer_sequence<int, C...>) {
+  (sb_fmac_lane<J + 1 + C>(w[J + 1 + C], s, e), ...);
+}
+
 // One column step (lines 7-10 of Algorithm 1), one row per lane, and those after it.
 template <int J>
 __device__ __forceinline__ void sb_steps(float (&w)[kSub], const float (&u)[kSub], const float (&p)[kSub], float dreg, const SbGrid& g,
@@ -234,10 +239,9 @@ __device__ __forceinline__ void sb_steps(float (&w)[kSub], const float (&u)[kSub
     const float e1 = sb_mul_lane<J>(dreg, t);              // -E_J
     w[J] = g.sc * d;
     cw[J >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(d + g.zr, J & 3, cw[J >> 2]);
-    [&]<int... C>(std::integer_sequence<int, C...>) {
-      (sb_fmac_lane<J + 1 + C>(w[J + 1 + C], p[J], v), ...);
-      (sb_fmac_lane<J + 1 + C>(w[J + 1 + C], u[J], e1), ...);
-    }(std::make_integer_sequence<int, kSub - 1 - J>{});
+    constexpr std::make_integer_sequence<int, kSub - 1 - J> later{};
+    sb_row_update<J>(w, p[J], v, later);
+    sb_row_update<J>(w, u[J], e1, later);
     if constexpr (J & 1) {
       const u32x2 pe = sb_split_e<J>(e_prev, e1, t_prev, t, dreg), pv = sb_split2(v_prev, v);
       pk[0][J >> 3][(J >> 1) & 3] = pe[0];
@@ -531,7 +535,8 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
         a.zeros[o] = g.zr;
       }
     };
-    auto event = [&]<int EB>(std::integral_constant<int, EB>) {
+    auto event = [&](auto number) {
+      constexpr int EB = decltype(number)::value;
       constexpr int R = EB >> 1, HALF = EB & 1, NEXT = (EB + 1) >> 1;      // current piece, its half, first piece with columns left
       const int x = first_own + EB, buf = x & 1;
       if (x >= last_own) return;
