@@ -277,11 +277,9 @@ extern "C" int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, floa
     // join: everything after the sweep runs on the caller's stream, and whatever the helper stream was given is behind it when
     // the call returns, also if a launch or an event call failed part-way
     hipEvent_t ev_join = side->events[3 * nob + 1];
-    const hipError_t keep = (hipError_t)gptaq_last_hip_error();
     hipError_t joined = hipEventRecord(ev_join, sb);
     if (joined == hipSuccess) joined = hipStreamWaitEvent(s, ev_join, 0);
-    if (ok) chk(joined);
-    else set_last_hip_error(keep);
+    chk(joined);
     if (!ok) return GPTAQ_ELAUNCH;
   }
   // U -> H (fp32) and the bf16 splits.

@@ -575,10 +575,10 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
   }
   if (two_chains) {
     // whatever was handed to the helper stream is behind the caller's stream when the call returns, error or not
-    const hipError_t keep = (hipError_t)gptaq_last_hip_error();
     hipEvent_t ev_join = side->events[2 * nsb];
-    if (hipEventRecord(ev_join, side->stream) == hipSuccess) hipStreamWaitEvent(s, ev_join, 0);
-    if (!ok) set_last_hip_error(keep);
+    hipError_t joined = hipEventRecord(ev_join, side->stream);
+    if (joined == hipSuccess) joined = hipStreamWaitEvent(s, ev_join, 0);
+    chk(joined);
   }
   return ok ? GPTAQ_OK : GPTAQ_ELAUNCH;
 }
@@ -638,10 +638,11 @@ static int quantize_layer_impl(float* W, int64_t m, int64_t n, int64_t ldw, cons
       const int rcA = quantize_layer_sb(W, mA, n, ldw, U, P, ldh, dead, bits, group, sym, codes, scales, zeros, buf, farop,
                                         s, terms, mse_grid, mse_steps, false, false);
       // the helper stream is behind the caller's stream when the call returns, error or not
-      const hipError_t keep = (hipError_t)gptaq_last_hip_error();
-      if (hipEventRecord(ev_join, side->stream) == hipSuccess) hipStreamWaitEvent(s, ev_join, 0);
-      if (rcA != GPTAQ_OK || rcB != GPTAQ_OK) set_last_hip_error(keep);
-      return rcA != GPTAQ_OK ? rcA : rcB;
+      hipError_t joined = hipEventRecord(ev_join, side->stream);
+      if (joined == hipSuccess) joined = hipStreamWaitEvent(s, ev_join, 0);
+      if (rcA != GPTAQ_OK || rcB != GPTAQ_OK) return rcA != GPTAQ_OK ? rcA : rcB;
+      if (joined != hipSuccess) { set_last_hip_error(joined); return GPTAQ_ELAUNCH; }
+      return GPTAQ_OK;
     }
     return quantize_layer_sb(W, m, n, ldw, U, P, ldh, dead, bits, group, sym, codes, scales, zeros, buf, farop, s, terms,
                              mse_grid, mse_steps);
