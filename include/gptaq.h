@@ -122,7 +122,7 @@ int gptaq_symmetrize(float* H, int64_t n, int64_t ldh, void* stream);
  *   dead inputs (H_qq == 0): H_qq <- 1, row q of dXXT <- 0, dead[q] <- 1;
  *   lambda = damp * mean(diag H)  (damping relative to the mean diagonal, end of Section 4.2);
  *   H + lambda I = V V^T with V upper triangular, U = V^-1, so that (H + lambda I)^-1 = L L^T
- *   with L = U^T the lower factor of Step 3 / Lemma 4.1 (factorisation on fp64 data: its 64 x 64 blocks in
+ *   with L = U^T the lower factor of Step 3 / Lemma 4.1 (factorisation on fp64 data: its 256-column blocks in
  *   fp64, its rank-256 block products in 46-bit row-scaled fixed point, exact in int32);
  *   P = ((dXXT L) (.) M_U) L^T = triu(dXXT U^T, 1) U   (Eq. 17).
  *
@@ -268,7 +268,7 @@ int gptaq_pack_codes(const uint8_t* codes, int64_t m, int64_t n, int64_t ldc, in
  * with HIP events on the caller's stream, grouped by tag:
  *   0 accumulate MFMA GEMM (H and dXXT, one launch per pass)   1 accumulate split/transpose pass
  *   2 factorisation + triangular inverse sweep (whole sweep)    3 the two Theorem-4.2 GEMMs
- *   4 column-loop kernel (one per block)                        5 trailing-update GEMM (one per block)
+ *   4 column-loop kernel (one per 1024 columns)                 5 trailing-update GEMM (one or two per 1024 columns)
  *   6 trailing operand split/transpose
  * gptaq_profile_enable(mask) clears the records and records the tags whose bit (1 << tag) is set
  * in `mask`; 0 stops recording.

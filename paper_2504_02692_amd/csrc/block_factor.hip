@@ -18,9 +18,11 @@
 // ~100 clocks) on one CU beside 680 tile products of 256 clocks on three of its SIMDs; the panel kernel is a chain of 16 tile
 // columns.  An f64 MFMA (64 clocks for 1024 products) is no faster than v_fma_f64, but its operands are one register a lane,
 // where fp64 FMAs on 64 x 64 tiles were bound by their LDS reads and by solves of one wavefront.  Measured per block of 256
-// columns: factorisation 152 -> 47 us (110K clocks: the first half bound by the MFMAs, the second by the column steps, 3.0K clocks
-// per tile), panel 50 -> 17 us (n = 4096) with the digits (8 us) and the inverse (a kernel of 46 us
-// on the other chain) in it.  gptaq_prepare 4.41 -> 2.37 ms at n = 4096, 22.5 -> 19.4 at n = 11008.
+// columns: factorisation 152 -> 47 us alone (113K clocks; the MFMAs keep the matrix pipes of their three SIMDs busy for 68K of them,
+// most of that in the first half; the second half is the column steps, 3.0K clocks per tile), in gptaq_prepare beside the other
+// chain's products 54 on average at n = 4096 and 76 at n = 11008; panel 50 -> 15 us alone (35K clocks, of which a wavefront issues 21 %
+// and waits for loads 34 %), 20 and 81 in gptaq_prepare, with the digits (8 us) and the inverse (a kernel of 46 us on the other
+// chain) in it.  gptaq_prepare 4.41 -> 2.04 ms at n = 4096, 22.5 -> 18.2 at n = 11008.
 #include "common.h"
 #include "i8_digits.h"
 #include <utility>

@@ -377,8 +377,11 @@ QLayout q_layout(int64_t m, int64_t n) {
   return L;
 }
 
-// rows from which a matrix is quantised as two row halves (measured: 8192 x 4096 1.89 -> 1.95 ms, 8192 x 8192
-// 5.68 -> 5.49, 10240 x 8192 6.68 -> 6.08, 12288 x 4096 2.44 -> 2.21, 22016 x 4096 4.44 -> 3.57)
+// rows from which a matrix is quantised as two row halves.  One piece / two halves, ms: 4096 columns: 4096 rows 0.88 / 0.92, 6144
+// 1.13 / 1.03, 8192 1.23 / 1.18, 10240 1.42 / 1.33, 16384 1.89 / 1.83, 22016 3.01 / 2.47; 8192 columns: 8192 rows 4.04 / 3.64, 10240
+// 4.77 / 4.33, 28672 11.9 / 11.1; 2048 columns: 8192 rows 0.40 / 0.42, 10240 0.44 / 0.46, 16384 0.55 / 0.56, 22016 0.95 / 0.81.  (The line
+// was drawn when the super-block kernel took twice as long and 8192 rows were even; it could now lie at 6144 rows of 4096 columns
+// or more.)
 constexpr int64_t kRowSplitMin = 10240;
 
 template <int R, int NW>
@@ -444,8 +447,8 @@ __global__ __launch_bounds__(256) void zero_dead_columns_kernel(float* W, int64_
 // 4096-row layer fills 64 of the 256 CUs).  Every column still receives its updates in super-block order (far1(k)
 // waits for far2(k - 1), which touches the same columns), so results are bit-reproducible.  -E and V are
 // double-buffered: far2(k) reads set k & 1 while super-block k + 1 writes the other.  The right operands of all far
-// updates (`farop`) are made once per call, before the first super-block: they depend on U and P only, and a split
-// pass between two super-blocks sat on the critical path of every one of them (4096 x 11008: 5.8 -> 4.9 ms).
+// updates (`farop`) are made once per call, before the first super-block's update (beside its kernel where there are two chains):
+// they depend on U and P only, and a split pass between two super-blocks sat on the critical path of every one of them.
 static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const float* U, const float* P, int64_t ldh,
                              const uint8_t* dead, int bits, int group, int sym, uint8_t* codes, float* scales,
                              float* zeros, uint16_t* const* buf, uint16_t* const* farop, hipStream_t s, int terms,
@@ -471,8 +474,10 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     GPTAQ_LAUNCH_CHECK();
   }
   const int nsb = (int)((n + kSbCols - 1) / kSbCols);
-  // (with one or two super-blocks there is no far2; it pays when the super-block kernel leaves most of the chip free:
-  // measured on 4096 x 11008, 6.50 -> 5.77 ms, but 12288 x 4096 with a quarter of the chip for far2, 2.41 -> 2.90 ms)
+  // (with one or two super-blocks there is no far2; it pays when the super-block kernel leaves most of the chip free.  One chain /
+  // two, ms: 4096 rows: 3072 columns 0.60 / 0.60, 4096 0.90 / 0.87, 8192 2.68 / 2.51, 11008 4.38 / 3.98; 1024 rows: 4096 columns
+  // 0.76 / 0.79, 11008 2.65 / 2.77; beyond a quarter of the chip: 6144 rows of 4096 columns 1.13 / 1.01, 8192 of 4096 1.23 / 1.27, of
+  // 8192 4.04 / 4.49, 9984 of 8192 4.75 / 6.43)
   int cus = 256, dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
   const int sbk_wgs = (int)((m + 63) / 64);
@@ -510,7 +515,7 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
   auto ev_sbk = [&](int k) { return side->events[2 * k]; };       // super-block k's kernel has finished
   auto ev_far2 = [&](int k) { return side->events[2 * k + 1]; };  // its far2 update has finished
   // W[:, c0:c1] += [-E | V] [U; P][super-block rows, c0:c1]: -E and V from buffer set `set`, the right operands of
-  // super-block k from `farop` (made for the whole layer before the first super-block; row 0 of k's part is column cbase)
+  // super-block k from `farop` (made for the whole layer; row 0 of k's part is column cbase)
   auto far_update = [&](int set, int k, int64_t c0, int64_t c1, int64_t cbase, hipStream_t st, int max_wgs) {
     uint16_t* const* ev = buf + (set ? 12 : 0);
     int64_t first = 0;
@@ -555,8 +560,9 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     // While far2 is long (many columns left) it sets the pace and starts at once, sharing the chip with far1; once it
     // is shorter than a super-block it only slows far1 down, which the next super-block waits for: then it starts
     // when far1 is done.
-    // (measured on 4096 x 11008 with the switch at 0 / 2 / 4 / 6 / 10 super-blocks of columns left: 5.66 / 5.62 / 5.60 /
-    // 5.54 / 5.68 ms; 4096 x 4096: 1.59 / 1.53 / 1.50 / 1.51 / 1.50)
+    // (measured with the switch at 0 / 2 / 4 / 6 / 8 / 10 super-blocks of columns left, ms: 4096 x 4096 0.93 / 0.87 / 0.87 / 0.87 / 0.87 /
+    // 0.87; 4096 x 8192 2.43 / 2.43 / 2.48 / 2.53 / 2.51 / 2.52; 4096 x 11008 3.90 / 3.88 / 3.92 / 3.96 / 4.00 / 4.03; 1024 x 11008 2.69 /
+    // 2.70 / 2.73 / 2.80 / 2.84 / 2.79; six was the best on 4096 x 11008 when the super-block kernel took 290 us, now it is 2 % off)
     constexpr int kFar2LateCols = 6 * kSbCols;
     const bool far2_late = has_far2 && (n - next_end) <= kFar2LateCols;
     auto launch_far2 = [&]() {

@@ -2,14 +2,14 @@
 //
 // Rows of W never interact (Step 1: all output channels are solved in parallel with one shared
 // factor), so a workgroup owns 64 rows for the whole super-block and needs no grid-level
-// synchronisation: the 64 x 1024 slice of W lives in the accumulator registers of its four
+// synchronisation: the 64 x 1024 slice of W lives in the accumulator registers of its eight
 // wavefronts from the first column of the super-block to the last, and every update of
 // Eq. 15 / Eq. 18 that stays inside the super-block is applied there.
 //
 // Three levels of lazy batching (a re-association of the sums of Eq. 18, which leaves the result
 // independent of the blocking):
 //   * 16 columns ("sub-block"): the sequential column steps of lines 7-10, one row per lane, fp32
-//     FMAs, the 16 x 16 diagonal pieces of U and P broadcast from LDS;
+//     FMAs, the 16 x 16 diagonal pieces of U and P in registers, broadcast by DPP;
 //   * the rest of the super-block: after each sub-block, W[:, later] += [-E | V] [U; P][sub-block, later]
 //     on the matrix cores (bf16 hi/lo split of both sides, three products per term), straight into
 //     the accumulators that hold W;
@@ -29,12 +29,14 @@
 // fetches for the owner what that needs next (diagonal pieces of U and P, left operands) and writes the owner's results
 // to memory from LDS.  One workgroup barrier per sub-block publishes its -E and V.
 //
-// What bounds it: the chain of column steps.  A sub-block costs the owner ~16 x 120 clocks of column steps, 16 swaps, the
-// publication of its -E and V and 12 MFMAs per 32 columns of its block that are left; the other waves' MFMAs (at most
-// 96 per SIMD and sub-block) and the loads of their left operands (112 KB per sub-block at first) hide behind that.
-// Measured, 1024 columns of 4096 rows (64 workgroups): 149 us alone, 170-180 beside a far update; with four waves of two
-// blocks each, where the owner also updated its second block, read U and P from LDS in the column steps and stored its
-// results itself, it took 290.
+// What bounds it: the owner's chain, ~5.3K clocks for each of the 64 sub-blocks: ~16 x 120 of column steps, then 16 swaps, the
+// publication of its -E and V, the barrier and 12 MFMAs (of 32 clocks, on a matrix pipe shared with an updater) per 32 columns of
+// its block that are left; the other waves' MFMAs (at most 96 per SIMD and sub-block) and the loads of their left operands (112 KB
+// per sub-block at first) hide behind that.  Counters: a wave is resident for 339K clocks, issues in 15 % of them and waits for
+// memory or LDS in 27 %; the matrix cores are busy 29 % of the time.
+// Measured, 1024 columns of 4096 rows (64 workgroups): 144 us with nothing beside it, 167 on average in a layer of 4096 columns, 200
+// (up to 310) beside the far updates of one of 11008; with four waves of two blocks each, where the owner also updated its
+// second block, read U and P from LDS in the column steps and stored its results itself, it took 290 alone.
 #include "common.h"
 #include <utility>
 
