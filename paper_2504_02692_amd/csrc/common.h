@@ -114,21 +114,31 @@ hipError_t launch_block_panel(const BlockPanel& a, hipStream_t s);
 
 // Column loop + in-super-block updates of a whole super-block in one launch (quantize_sb.hip).
 constexpr int kSbCols = 1024;       // columns per super-block
+// What the kernel reads of U and P, made for every super-block of a layer (layout: near_operands_kernel).
+struct SbNear {
+  uint16_t* left;                    // U hi, U lo, P hi, P lo, `stride` elements apart: kSbCols * kSbCols bf16 per super-block each
+  int64_t stride;
+  float* diag;                       // kSbCols / 16 * 512 floats per super-block
+  __host__ SbNear at(int sb) const {
+    SbNear o = *this;
+    o.left += (int64_t)sb * kSbCols * kSbCols;
+    o.diag += (int64_t)sb * (kSbCols / 16) * 512;
+    return o;
+  }
+};
 struct SbArgs {
   float* W; int64_t ldw; int m, n;
   int sb0, sbw;                      // first column and width (<= kSbCols) of the super-block
-  const float* U; const float* P; int64_t ldh;
-  const uint16_t* Nop[4];            // launch_near_operands output: U hi, U lo, P hi, P lo
+  SbNear near;                       // of this super-block
   float maxq; int group, sym, G, terms;
   float* scales; float* zeros; uint8_t* codes;
-  uint16_t *Eh, *El, *Vh, *Vl;       // -E and V of the super-block as bf16 hi/lo, k-tile-major (NULL: not wanted): element
-  int64_t evkt;                      // (row, k) at (k / 32) * evkt + 32 * row + k % 32
+  uint16_t* EV;                      // -E hi, -E lo, V hi, V lo of the super-block, `evstride` elements apart, k-tile-major (NULL: not
+  int64_t evstride, evkt;            // wanted): element (row, k) at (k / 32) * evkt + 32 * row + k % 32
   int clip_grid, clip_steps;         // clip-range search of every group (0 steps: plain min-max; groups only)
   int fast_rows;                     // rows of W and of codes may be stored 16 bytes at a time
 };
-// N4: four buffers of (kSbCols / 16) * kSbCols * 16 bf16 each.
-hipError_t launch_near_operands(const float* U, const float* P, int64_t ldh, int n, int sb0, int sbw, uint16_t* const* N4,
-                                hipStream_t s);
+// Operands of super-blocks first .. first + count - 1.
+hipError_t launch_near_operands(const float* U, const float* P, int64_t ldh, int n, int first, int count, const SbNear& o, hipStream_t s);
 hipError_t launch_quant_sb(const SbArgs& a, hipStream_t s);
 
 void set_last_hip_error(hipError_t e);

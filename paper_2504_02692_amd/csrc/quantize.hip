@@ -352,23 +352,25 @@ constexpr int SB = 8;                         // column blocks per super-block (
 constexpr int KS = SB * QB;
 struct QLayout {
   int64_t mp, np;
-  size_t off[24], off_far[4], total;
+  size_t off[16], off_near, off_far[4], total;
 };
 QLayout q_layout(int64_t m, int64_t n) {
   QLayout L;
   L.mp = round_up(m, 256);
   L.np = round_up(n, 256);
   size_t o = 0;
-  for (int i = 0; i < 24; ++i) {
+  for (int i = 0; i < 16; ++i) {
     L.off[i] = o;
     // 0-3: -E, V (hi, lo) of one super-block; 4-7: right operands of the updates of one super-block as the
     // block-per-wave path makes them (all columns from the super-block's first on, plus a tile of padding rows);
-    // 8-11: left operands of the updates inside a super-block (quantize_sb.hip); 12-15 and 20-23: a second set of 0-3
-    // and 8-11 (the far update of a super-block runs beside the next super-block, which writes its own -E and V; or
-    // the two row halves of a tall matrix run as two chains, each at its own super-block); 16-19: unused
-    const int k = i < 12 ? i : i - 12;
-    o += (size_t)(k < 4 ? L.mp * KS * 2 : k < 8 ? (i < 12 ? (L.np + 256) * KS * 2 : 0) : (int64_t)(kSbCols / 16) * kSbCols * 16 * 2);
+    // 12-15: a second set of 0-3 (the far update of a super-block runs beside the next super-block, which writes its own -E
+    // and V; or the two row halves of a tall matrix run as two chains, each at its own super-block); 8-11: unused
+    o += (size_t)(i % 12 < 4 ? L.mp * KS * 2 : i < 8 ? (L.np + 256) * KS * 2 : 0);
   }
+  // what the super-block kernel reads of U and P, of every super-block (near_operands_kernel)
+  const int64_t nsb = (n + kSbCols - 1) / kSbCols;
+  L.off_near = o;
+  o += (size_t)(nsb * (4 * (int64_t)kSbCols * kSbCols * 2 + (int64_t)(kSbCols / 16) * 512 * 4));
   // the far right operands of every super-block of the layer (far_operands_all_kernel), made once per call
   int64_t rows = 0;
   for (int k = 0; (int64_t)(k + 1) * kSbCols < n; ++k) rows += far_rows(n, k);
@@ -451,8 +453,8 @@ __global__ __launch_bounds__(256) void zero_dead_columns_kernel(float* W, int64_
 // they depend on U and P only, and a split pass between two super-blocks sat on the critical path of every one of them.
 static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const float* U, const float* P, int64_t ldh,
                              const uint8_t* dead, int bits, int group, int sym, uint8_t* codes, float* scales,
-                             float* zeros, uint16_t* const* buf, uint16_t* const* farop, hipStream_t s, int terms,
-                             int mse_grid, int mse_steps, bool may_use_helper = true, bool make_farop = true) {
+                             float* zeros, uint16_t* const* buf, const SbNear& near, uint16_t* const* farop, hipStream_t s, int terms,
+                             int mse_grid, int mse_steps, bool may_use_helper = true, bool make_operands = true, hipEvent_t operands_made = nullptr) {
   const int64_t ev_kt = round_up(m, 256) * 32;   // a k-tile of the -E / V buffers, in elements
   if (dead) {
     hipLaunchKernelGGL(zero_dead_columns_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, s, W, ldw, (int)m, (int)n, dead);
@@ -460,8 +462,6 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
   }
   SbArgs a;
   a.W = W; a.ldw = ldw; a.m = (int)m; a.n = (int)n;
-  a.U = U; a.P = (terms & 2) ? P : U; a.ldh = ldh;
-  for (int i = 0; i < 4; ++i) a.Nop[i] = buf[8 + i];
   a.maxq = (float)((1 << bits) - 1); a.group = group; a.sym = sym; a.terms = terms;
   a.G = group > 0 ? (int)(n / group) : 1;
   a.scales = scales; a.zeros = zeros; a.codes = codes;
@@ -505,13 +505,17 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     }
     {
       ProfScope ps(kProfTrailSplit, st);
+      if (nsb > 1) chk(launch_near_operands(U, (terms & 2) ? P : U, ldh, (int)n, 1, nsb - 1, near, st));
       hipLaunchKernelGGL(far_operands_all_kernel, dim3((unsigned)(far_rows(n, 0) / 64), 2, (unsigned)((nsb - 1) * (kSbCols / QB))),
                          dim3(256), 0, st, U, (terms & 2) ? P : U, ldh, (int)n, farop[0], farop[1], farop[2], farop[3]);
       chk(hipGetLastError());
     }
-    if (two_chains) chk(hipEventRecord(side->events[2 * nsb + 2], st));
+    if (two_chains) {
+      operands_made = side->events[2 * nsb + 2];
+      chk(hipEventRecord(operands_made, st));
+    }
   };
-  const bool far_operands = make_farop && terms != 0 && nsb >= 2;
+  const bool far_operands = make_operands && terms != 0 && nsb >= 2;
   auto ev_sbk = [&](int k) { return side->events[2 * k]; };       // super-block k's kernel has finished
   auto ev_far2 = [&](int k) { return side->events[2 * k + 1]; };  // its far2 update has finished
   // W[:, c0:c1] += [-E | V] [U; P][super-block rows, c0:c1]: -E and V from buffer set `set`, the right operands of
@@ -542,12 +546,13 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     const int set = two_chains ? (k & 1) : 0;
     uint16_t* const* ev = buf + (set ? 12 : 0);
     a.sb0 = (int)sb0; a.sbw = (int)(sb_end - sb0);
-    a.Eh = far ? ev[0] : nullptr; a.El = ev[1]; a.Vh = ev[2]; a.Vl = ev[3];
+    a.EV = far ? ev[0] : nullptr; a.evstride = ev[1] - ev[0];
     // this super-block's columns must have every earlier update, and its buffer set must be free again
     if (two_chains && k >= 2) chk(hipStreamWaitEvent(s, ev_far2(k - 2), 0));
-    if (terms != 0) {
+    a.near = near.at(k);
+    if (k == 0 && make_operands && terms != 0) {
       ProfScope ps(kProfTrailSplit, s);
-      chk(launch_near_operands(U, (terms & 2) ? P : nullptr, ldh, (int)n, (int)sb0, a.sbw, buf + 8, s));
+      chk(launch_near_operands(U, (terms & 2) ? P : U, ldh, (int)n, 0, 1, near, s));
     }
     if (k == 0 && far_operands) make_far_operands();
     {
@@ -575,7 +580,7 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     };
     if (has_far2 && !far2_late) launch_far2();
     if (two_chains && k >= 1) chk(hipStreamWaitEvent(s, ev_far2(k - 1), 0));   // it adds to the same columns: keep the order
-    if (two_chains && k == 0 && make_farop) chk(hipStreamWaitEvent(s, side->events[2 * nsb + 2], 0));   // the far operands
+    if (k == 0 && operands_made) chk(hipStreamWaitEvent(s, operands_made, 0));
     far_update(set, k, sb_end, two_chains ? next_end : n, sb_end, s, 0);   // far1: the next super-block's columns (or all of them)
     if (far2_late) launch_far2();
   }
@@ -604,8 +609,8 @@ static int quantize_layer_impl(float* W, int64_t m, int64_t n, int64_t ldw, cons
   if (ws_bytes < L.total) return GPTAQ_EWORKSPACE;
   hipStream_t s = (hipStream_t)stream;
   unsigned char* base = (unsigned char*)ws;
-  uint16_t* buf[24];
-  for (int i = 0; i < 24; ++i) buf[i] = (uint16_t*)(base + L.off[i]);
+  uint16_t* buf[16];
+  for (int i = 0; i < 16; ++i) buf[i] = (uint16_t*)(base + L.off[i]);
 
   // The super-block kernel takes groups that tile its 16/32/128-column pieces; other group sizes go through the
   // block-by-block kernels below.
@@ -617,32 +622,48 @@ static int quantize_layer_impl(float* W, int64_t m, int64_t n, int64_t ldw, cons
     const int64_t nsb = (n + kSbCols - 1) / kSbCols;
     uint16_t* farop[4];
     for (int i = 0; i < 4; ++i) farop[i] = (uint16_t*)(base + L.off_far[i]);
+    SbNear near;
+    near.left = (uint16_t*)(base + L.off_near);
+    near.stride = nsb * kSbCols * kSbCols;
+    near.diag = (float*)(near.left + 4 * near.stride);
     if (terms != 0 && nsb >= 2 && m >= kRowSplitMin) {
-      {
-        // the far operands serve both halves: made once, before the streams fork
-        ProfScope ps(kProfTrailSplit, s);
-        hipLaunchKernelGGL(far_operands_all_kernel, dim3((unsigned)(far_rows(n, 0) / 64), 2, (unsigned)((nsb - 1) * (kSbCols / QB))),
-                           dim3(256), 0, s, U, (terms & 2) ? P : U, ldh, (int)n, farop[0], farop[1], farop[2], farop[3]);
-        GPTAQ_LAUNCH_CHECK();
-      }
       const int64_t mA = round_up((m + 1) / 2, 256), mB = m - mA;   // (a multiple of the GEMM's row tile: the halves' padded
                                                                     //  rows of the -E / V buffers then do not overlap)
       const int64_t G = group > 0 ? n / group : 1;
       std::lock_guard<std::mutex> side_lock(side_stream_mutex());
-      SideStream* side = side_stream(2);
+      SideStream* side = side_stream(3);
       if (!side) { set_last_hip_error(hipGetLastError()); return GPTAQ_ELAUNCH; }
-      hipEvent_t ev_fork = side->events[0], ev_join = side->events[1];
-      if (hipEventRecord(ev_fork, s) != hipSuccess || hipStreamWaitEvent(side->stream, ev_fork, 0) != hipSuccess) {
-        set_last_hip_error(hipGetLastError());
-        return GPTAQ_ELAUNCH;
+      hipEvent_t ev_fork = side->events[0], ev_join = side->events[1], ev_operands = side->events[2];
+      // The operands made of U and P serve both halves: those of the first super-block before the streams fork, the others in front of
+      // the second half, beside the first half's first super-block.
+      const float* Pt = (terms & 2) ? P : U;
+      hipError_t e;
+      {
+        ProfScope ps(kProfTrailSplit, s);
+        e = launch_near_operands(U, Pt, ldh, (int)n, 0, 1, near, s);
       }
-      uint16_t* bufB[12];
+      if (e == hipSuccess) e = hipEventRecord(ev_fork, s);
+      if (e == hipSuccess) e = hipStreamWaitEvent(side->stream, ev_fork, 0);
+      if (e != hipSuccess) { set_last_hip_error(e); return GPTAQ_ELAUNCH; }
+      {
+        ProfScope ps(kProfTrailSplit, side->stream);
+        e = launch_near_operands(U, Pt, ldh, (int)n, 1, (int)nsb - 1, near, side->stream);
+        hipLaunchKernelGGL(far_operands_all_kernel, dim3((unsigned)(far_rows(n, 0) / 64), 2, (unsigned)((nsb - 1) * (kSbCols / QB))),
+                           dim3(256), 0, side->stream, U, Pt, ldh, (int)n, farop[0], farop[1], farop[2], farop[3]);
+        if (e == hipSuccess) e = hipGetLastError();
+      }
+      if (e == hipSuccess) e = hipEventRecord(ev_operands, side->stream);
+      uint16_t* bufB[4];
       for (int i = 0; i < 4; ++i) bufB[i] = buf[i] + mA * kSbCols;          // its rows of the -E / V buffers
-      for (int i = 4; i < 12; ++i) bufB[i] = buf[12 + i];                  // operands of its own
-      const int rcB = quantize_layer_sb(W + mA * ldw, mB, n, ldw, U, P, ldh, dead, bits, group, sym, codes + mA * n,
-                                        scales + mA * G, zeros + mA * G, bufB, farop, side->stream, terms, mse_grid, mse_steps, false, false);
-      const int rcA = quantize_layer_sb(W, mA, n, ldw, U, P, ldh, dead, bits, group, sym, codes, scales, zeros, buf, farop,
-                                        s, terms, mse_grid, mse_steps, false, false);
+      int rcA = GPTAQ_ELAUNCH, rcB = GPTAQ_ELAUNCH;
+      if (e != hipSuccess) {
+        set_last_hip_error(e);
+      } else {
+        rcA = quantize_layer_sb(W, mA, n, ldw, U, P, ldh, dead, bits, group, sym, codes, scales, zeros, buf, near, farop, s, terms,
+                                mse_grid, mse_steps, false, false, ev_operands);
+        rcB = quantize_layer_sb(W + mA * ldw, mB, n, ldw, U, P, ldh, dead, bits, group, sym, codes + mA * n, scales + mA * G,
+                                zeros + mA * G, bufB, near, farop, side->stream, terms, mse_grid, mse_steps, false, false);
+      }
       // the helper stream is behind the caller's stream when the call returns, error or not
       hipError_t joined = hipEventRecord(ev_join, side->stream);
       if (joined == hipSuccess) joined = hipStreamWaitEvent(s, ev_join, 0);
@@ -650,7 +671,7 @@ static int quantize_layer_impl(float* W, int64_t m, int64_t n, int64_t ldw, cons
       if (joined != hipSuccess) { set_last_hip_error(joined); return GPTAQ_ELAUNCH; }
       return GPTAQ_OK;
     }
-    return quantize_layer_sb(W, m, n, ldw, U, P, ldh, dead, bits, group, sym, codes, scales, zeros, buf, farop, s, terms,
+    return quantize_layer_sb(W, m, n, ldw, U, P, ldh, dead, bits, group, sym, codes, scales, zeros, buf, near, farop, s, terms,
                              mse_grid, mse_steps);
   }
 

@@ -24,19 +24,20 @@
 // MFMA operands without a trip through LDS.
 //
 // A wave's life has three parts.  Updater: its block lies after the one being worked on; it applies every sub-block's
-// update to its four pieces, the left operands fetched into registers one sub-block ahead.  Owner: it runs the column
-// steps of its eight sub-blocks; between two of them it only updates the rest of its own block.  Finished: as one of two helpers it
-// fetches for the owner what that needs next (diagonal pieces of U and P, left operands) and writes the owner's results
-// to memory from LDS.  One workgroup barrier per sub-block publishes its -E and V.
+// update to its four pieces, the left operands fetched into registers a sub-block ahead.  Owner: it runs the column
+// steps of its eight sub-blocks; of its own block it updates the piece that its next sub-block lies in at once, the other pieces beside
+// that sub-block's column steps.  Finished.  One workgroup barrier per sub-block publishes its -E and V.  What the owner needs
+// next from memory (diagonal pieces of U and P, left operands) the others fetch into LDS, and they form and store its results.
 //
-// What bounds it: the owner's chain, ~5.3K clocks for each of the 64 sub-blocks: ~16 x 120 of column steps, then 16 swaps, the
-// publication of its -E and V, the barrier and 12 MFMAs (of 32 clocks, on a matrix pipe shared with an updater) per 32 columns of
-// its block that are left; the other waves' MFMAs (at most 96 per SIMD and sub-block) and the loads of their left operands (112 KB
-// per sub-block at first) hide behind that.  Counters: a wave is resident for 339K clocks, issues in 15 % of them and waits for
-// memory or LDS in 27 %; the matrix cores are busy 29 % of the time.
-// Measured, 1024 columns of 4096 rows (64 workgroups): 144 us with nothing beside it, 167 on average in a layer of 4096 columns, 200
-// (up to 310) beside the far updates of one of 11008; with four waves of two blocks each, where the owner also updated its
-// second block, read U and P from LDS in the column steps and stored its results itself, it took 290 alone.
+// What bounds it: the owner's chain, of the 64 sub-blocks about 3.3K clocks each (4.5K in the first two blocks, where two updaters to a SIMD
+// keep it waiting): 1.8K of column steps (376 vector instructions at 4.7 clocks; 400 more when 24 MFMAs run beside them), 170 to bring the
+// 16 columns into one row per lane, 1.0K for the operands and the 12 MFMAs of the next sub-block's piece; and 3.5K from one block to the
+// next (48 MFMAs of the new owner, the group's range and grid).  The matrix pipes of a SIMD with two updaters need 3.1K a sub-block.
+// What that took, on the way from 5.3K a sub-block (151 -> 137 us for 1024 columns of 4096 rows, 64 workgroups, with nothing beside it;
+// rows' outputs the same bits): W^ and codes formed by the wavefront that stores them; V split and LDS written under the next
+// piece's MFMAs; single MFMAs between column steps (7 clocks of the wavefront each, but 32 behind another MFMA); loads to LDS shared out
+// over all wavefronts and hidden from the compiler's wait counts; updaters' loads one by one between their MFMAs and a whole
+// sub-block ahead.
 #include "common.h"
 #include <utility>
 
@@ -70,18 +71,20 @@ __device__ __forceinline__ float sb_clip_scale(double base, int i, int grid) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Left operands of the in-super-block updates: for sub-block e (rows sb0 + 16 e .. + 15 of U and P) and
-// super-block column c, the 16 entries S[sb0 + 16 e + k][sb0 + c], k = 0..15, split into bf16 hi and lo, at
-// out[(e * 1024 + c) * 16 + k]: the 32 columns x 16 k a wavefront needs for one MFMA operand are 1 KB in a row.
-// grid (16, events, 2): blockIdx.x = tile of 64 columns, blockIdx.z = 0 for U, 1 for P.
-__global__ __launch_bounds__(256) void near_operands_kernel(const float* U, const float* P, int64_t ldh, int n, int sb0,
-                                                            uint16_t* Uh, uint16_t* Ul, uint16_t* Ph, uint16_t* Pl) {
+// What the super-block kernel reads of U and P, for super-block sb (rows and columns sb0 = 1024 sb on) and its sub-blocks e:
+//   * left operands of the updates: for super-block column c behind the sub-block, the 16 entries S[sb0 + 16 e + k][sb0 + c], k = 0..15,
+//     split into bf16 hi and lo, at ((64 sb + e) * 1024 + c) * 16 + k of its array: the 32 columns x 16 k a wavefront needs for one MFMA
+//     operand are 1 KB in a row (zeros for the sub-block's own columns, which take no update from it);
+//   * the diagonal piece, 512 floats at diag + 512 (64 sb + e): entry (step j, column c) of U at sb_diag_at(c, j) and of P 256 further on
+//     (c > j; zeros outside the matrix), and 1 / U_jj at 256 + j (column 0 of P has no entry of its own).
+// grid (16, events, 2 per super-block): blockIdx.x = tile of 64 columns, blockIdx.z = 2 (sb - first) + (0 for U, 1 for P).
+__host__ __device__ constexpr int sb_diag_at(int c, int j) { return 16 * c + 4 * ((j >> 2) ^ ((c >> 2) & 3)) + (j & 3); }   // (no bank conflicts)
+__global__ __launch_bounds__(256) void near_operands_kernel(const float* U, const float* P, int64_t ldh, int n, int first, SbNear o) {
   __shared__ float t[kSub][65];
-  const int e = blockIdx.y, c0 = blockIdx.x * 64;
-  if (c0 + 64 <= kSub * e) return;                         // entirely left of the sub-block: never read
-  const float* S = blockIdx.z ? P : U;
-  uint16_t* oh = blockIdx.z ? Ph : Uh;
-  uint16_t* ol = blockIdx.z ? Pl : Ul;
+  const int e = blockIdx.y, c0 = blockIdx.x * 64, isP = blockIdx.z & 1, sb = first + (blockIdx.z >> 1), sb0 = sb * kSbCols;
+  if (c0 + 64 <= kSub * e || sb0 + kSub * e >= n) return;  // entirely left of the sub-block, or no sub-block: never read
+  const float* S = isP ? P : U;
+  const int64_t ev = (int64_t)sb * (kSbCols / kSub) + e;
   const int c = threadIdx.x & 63, kq = threadIdx.x >> 6;
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
@@ -90,34 +93,45 @@ __global__ __launch_bounds__(256) void near_operands_kernel(const float* U, cons
     t[k][c] = (row < n && col < n) ? S[row * ldh + col] : 0.f;
   }
   __syncthreads();
+  const int own = kSub * e - c0;                           // the sub-block's own columns, from the tile's first
+  if (own >= 0) {
+    const int j = threadIdx.x & 15, cc = threadIdx.x >> 4;
+    const float v = t[j][own + cc];
+    float* d = o.diag + 512 * ev;
+    if (!isP) {
+      d[sb_diag_at(cc, j)] = cc > j ? v : 0.f;
+      if (cc == j) d[256 + j] = v != 0.f ? 1.f / v : 0.f;
+    } else if (cc > 0) {
+      d[256 + sb_diag_at(cc, j)] = cc > j ? v : 0.f;
+    }
+  }
   const int cc = threadIdx.x >> 2, k4 = (threadIdx.x & 3) * 4;
   uint16_t h[4], l[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const float v = t[k4 + i][cc];
+    const float v = cc >= own + kSub ? t[k4 + i][cc] : 0.f;
     h[i] = sb_bf16_rne(v);
     l[i] = sb_bf16_rne(v - sb_bf16_f32(h[i]));
   }
-  const int64_t o = ((int64_t)e * kSbCols + c0 + cc) * kSub + k4;
+  const int64_t at = (ev * kSbCols + c0 + cc) * kSub + k4;
   u32x2 vh = {(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
   u32x2 vl = {(uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16)};
-  *reinterpret_cast<u32x2*>(oh + o) = vh;
-  *reinterpret_cast<u32x2*>(ol + o) = vl;
+  *reinterpret_cast<u32x2*>(o.left + 2 * isP * o.stride + at) = vh;
+  *reinterpret_cast<u32x2*>(o.left + (2 * isP + 1) * o.stride + at) = vl;
 }
 
 // ---------------------------------------------------------------------------------------------------
 constexpr int kSbWaves = 8;                      // one 128-column block each
-constexpr int kSbDiagLd = 20;                    // padded row of a staged 16 x 16 piece, in floats
+constexpr int kSbRowLd = 20;                     // padded row of 16 results in LDS, in floats
 static_assert(kSbBlocks == kSbWaves, "one block per wave");
 struct SbShared {
   // operands [-E | V]^T of a sub-block's update in MFMA fragment order: [buffer][-E hi, -E lo, V hi, V lo][row half][lane]
   u32x4 frag[2][4][2][64];
   // left operands for the owner's own pieces: [buffer][piece][U hi, U lo, P hi, P lo], 1 KB each
-  u32x4 left[3][4][4][64];
-  float x[2][64][kSbDiagLd];                     // W^ of a sub-block, a row per row
-  u32x4 codes[2][64];
-  float Ud[2][kSub][kSbDiagLd], Pd[2][kSub][kSbDiagLd];     // diagonal pieces of U and P, transposed: [column][step]
-  float dinv[2][kSub];                           // 1 / U_jj
+  u32x4 left[4][4][4][64];
+  float d[2][64][kSbRowLd];                      // W^ of a sub-block in steps of the grid, less the zero-point, a row per row
+  float grid[2][64][2];                          // scale and zero-point of each row
+  float diag[4][2 * kSub * kSub];                // diagonal pieces of U and P and 1 / U_jj (see near_operands_kernel)
 };
 
 // Clip-range search of a group of the current weights (Section 5.1; candidates p = 1 - i / grid of the min-max range, the smallest
@@ -140,10 +154,15 @@ struct SbClip {
   int cand[kSbWaves][64];
 };
 
-// 1 KB per wavefront from global memory straight into LDS: lane l's 16 bytes land at lds + 16 l.
-__device__ __forceinline__ void sb_load_lds(const uint16_t* src, void* lds) {
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                   (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+__device__ __forceinline__ uint32_t sb_lds_address(const void* p) { return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p; }
+
+// 1 KB per wavefront from global memory straight into LDS: lane l's 16 bytes land at lds + 16 l (lds the same in all lanes).
+// It writes no register.  In asm because the compiler, once it has seen such a load, waits for all of a wavefront's loads before each
+// of its own reads of LDS and before each use of a loaded register, and an updater stood for a memory latency in every sub-block.  Unseen,
+// it can only make the compiler's waits for loads longer (they count in order); the waits for it are written out before a barrier.
+__device__ __forceinline__ void sb_load_lds(const void* src, void* lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+               : : "s"(__builtin_amdgcn_readfirstlane(sb_lds_address(lds))), "v"(src) : "memory", "m0");
 }
 
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits for every outstanding global
@@ -205,8 +224,12 @@ __device__ __forceinline__ void sb_extract(const f32x16 (&t)[2], float (&w)[kSub
   }
 }
 
-// t += left operands (U hi, U lo, P hi, P lo of 32 columns) x fragments (-E hi, -E lo, V hi, V lo): three products per term
-__device__ __forceinline__ void sb_piece_update(f32x16 (&t)[2], const u32x4 (&left)[4], const u32x4 (&fr)[4][2], bool useE, bool useP) {
+// t += left operands (U hi, U lo, P hi, P lo of 32 columns) x fragments (-E hi, -E lo, V hi, V lo): three products per term.
+// between(m) comes behind the m-th MFMA.
+template <class Between>
+__device__ __forceinline__ void sb_piece_update(f32x16 (&t)[2], const u32x4 (&left)[4], const u32x4 (&fr)[4][2], bool useE, bool useP,
+                                                Between&& between) {
+  int m = 0;
 #pragma unroll
   for (int tm = 0; tm < 2; ++tm) {
     if (!(tm ? useP : useE)) continue;
@@ -214,8 +237,12 @@ __device__ __forceinline__ void sb_piece_update(f32x16 (&t)[2], const u32x4 (&le
 #pragma unroll
     for (int q = 0; q < 3; ++q)
 #pragma unroll
-      for (int rh = 0; rh < 2; ++rh)
+      for (int rh = 0; rh < 2; ++rh) {
         t[rh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q == 2 ? al : ah, __builtin_bit_cast(bf16x8, fr[2 * tm + (q == 1)][rh]), t[rh], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        between(m++);
+        __builtin_amdgcn_sched_barrier(0);
+      }
   }
 }
 
@@ -228,32 +255,49 @@ __device__ __forceinline__ void sb_row_update(float (&w)[kSub], float s, float e
   (sb_fmac_lane<J + 1 + C>(w[J + 1 + C], s, e), ...);
 }
 
-// One column step (lines 7-10 of Algorithm 1), one row per lane, and those after it.
-template <int J>
-__device__ __forceinline__ void sb_steps(float (&w)[kSub], const float (&u)[kSub], const float (&p)[kSub], float dreg, const SbGrid& g,
-                                         float dlo, float dhi, float e_prev, float t_prev, float v_prev, u32x4 (&pk)[4][2], u32x4& cw) {
+// One column step (lines 7-10 of Algorithm 1), one row per lane, and those after it.  w[J] stays the value before rounding, d[J] is
+// its rounded value in steps of the grid, less the zero-point.  between(2 J) and between(2 J + 1) put other work of the wavefront
+// beside step J.
+template <int TERMS, int J, class Between>
+__device__ __forceinline__ void sb_steps(float (&w)[kSub], float (&d)[kSub], const float (&u)[kSub], const float (&p)[kSub], float dreg,
+                                         const SbGrid& g, float dlo, float dhi, float e_prev, float t_prev, u32x4 (&pe)[2][2],
+                                         Between&& between) {
   if constexpr (J < kSub) {
+    between(std::integral_constant<int, 2 * J>{});
     const float v = w[J];
     // code - zero = clamp(rint(v / scale), -zero, maxq - zero): the same integers as clamp(rint(.) + zero, 0, maxq)
     // - zero, with a shorter dependency chain in front of the updates (one median instead of add, max, min, sub)
-    const float d = __builtin_amdgcn_fmed3f(rintf(v * g.isc), dlo, dhi);
-    const float t = fmaf(g.sc, d, -v);                     // W^ - v, rounded once
+    d[J] = __builtin_amdgcn_fmed3f(rintf(v * g.isc), dlo, dhi);
+    const float t = fmaf(g.sc, d[J], -v);                  // W^ - v, rounded once
     const float e1 = sb_mul_lane<J>(dreg, t);              // -E_J
-    w[J] = g.sc * d;
-    cw[J >> 2] = __builtin_amdgcn_cvt_pk_u8_f32(d + g.zr, J & 3, cw[J >> 2]);
     constexpr std::make_integer_sequence<int, kSub - 1 - J> later{};
-    sb_row_update<J>(w, p[J], v, later);
-    sb_row_update<J>(w, u[J], e1, later);
+    if constexpr (TERMS & 2) sb_row_update<J>(w, p[J], v, later);
+    between(std::integral_constant<int, 2 * J + 1>{});
+    if constexpr (TERMS & 1) sb_row_update<J>(w, u[J], e1, later);
     if constexpr (J & 1) {
-      const u32x2 pe = sb_split_e<J>(e_prev, e1, t_prev, t, dreg), pv = sb_split2(v_prev, v);
-      pk[0][J >> 3][(J >> 1) & 3] = pe[0];
-      pk[1][J >> 3][(J >> 1) & 3] = pe[1];
-      pk[2][J >> 3][(J >> 1) & 3] = pv[0];
-      pk[3][J >> 3][(J >> 1) & 3] = pv[1];
+      const u32x2 x = sb_split_e<J>(e_prev, e1, t_prev, t, dreg);
+      pe[0][J >> 3][(J >> 1) & 3] = x[0];
+      pe[1][J >> 3][(J >> 1) & 3] = x[1];
     }
-    sb_steps<J + 1>(w, u, p, dreg, g, dlo, dhi, e1, t, v, pk, cw);
+    sb_steps<TERMS, J + 1>(w, d, u, p, dreg, g, dlo, dhi, e1, t, pe, between);
   }
 }
+
+// one row and two chunks of eight columns per lane -> one chunk and a row of each half per lane (an MFMA operand)
+__device__ __forceinline__ void sb_to_operand(u32x4 (&x)[2]) {
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const u32x2 r = __builtin_amdgcn_permlane32_swap(x[0][k], x[1][k], false, false);
+    x[0][k] = r[0];
+    x[1][k] = r[1];
+  }
+}
+
+// Of an owner's update by its sub-block `eb` of the block: the piece its next sub-block lies in is updated at once, and pieces
+// first_deferred(eb) .. 3 beside the next sub-block's column steps.  (A group of 64 may start at sub-block 4 and needs every piece from 2
+// on; more than two pieces would not fit beside the steps.)
+__host__ __device__ constexpr int sb_next_piece(int eb) { return (eb + 1) >> 1; }
+__host__ __device__ constexpr int sb_first_deferred(int eb) { return eb < 0 || eb == 3 ? 4 : eb == 0 ? 2 : sb_next_piece(eb) + 1; }
 
 // FAST: rows of W and of the codes are 16-byte aligned and n is a multiple of 16 (vector loads and stores).
 // TERMS: the update terms of Eq. 15 that are applied (3: both; a run-time choice would cost branches around every MFMA group,
@@ -303,86 +347,87 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
     }
   }
 
-  // ---- the two helpers of sub-block x: wave (block + 7) % 8 fetches, wave (block + 6) % 8 stores
-  // what the owner of sub-block x needs besides its accumulators: the diagonal pieces of U and P (transposed into
-  // buffer x & 1) and the left operands of the update of its own later columns (buffer x % 3)
+  // ---- what the wavefronts that do not own block b do for the one that does.
+  // All: fetch what it needs besides its accumulators, the diagonal pieces of U and P and the left operands of the update of its own
+  // later columns, both into buffer x & 3 and two sub-blocks ahead (the owner reads the diagonal pieces of x before barrier x - 1, and the
+  // last left operands of x before barrier x + 1).  The loads are requested behind a barrier and waited for in front of the next one.
+  // (A wavefront hands one such load over in some 80 clocks.  Up to 18 of them in one wavefront made it late at the barrier
+  // while it was an updater itself, in the first two blocks: 3K clocks a sub-block.)
+  // And store its results: wave b - 1, or all for the first block.
   auto own_lane = [&]() {                                 // (the search leaves no registers for addresses kept between the events)
     int l = lane;
-    if (CLIP) asm volatile("" : "+v"(l));
+    asm volatile("" : "+v"(l));
     return l;
   };
-  auto fetch_for_owner = [&](int x) {
+  auto request = [&](int x, int t) {                        // item t of sub-block x
     const int lane = own_lane();
-    const uint32_t lane_off = (uint32_t)((lane & 31) * kSub + 8 * (lane >> 5));
-    const int b = x >> 3, eb = x & 7;
-    if (update) {
-      for (int i = (eb + 1) >> 1; i < 4; ++i) {
-        const int64_t o = ((int64_t)x * kSbCols + 128 * b + 32 * i) * kSub;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (q < 2 ? useE : useP) sb_load_lds(a.Nop[q] + o + lane_off, &sh.left[x % 3][i][q][0]);
-      }
-    }
-    const int j = lane >> 2, c4 = (lane & 3) * 4;
-    const int64_t r = (int64_t)a.sb0 + kSub * x + j;
-    float u[4], p[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t c = (int64_t)a.sb0 + kSub * x + c4 + i;
-      const bool in = r < a.n && c < a.n;
-      u[i] = (in && c4 + i >= j && (useE || c4 + i == j)) ? a.U[r * a.ldh + c] : 0.f;   // the diagonal of U is always needed
-      p[i] = (in && c4 + i > j && useP) ? a.P[r * a.ldh + c] : 0.f;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      sh.Ud[x & 1][c4 + i][j] = u[i];
-      sh.Pd[x & 1][c4 + i][j] = p[i];
-      if (c4 + i == j) sh.dinv[x & 1][j] = u[i] != 0.f ? 1.f / u[i] : 0.f;
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // the left operands have landed
+    const int eb = x & 7, count = update ? 4 * (4 - sb_next_piece(eb)) + 2 : 0;
+    const int i = 3 - ((t - 2) >> 2), q = (t & 3) ^ 2;      // t = 0, 1: the diagonal pieces; then the four left operands of piece 3, 2, ...
+    if (t >= count) return;
+    if (t < 2) sb_load_lds(a.near.diag + 512 * x + 256 * t + 4 * lane, &sh.diag[x & 3][256 * t]);
+    else if (q < 2 ? useE : useP)
+      sb_load_lds(a.near.left + q * a.near.stride + ((x * kSbCols + 128 * (x >> 3) + 32 * i) * kSub + (lane & 31) * kSub + 8 * (lane >> 5)),
+                  &sh.left[x & 3][i][q][0]);
   };
-  // results of sub-block x from LDS to memory: W^, codes, and -E and V for the update of the columns after the super-block
-  auto store_results = [&](int x) {
+  // results of sub-block x, from LDS to memory.  W^ and codes (formed here: the owner has the longer chain), 16 rows at a time:
+  auto store_rows = [&](int x, int it) {
     const int lane = own_lane();
     const int buf = x & 1, colg = a.sb0 + kSub * x;
+    const int r = FAST ? 16 * it + (lane >> 2) : 16 * it + (lane & 15), c = FAST ? 4 * (lane & 3) : 4 * (lane >> 4);
+    const f32x4 d = *reinterpret_cast<const f32x4*>(&sh.d[buf][r][c]);
+    const float sc = sh.grid[buf][r][0], zr = sh.grid[buf][r][1];
+    uint32_t cw = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) cw = __builtin_amdgcn_cvt_pk_u8_f32(d[k] + zr, k, cw);
+    if (row0 + r >= a.m) return;
+    float* w = a.W + (int64_t)(row0 + r) * a.ldw + colg + c;
+    uint8_t* code = a.codes + (int64_t)(row0 + r) * a.n + colg + c;
     if (FAST) {
+      *reinterpret_cast<f32x4*>(w) = f32x4{sc * d[0], sc * d[1], sc * d[2], sc * d[3]};
+      *reinterpret_cast<uint32_t*>(code) = cw;
+    } else {
 #pragma unroll
-      for (int it = 0; it < 4; ++it) {
-        const int item = lane + 64 * it, r = item >> 2, q = item & 3;
-        if (row0 + r < a.m)
-          *reinterpret_cast<f32x4*>(a.W + (int64_t)(row0 + r) * a.ldw + colg + 4 * q) = *reinterpret_cast<const f32x4*>(&sh.x[buf][r][4 * q]);
-      }
-      if (row0 + lane < a.m) *reinterpret_cast<u32x4*>(a.codes + (int64_t)(row0 + lane) * a.n + colg) = sh.codes[buf][lane];
-    } else if (row0 + lane < a.m) {
-      const u32x4 cw = sh.codes[buf][lane];
-#pragma unroll
-      for (int c = 0; c < kSub; ++c)
-        if (colg + c < a.n) {
-          a.W[(int64_t)(row0 + lane) * a.ldw + colg + c] = sh.x[buf][lane][c];
-          a.codes[(int64_t)(row0 + lane) * a.n + colg + c] = (uint8_t)(cw[c >> 2] >> (8 * (c & 3)));
+      for (int k = 0; k < 4; ++k)
+        if (colg + c + k < a.n) {
+          w[k] = sc * d[k];
+          code[k] = (uint8_t)(cw >> (8 * k));
         }
     }
-    if (a.Eh) {
+  };
+  // and, 32 rows at a time, -E hi, -E lo, V hi and V lo for the update of the columns after the super-block
+  auto store_operands = [&](int x, int it) {
+    const int lane = own_lane();
+    const int item = lane + 64 * it, r = item >> 1, ch = item & 1;
+    u32x4 v[4];
 #pragma unroll
-      for (int it = 0; it < 2; ++it) {
-        const int item = lane + 64 * it, r = item >> 1, ch = item & 1;
-        if (row0 + r < a.m) {
-          const int64_t o = (int64_t)(x >> 1) * a.evkt + (int64_t)(row0 + r) * 32 + kSub * (x & 1) + 8 * ch;
-          *reinterpret_cast<u32x4*>(a.Eh + o) = sh.frag[buf][0][r >> 5][32 * ch + (r & 31)];
-          *reinterpret_cast<u32x4*>(a.El + o) = sh.frag[buf][1][r >> 5][32 * ch + (r & 31)];
-          *reinterpret_cast<u32x4*>(a.Vh + o) = sh.frag[buf][2][r >> 5][32 * ch + (r & 31)];
-          *reinterpret_cast<u32x4*>(a.Vl + o) = sh.frag[buf][3][r >> 5][32 * ch + (r & 31)];
-        }
-      }
+    for (int q = 0; q < 4; ++q) v[q] = sh.frag[x & 1][q][r >> 5][32 * ch + (r & 31)];
+    uint16_t* dst = a.EV + (int64_t)(x >> 1) * a.evkt + (int64_t)(row0 + r) * 32 + kSub * (x & 1) + 8 * ch;
+    if (row0 + r >= a.m) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) *reinterpret_cast<u32x4*>(dst + q * a.evstride) = v[q];
+  };
+  // this wavefront's part in the time between barrier x - 1 and barrier x, begin and end (x == nev: after the last barrier)
+  auto help_begin = [&](int x) {
+    const int r = (wave - (x >> 3) - 1) & 7;               // (7: the owner)
+    if (r < 7 && x + 2 < nev) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) request(x + 2, r + 7 * k);
     }
   };
-  // a helper's part of the time between barrier x - 1 and barrier x (x == nev: after the last one)
-  auto help = [&](int x) {
-    const int b = min(x, nev - 1) >> 3;
-    if (wave == ((b + 7) & 7) && x + 1 < nev) fetch_for_owner(x + 1);
-    if (wave == ((b + 6) & 7) && x >= 1) store_results(x - 1);
+  auto help_end = [&](int x) {
+    // (in the first block no wavefront is without updates, and each takes a share)
+    const int b = min(x, nev - 1) >> 3, r = b == 0 ? wave - 1 : wave == b - 1 ? 0 : -1, step = b == 0 ? 7 : 1;
+    if (x < 1 || r < 0) return;
+    for (int t = r; t < (a.EV ? 6 : 4); t += step) {
+      if (t < 4) store_rows(x - 1, t);
+      else store_operands(x - 1, t - 4);
+    }
   };
-  if (wave == 7) fetch_for_owner(0);
+  for (int k = 0; k < 3; ++k) {
+    request(0, wave + 8 * k);
+    if (nev > 1) request(1, wave + 8 * k);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 
   // this wavefront's part of the search for the group that starts at sub-block x; all wavefronts come here at the same x
@@ -468,41 +513,52 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
     cl.cand[wave][lane] = cand;
     sb_barrier();
   };
-  auto group_starts = [&](int x) { return CLIP && (kSub * (x & 7)) % a.group == 0; };
+  auto group_starts = [&](int x) { return CLIP && ((kSub * (x & 7)) & (a.group - 1)) == 0; };      // (groups are powers of two here)
 
   // ================= updater: sub-blocks before this wave's own
   int e = 0;
   if (first_own < last_own && first_own > 0) {
-    // left operands of piece t % 4 of sub-block t / 4, requested two pieces ahead of their use (three register sets would
-    // not fit beside the accumulators; two pieces' MFMAs and the other wave of the SIMD cover an L2 round trip)
-    u32x4 left[2][4];
-    auto load_left = [&](int x, int i, u32x4 (&dst)[4]) {
-      const int64_t o = ((int64_t)x * kSbCols + 128 * wave + 32 * i) * kSub;
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if (q < 2 ? useE : useP) dst[q] = *reinterpret_cast<const u32x4*>(a.Nop[q] + o + lane_off);
+    // left operands of the four pieces, a register set each.  A piece's set is filled again between the MFMAs of the piece behind it, a
+    // load at a time, for the next sub-block.  (Two sets, filled two pieces ahead: an L2 round trip is longer than the MFMAs of a piece.
+    // Four loads in a row behind each piece: up to 28 wavefront loads of all updaters at once, and the matrix cores idle.)
+    constexpr int PER = 2 * ((TERMS & 1) + (TERMS >> 1));  // loads per piece
+    u32x4 left[4][4];
+    auto load_left = [&](int x, int i, int k) {            // the k-th of them
+      const int q = useE ? k : k + 2;
+      left[i][q] = *reinterpret_cast<const u32x4*>(a.near.left + q * a.near.stride + ((x * kSbCols + 128 * wave + 32 * i) * kSub + (int)lane_off));
     };
-    if (update) {
-      load_left(0, 0, left[0]);
-      load_left(0, 1, left[1]);
-    }
+    auto load_first = [&](int x) {
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int k = 0; k < PER; ++k) load_left(x, i, k);
+    };
+    help_begin(0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (update) load_first(0);
     for (; e < first_own; ++e) {
-      if (group_starts(e)) search();
-      help(e);
+      if (group_starts(e)) {
+        search();
+        if (update) load_first(e);                         // (again: the search leaves no registers for them)
+      }
+      // (the requests for the owner are older than those for this wavefront's next update)
+      if (update) asm volatile("s_waitcnt vmcnt(%0)" :: "n"(3 * PER) : "memory");
+      help_end(e);
       sb_barrier();
       if (!update) continue;
+      if (e == first_own - 1) __builtin_amdgcn_s_setprio(3);   // the other waves wait for this one from here on
       u32x4 fr[4][2];
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int rh = 0; rh < 2; ++rh) fr[q][rh] = sh.frag[e & 1][q][rh][lane];
-      const int nx = min(e + 1, first_own - 1);            // (the last request is a repeat that nobody uses)
+      help_begin(e + 1);
+      const int nx = min(e + 1, first_own - 1);            // (the last requests are repeats that nobody uses)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        sb_piece_update(acc[i], left[i & 1], fr, useE, useP);
-        load_left(i < 2 ? e : nx, (i + 2) & 3, left[i & 1]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+      for (int i = 0; i < 4; ++i)
+        sb_piece_update(acc[i], left[i], fr, useE, useP, [&](int m) {
+          if (m % 3 == 2 && m / 3 < PER) load_left(i == 0 ? e : nx, (i + 3) & 3, m / 3);
+        });
     }
   }
 
@@ -532,30 +588,43 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
       }
       g.isc = 1.f / g.sc;
       if (row < a.m) {
-        const int64_t o = (int64_t)row * a.G + (a.sb0 + kSub * x) / a.group;
+        const int64_t o = (int64_t)row * a.G + ((a.sb0 + kSub * x) >> (31 - __builtin_clz(a.group)));
         a.scales[o] = g.sc;
         a.zeros[o] = g.zr;
       }
     };
+    __builtin_amdgcn_s_setprio(3);
+    float u[kSub], p[kSub], dreg;
+    auto load_diag = [&](int x) {
+      const int c = lane & 15;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const f32x4 a4 = *reinterpret_cast<const f32x4*>(&sh.diag[x & 3][sb_diag_at(c, 4 * q)]);
+        const f32x4 b4 = *reinterpret_cast<const f32x4*>(&sh.diag[x & 3][256 + sb_diag_at(c, 4 * q)]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { u[4 * q + k] = a4[k]; p[4 * q + k] = b4[k]; }
+      }
+      dreg = sh.diag[x & 3][256 + c];
+    };
+    if (!CLIP) load_diag(first_own);
     auto event = [&](auto number) {
       constexpr int EB = decltype(number)::value;
-      constexpr int R = EB >> 1, HALF = EB & 1, NEXT = (EB + 1) >> 1;      // current piece, its half, first piece with columns left
+      constexpr int R = EB >> 1, HALF = EB & 1, NEXT = sb_next_piece(EB);  // current piece, its half, the next sub-block's piece
       const int x = first_own + EB, buf = x & 1;
       if (x >= last_own) return;
       // ---- group range over the current (error-compensated) weights: the group's pieces are all in this wave
-      if (HALF == 0 && a.group >= 32 && (32 * R) % a.group == 0) {
-        float mn[2], mx[2];
+      if (HALF == 0 && a.group >= 32 && ((32 * R) & (a.group - 1)) == 0) {
+        float lo[2] = {0.f, 0.f}, hi[2] = {0.f, 0.f}, mn[2], mx[2];
 #pragma unroll
         for (int rh = 0; rh < 2; ++rh) {
-          float lo = 0.f, hi = 0.f;
 #pragma unroll
           for (int i = R; i < 4; ++i)
             if (32 * (i - R) < a.group) {
 #pragma unroll
-              for (int v = 0; v < 16; ++v) { lo = fminf(lo, acc[i][rh][v]); hi = fmaxf(hi, acc[i][rh][v]); }
+              for (int v = 0; v < 16; ++v) { lo[rh] = fminf(lo[rh], acc[i][rh][v]); hi[rh] = fmaxf(hi[rh], acc[i][rh][v]); }
             }
-          const u32x2 r0 = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(lo), false, false);
-          const u32x2 r1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(hi), __float_as_uint(hi), false, false);
+          const u32x2 r0 = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo[rh]), __float_as_uint(lo[rh]), false, false);
+          const u32x2 r1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(hi[rh]), __float_as_uint(hi[rh]), false, false);
           mn[rh] = fminf(__uint_as_float(r0[0]), __uint_as_float(r0[1]));
           mx[rh] = fmaxf(__uint_as_float(r1[0]), __uint_as_float(r1[1]));
         }
@@ -571,20 +640,9 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
         }
         new_grid(lh ? mn[1] : mn[0], lh ? mx[1] : mx[0], x);
       }
-      float w[kSub], u[kSub], p[kSub], dreg;
-      auto load_diag = [&]() {
-        const float* ud = sh.Ud[buf][lane & 15];
-        const float* pd = sh.Pd[buf][lane & 15];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 a4 = *reinterpret_cast<const f32x4*>(ud + 4 * q), b4 = *reinterpret_cast<const f32x4*>(pd + 4 * q);
-#pragma unroll
-          for (int k = 0; k < 4; ++k) { u[4 * q + k] = a4[k]; p[4 * q + k] = b4[k]; }
-        }
-        dreg = sh.dinv[buf][lane & 15];
-      };
+      float w[kSub], d[kSub];
       const bool late = CLIP && a.group == kSub;           // (a search in between leaves no registers for them)
-      if (!late) load_diag();
+      if (CLIP && !late) load_diag(x);                     // (without a search they have been read already)
       sb_extract<HALF>(acc[R], w);
       if (a.group == kSub) {                               // the group is this sub-block: its grid comes from the registers
         float mn = 0.f, mx = 0.f;
@@ -596,45 +654,91 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
         }
         new_grid(mn, mx, x);
       }
-      if (late) load_diag();
+      if (late) load_diag(x);
       sb_pin(u);
       sb_pin(p);
       asm volatile("s_nop 1" : "+v"(dreg));
-      u32x4 pk[4][2];                                      // -E hi, -E lo, V hi, V lo: 16 columns as two chunks of eight
-      u32x4 cw = {0u, 0u, 0u, 0u};                         // the codes, one byte each
-      sb_steps<0>(w, u, p, dreg, g, -g.zr, a.maxq - g.zr, 0.f, 0.f, 0.f, pk, cw);
-      // one row and two chunks of eight columns per lane -> one chunk and a row of each half per lane (an MFMA operand)
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const u32x2 r = __builtin_amdgcn_permlane32_swap(pk[q][0][k], pk[q][1][k], false, false);
-          pk[q][0][k] = r[0];
-          pk[q][1][k] = r[1];
-        }
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int rh = 0; rh < 2; ++rh) sh.frag[buf][q][rh][lane] = pk[q][rh];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) *reinterpret_cast<f32x4*>(&sh.x[buf][lane][4 * q]) = f32x4{w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]};
-      sh.codes[buf][lane] = cw;
-      sb_barrier();
-      if (update) {
-        // the columns of this block that are left, the next sub-block's piece first
-#pragma unroll
-        for (int i = R; i < 4; ++i) {
-          if (i < NEXT) continue;
-          u32x4 left[4];
-#pragma unroll
-          for (int q = 0; q < 4; ++q) left[q] = sh.left[x % 3][i][q][lane];
-          if (HALF == 0 && i == R) {
-            // the sub-block's own columns, the first half of its piece, take no update
-            const bool keep = l32 >= kSub;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) left[q] = keep ? left[q] : u32x4{0u, 0u, 0u, 0u};
+      // ---- the column steps.  Beside them, two MFMAs (one product for both row halves) per step from step 1 on: what the sub-block
+      // before has left of its update.  Their operands are read from LDS one step ahead.  (An MFMA alone takes 7 clocks of the
+      // wavefront's time here; right behind another one 32.)
+      constexpr int D0 = sb_first_deferred(EB - 1), PER = update ? 3 * ((TERMS & 1) + (TERMS >> 1)) : 0, NSLOT = (4 - D0) * PER;
+      static_assert(NSLOT < kSub, "a product per step");
+      u32x4 dl[2], df[2][2];
+      auto between = [&](auto point) {
+        constexpr int J = decltype(point)::value / 2, rh = decltype(point)::value & 1;
+        if constexpr (rh == 0 && J > 0 && J % 4 == 0)
+          *reinterpret_cast<f32x4*>(&sh.d[buf][lane][J - 4]) = f32x4{d[J - 4], d[J - 3], d[J - 2], d[J - 1]};
+        if constexpr (NSLOT > 0) {
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (J < NSLOT && rh == 0) {
+            constexpr int i = D0 + J / PER, tm = useE ? J % PER / 3 : 1, q = J % 3;
+            dl[J & 1] = sh.left[(x - 1) & 3][i][2 * tm + (q == 2)][lane];
+            df[J & 1][0] = sh.frag[(x - 1) & 1][2 * tm + (q == 1)][0][lane];
+            df[J & 1][1] = sh.frag[(x - 1) & 1][2 * tm + (q == 1)][1][lane];
           }
-          sb_piece_update(acc[i], left, pk, useE, useP);
+          if constexpr (J >= 1 && J <= NSLOT) {
+            constexpr int i = D0 + (J - 1) / PER, b = (J - 1) & 1;
+            acc[i][rh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, dl[b]), __builtin_bit_cast(bf16x8, df[b][rh]), acc[i][rh], 0, 0, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      };
+      u32x4 pe[2][2], pv[2][2];                            // -E and V as bf16 hi, lo: 16 columns as two chunks of eight
+      sb_steps<TERMS, 0>(w, d, u, p, dreg, g, -g.zr, a.maxq - g.zr, 0.f, 0.f, pe, between);
+      // ---- the update of the next sub-block's piece, the one thing that sub-block waits for.  Its MFMAs run beside the rest of this
+      // one's work, the split of V under the products of -E, and the writes to LDS.
+      constexpr bool own = update && NEXT < 4;
+      u32x4 left[4];
+      if constexpr (own) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (q < 2 ? useE : useP) left[q] = sh.left[x & 3][NEXT][q][lane];
+      }
+      auto product = [&](int tm, int k, const u32x4 (&f)[2][2]) {        // k-th MFMA of a term
+        if constexpr (own) {
+          const int q = k >> 1, rh = k & 1;
+          acc[NEXT][rh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, left[2 * tm + (q == 2)]),
+                                                                  __builtin_bit_cast(bf16x8, f[q == 1][rh]), acc[NEXT][rh], 0, 0, 0);
+        }
+      };
+      auto split_v = [&](int k) {                                         // V of columns 2 k and 2 k + 1
+        const u32x2 s = sb_split2(w[2 * k], w[2 * k + 1]);
+        pv[0][k >> 2][k & 3] = s[0];
+        pv[1][k >> 2][k & 3] = s[1];
+      };
+      sb_to_operand(pe[0]);
+      sb_to_operand(pe[1]);
+      *reinterpret_cast<f32x4*>(&sh.d[buf][lane][12]) = f32x4{d[12], d[13], d[14], d[15]};
+      *reinterpret_cast<u32x2*>(&sh.grid[buf][lane][0]) = u32x2{__float_as_uint(g.sc), __float_as_uint(g.zr)};
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        if (useE) product(0, k, pe);
+        __builtin_amdgcn_sched_barrier(0);
+        if (k < 4) sh.frag[buf][k >> 1][k & 1][lane] = pe[k >> 1][k & 1];
+        split_v(k);
+        if (k >= 4) split_v(k + 2);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      sb_to_operand(pv[0]);
+      sb_to_operand(pv[1]);
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        if (useP) product(1, k, pv);
+        __builtin_amdgcn_sched_barrier(0);
+        if (k < 4) sh.frag[buf][2 + (k >> 1)][k & 1][lane] = pv[k >> 1][k & 1];
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (!CLIP && EB < 7 && x + 1 < last_own) load_diag(x + 1);
+      sb_barrier();
+      if constexpr (own) {
+        // the other pieces that cannot wait for the next column steps
+#pragma unroll
+        for (int i = NEXT + 1; i < sb_first_deferred(EB); ++i) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (q < 2 ? useE : useP) left[q] = sh.left[x & 3][i][q][lane];
+          const u32x4 fr[4][2] = {{pe[0][0], pe[0][1]}, {pe[1][0], pe[1][1]}, {pv[0][0], pv[0][1]}, {pv[1][0], pv[1][1]}};
+          sb_piece_update(acc[i], left, fr, useE, useP, [](int) {});
         }
       }
     };
@@ -647,22 +751,22 @@ __global__ __launch_bounds__(64 * kSbWaves) void quant_sb_kernel(SbArgs a) {
     event(std::integral_constant<int, 6>{});
     event(std::integral_constant<int, 7>{});
     e = last_own;
+    __builtin_amdgcn_s_setprio(0);
   }
 
   // ================= finished
   for (; e < nev; ++e) {
+    help_begin(e);
     if (group_starts(e)) search();
-    help(e);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    help_end(e);
     sb_barrier();
   }
-  help(nev);
+  help_end(nev);
 }
 
-hipError_t launch_near_operands(const float* U, const float* P, int64_t ldh, int n, int sb0, int sbw, uint16_t* const* N4,
-                                hipStream_t s) {
-  const int nev = (sbw + kSub - 1) / kSub;
-  hipLaunchKernelGGL(near_operands_kernel, dim3(kSbCols / 64, nev, P ? 2 : 1), dim3(256), 0, s, U, P ? P : U, ldh, n, sb0,
-                     N4[0], N4[1], N4[2], N4[3]);
+hipError_t launch_near_operands(const float* U, const float* P, int64_t ldh, int n, int first, int count, const SbNear& o, hipStream_t s) {
+  hipLaunchKernelGGL(near_operands_kernel, dim3(kSbCols / 64, kSbCols / kSub, 2 * count), dim3(256), 0, s, U, P, ldh, n, first, o);
   return hipGetLastError();
 }
 
