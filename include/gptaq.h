@@ -58,7 +58,8 @@ int gptaq_last_hip_error(void);
  *   dXXT      : (n x n) fp32, ldh >= n, all entries maintained (not symmetric).
  *   ws        : >= gptaq_accumulate_workspace_bytes(tokens, n) bytes, 256-byte aligned.  A
  *               smaller workspace is accepted down to the size for 64 tokens; the chunk is
- *               then processed in several passes.
+ *               then processed in several passes.  (With few columns the size has room for sums
+ *               taken in parts of the tokens; a workspace without it takes them in one part.)
  * dX is formed in fp32 and split exactly into two bf16 terms, so products are exact and
  * only fp32 accumulation rounding remains.
  */

@@ -118,6 +118,42 @@ __global__ void invert_permutation_kernel(const int32_t* perm, int n, int32_t* i
 
 static int64_t padded_n(int64_t n) { return round_up(n, gemm_tile_for(n, n)); }
 
+// In how many parts of their tokens the sums of a pass are taken, and what the parts' sums need beside the operands.
+// With few columns the tiles of H and dXXT leave most of the chip idle (n = 1024: 72 or 100 of 512 places for 128-tiles).  dXXT's tiles,
+// of two products, are split in `split` parts and H's, of one, in half as many, so that all workgroups take the same time.  The number is
+// the one with the least time for both forms of the call together (it must not depend on the form: the upper form is bit for bit the
+// full one where it is defined), from: 18 ns per token in a round of more than 256 workgroups (two to a CU), 11 in one of fewer; 5 us per
+// round; parts written and read at 4 TB/s, and a launch for them.  (Four workgroups a tile row sum H's diagonal in one part: see
+// diagonal_block.)
+// Measured, one part / so many, us per call of 32768 tokens, upper form (full): n = 256 313 / 78 (311 / 79), 512 321 / 94 (312 / 106), 768
+// 335 / 133 (327 / 153), 1024 383 / 197 (386 / 240), 1280 491 / 262 (489 / 354), 1536 536 / 342 (541 / 442); of 8192 tokens 512 92 / 39, 1024
+// 98 / 56 (99 / 73).  Where the estimate promises less than a factor of 1.5 there was little to be had (without the diagonal's
+// workgroups: 2048 594 / 511 (687 / 699), 2736 888 / 861 (1241 / 1277), 3072 and 8192 tokens 257 / 277 (352 / 384)).  Errors against 64 bits
+// fall with the length of the sums: dXXT 8.7e-7 to 2.4e-7 at n = 1024.
+static int split_for(int64_t n, int64_t tokens) {
+  if (gemm_tile_for(n, n) != 128) return 1;      // (256-tiles: they fill the chip, and the power limit takes what a fuller last round gives)
+  if (tokens < 8192) return 1;                   // (the workspace of a call with few samples stays that of its operands)
+  const int64_t t = (n + 127) / 128, upper = t * (t + 1) / 2;
+  int best = 1;
+  double least = 0.;
+  for (int split : {1, 2, 4, 6, 8, 12, 16}) {
+    double us = 0.;
+    for (int64_t dxxt : {upper, t * t}) {
+      const int64_t wgs = dxxt * split + upper * ((split + 1) / 2) + (split > 1 ? 4 * t : 0), rounds = wgs / 512, rest = wgs % 512;
+      us += (0.018 * (double)rounds + (rest == 0 ? 0. : rest <= 256 ? 0.0112 : 0.018)) * (double)tokens / split;
+      us += 5. * (double)(rounds + (rest > 0)) + (split > 1 ? (double)wgs * 0.033 + 6. : 0.);
+    }
+    if (split == 1) least = us / 1.5;
+    else if (us < least) { best = split; least = us; }
+  }
+  return best;
+}
+static size_t partial_bytes(int64_t n, int split) {
+  if (split <= 1) return 0;
+  const int64_t t = (n + 127) / 128;
+  return (size_t)(t * t * split + t * (t + 1) / 2 * (split / 2)) * (128 * 128 * 4);
+}
+
 }  // namespace gptaq
 
 using namespace gptaq;
@@ -125,7 +161,7 @@ using namespace gptaq;
 extern "C" size_t gptaq_accumulate_workspace_bytes(int64_t tokens, int64_t n) {
   if (tokens <= 0 || n <= 0) return 0;
   const int64_t c = round_up(tokens < 32768 ? tokens : 32768, 64);
-  return (size_t)(3 * padded_n(n) * c * 2);
+  return (size_t)(3 * padded_n(n) * c * 2) + partial_bytes(n, split_for(n, c));
 }
 
 // H += X X^T (upper tiles) and dXXT += (hi + lo) X^T over cp tokens of split operands, as one launch.
@@ -133,7 +169,8 @@ extern "C" size_t gptaq_accumulate_workspace_bytes(int64_t tokens, int64_t n) {
 // L is lower triangular, so entry (i, k) of dXXT reaches P only through sums over k >= j > i: in the natural column
 // order nothing on or below the diagonal is ever read, and two fifths of the products of the launch can be left out.
 static hipError_t launch_products(const uint16_t* oX, const uint16_t* oHi, const uint16_t* oLo, int64_t np, int64_t cp,
-                                  int64_t n, float* H, float* dXXT, int64_t ldh, bool dxxt_upper, hipStream_t s) {
+                                  int64_t n, float* H, float* dXXT, int64_t ldh, bool dxxt_upper, void* ws, size_t ws_bytes, size_t operand_bytes,
+                                  hipStream_t s) {
   const int tile = gemm_tile_for(n, n);
   GemmBatch b{};
   b.nprob = 2;
@@ -147,6 +184,13 @@ static hipError_t launch_products(const uint16_t* oX, const uint16_t* oHi, const
   h = a;
   h.C = H; h.kind = 0; h.tile_mode = 2;
   h.term[0] = {{oX, oX}, {oX, oX}, 32, 32, np * 32, np * 32};
+  const int split = split_for(n, cp);
+  if (split > 1 && operand_bytes + partial_bytes(n, split) <= ws_bytes) {      // (a smaller workspace: sums in one part)
+    a.split = split;
+    a.partial = (float*)((unsigned char*)ws + operand_bytes);
+    h.split = split / 2;
+    h.partial = a.partial + (int64_t)a.tiles_m * a.tiles_m * split * (128 * 128);
+  }
   ProfScope ps(kProfAccumGemm, s);
   return launch_gemm(b, s);
 }
@@ -174,6 +218,9 @@ static int accumulate_impl(const uint16_t* X, const uint16_t* Xtilde, int64_t to
   int64_t cmax = (int64_t)(ws_bytes / (size_t)(6 * np)) / 64 * 64;
   if (cmax < 64) return GPTAQ_EWORKSPACE;
   if (cmax > 32768) cmax = 32768;    // keeps one fp32 running sum short (accuracy), and K in int32
+  // (all tokens in passes of one size, if that leaves the place for parts that the size was given for)
+  const int64_t whole = round_up(tokens < 32768 ? tokens : 32768, 64);
+  if (cmax > whole && (size_t)(6 * np * whole) + partial_bytes(n, split_for(n, whole)) <= ws_bytes) cmax = whole;
   for (int64_t t0 = 0; t0 < tokens; t0 += cmax) {
     const int64_t c = tokens - t0 < cmax ? tokens - t0 : cmax;
     const int64_t cp = round_up(c, 64);
@@ -187,7 +234,7 @@ static int accumulate_impl(const uint16_t* X, const uint16_t* Xtilde, int64_t to
                          oX, oHi, oLo, np, 0, row_of);
     }
     GPTAQ_LAUNCH_CHECK();
-    hipError_t e = launch_products(oX, oHi, oLo, np, cp, n, H, dXXT, ldh, dxxt_upper, s);
+    hipError_t e = launch_products(oX, oHi, oLo, np, cp, n, H, dXXT, ldh, dxxt_upper, ws, ws_bytes, (size_t)(6 * np * cp), s);
     if (e != hipSuccess) { set_last_hip_error(e); return GPTAQ_ELAUNCH; }
   }
   return GPTAQ_OK;
@@ -274,7 +321,7 @@ static int accumulate_staged_impl(const uint16_t* X, const uint16_t* Xtilde, int
   if (((uintptr_t)ws & 255) || ws_bytes < (size_t)(6 * np * CAP)) return GPTAQ_EWORKSPACE;
   hipStream_t s = (hipStream_t)stream;
   uint16_t *oX = (uint16_t*)ws, *oHi = oX + np * CAP, *oLo = oHi + np * CAP;
-  auto products = [&](int64_t cp) { return launch_products(oX, oHi, oLo, np, cp, n, H, dXXT, ldh, dxxt_upper, s); };
+  auto products = [&](int64_t cp) { return launch_products(oX, oHi, oLo, np, cp, n, H, dXXT, ldh, dxxt_upper, ws, ws_bytes, (size_t)(6 * np * CAP), s); };
   int64_t done = 0, pend = *pending;
   while (done < tokens) {
     const int64_t take = tokens - done < CAP - pend ? tokens - done : CAP - pend, cp = round_up(take, 64);

@@ -12,6 +12,7 @@ namespace gptaq {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kGemmBK = 32;          // bf16 elements per k-tile of the MFMA GEMM
 
@@ -45,6 +46,8 @@ struct GemmProblem {
   int32_t store_mode;    // 0: C += acc; 1: C = acc; 2: C = acc where col > row, else 0
   int32_t deal;          // how the tile list is shared out to the 8 XCDs: 0: one contiguous run each (tiles of equal
                          // length); 1: dealt four tiles at a time (tile lengths that vary along the list: k_mode 1, 2)
+  int32_t split;         // > 1 (128-tiles, k_mode 0, store_mode 0): K in so many parts, each summed by workgroups of its own into
+  float* partial;        // `partial` (tiles * split * 128 * 128 floats), and added to C by a second kernel; 0 counts as 1
   GemmTerm term[2];
 };
 
@@ -52,6 +55,7 @@ struct GemmBatch {
   int32_t nprob;
   int32_t tile;          // 128 or 256 (square block tile)
   int32_t ntiles[2];     // filled by launch_gemm
+  int32_t diag_wgs;      // filled by launch_gemm: workgroups that sum the diagonal of a split upper-triangular second problem in one part
   int32_t max_wgs;       // 0: one workgroup per tile; else at most this many workgroups, each taking several tiles
   GemmProblem p[2];
 };

@@ -308,31 +308,8 @@ __device__ __forceinline__ void store_tile(float* C, int64_t ldc, int M, int N, 
   else store_tile_as<BT, 2, false, false>(C, ldc, M, N, store_mode, m0, n0, acc);
 }
 
-// One BT x BT tile of C: tile number `wid` of the batch (see the numbering below).
-template <int BT>
-__device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* smem, int wid) {
-  constexpr int WT = BT / 2;             // wave tile edge
-  constexpr int FR = WT / 32;            // 32x32 MFMA blocks per wave tile edge
-
-  // ---- which tile.  Workgroups are dealt round-robin to the 8 XCDs; inside each problem, give every
-  // XCD one contiguous run of tiles so that they share operand tiles in that XCD's L2, and so that
-  // every XCD gets the same share of each problem (the problems differ in K).
-  int id = wid;
-  int pi = 0;
-  int ntile = b.ntiles[0];
-  if (id >= ntile) { pi = 1; id -= ntile; ntile = b.ntiles[1]; }
-  const GemmProblem& P = b.p[pi];
-  if (!P.deal) {
-    const int per = ntile >> 3, rem = ntile & 7, xcd = id & 7, loc = id >> 3;
-    id = xcd < rem ? xcd * (per + 1) + loc : rem * (per + 1) + (xcd - rem) * per + loc;
-  } else if (id < (ntile & ~31)) {
-    // With triangular k ranges a contiguous run per XCD would give one XCD the long tiles and another the short ones.
-    // Here every XCD takes four consecutive tiles (the four tile rows of one column of a group) out of each 32, so
-    // each gets the same mix of lengths, and the 32 workgroups it runs side by side still share four left tiles.
-    const int xcd = id & 7, loc = id >> 3;
-    id = (((loc >> 2) << 3) + xcd) * 4 + (loc & 3);
-  }
-  int tm, tn;
+// Tile row and column of tile number `id` of a problem.
+__device__ __forceinline__ void tile_position(const GemmProblem& P, int id, int& tm, int& tn) {
   // Tiles are numbered in groups of GROUP tile rows, column by column inside a group, so the workgroups
   // an XCD runs side by side form a GROUP x 8 patch that shares GROUP left and 8 right operand tiles.
   constexpr int GROUP = 4;
@@ -366,12 +343,64 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* sme
     tm = first + r % gsz;
     tn = r / gsz;
   }
+}
+
+// A part's BT x BT tile of sums as the accumulators hold it: 16 bytes of a lane are registers 4 v .. 4 v + 3 of a 32 x 32 block (four
+// rows of one column), a wavefront's 1 KB one after the other.
+template <int BT>
+__device__ __forceinline__ void store_partial(float* dst, const f32x16 (&acc)[BT / 64][BT / 64]) {
+  constexpr int FR = BT / 64;
+  u32x4* out = reinterpret_cast<u32x4*>(dst) + (threadIdx.x >> 6) * (FR * FR * 256) + (threadIdx.x & 63);
+#pragma unroll
+  for (int i = 0; i < FR; ++i)
+#pragma unroll
+    for (int j = 0; j < FR; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        out[((i * FR + j) * 4 + v) * 64] = u32x4{__float_as_uint(acc[i][j][4 * v]), __float_as_uint(acc[i][j][4 * v + 1]),
+                                                 __float_as_uint(acc[i][j][4 * v + 2]), __float_as_uint(acc[i][j][4 * v + 3])};
+}
+
+// One BT x BT tile of C: tile number `wid` of the batch (see the numbering below).
+template <int BT, bool SPLIT>
+__device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* smem, int wid) {
+  constexpr int WT = BT / 2;             // wave tile edge
+  constexpr int FR = WT / 32;            // 32x32 MFMA blocks per wave tile edge
+
+  // ---- which tile.  Workgroups are dealt round-robin to the 8 XCDs; inside each problem, give every
+  // XCD one contiguous run of tiles so that they share operand tiles in that XCD's L2, and so that
+  // every XCD gets the same share of each problem (the problems differ in K).
+  int id = wid;
+  int pi = 0;
+  int ntile = b.ntiles[0];
+  if (id >= ntile) { pi = 1; id -= ntile; ntile = b.ntiles[1]; }
+  const GemmProblem& P = b.p[pi];
+  if (!P.deal) {
+    const int per = ntile >> 3, rem = ntile & 7, xcd = id & 7, loc = id >> 3;
+    id = xcd < rem ? xcd * (per + 1) + loc : rem * (per + 1) + (xcd - rem) * per + loc;
+  } else if (id < (ntile & ~31)) {
+    // With triangular k ranges a contiguous run per XCD would give one XCD the long tiles and another the short ones.
+    // Here every XCD takes four consecutive tiles (the four tile rows of one column of a group) out of each 32, so
+    // each gets the same mix of lengths, and the 32 workgroups it runs side by side still share four left tiles.
+    const int xcd = id & 7, loc = id >> 3;
+    id = (((loc >> 2) << 3) + xcd) * 4 + (loc & 3);
+  }
+  // Split along K: the tiles of the first part of K, then those of the second, ..., so that what runs side by side shares operands.
+  const int nt = SPLIT ? ntile / P.split : ntile, part = SPLIT ? id / nt : 0;
+  id -= part * nt;
+  int tm, tn;
+  tile_position(P, id, tm, tn);
   const int m0 = uniform(tm * BT), n0 = uniform(tn * BT);
 
   const bool skipped = P.tile_mode == 1 && n0 + BT <= m0;
   int klo = 0, khi = P.K;
   if (P.k_mode == 1) klo = min(n0, P.K);
   if (P.k_mode == 2) { klo = min(m0, P.K); khi = min(P.K, n0 + BT); }
+  if (SPLIT && P.split > 1) {            // (k_mode 0)
+    const int kt = P.K / kGemmBK;
+    klo = (int)((int64_t)kt * part / P.split) * kGemmBK;
+    khi = (int)((int64_t)kt * (part + 1) / P.split) * kGemmBK;
+  }
   const int nk = (skipped || khi <= klo) ? 0 : (khi - klo) / kGemmBK;
 
   f32x16 acc[FR][FR];
@@ -395,42 +424,141 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* sme
   // ---- epilogue.  MFMA 32x32 result: register v of a lane holds row 8*(v/4) + 4*(lane/32) + v%4,
   // column lane%32 of the block.
   if (skipped && P.store_mode == 0) return;
+  if (SPLIT && P.split > 1) {
+    store_partial<BT>(P.partial + (int64_t)(part * nt + id) * (BT * BT), acc);
+    return;
+  }
   store_tile<BT>(P.C, uniform(P.ldc), uniform(P.M), uniform(P.N), uniform(P.store_mode), m0, n0, acc);
+}
+
+// C[i][i] += sum_k L0[i][k]^2 over all of K, of a problem whose other sums are taken in parts: a workgroup's first wavefront per 32 rows, which takes the
+// 32 x 32 block of its tile's products in the same order as a tile that is not split.  (The diagonal of H decides the order of the columns
+// in act_order, by differences that are of the size of the rounding; the same sums keep the same order.)  A chain of K / 16 MFMAs whose
+// one operand comes straight from memory, 40 loads ahead; it ends before the parts do.
+__device__ __forceinline__ void diagonal_block(const GemmProblem& P, int block) {
+  const int lane = threadIdx.x & 63, rl = lane & 31, row = 32 * block + rl;
+  if (32 * block >= P.M) return;
+  constexpr int AHEAD = 40;                // k-steps of 16
+  const int steps = P.K / 16;              // (even; K is far more than 16 * AHEAD)
+  const uint16_t* src = P.term[0].L[0] + (int64_t)row * 32 + 8 * (lane >> 5);
+  auto at = [&](int step) { return *reinterpret_cast<const u32x4*>(src + (int64_t)(step >> 1) * P.term[0].ktl + (step & 1) * 16); };
+  u32x4 f[AHEAD];
+#pragma unroll
+  for (int a = 0; a < AHEAD; ++a) f[a] = at(min(a, steps - 1));
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+  auto multiply = [&](const u32x4& r) {
+    const bf16x8 x = __builtin_bit_cast(bf16x8, r);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x, x, acc, 0, 0, 0);
+  };
+  int s0 = 0;
+  // (a running pointer: the address of a step from its number takes longer than the step)
+  const uint16_t* next = src + (AHEAD / 2) * P.term[0].ktl;
+  for (; s0 + 2 * AHEAD <= steps; s0 += AHEAD)
+#pragma unroll
+    for (int a = 0; a < AHEAD; a += 2) {
+      multiply(f[a]);
+      f[a] = *reinterpret_cast<const u32x4*>(next);
+      multiply(f[a + 1]);
+      f[a + 1] = *reinterpret_cast<const u32x4*>(next + 16);
+      next += P.term[0].ktl;
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  for (; s0 + AHEAD <= steps; s0 += AHEAD)
+#pragma unroll
+    for (int a = 0; a < AHEAD; ++a) {
+      multiply(f[a]);
+      f[a] = at(min(s0 + a + AHEAD, steps - 1));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+  for (int a = 0; a < AHEAD; ++a)
+    if (s0 + a < steps) multiply(f[a]);
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+    if (8 * (v >> 2) + 4 * (lane >> 5) + (v & 3) == rl && row < P.M) P.C[(int64_t)row * P.ldc + row] += acc[v];
 }
 
 // CAPPED = false: one workgroup per tile.  CAPPED = true: a workgroup takes tiles blockIdx.x, blockIdx.x + gridDim.x,
 // ...: the caller caps the grid to leave compute units to a kernel running beside this one.  The grid is a multiple
 // of 8 then, so a workgroup's tiles all belong to its own XCD's share.
-template <int BT, bool CAPPED>
+template <int BT, bool CAPPED, bool SPLIT = false>
 __global__ __launch_bounds__(256, BT == 128 ? 2 : 1) void gemm_nt_kernel(GemmBatch b) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if (!CAPPED) {
-    gemm_tile<BT>(b, smem, blockIdx.x);
+    if (SPLIT && (int)blockIdx.x < b.diag_wgs) { if (threadIdx.x < 64) diagonal_block(b.p[1], blockIdx.x); }
+    else gemm_tile<BT, SPLIT>(b, smem, blockIdx.x - (SPLIT ? b.diag_wgs : 0));
   } else {
     const int total = b.ntiles[0] + b.ntiles[1];
     for (int wid = blockIdx.x; wid < total; wid += gridDim.x) {
-      gemm_tile<BT>(b, smem, wid);
+      gemm_tile<BT, false>(b, smem, wid);
       __syncthreads();                   // the last fragment reads of this tile before the next tile's loads land in LDS
     }
   }
 }
 
-static LdsLimitOnce g_lds256, g_lds128, g_lds256c, g_lds128c;
+// C += the sums of the parts of K, in their order.  grid: four workgroups (the four wavefronts of the product) per tile, problem after
+// problem; a wavefront takes a 32 x 32 block.  Bound by its reads, 64 KB a tile and part.
+__global__ __launch_bounds__(256) void add_parts_kernel(GemmBatch b) {
+  constexpr int BT = 128, FR = 2;
+  const int first = b.p[0].split > 1 ? b.ntiles[0] / b.p[0].split : 0;       // (a problem that is not split has nothing here)
+  int id = blockIdx.x >> 2, pi = 0;
+  if (id >= first) { id -= first; pi = 1; }
+  const GemmProblem& P = b.p[pi];
+  const int w = blockIdx.x & 3, blk = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  int tm, tn;
+  tile_position(P, id, tm, tn);
+  const int row0 = tm * BT + (w >> 1) * 64 + (blk / FR) * 32 + 4 * (lane >> 5), col = tn * BT + (w & 1) * 64 + (blk % FR) * 32 + (lane & 31);
+  const f32x4* src = reinterpret_cast<const f32x4*>(P.partial + (int64_t)id * (BT * BT)) + (w * (FR * FR) + blk) * 256 + lane;
+  const int64_t step = (int64_t)(b.ntiles[pi] / P.split) * (BT * BT / 4);
+  float c[4][4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int row = row0 + 8 * v + q;
+      c[v][q] = P.C[(int64_t)min(row, P.M - 1) * P.ldc + min(col, P.N - 1)];
+    }
+  for (int s = 0; s < P.split; ++s)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const f32x4 x = src[s * step + 64 * v];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) c[v][q] += x[q];
+    }
+#pragma unroll
+  for (int v = 0; v < 4; ++v)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      if (row0 + 8 * v + q < P.M && col < P.N && !(pi && b.diag_wgs && row0 + 8 * v + q == col)) P.C[(int64_t)(row0 + 8 * v + q) * P.ldc + col] = c[v][q];
+}
+
+static LdsLimitOnce g_lds256, g_lds128, g_lds256c, g_lds128c, g_lds128s;
 hipError_t launch_gemm(const GemmBatch& b, hipStream_t s) {
   GemmBatch bb = b;
-  int total = 0;
+  int total = 0, part_tiles = 0;
   for (int i = 0; i < 2; ++i) {
     const GemmProblem& q = bb.p[i];
-    bb.ntiles[i] = i >= bb.nprob ? 0 : q.tile_mode == 2 ? q.tiles_m * (q.tiles_m + 1) / 2 : q.tiles_m * q.tiles_n;
+    if (bb.p[i].split < 1) bb.p[i].split = 1;
+    bb.ntiles[i] = i >= bb.nprob ? 0 : q.split * (q.tile_mode == 2 ? q.tiles_m * (q.tiles_m + 1) / 2 : q.tiles_m * q.tiles_n);
+    if (q.split > 1 && (bb.tile != 128 || q.k_mode || q.store_mode || q.deal || !q.partial)) return hipErrorInvalidValue;
     total += bb.ntiles[i];
+    if (q.split > 1) part_tiles += bb.ntiles[i] / q.split;
   }
   if (total == 0) return hipSuccess;
+  // (a multiple of 8, which leaves the tiles on their XCDs; the last ones may have no rows)
+  bb.diag_wgs = bb.nprob == 2 && bb.p[1].split > 1 && bb.p[1].tile_mode == 2 ? (4 * bb.p[1].tiles_m + 7) / 8 * 8 : 0;
   hipError_t e = g_lds256.ensure(reinterpret_cast<const void*>(&gemm_nt_kernel<256, false>), kLds256);
   if (e == hipSuccess) e = g_lds128.ensure(reinterpret_cast<const void*>(&gemm_nt_kernel<128, false>), kLds128);
   if (e == hipSuccess) e = g_lds256c.ensure(reinterpret_cast<const void*>(&gemm_nt_kernel<256, true>), kLds256);
   if (e == hipSuccess) e = g_lds128c.ensure(reinterpret_cast<const void*>(&gemm_nt_kernel<128, true>), kLds128);
+  if (e == hipSuccess) e = g_lds128s.ensure(reinterpret_cast<const void*>(&gemm_nt_kernel<128, false, true>), kLds128);
   if (e != hipSuccess) return e;
-  if (b.max_wgs > 0 && b.max_wgs < total) {
+  if (part_tiles) {
+    hipLaunchKernelGGL((gemm_nt_kernel<128, false, true>), dim3(bb.diag_wgs + total), dim3(256), kLds128, s, bb);
+    hipLaunchKernelGGL(add_parts_kernel, dim3(4 * part_tiles), dim3(256), 0, s, bb);
+  } else if (b.max_wgs > 0 && b.max_wgs < total) {
     const int grid = b.max_wgs >= 8 ? b.max_wgs / 8 * 8 : 8;
     if (b.tile == 256)
       hipLaunchKernelGGL((gemm_nt_kernel<256, true>), dim3(grid), dim3(256), kLds256, s, bb);

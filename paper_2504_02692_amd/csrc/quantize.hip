@@ -366,11 +366,15 @@ QLayout q_layout(int64_t m, int64_t n) {
     // 12-15: a second set of 0-3 (the far update of a super-block runs beside the next super-block, which writes its own -E
     // and V; or the two row halves of a tall matrix run as two chains, each at its own super-block); 8-11: unused
     o += (size_t)(i % 12 < 4 ? L.mp * KS * 2 : i < 8 ? (L.np + 256) * KS * 2 : 0);
+    if (i == 7) {
+      // what the super-block kernel reads of U and P, of every super-block (near_operands_kernel), in the place of 4-7 and behind
+      const int64_t nsb = (n + kSbCols - 1) / kSbCols;
+      L.off_near = L.off[4];
+      const size_t near = (size_t)(nsb * (4 * (int64_t)kSbCols * kSbCols * 2 + (int64_t)(kSbCols / 16) * 512 * 4));
+      const size_t behind = (size_t)8 * kSbCols * kSbCols * 2;
+      o = o + behind > L.off_near + near ? o + behind : (L.off_near + near + 255) / 256 * 256;
+    }
   }
-  // what the super-block kernel reads of U and P, of every super-block (near_operands_kernel)
-  const int64_t nsb = (n + kSbCols - 1) / kSbCols;
-  L.off_near = o;
-  o += (size_t)(nsb * (4 * (int64_t)kSbCols * kSbCols * 2 + (int64_t)(kSbCols / 16) * 512 * 4));
   // the far right operands of every super-block of the layer (far_operands_all_kernel), made once per call
   int64_t rows = 0;
   for (int k = 0; (int64_t)(k + 1) * kSbCols < n; ++k) rows += far_rows(n, k);

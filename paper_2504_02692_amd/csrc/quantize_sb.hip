@@ -52,7 +52,6 @@ __device__ __forceinline__ uint16_t sb_bf16_rne(float f) {
 }
 __device__ __forceinline__ float sb_bf16_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // Uniform affine min-max grid with 0 inside the range; the few operations per group are done in fp64 so
 // that the fp32 scale is the correctly rounded (xmax - xmin) / maxq.

@@ -284,3 +284,33 @@ def test_a_solve_can_be_captured():
         for a, b in zip(out, eager):
             assert torch.equal(a, b)
         solve()
+
+
+# Sums taken in several parts of the tokens (few columns, many tokens): one tile and its edge, several tiles, k-tiles that do not divide
+# over the parts, most and fewest parts; in a workspace of the operands alone they are taken in one part.
+@pytest.mark.parametrize("n,ld,tokens", [(8, 8, 8192), (136, 140, 8200), (392, 392, 10016), (1032, 1040, 16448), (1536, 1536, 32768)])
+def test_sums_in_parts_are_the_sums(n, ld, tokens):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    X = torch.randn((tokens, n), device="cuda", generator=g).bfloat16()
+    Xt = (X.float() + 0.05 * torch.randn((tokens, n), device="cuda", generator=g)).bfloat16()
+    start = torch.randn((n, n), device="cuda", generator=g)
+    size = B.gptaq_accumulate_workspace_bytes(tokens, n)
+    operands = 6 * -(-n // 128) * 128 * (-(-tokens // 64) * 64)
+    assert size > operands
+    out = {}
+    for name, nb, call in (("full", size, B.gptaq_accumulate), ("upper", size, B.gptaq_accumulate_upper), ("one part", operands, B.gptaq_accumulate)):
+        whole = [torch.full((n, ld), -7.0, device="cuda") for _ in range(2)]
+        H, A = whole[0][:, :n], whole[1][:, :n]
+        H.copy_(start)
+        A.copy_(start)
+        call(X, Xt, H, A, B.workspace(nb))
+        torch.cuda.synchronize()
+        assert ld == n or (whole[0][:, n:] == -7.0).all() and (whole[1][:, n:] == -7.0).all()
+        out[name] = (H.triu(), A.triu() if name == "upper" else A.clone())
+    assert torch.equal(out["full"][0], out["upper"][0]) and torch.equal(out["full"][1].triu(), out["upper"][1])
+    Xd, Dd = X.double(), Xt.double() - X.double()
+    refs = ((start.double() + Xd.T.contiguous() @ Xd).triu(), start.double() + Dd.T.contiguous() @ Xd)
+    for name in ("full", "one part"):
+        for got, ref in zip(out[name], refs):
+            # fp32 sums of exact products: sqrt(tokens) 2^-24 = 1.1e-5 at most if every addition rounded the whole sum alike; 9e-7 seen
+            assert float((got.double() - ref).norm() / ref.norm()) <= 3e-6
