@@ -383,12 +383,22 @@ QLayout q_layout(int64_t m, int64_t n) {
   return L;
 }
 
-// rows from which a matrix is quantised as two row halves.  One piece / two halves, ms: 4096 columns: 4096 rows 0.88 / 0.92, 6144
-// 1.13 / 1.03, 8192 1.23 / 1.18, 10240 1.42 / 1.33, 16384 1.89 / 1.83, 22016 3.01 / 2.47; 8192 columns: 8192 rows 4.04 / 3.64, 10240
-// 4.77 / 4.33, 28672 11.9 / 11.1; 2048 columns: 8192 rows 0.40 / 0.42, 10240 0.44 / 0.46, 16384 0.55 / 0.56, 22016 0.95 / 0.81.  (The line
-// was drawn when the super-block kernel took twice as long and 8192 rows were even; it could now lie at 6144 rows of 4096 columns
-// or more.)
-constexpr int64_t kRowSplitMin = 10240;
+// Whether a matrix of m rows and nsb super-blocks is quantised as two row halves (on two streams, so that each half's super-block kernel
+// runs beside the other's far update).  Instead, up to 4096 rows go through as two chains (quantize_layer_sb) and more as one.  Both
+// measured, in their order, ms, W4 g128, both terms: 3072 columns: 7168 rows 0.69 / 0.69, 8192 0.74 / 0.73, 9216 0.90 / 0.79; 4096: 4096
+// 0.83 / 0.86, 4352 0.93 / 0.88, 6144 1.15 / 1.00, 8192 1.35 / 1.26; 5120: 4096 1.18 / 1.26, 5120 1.47 / 1.39; from six super-blocks
+// on the far updates set the pace: 5504: 4096 1.54 / 1.38, 6144 1.96 / 1.65; 8192: 1024 1.84 / 1.75, 2048 1.98 / 1.96, 4096 2.51 / 2.44,
+// 6144 3.55 / 2.94; 11008: 1024 2.71 / 2.43, 2048 2.99 / 2.85, 3584 3.72 / 3.61, 4096 3.97 / 3.76; 14336: 640 3.35 / 3.20, 4096 6.11 / 5.74.
+// Not there: 3072 rows of 6144 columns 1.43 / 1.52, of 11008 3.49 / 3.60; 1024 of 6144 1.21 / 1.22; and with the clip search, where the
+// super-block kernel sets the pace again, 4096 x 8192 3.54 / 3.72 (it and single terms keep the line from 10240 rows on).
+bool row_halves(int64_t m, int64_t nsb, int terms, bool clip) {
+  if (terms == 0 || nsb < 2) return false;
+  if (m >= 10240) return true;
+  if (terms != 3 || clip || nsb == 2) return false;
+  if (nsb == 3) return m >= 8192;
+  if (nsb < 6) return m > 4096;
+  return m >= 3584 || (m <= 2048 && m * nsb >= 8192);
+}
 
 template <int R, int NW>
 hipError_t launch_quant(const QuantArgs& a, hipStream_t s) {
@@ -478,10 +488,10 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     GPTAQ_LAUNCH_CHECK();
   }
   const int nsb = (int)((n + kSbCols - 1) / kSbCols);
-  // (with one or two super-blocks there is no far2; it pays when the super-block kernel leaves most of the chip free.  One chain /
-  // two, ms: 4096 rows: 3072 columns 0.60 / 0.60, 4096 0.90 / 0.87, 8192 2.68 / 2.51, 11008 4.38 / 3.98; 1024 rows: 4096 columns
-  // 0.76 / 0.79, 11008 2.65 / 2.77; beyond a quarter of the chip: 6144 rows of 4096 columns 1.13 / 1.01, 8192 of 4096 1.23 / 1.27, of
-  // 8192 4.04 / 4.49, 9984 of 8192 4.75 / 6.43)
+  // (with one or two super-blocks there is no far2; it pays when the super-block kernel leaves most of the chip free.  One chain / two,
+  // ms: 4096 rows: 3072 columns 0.56 / 0.56, 4096 0.86 / 0.83, 5120 1.27 / 1.18; 3072 rows: 4096 0.81 / 0.76, 8192 2.47 / 2.28, 11008
+  // 3.82 / 3.51; fewer rows lose: 1024 of 3072 0.52 / 0.55, of 4096 0.70 / 0.73, of 5120 0.91 / 0.94.  More rows, and most matrices of
+  // more columns, go through as row halves: see row_halves)
   int cus = 256, dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
   const int sbk_wgs = (int)((m + 63) / 64);
@@ -569,9 +579,8 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     // While far2 is long (many columns left) it sets the pace and starts at once, sharing the chip with far1; once it
     // is shorter than a super-block it only slows far1 down, which the next super-block waits for: then it starts
     // when far1 is done.
-    // (measured with the switch at 0 / 2 / 4 / 6 / 8 / 10 super-blocks of columns left, ms: 4096 x 4096 0.93 / 0.87 / 0.87 / 0.87 / 0.87 /
-    // 0.87; 4096 x 8192 2.43 / 2.43 / 2.48 / 2.53 / 2.51 / 2.52; 4096 x 11008 3.90 / 3.88 / 3.92 / 3.96 / 4.00 / 4.03; 1024 x 11008 2.69 /
-    // 2.70 / 2.73 / 2.80 / 2.84 / 2.79; six was the best on 4096 x 11008 when the super-block kernel took 290 us, now it is 2 % off)
+    // (measured with the switch at 6 / 3 / 2 / 1 super-blocks of columns left, ms: 3072 x 5504 1.28 / 1.37 / 1.39 / 1.39; 3072 x 8192 2.28 /
+    // 2.30 / 2.32 / 2.35; 3072 x 11008 3.51 / 3.47 / 3.48 / 3.50)
     constexpr int kFar2LateCols = 6 * kSbCols;
     const bool far2_late = has_far2 && (n - next_end) <= kFar2LateCols;
     auto launch_far2 = [&]() {
@@ -619,7 +628,7 @@ static int quantize_layer_impl(float* W, int64_t m, int64_t n, int64_t ldw, cons
   // The super-block kernel takes groups that tile its 16/32/128-column pieces; other group sizes go through the
   // block-by-block kernels below.
   if (group <= 0 || group == 16 || group == 32 || group == 64 || group == 128) {
-    // Rows are independent (Step 1).  A tall matrix goes through as two row halves on two streams: the super-block
+    // Rows are independent (Step 1).  Where row_halves says so, the matrix goes through as two row halves on two streams: the super-block
     // kernel of one half, whose length is a chain of column steps whatever the number of rows, then runs beside the
     // far update of the other half instead of leaving the chip to it alone (and 344 workgroups of 64 rows no
     // longer make a second, mostly empty round on 256 CUs).
@@ -630,7 +639,7 @@ static int quantize_layer_impl(float* W, int64_t m, int64_t n, int64_t ldw, cons
     near.left = (uint16_t*)(base + L.off_near);
     near.stride = nsb * kSbCols * kSbCols;
     near.diag = (float*)(near.left + 4 * near.stride);
-    if (terms != 0 && nsb >= 2 && m >= kRowSplitMin) {
+    if (row_halves(m, nsb, terms, group > 0 && mse_steps > 0)) {
       const int64_t mA = round_up((m + 1) / 2, 256), mB = m - mA;   // (a multiple of the GEMM's row tile: the halves' padded
                                                                     //  rows of the -E / V buffers then do not overlap)
       const int64_t G = group > 0 ? n / group : 1;

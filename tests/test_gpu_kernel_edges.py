@@ -314,3 +314,25 @@ def test_sums_in_parts_are_the_sums(n, ld, tokens):
         for got, ref in zip(out[name], refs):
             # fp32 sums of exact products: sqrt(tokens) 2^-24 = 1.1e-5 at most if every addition rounded the whole sum alike; 9e-7 seen
             assert float((got.double() - ref).norm() / ref.norm()) <= 3e-6
+
+
+# Two row halves: the lines of the rule by rows and super-blocks, with and without vector stores; the last one is just on the other side.
+@pytest.mark.parametrize("m,n,group", [(8193, 2064, 0), (4097, 3201, 0), (3585, 5248, 128), (1300, 6784, 64), (760, 10250, 0), (744, 11264, 128)])
+def test_row_halves_equal_separate_calls(m, n, group):
+    """Rows are independent: the result is bit for bit that of calls on 600 rows at a time, which are too few for halves."""
+    g = torch.Generator(device="cuda").manual_seed(m)
+    U = torch.randn((n, n), device="cuda", generator=g).mul_(n ** -0.5).triu_(1)
+    U.diagonal().copy_(0.5 + torch.rand(n, device="cuda", generator=g))
+    P = torch.randn((n, n), device="cuda", generator=g).mul_(0.1 * n ** -0.5).triu_(1)
+    W0 = 0.02 * torch.randn((m, n), device="cuda", generator=g)
+
+    def quantize(W):
+        W = W.clone()
+        out = B.gptaq_quantize_layer(W, U, P, 4, group, False, 128, B.workspace(B.gptaq_quantize_workspace_bytes(W.shape[0], n)))
+        torch.cuda.synchronize()
+        return (W, *out)
+
+    whole = quantize(W0)
+    parts = [quantize(W0[r:r + 600]) for r in range(0, m, 600)]
+    for i, got in enumerate(whole):
+        assert torch.equal(got, torch.cat([p[i].reshape(-1, got.shape[1]) for p in parts]))
