@@ -14,6 +14,7 @@
 // Trailing update (lines 11-12, Eq. 18):  W[:, i+B:] += [-E | V] [U; P][i:i+B, i+B:] on the
 // MFMA GEMM with three bf16 cross products per term (operands carried to about 2^-17 relative, fp32 sums).
 #include "common.h"
+#include "row_halves.h"
 #include <mutex>
 
 namespace gptaq {
@@ -383,23 +384,6 @@ QLayout q_layout(int64_t m, int64_t n) {
   return L;
 }
 
-// Whether a matrix of m rows and nsb super-blocks is quantised as two row halves (on two streams, so that each half's super-block kernel
-// runs beside the other's far update).  Instead, up to 4096 rows go through as two chains (quantize_layer_sb) and more as one.  Both
-// measured, in their order, ms, W4 g128, both terms: 3072 columns: 7168 rows 0.69 / 0.69, 8192 0.74 / 0.73, 9216 0.90 / 0.79; 4096: 4096
-// 0.83 / 0.86, 4352 0.93 / 0.88, 6144 1.15 / 1.00, 8192 1.35 / 1.26; 5120: 4096 1.18 / 1.26, 5120 1.47 / 1.39; from six super-blocks
-// on the far updates set the pace: 5504: 4096 1.54 / 1.38, 6144 1.96 / 1.65; 8192: 1024 1.84 / 1.75, 2048 1.98 / 1.96, 4096 2.51 / 2.44,
-// 6144 3.55 / 2.94; 11008: 1024 2.71 / 2.43, 2048 2.99 / 2.85, 3584 3.72 / 3.61, 4096 3.97 / 3.76; 14336: 640 3.35 / 3.20, 4096 6.11 / 5.74.
-// Not there: 3072 rows of 6144 columns 1.43 / 1.52, of 11008 3.49 / 3.60; 1024 of 6144 1.21 / 1.22; and with the clip search, where the
-// super-block kernel sets the pace again, 4096 x 8192 3.54 / 3.72 (it and single terms keep the line from 10240 rows on).
-bool row_halves(int64_t m, int64_t nsb, int terms, bool clip) {
-  if (terms == 0 || nsb < 2) return false;
-  if (m >= 10240) return true;
-  if (terms != 3 || clip || nsb == 2) return false;
-  if (nsb == 3) return m >= 8192;
-  if (nsb < 6) return m > 4096;
-  return m >= 3584 || (m <= 2048 && m * nsb >= 8192);
-}
-
 template <int R, int NW>
 hipError_t launch_quant(const QuantArgs& a, hipStream_t s) {
   static LdsLimitOnce lds_once;                  // per instantiation
@@ -491,7 +475,7 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
   // (with one or two super-blocks there is no far2; it pays when the super-block kernel leaves most of the chip free.  One chain / two,
   // ms: 4096 rows: 3072 columns 0.56 / 0.56, 4096 0.86 / 0.83, 5120 1.27 / 1.18; 3072 rows: 4096 0.81 / 0.76, 8192 2.47 / 2.28, 11008
   // 3.82 / 3.51; fewer rows lose: 1024 of 3072 0.52 / 0.55, of 4096 0.70 / 0.73, of 5120 0.91 / 0.94.  More rows, and most matrices of
-  // more columns, go through as row halves: see row_halves)
+  // more columns, go through as row halves: see first_row_half)
   int cus = 256, dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
   const int sbk_wgs = (int)((m + 63) / 64);
@@ -628,7 +612,7 @@ static int quantize_layer_impl(float* W, int64_t m, int64_t n, int64_t ldw, cons
   // The super-block kernel takes groups that tile its 16/32/128-column pieces; other group sizes go through the
   // block-by-block kernels below.
   if (group <= 0 || group == 16 || group == 32 || group == 64 || group == 128) {
-    // Rows are independent (Step 1).  Where row_halves says so, the matrix goes through as two row halves on two streams: the super-block
+    // Rows are independent (Step 1).  Where first_row_half says so, the matrix goes through as two row halves on two streams: the super-block
     // kernel of one half, whose length is a chain of column steps whatever the number of rows, then runs beside the
     // far update of the other half instead of leaving the chip to it alone (and 344 workgroups of 64 rows no
     // longer make a second, mostly empty round on 256 CUs).
@@ -639,9 +623,8 @@ static int quantize_layer_impl(float* W, int64_t m, int64_t n, int64_t ldw, cons
     near.left = (uint16_t*)(base + L.off_near);
     near.stride = nsb * kSbCols * kSbCols;
     near.diag = (float*)(near.left + 4 * near.stride);
-    if (row_halves(m, nsb, terms, group > 0 && mse_steps > 0)) {
-      const int64_t mA = round_up((m + 1) / 2, 256), mB = m - mA;   // (a multiple of the GEMM's row tile: the halves' padded
-                                                                    //  rows of the -E / V buffers then do not overlap)
+    const int64_t mA = first_row_half(m, nsb, terms, group > 0 && mse_steps > 0), mB = m - mA;
+    if (mA > 0) {
       const int64_t G = group > 0 ? n / group : 1;
       std::lock_guard<std::mutex> side_lock(side_stream_mutex());
       SideStream* side = side_stream(3);

@@ -3,6 +3,7 @@ rejects bad arguments on the host before anything is launched (no GPU needed).""
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -107,3 +108,36 @@ def test_events_between_the_streams_release_what_they_order():
             code = re.sub(r"//[^\n]*", "", open(os.path.join(csrc, f)).read())
             flags += re.findall(r"hipEventCreateWithFlags\([^,]*,([^)]*)\)", code)
     assert [x.strip() for x in flags] == ["hipEventDisableTiming"]
+
+
+def test_row_halves_have_rows(tmp_path):
+    """Where the column loop takes a matrix as two row halves, the first is whole tiles of 256 rows and the second has rows: for every
+    number of rows and super-blocks around the rule's lines, up to the most super-blocks that the column loop accepts."""
+    src = tmp_path / "check.cpp"
+    src.write_text("""#include "row_halves.h"
+#include <cstdio>
+int main() {
+  long taken = 0, bad = 0;
+  auto check = [&](int64_t m, int64_t nsb) {
+    for (int terms = 0; terms < 4; ++terms)
+      for (int clip = 0; clip < 2; ++clip) {
+        const int64_t first = gptaq::first_row_half(m, nsb, terms, clip != 0);
+        if (first == 0) continue;
+        ++taken;
+        if ((first < 1 || first >= m || first % 256 != 0) && bad++ == 0)
+          std::printf("m %lld, super-blocks %lld: first half %lld rows\\n", (long long)m, (long long)nsb, (long long)first);
+      }
+  };
+  for (int64_t m = 1; m <= 20000; ++m)
+    for (int64_t nsb = 1; nsb <= 64; ++nsb) check(m, nsb);
+  for (int64_t m = 1; m <= 2100; ++m)
+    for (int64_t nsb = 65; nsb <= 16384; nsb = nsb * 9 / 8) check(m, nsb);
+  if (!bad) std::printf("%ld\\n", taken);
+  return bad != 0;
+}
+""")
+    exe = tmp_path / "check"
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2504_02692_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+    assert int(r.stdout) > 1000000

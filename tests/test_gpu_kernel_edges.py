@@ -336,3 +336,31 @@ def test_row_halves_equal_separate_calls(m, n, group):
     parts = [quantize(W0[r:r + 600]) for r in range(0, m, 600)]
     for i, got in enumerate(whole):
         assert torch.equal(got, torch.cat([p[i].reshape(-1, got.shape[1]) for p in parts]))
+
+
+# So few rows of so wide a matrix that only one half of whole tiles has rows, and the fewest of which both have.
+@pytest.mark.parametrize("m,n", [(200, 42000), (256, 32768), (257, 32768)])
+def test_few_rows_of_a_wide_matrix(m, n):
+    """The result is bit for bit that of calls on 100 rows at a time, and nothing behind the last row is touched."""
+    g = torch.Generator(device="cuda").manual_seed(m)
+    U, P = torch.empty((n, n), device="cuda"), torch.empty((n, n), device="cuda")
+    U.normal_(0, n ** -0.5, generator=g).triu_(1)
+    U.diagonal().copy_(0.5 + torch.rand(n, device="cuda", generator=g))
+    P.normal_(0, 0.1 * n ** -0.5, generator=g).triu_(1)
+    W0 = 0.02 * torch.randn((m, n), device="cuda", generator=g)
+
+    def quantize(W):
+        out = [torch.full((W.shape[0] + 256, n), -7.0, device="cuda"), torch.full((W.shape[0] + 256, n), 99, dtype=torch.uint8, device="cuda"),
+               *(torch.full((W.shape[0] + 256, 1), -7.0, device="cuda") for _ in range(2))]
+        mine = [t[:W.shape[0]] for t in out]
+        mine[0].copy_(W)
+        B.gptaq_quantize_layer(mine[0], U, P, 4, 0, False, 128, B.workspace(B.gptaq_quantize_workspace_bytes(W.shape[0], n)), codes=mine[1],
+                               scales=mine[2], zeros=mine[3])
+        torch.cuda.synchronize()
+        assert all((t[W.shape[0]:] == v).all() for t, v in zip(out, (-7.0, 99, -7.0, -7.0)))
+        return mine
+
+    whole = quantize(W0)
+    parts = [quantize(W0[r:r + 100]) for r in range(0, m, 100)]
+    for i, got in enumerate(whole):
+        assert torch.equal(got, torch.cat([p[i] for p in parts]))
