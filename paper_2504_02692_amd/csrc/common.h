@@ -118,7 +118,7 @@ hipError_t launch_block_panel(const BlockPanel& a, hipStream_t s);
 
 // Column loop + in-super-block updates of a whole super-block in one launch (quantize_sb.hip).
 constexpr int kSbCols = 1024;       // columns per super-block
-// What the kernel reads of U and P, made for every super-block of a layer (layout: near_operands_kernel).
+// What the kernel reads of U and P: places for every super-block of a layer (layout: near_operands_kernel).
 struct SbNear {
   uint16_t* left;                    // U hi, U lo, P hi, P lo, `stride` elements apart: kSbCols * kSbCols bf16 per super-block each
   int64_t stride;
@@ -141,7 +141,7 @@ struct SbArgs {
   int clip_grid, clip_steps;         // clip-range search of every group (0 steps: plain min-max; groups only)
   int fast_rows;                     // rows of W and of codes may be stored 16 bytes at a time
 };
-// Operands of super-blocks first .. first + count - 1.
+// Operands of super-blocks first .. first + count - 1, to the first `count` places of o.
 hipError_t launch_near_operands(const float* U, const float* P, int64_t ldh, int n, int first, int count, const SbNear& o, hipStream_t s);
 hipError_t launch_quant_sb(const SbArgs& a, hipStream_t s);
 

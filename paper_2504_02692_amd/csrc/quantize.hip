@@ -452,7 +452,8 @@ __global__ __launch_bounds__(256) void zero_dead_columns_kernel(float* W, int64_
 static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const float* U, const float* P, int64_t ldh,
                              const uint8_t* dead, int bits, int group, int sym, uint8_t* codes, float* scales,
                              float* zeros, uint16_t* const* buf, const SbNear& near, uint16_t* const* farop, hipStream_t s, int terms,
-                             int mse_grid, int mse_steps, bool may_use_helper = true, bool make_operands = true, hipEvent_t operands_made = nullptr) {
+                             int mse_grid, int mse_steps, bool may_use_helper = true, bool make_farop = true, bool near_made = false,
+                             hipEvent_t operands_made = nullptr) {
   const int64_t ev_kt = round_up(m, 256) * 32;   // a k-tile of the -E / V buffers, in elements
   if (dead) {
     hipLaunchKernelGGL(zero_dead_columns_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, s, W, ldw, (int)m, (int)n, dead);
@@ -503,7 +504,7 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     }
     {
       ProfScope ps(kProfTrailSplit, st);
-      if (nsb > 1) chk(launch_near_operands(U, (terms & 2) ? P : U, ldh, (int)n, 1, nsb - 1, near, st));
+      if (two_chains) chk(launch_near_operands(U, (terms & 2) ? P : U, ldh, (int)n, 1, nsb - 1, near.at(1), st));
       hipLaunchKernelGGL(far_operands_all_kernel, dim3((unsigned)(far_rows(n, 0) / 64), 2, (unsigned)((nsb - 1) * (kSbCols / QB))),
                          dim3(256), 0, st, U, (terms & 2) ? P : U, ldh, (int)n, farop[0], farop[1], farop[2], farop[3]);
       chk(hipGetLastError());
@@ -513,7 +514,15 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
       chk(hipEventRecord(operands_made, st));
     }
   };
-  const bool far_operands = make_operands && terms != 0 && nsb >= 2;
+  // Where the operands of the super-block kernel are made.  Right in front of it they are still in the caches when it reads them; made
+  // for all super-blocks in front of the first one, the far updates' passes over W have driven them out (8192 x 8192, E term alone:
+  // the kernel takes 175 instead of 123 us), against 7 us of the chain.  With two chains, which have fewer rows, the helper stream
+  // makes them beside the first super-block, and that is the better side.  In front of each / beside the first, ms: one chain, E term
+  // alone: 4608 x 4096 0.66 / 0.67, 6144 x 4096 0.75 / 0.81, 9984 x 4096 0.91 / 1.03, 8192 x 8192 2.56 / 2.96, 8192 x 11008 4.23 / 4.56;
+  // both terms and 80 candidates: 6144 x 4096 1.74 / 1.81, 8192 x 8192 5.13 / 5.49; two chains: 1024 x 4096 0.75 / 0.73, 4096 x 4096
+  // 0.84 / 0.82, with 80 candidates 1.53 / 1.50, 3072 x 8192 2.30 / 2.28, 3072 x 11008 3.50 / 3.47.  (Row halves: see there.)
+  const bool near_in_front = !two_chains && !near_made;
+  const bool far_operands = make_farop && terms != 0 && nsb >= 2;
   auto ev_sbk = [&](int k) { return side->events[2 * k]; };       // super-block k's kernel has finished
   auto ev_far2 = [&](int k) { return side->events[2 * k + 1]; };  // its far2 update has finished
   // W[:, c0:c1] += [-E | V] [U; P][super-block rows, c0:c1]: -E and V from buffer set `set`, the right operands of
@@ -547,12 +556,13 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     a.EV = far ? ev[0] : nullptr; a.evstride = ev[1] - ev[0];
     // this super-block's columns must have every earlier update, and its buffer set must be free again
     if (two_chains && k >= 2) chk(hipStreamWaitEvent(s, ev_far2(k - 2), 0));
-    a.near = near.at(k);
-    if (k == 0 && make_operands && terms != 0) {
+    if (k == 0 && far_operands && !two_chains) make_far_operands();
+    a.near = near_in_front ? near : near.at(k);
+    if (terms != 0 && (near_in_front || (k == 0 && !near_made))) {
       ProfScope ps(kProfTrailSplit, s);
-      chk(launch_near_operands(U, (terms & 2) ? P : U, ldh, (int)n, 0, 1, near, s));
+      chk(launch_near_operands(U, (terms & 2) ? P : U, ldh, (int)n, k, 1, a.near, s));
     }
-    if (k == 0 && far_operands) make_far_operands();
+    if (k == 0 && far_operands && two_chains) make_far_operands();
     {
       ProfScope ps(kProfColumnLoop, s);
       chk(launch_quant_sb(a, s));
@@ -630,11 +640,16 @@ static int quantize_layer_impl(float* W, int64_t m, int64_t n, int64_t ldw, cons
       SideStream* side = side_stream(3);
       if (!side) { set_last_hip_error(hipGetLastError()); return GPTAQ_ELAUNCH; }
       hipEvent_t ev_fork = side->events[0], ev_join = side->events[1], ev_operands = side->events[2];
-      // The operands made of U and P serve both halves: those of the first super-block before the streams fork, the others in front of
-      // the second half, beside the first half's first super-block.
+      // The far operands serve both halves: made in front of the second half, beside the first half's first super-block.  So do, with
+      // both terms and no search, those of the super-block kernel (the first one's are made before the streams fork); otherwise each half
+      // makes its own in front of each of its super-blocks.  The latter / the former, ms: E term alone 16640 x 2048 0.50 / 0.53, 22016 x
+      // 4096 1.63 / 1.68; 80 candidates, 22016 x 4096 3.36 / 3.50; both terms 12288 x 2048 0.48 / 0.47, 16640 x 2048 0.70 / 0.71, 9216 x
+      // 3072 0.79 / 0.78, 22016 x 4096 2.46 / 2.40, 4096 x 11008 3.81 / 3.74, 8192 x 11008 6.04 / 6.04.  (The line is not the best one:
+      // 9984 x 4096 1.27 / 1.34, 4096 x 8192 2.38 / 2.46, 8192 x 8192 3.55 / 3.68, 1024 x 11008 2.36 / 2.43.)
       const float* Pt = (terms & 2) ? P : U;
-      hipError_t e;
-      {
+      const bool near_once = terms == 3 && !(group > 0 && mse_steps > 0);
+      hipError_t e = hipSuccess;
+      if (near_once) {
         ProfScope ps(kProfTrailSplit, s);
         e = launch_near_operands(U, Pt, ldh, (int)n, 0, 1, near, s);
       }
@@ -643,7 +658,7 @@ static int quantize_layer_impl(float* W, int64_t m, int64_t n, int64_t ldw, cons
       if (e != hipSuccess) { set_last_hip_error(e); return GPTAQ_ELAUNCH; }
       {
         ProfScope ps(kProfTrailSplit, side->stream);
-        e = launch_near_operands(U, Pt, ldh, (int)n, 1, (int)nsb - 1, near, side->stream);
+        if (near_once) e = launch_near_operands(U, Pt, ldh, (int)n, 1, (int)nsb - 1, near.at(1), side->stream);
         hipLaunchKernelGGL(far_operands_all_kernel, dim3((unsigned)(far_rows(n, 0) / 64), 2, (unsigned)((nsb - 1) * (kSbCols / QB))),
                            dim3(256), 0, side->stream, U, Pt, ldh, (int)n, farop[0], farop[1], farop[2], farop[3]);
         if (e == hipSuccess) e = hipGetLastError();
@@ -656,9 +671,10 @@ static int quantize_layer_impl(float* W, int64_t m, int64_t n, int64_t ldw, cons
         set_last_hip_error(e);
       } else {
         rcA = quantize_layer_sb(W, mA, n, ldw, U, P, ldh, dead, bits, group, sym, codes, scales, zeros, buf, near, farop, s, terms,
-                                mse_grid, mse_steps, false, false, ev_operands);
+                                mse_grid, mse_steps, false, false, near_once, ev_operands);
         rcB = quantize_layer_sb(W + mA * ldw, mB, n, ldw, U, P, ldh, dead, bits, group, sym, codes + mA * n, scales + mA * G,
-                                zeros + mA * G, bufB, near, farop, side->stream, terms, mse_grid, mse_steps, false, false);
+                                zeros + mA * G, bufB, near_once ? near : near.at(1), farop, side->stream, terms, mse_grid, mse_steps, false, false,
+                                near_once);
       }
       // the helper stream is behind the caller's stream when the call returns, error or not
       hipError_t joined = hipEventRecord(ev_join, side->stream);

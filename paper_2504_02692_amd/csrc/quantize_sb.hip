@@ -70,20 +70,20 @@ __device__ __forceinline__ float sb_clip_scale(double base, int i, int grid) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// What the super-block kernel reads of U and P, for super-block sb (rows and columns sb0 = 1024 sb on) and its sub-blocks e:
+// What the super-block kernel reads of U and P, for super-block first + i (rows and columns sb0 = 1024 (first + i) on) and its sub-blocks e:
 //   * left operands of the updates: for super-block column c behind the sub-block, the 16 entries S[sb0 + 16 e + k][sb0 + c], k = 0..15,
-//     split into bf16 hi and lo, at ((64 sb + e) * 1024 + c) * 16 + k of its array: the 32 columns x 16 k a wavefront needs for one MFMA
+//     split into bf16 hi and lo, at ((64 i + e) * 1024 + c) * 16 + k of its array: the 32 columns x 16 k a wavefront needs for one MFMA
 //     operand are 1 KB in a row (zeros for the sub-block's own columns, which take no update from it);
-//   * the diagonal piece, 512 floats at diag + 512 (64 sb + e): entry (step j, column c) of U at sb_diag_at(c, j) and of P 256 further on
+//   * the diagonal piece, 512 floats at diag + 512 (64 i + e): entry (step j, column c) of U at sb_diag_at(c, j) and of P 256 further on
 //     (c > j; zeros outside the matrix), and 1 / U_jj at 256 + j (column 0 of P has no entry of its own).
-// grid (16, events, 2 per super-block): blockIdx.x = tile of 64 columns, blockIdx.z = 2 (sb - first) + (0 for U, 1 for P).
+// grid (16, events, 2 per super-block): blockIdx.x = tile of 64 columns, blockIdx.z = 2 i + (0 for U, 1 for P).
 __host__ __device__ constexpr int sb_diag_at(int c, int j) { return 16 * c + 4 * ((j >> 2) ^ ((c >> 2) & 3)) + (j & 3); }   // (no bank conflicts)
 __global__ __launch_bounds__(256) void near_operands_kernel(const float* U, const float* P, int64_t ldh, int n, int first, SbNear o) {
   __shared__ float t[kSub][65];
-  const int e = blockIdx.y, c0 = blockIdx.x * 64, isP = blockIdx.z & 1, sb = first + (blockIdx.z >> 1), sb0 = sb * kSbCols;
+  const int e = blockIdx.y, c0 = blockIdx.x * 64, isP = blockIdx.z & 1, place = blockIdx.z >> 1, sb0 = (first + place) * kSbCols;
   if (c0 + 64 <= kSub * e || sb0 + kSub * e >= n) return;  // entirely left of the sub-block, or no sub-block: never read
   const float* S = isP ? P : U;
-  const int64_t ev = (int64_t)sb * (kSbCols / kSub) + e;
+  const int64_t ev = (int64_t)place * (kSbCols / kSub) + e;
   const int c = threadIdx.x & 63, kq = threadIdx.x >> 6;
 #pragma unroll
   for (int p = 0; p < 4; ++p) {

@@ -364,3 +364,46 @@ def test_few_rows_of_a_wide_matrix(m, n):
     parts = [quantize(W0[r:r + 100]) for r in range(0, m, 100)]
     for i, got in enumerate(whole):
         assert torch.equal(got, torch.cat([p[i] for p in parts]))
+
+
+# Row halves that make the super-block kernel's operands for themselves, against calls on 600 rows at a time (one chain, and two).
+@pytest.mark.parametrize("n,terms,steps", [(2064, 1, 0), (3200, 2, 0), (3072, 3, 5)])
+def test_row_halves_with_operands_of_their_own(n, terms, steps):
+    m, group = 10300, 64 if steps else 0
+    g = torch.Generator(device="cuda").manual_seed(n)
+    U, P = (torch.randn((n, n), device="cuda", generator=g).mul_(f * n ** -0.5).triu_(1) for f in (1.0, 0.1))
+    U.diagonal().copy_(0.5 + torch.rand(n, device="cuda", generator=g))
+    W0 = 0.02 * torch.randn((m, n), device="cuda", generator=g)
+
+    def quantize(W):
+        W = W.clone()
+        out = B.gptaq_quantize_layer(W, U, P, 4, group, False, 128, B.workspace(B.gptaq_quantize_workspace_bytes(W.shape[0], n)), terms=terms,
+                                     mse_grid=8 if steps else 0, mse_steps=steps)
+        torch.cuda.synchronize()
+        return (W, *out)
+
+    whole = quantize(W0)
+    parts = [quantize(W0[r:r + 600]) for r in range(0, m, 600)]
+    for i, got in enumerate(whole):
+        assert torch.equal(got, torch.cat([p[i].reshape(-1, got.shape[1]) for p in parts]))
+
+
+def test_super_block_kernel_finds_its_operands_in_the_caches():
+    """Behind the far updates of a large layer a super-block takes little longer than alone (1.17 times as long when this was written,
+    1.66 with operands made for all super-blocks in front of the first)."""
+    m, us = 8192, {}
+    for n in (1024, 8192):
+        U = torch.eye(n, device="cuda")
+        W0 = 0.02 * torch.randn((m, n), device="cuda")
+        ws = B.workspace(B.gptaq_quantize_workspace_bytes(m, n))
+        times = []
+        for _ in range(5):
+            W = W0.clone()
+            B.gptaq_profile_enable(1 << 4)
+            B.gptaq_quantize_layer(W, U, None, 4, 128, False, 128, ws, terms=1)
+            launches, ms = B.gptaq_profile_read(4)
+            B.gptaq_profile_enable(0)
+            assert launches == n // 1024
+            times.append(1e3 * ms / launches)
+        us[n] = min(times)
+    assert us[8192] <= 1.4 * us[1024], us
