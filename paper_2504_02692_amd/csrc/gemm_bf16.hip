@@ -498,7 +498,9 @@ __global__ __launch_bounds__(256, BT == 128 ? 2 : 1) void gemm_nt_kernel(GemmBat
   }
 }
 
-// C += the sums of the parts of K, in their order.  grid: four workgroups (the four wavefronts of the product) per tile, problem after
+// C += the sum of the parts of K, taken in their order: C is rounded once a call, as with one part (added to it one by one, the parts cost
+// up to 16 roundings of a total that a series of calls has made large: error of dXXT at n = 512 after 16 calls of 8192 tokens 3.5e-7,
+// 2.0e-7 so, 3.1e-7 without parts; 105 us a call of 32768 tokens either way).  grid: four workgroups (the four wavefronts of the product) per tile, problem after
 // problem; a wavefront takes a 32 x 32 block.  Bound by its reads, 64 KB a tile and part.
 __global__ __launch_bounds__(256) void add_parts_kernel(GemmBatch b) {
   constexpr int BT = 128, FR = 2;
@@ -512,26 +514,27 @@ __global__ __launch_bounds__(256) void add_parts_kernel(GemmBatch b) {
   const int row0 = tm * BT + (w >> 1) * 64 + (blk / FR) * 32 + 4 * (lane >> 5), col = tn * BT + (w & 1) * 64 + (blk % FR) * 32 + (lane & 31);
   const f32x4* src = reinterpret_cast<const f32x4*>(P.partial + (int64_t)id * (BT * BT)) + (w * (FR * FR) + blk) * 256 + lane;
   const int64_t step = (int64_t)(b.ntiles[pi] / P.split) * (BT * BT / 4);
-  float c[4][4];
+  float c[4][4], sum[4][4];
 #pragma unroll
   for (int v = 0; v < 4; ++v)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int row = row0 + 8 * v + q;
       c[v][q] = P.C[(int64_t)min(row, P.M - 1) * P.ldc + min(col, P.N - 1)];
+      sum[v][q] = 0.f;
     }
   for (int s = 0; s < P.split; ++s)
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const f32x4 x = src[s * step + 64 * v];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) c[v][q] += x[q];
+      for (int q = 0; q < 4; ++q) sum[v][q] += x[q];
     }
 #pragma unroll
   for (int v = 0; v < 4; ++v)
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      if (row0 + 8 * v + q < P.M && col < P.N && !(pi && b.diag_wgs && row0 + 8 * v + q == col)) P.C[(int64_t)(row0 + 8 * v + q) * P.ldc + col] = c[v][q];
+      if (row0 + 8 * v + q < P.M && col < P.N && !(pi && b.diag_wgs && row0 + 8 * v + q == col)) P.C[(int64_t)(row0 + 8 * v + q) * P.ldc + col] = c[v][q] + sum[v][q];
 }
 
 static LdsLimitOnce g_lds256, g_lds128, g_lds256c, g_lds128c, g_lds128s;

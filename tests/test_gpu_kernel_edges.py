@@ -316,6 +316,27 @@ def test_sums_in_parts_are_the_sums(n, ld, tokens):
             assert float((got.double() - ref).norm() / ref.norm()) <= 3e-6
 
 
+@pytest.mark.parametrize("n,tokens", [(264, 8192), (520, 16448), (1032, 32768)])
+def test_sums_in_parts_round_the_total_once(n, tokens):
+    """Whole numbers, whose sums are exact in fp32 in any order, on totals of 2^25 (steps of 2 and 4): what a call leaves is the exact
+    total rounded once, in parts as in one part."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    X = torch.randint(-2, 3, (tokens, n), device="cuda", generator=g).bfloat16()
+    D = torch.randint(-1, 2, (tokens, n), device="cuda", generator=g).bfloat16()
+    start = (2.0 ** 25 * (0.5 + torch.rand((n, n), device="cuda", generator=g)))
+    size = B.gptaq_accumulate_workspace_bytes(tokens, n)
+    assert size > 6 * -(-n // 128) * 128 * (-(-tokens // 64) * 64)
+    Xd, Dd = X.double(), D.double()
+    refs = [(start.double() + S.T.contiguous() @ Xd).float() for S in (Xd, Dd)]
+    for call in (B.gptaq_accumulate, B.gptaq_accumulate_upper):
+        H, A = start.clone(), start.clone()
+        call(X, X + D, H, A, B.workspace(size))
+        torch.cuda.synchronize()
+        assert torch.equal(H.triu(), refs[0].triu())
+        assert torch.equal(A.triu(), refs[1].triu())
+        assert call is B.gptaq_accumulate_upper or torch.equal(A, refs[1])
+
+
 # Two row halves: the lines of the rule by rows and super-blocks, with and without vector stores; the last one is just on the other side.
 @pytest.mark.parametrize("m,n,group", [(8193, 2064, 0), (4097, 3201, 0), (3585, 5248, 128), (1300, 6784, 64), (760, 10250, 0), (744, 11264, 128)])
 def test_row_halves_equal_separate_calls(m, n, group):
