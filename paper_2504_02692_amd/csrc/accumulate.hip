@@ -218,9 +218,6 @@ static int accumulate_impl(const uint16_t* X, const uint16_t* Xtilde, int64_t to
   int64_t cmax = (int64_t)(ws_bytes / (size_t)(6 * np)) / 64 * 64;
   if (cmax < 64) return GPTAQ_EWORKSPACE;
   if (cmax > 32768) cmax = 32768;    // keeps one fp32 running sum short (accuracy), and K in int32
-  // (all tokens in passes of one size, if that leaves the place for parts that the size was given for)
-  const int64_t whole = round_up(tokens < 32768 ? tokens : 32768, 64);
-  if (cmax > whole && (size_t)(6 * np * whole) + partial_bytes(n, split_for(n, whole)) <= ws_bytes) cmax = whole;
   for (int64_t t0 = 0; t0 < tokens; t0 += cmax) {
     const int64_t c = tokens - t0 < cmax ? tokens - t0 : cmax;
     const int64_t cp = round_up(c, 64);
