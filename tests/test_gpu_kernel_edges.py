@@ -287,8 +287,9 @@ def test_a_solve_can_be_captured():
 
 
 # Sums taken in several parts of the tokens (few columns, many tokens): one tile and its edge, several tiles, k-tiles that do not divide
-# over the parts, most and fewest parts; in a workspace of the operands alone they are taken in one part.
-@pytest.mark.parametrize("n,ld,tokens", [(8, 8, 8192), (136, 140, 8200), (392, 392, 10016), (1032, 1040, 16448), (1536, 1536, 32768)])
+# over the parts, most and fewest parts; in a workspace of the operands alone they are taken in one part.  The diagonal of H, which
+# act_order ranks by, has the bits of one part (8320 tokens: its loads' last round is a whole one).
+@pytest.mark.parametrize("n,ld,tokens", [(8, 8, 8192), (136, 140, 8200), (264, 264, 8320), (392, 392, 10016), (1032, 1040, 16448), (1536, 1536, 32768)])
 def test_sums_in_parts_are_the_sums(n, ld, tokens):
     g = torch.Generator(device="cuda").manual_seed(n)
     X = torch.randn((tokens, n), device="cuda", generator=g).bfloat16()
@@ -308,6 +309,8 @@ def test_sums_in_parts_are_the_sums(n, ld, tokens):
         assert ld == n or (whole[0][:, n:] == -7.0).all() and (whole[1][:, n:] == -7.0).all()
         out[name] = (H.triu(), A.triu() if name == "upper" else A.clone())
     assert torch.equal(out["full"][0], out["upper"][0]) and torch.equal(out["full"][1].triu(), out["upper"][1])
+    assert torch.equal(out["full"][0].diagonal(), out["one part"][0].diagonal())
+    assert n < 128 or not torch.equal(out["full"][1], out["one part"][1])          # (the parts were taken)
     Xd, Dd = X.double(), Xt.double() - X.double()
     refs = ((start.double() + Xd.T.contiguous() @ Xd).triu(), start.double() + Dd.T.contiguous() @ Xd)
     for name in ("full", "one part"):

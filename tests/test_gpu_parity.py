@@ -372,7 +372,8 @@ def test_act_order_path():
     assert np.array_equal(What.cpu().numpy()[:, ref["perm"]], got["What"])
 
 
-@pytest.mark.parametrize("tokens,n,chunks", [(3000, 384, None), (1500, 1096, [0, 700, 1500]), (900, 2304, None)])
+@pytest.mark.parametrize("tokens,n,chunks", [(3000, 384, None), (1500, 1096, [0, 700, 1500]), (900, 2304, None), (8256, 264, None),
+                                             (17000, 520, [0, 8704, 17000])])
 def test_act_order_with_the_upper_triangle_accumulation(tokens, n, chunks):
     """The two-pass route: the diagonal of H first, the order from it, then H and the upper triangle of dXXT of the
     reordered inputs directly.  Against the one-pass route (full sums, gptaq_act_order, gptaq_permute_hessian): the same
