@@ -365,10 +365,11 @@ QLayout q_layout(int64_t m, int64_t n) {
     // 0-3: -E, V (hi, lo) of one super-block; 4-7: right operands of the updates of one super-block as the
     // block-per-wave path makes them (all columns from the super-block's first on, plus a tile of padding rows);
     // 12-15: a second set of 0-3 (the far update of a super-block runs beside the next super-block, which writes its own -E
-    // and V; or the two row halves of a tall matrix run as two chains, each at its own super-block); 8-11: unused
+    // and V; or the two row halves of a tall matrix run as two chains, each at its own super-block); 8-11: none
     o += (size_t)(i % 12 < 4 ? L.mp * KS * 2 : i < 8 ? (L.np + 256) * KS * 2 : 0);
     if (i == 7) {
-      // what the super-block kernel reads of U and P, of every super-block (near_operands_kernel), in the place of 4-7 and behind
+      // what the super-block kernel reads of U and P, places for every super-block (near_operands_kernel): in the place of 4-7 and the
+      // 16 MB behind (4 of them are needed with few columns; all are kept, so that a workspace is as large as callers know it)
       const int64_t nsb = (n + kSbCols - 1) / kSbCols;
       L.off_near = L.off[4];
       const size_t near = (size_t)(nsb * (4 * (int64_t)kSbCols * kSbCols * 2 + (int64_t)(kSbCols / 16) * 512 * 4));

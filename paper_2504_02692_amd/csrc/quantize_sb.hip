@@ -29,10 +29,11 @@
 // that sub-block's column steps.  Finished.  One workgroup barrier per sub-block publishes its -E and V.  What the owner needs
 // next from memory (diagonal pieces of U and P, left operands) the others fetch into LDS, and they form and store its results.
 //
-// What bounds it: the owner's chain, of the 64 sub-blocks about 3.3K clocks each (4.5K in the first two blocks, where two updaters to a SIMD
-// keep it waiting): 1.8K of column steps (376 vector instructions at 4.7 clocks; 400 more when 24 MFMAs run beside them), 170 to bring the
-// 16 columns into one row per lane, 1.0K for the operands and the 12 MFMAs of the next sub-block's piece; and 3.5K from one block to the
-// next (48 MFMAs of the new owner, the group's range and grid).  The matrix pipes of a SIMD with two updaters need 3.1K a sub-block.
+// What bounds it: the owner's chain, of the 64 sub-blocks about 4.3K clocks each in the first four blocks, where an updater shares the owner's
+// SIMD, and 3.7K in the last four: 1.9K of column steps (376 vector instructions at 5 clocks; 650 more when 24 MFMAs run beside them),
+// 200 to bring the 16 columns into one row per lane, 1.0K for the operands and the 12 MFMAs of the next sub-block's piece; and 3.7K from
+// one block to the next (48 MFMAs of the new owner, the group's range and grid).  The matrix pipes of a SIMD with two updaters need 3.1K
+// a sub-block.
 // What that took, on the way from 5.3K a sub-block (151 -> 137 us for 1024 columns of 4096 rows, 64 workgroups, with nothing beside it;
 // rows' outputs the same bits): W^ and codes formed by the wavefront that stores them; V split and LDS written under the next
 // piece's MFMAs; single MFMAs between column steps (7 clocks of the wavefront each, but 32 behind another MFMA); loads to LDS shared out
