@@ -25,10 +25,12 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float f) {
 
 // grid: (n_pad / 64, c_pad / 64).  Writes zeros where the source is out of range, so the
 // GEMM can run on whole tiles.
+// SPARSE: lo in the form of GemmTerm's kind 3 (sparse_remainder), else like hi.
+template <bool SPARSE>
 __global__ __launch_bounds__(256) void split_transpose_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ Xt, int64_t ldx,
     int tokens, int n, uint16_t* __restrict__ oX, uint16_t* __restrict__ oHi,
-    uint16_t* __restrict__ oLo, int64_t ldo /* padded rows */, int tile0 /* first 64-token tile of the output */,
+    uint16_t* __restrict__ oLo, uint16_t* __restrict__ oLo2, int64_t ldo /* padded rows */, int tile0 /* first 64-token tile of the output */,
     const int32_t* __restrict__ row_of /* NULL, or operand row of input column j (a permutation of 0 .. n-1) */) {
   constexpr int LS = 72;                                  // padded LDS row, 144 bytes
   __shared__ __attribute__((aligned(16))) uint16_t sx[64 * LS], sh[64 * LS], sl[64 * LS];
@@ -67,7 +69,52 @@ __global__ __launch_bounds__(256) void split_transpose_kernel(
     const int64_t g = (((int64_t)(blockIdx.y + tile0) * 2 + (c >> 2)) * ldo + row) * 32 + (c & 3) * 8;   // k-tile-major
     *reinterpret_cast<u32x4*>(oX + g) = *reinterpret_cast<const u32x4*>(sx + nl * LS + c * 8);
     *reinterpret_cast<u32x4*>(oHi + g) = *reinterpret_cast<const u32x4*>(sh + nl * LS + c * 8);
-    *reinterpret_cast<u32x4*>(oLo + g) = *reinterpret_cast<const u32x4*>(sl + nl * LS + c * 8);
+    if (!SPARSE) *reinterpret_cast<u32x4*>(oLo + g) = *reinterpret_cast<const u32x4*>(sl + nl * LS + c * 8);
+  }
+  if (!SPARSE) return;
+  // lo, in the form that GemmTerm describes: a wavefront has a 32 x 32 block and a lane the 16 tokens of its row that it has there
+  const int lane = tid & 63, nl = (tid >> 7) * 32 + (lane & 31), k = tid >> 6 & 1;
+  int64_t row = n0 + nl;
+  if (row_of && row < n) {
+    const int32_t rr = row_of[row];
+    if (rr >= 0 && rr < n) row = rr;
+  }
+  uint64_t q[4];
+  int nz[4];
+  bool more = row_of != nullptr;                            // (rows that go elsewhere: their blocks are not known here, and are dense)
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const u32x4 x = *reinterpret_cast<const u32x4*>(sl + nl * LS + k * 32 + (lane >> 5) * 16 + h * 8);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const uint32_t a = x[2 * e], b = x[2 * e + 1];
+      const int z = (a & 0x7fffu ? 1 : 0) | (a & 0x7fff0000u ? 2 : 0) | (b & 0x7fffu ? 4 : 0) | (b & 0x7fff0000u ? 8 : 0);
+      q[2 * h + e] = (uint64_t)b << 32 | a;
+      nz[2 * h + e] = z;
+      more |= __builtin_popcount(z) > 2;
+    }
+  }
+  const bool dense = __ballot(more) != 0;
+  uint32_t v[4], v2[4], places = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    // places of two values that hold what is not zero: (0,1) (0,3) (1,3) (0,1) | (2,3) (0,2) (1,2) - | (2,3) (0,3) (1,3) - | (2,3) - - -,
+    // and (0,1) where two do not
+    const uint32_t at = (uint32_t)(0x444E4DCE498E4DC4ull >> (4 * nz[e]) & 15);
+    v[e] = (uint32_t)(q[e] >> (16 * (at & 3)) & 0xffff) | (uint32_t)(q[e] >> (16 * (at >> 2))) << 16;
+    v2[e] = __builtin_popcount(nz[e]) > 2 ? (uint32_t)(q[e] >> 32) : kPositionsMark | at << (4 * e);
+    places |= at << (4 * e);
+  }
+  const int64_t kt = (int64_t)(blockIdx.y + tile0) * 2 + k;
+  const int to = (int)(row & 31) + (lane & 32), blk = (int)(row & 127) >> 5;
+  *reinterpret_cast<u32x4*>(oLo + (kt * ldo + (row & ~31)) * 16 + to * 8) = u32x4{v[0], v[1], v[2], v[3]};
+  unsigned char* second = reinterpret_cast<unsigned char*>(oLo2 + (kt * ldo + (row & ~127)) * 16);
+  if (dense) {
+    unsigned char* dst = to == 0 ? second + 16 * blk : to < 9 ? second + 64 + 128 * blk + 16 * (to - 1) : second + 576 + 880 * blk + 16 * (to - 9);
+    *reinterpret_cast<u32x4*>(dst) = u32x4{v2[0], v2[1], v2[2], v2[3]};
+  } else {
+    *reinterpret_cast<uint16_t*>(second + 64 + 128 * blk + 2 * to) = (uint16_t)places;
+    if (to == 0) *reinterpret_cast<u32x4*>(second + 16 * blk) = u32x4{kSparseMark, kSparseMark, kSparseMark, kSparseMark};
   }
 }
 
@@ -115,6 +162,18 @@ __global__ void invert_permutation_kernel(const int32_t* perm, int n, int32_t* i
     if (i >= 0 && i < n) inv[i] = r;
   }
 }
+
+// Whether the remainder's products are taken as sparse ones (kind 3): from 1921 columns on, where the upper form has more tiles than the
+// chip has CUs.  dX does not fit a bf16 only where it is larger than the smaller of X and X~ (2.7 % of the entries where the two differ
+// by 5 % of a channel's deviation), so most of lo is zero.  Fewer matrix instructions and operand bytes (41 KB instead of 48 for
+// 32 tokens of a 256-tile, which is what bounds these launches).  By n alone: a staged call writes its operands before the number of
+// tokens is known, and the sums do not depend on the form of the call.  Measured, us per call, upper form, as
+// dense operands / so: 2048 columns and 32768 tokens 588 / 568, 2736 872 / 828 (full form 1275 / 1115), 2736 and 4096 tokens 115 / 104,
+// 3072 and 16384 588 / 490, 4096 and 2048 135 / 117, 4096 and 32768 1556 / 1453, 11008 and 32768 9330 / 8790.  With fewer columns a
+// workgroup has its CU to itself and the branches of the loop show: 512 and 4096 tokens 54 / 58, 1536 and 4096 58 / 66.  Where every
+// block is dense (X~ 20 % off X or more, or the call permutes) the second sparse product takes the time back: 11008 9370 / 9860.
+// Error of dXXT against 64 bits as before: 2.96e-7 / 2.91e-7 at 4104 columns and 6144 tokens.
+static bool sparse_remainder(int64_t n) { const int64_t t = (n + 127) / 128; return t * (t + 1) > 256; }
 
 static int64_t padded_n(int64_t n) { return round_up(n, gemm_tile_for(n, n)); }
 
@@ -168,7 +227,7 @@ extern "C" size_t gptaq_accumulate_workspace_bytes(int64_t tokens, int64_t n) {
 // dxxt_upper: only the tiles of dXXT that touch its upper triangle.  Eq. 17 masks dXXT L to its strictly upper part and
 // L is lower triangular, so entry (i, k) of dXXT reaches P only through sums over k >= j > i: in the natural column
 // order nothing on or below the diagonal is ever read, and two fifths of the products of the launch can be left out.
-static hipError_t launch_products(const uint16_t* oX, const uint16_t* oHi, const uint16_t* oLo, int64_t np, int64_t cp,
+static hipError_t launch_products(const uint16_t* oX, const uint16_t* oHi, const uint16_t* oLo, const uint16_t* oLo2, int64_t np, int64_t cp,
                                   int64_t n, float* H, float* dXXT, int64_t ldh, bool dxxt_upper, void* ws, size_t ws_bytes, size_t operand_bytes,
                                   hipStream_t s) {
   const int tile = gemm_tile_for(n, n);
@@ -178,8 +237,8 @@ static hipError_t launch_products(const uint16_t* oX, const uint16_t* oHi, const
   GemmProblem& a = b.p[0];
   a.C = dXXT; a.ldc = ldh; a.M = (int)n; a.N = (int)n; a.K = (int)cp;
   a.tiles_m = a.tiles_n = (int)(np / tile);
-  a.kind = 1; a.nterm = 1; a.tile_mode = dxxt_upper ? 2 : 0; a.k_mode = 0; a.store_mode = 0;
-  a.term[0] = {{oHi, oLo}, {oX, oX}, 32, 32, np * 32, np * 32};
+  a.kind = sparse_remainder(n) ? 3 : 1; a.nterm = 1; a.tile_mode = dxxt_upper ? 2 : 0; a.k_mode = 0; a.store_mode = 0;
+  a.term[0] = {{oHi, oLo}, {oX, oLo2}, 32, 32, np * 32, np * 32};
   GemmProblem& h = b.p[1];
   h = a;
   h.C = H; h.kind = 0; h.tile_mode = 2;
@@ -223,15 +282,15 @@ static int accumulate_impl(const uint16_t* X, const uint16_t* Xtilde, int64_t to
     const int64_t cp = round_up(c, 64);
     uint16_t* oX = (uint16_t*)ws;
     uint16_t* oHi = oX + np * cp;
-    uint16_t* oLo = oHi + np * cp;
+    uint16_t *oLo = oHi + np * cp, *oLo2 = oLo + np * cp / 2;
     {
       ProfScope ps(kProfAccumSplit, s);
-      hipLaunchKernelGGL(split_transpose_kernel, dim3((unsigned)(np / 64), (unsigned)(cp / 64)),
+      hipLaunchKernelGGL(sparse_remainder(n) ? split_transpose_kernel<true> : split_transpose_kernel<false>, dim3((unsigned)(np / 64), (unsigned)(cp / 64)),
                          dim3(256), 0, s, X + t0 * ldx, Xtilde + t0 * ldx, ldx, (int)c, (int)n,
-                         oX, oHi, oLo, np, 0, row_of);
+                         oX, oHi, oLo, oLo2, np, 0, row_of);
     }
     GPTAQ_LAUNCH_CHECK();
-    hipError_t e = launch_products(oX, oHi, oLo, np, cp, n, H, dXXT, ldh, dxxt_upper, ws, ws_bytes, (size_t)(6 * np * cp), s);
+    hipError_t e = launch_products(oX, oHi, oLo, oLo2, np, cp, n, H, dXXT, ldh, dxxt_upper, ws, ws_bytes, (size_t)(6 * np * cp), s);
     if (e != hipSuccess) { set_last_hip_error(e); return GPTAQ_ELAUNCH; }
   }
   return GPTAQ_OK;
@@ -317,15 +376,15 @@ static int accumulate_staged_impl(const uint16_t* X, const uint16_t* Xtilde, int
   const int64_t np = padded_n(n);
   if (((uintptr_t)ws & 255) || ws_bytes < (size_t)(6 * np * CAP)) return GPTAQ_EWORKSPACE;
   hipStream_t s = (hipStream_t)stream;
-  uint16_t *oX = (uint16_t*)ws, *oHi = oX + np * CAP, *oLo = oHi + np * CAP;
-  auto products = [&](int64_t cp) { return launch_products(oX, oHi, oLo, np, cp, n, H, dXXT, ldh, dxxt_upper, ws, ws_bytes, (size_t)(6 * np * CAP), s); };
+  uint16_t *oX = (uint16_t*)ws, *oHi = oX + np * CAP, *oLo = oHi + np * CAP, *oLo2 = oLo + np * CAP / 2;
+  auto products = [&](int64_t cp) { return launch_products(oX, oHi, oLo, oLo2, np, cp, n, H, dXXT, ldh, dxxt_upper, ws, ws_bytes, (size_t)(6 * np * CAP), s); };
   int64_t done = 0, pend = *pending;
   while (done < tokens) {
     const int64_t take = tokens - done < CAP - pend ? tokens - done : CAP - pend, cp = round_up(take, 64);
     {
       ProfScope ps(kProfAccumSplit, s);
-      hipLaunchKernelGGL(split_transpose_kernel, dim3((unsigned)(np / 64), (unsigned)(cp / 64)), dim3(256), 0, s,
-                         X + done * ldx, Xtilde + done * ldx, ldx, (int)take, (int)n, oX, oHi, oLo, np, (int)(pend / 64), (const int32_t*)nullptr);
+      hipLaunchKernelGGL(sparse_remainder(n) ? split_transpose_kernel<true> : split_transpose_kernel<false>, dim3((unsigned)(np / 64), (unsigned)(cp / 64)), dim3(256), 0, s,
+                         X + done * ldx, Xtilde + done * ldx, ldx, (int)take, (int)n, oX, oHi, oLo, oLo2, np, (int)(pend / 64), (const int32_t*)nullptr);
     }
     GPTAQ_LAUNCH_CHECK();
     done += take;

@@ -10,6 +10,7 @@
 namespace gptaq {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(16))) __bf16 bf16x16;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -30,8 +31,21 @@ struct GemmTerm {
   int64_t ktl, ktr;
 };
 
+// Kind 3: L[0] = hi and R[0] = X as above, k-tile-major.  Of lo, the remainder of hi, few entries are not zero, so it is stored by
+// 32 x 32 blocks (rows x tokens of one k-tile) in the form of v_smfmac_f32_32x32x32_bf16: two values of every four tokens, lane l the
+// values of row l % 32 and tokens 16 (l / 32) .. + 15, 16 bytes a lane.  L[1]: those values (lo1), block (k-tile, row / 32) after block.
+// R[1]: as many bytes again, 4 KB for the four blocks of 128 rows: four heads of 16 bytes, four position fields of 128 (16 bits a lane:
+// where among its four tokens each value sits), four tails of 880.  Where no four tokens of a row hold more than two values, a
+// block's head is kSparseMark and its tail is not used.  Else the block is dense: head, position field and tail, one after the other,
+// are 16 bytes a lane (lo2), a pair for every four tokens: where these hold more than two values, lo1 has those of tokens 0 and 1 and
+// the pair those of tokens 2 and 3; where not, the pair is kPositionsMark with the positions of lo1's values at their bits of the 16.
+// (So the order in which a row's products are added does not depend on the other rows of its block.  The marks are NaNs that no
+// remainder is: those that arithmetic makes are quiet.)
+constexpr uint32_t kSparseMark = 0x7f817f81u, kPositionsMark = 0x7f810000u;
+constexpr int kMaxRemainderK = 32768;      // K of a problem of kind 3
+
 // C (+)= sum_t sum_pairs L R^T.  kind 0: L0 R0.  kind 1: L0 R0 + L1 R0 (two left operands share the
-// right one).  kind 2: L0 R0 + L0 R1 + L1 R0 (hi/lo split of both sides, lo*lo dropped).
+// right one).  kind 2: L0 R0 + L0 R1 + L1 R0 (hi/lo split of both sides, lo*lo dropped).  kind 3: (hi + lo) X^T (one term; see above).
 // Operand buffers are zero-padded to whole tiles in rows and to a multiple of kGemmBK in K, so the
 // main loop needs no bounds checks; stores are bounded by M and N.
 struct GemmProblem {

@@ -28,7 +28,7 @@ template <int KIND> struct KindTraits;
 template <> struct KindTraits<0> { static constexpr int NL = 1, NR = 1, NPAIR = 1, NSTAGE = 4; };
 template <> struct KindTraits<1> { static constexpr int NL = 2, NR = 1, NPAIR = 2, NSTAGE = 3; };
 template <> struct KindTraits<2> { static constexpr int NL = 2, NR = 2, NPAIR = 3, NSTAGE = 2; };
-// pair p of a kind: (left index, right index)
+// pair p of a kind: (left index, right index)  (kind 3 has a loop of its own: remainder_loop)
 __device__ __forceinline__ constexpr int pair_l(int kind, int p) { return kind == 0 ? 0 : kind == 1 ? p : (p == 2 ? 1 : 0); }
 __device__ __forceinline__ constexpr int pair_r(int kind, int p) { return kind == 2 ? (p == 1 ? 1 : 0) : 0; }
 
@@ -46,8 +46,9 @@ template <int N> __device__ __forceinline__ void wait_vm_and_lds() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
 }
 
-constexpr int kLds256 = 3 * 3 * 256 * 64;    // largest ring: 3 stages x 3 operand tiles (2 x 4 and 4 x 2 are smaller)
-constexpr int kLds128 = 3 * 3 * 128 * 64;
+constexpr int kFlagBytes = kMaxRemainderK / kGemmBK;      // kind 3: a byte per k-tile
+constexpr int kLds256 = 3 * 3 * 256 * 64 + kFlagBytes;    // largest ring: kinds 1 and 3, 3 stages x 3 operand tiles (2 x 4 and 4 x 2 are smaller)
+constexpr int kLds128 = 3 * 3 * 128 * 64 + kFlagBytes;
 
 template <int BT, int KIND, bool MULTI>
 __device__ __forceinline__ void tile_loop(const GemmProblem& P, unsigned char* smem, int m0, int n0, int klo, int nk,
@@ -217,6 +218,233 @@ __device__ __forceinline__ void tile_loop(const GemmProblem& P, unsigned char* s
   wait_vm_and_lds<0>();   // the surplus loads past the last k-tile
 }
 
+// The products of remainder_loop are assembly: v_smfmac's result is its accumulator, and from the builtins the compiler made copies of
+// accumulators, for which there are no registers (1.8 KB of scratch a lane).  It does not look into assembly: an operand must not have
+// been written by one of the two instructions before (a nop stands for them), and what reads the accumulators as registers waits for the
+// last of them (settle); that one product adds to what another has just written is the hardware's to order.
+__device__ __forceinline__ void dense_product(f32x16& acc, bf16x8 l, bf16x8 x) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(l), "v"(x));
+}
+__device__ __forceinline__ void sparse_product(f32x16& acc, bf16x8 lo, bf16x16 x, int pos) {      // 32 tokens
+  asm volatile("s_nop 1\n\tv_smfmac_f32_32x32x32_bf16 %0, %1, %2, %3" : "+a"(acc) : "v"(lo), "v"(x), "v"(pos));
+}
+// (two, if on != 0: the branch is inside, so that no accumulator has two ways to come from)
+__device__ __forceinline__ void sparse_products_if(int on, f32x16& a0, f32x16& a1, bf16x8 lo, bf16x16 x0, bf16x16 x1, int pos) {
+  asm volatile("s_cmp_eq_u32 %6, 0\n\ts_cbranch_scc1 .Lnone%=\n\ts_nop 1\n\t"
+               "v_smfmac_f32_32x32x32_bf16 %0, %2, %3, %5\n\tv_smfmac_f32_32x32x32_bf16 %1, %2, %4, %5\n.Lnone%=:"
+               : "+a"(a0), "+a"(a1) : "v"(lo), "v"(x0), "v"(x1), "v"(pos), "s"(on) : "scc");
+}
+__device__ __forceinline__ void settle(f32x16& acc) { asm volatile("s_nop 15\n\ts_nop 7" : "+a"(acc)); }
+
+// Kind 3: acc += (hi + lo) X^T, hi and X bf16 operands as above, lo the remainder of hi, of which few entries are not zero
+// (GemmTerm says how it is stored).  lo takes a v_smfmac_f32_32x32x32_bf16 per 32 x 32 block and k-tile, at twice the rate of a
+// dense product; a second one (lo2) where the block is marked as dense.  Bound by its operand bytes (41 KB per 32 tokens of a 256-tile, for
+// 1536 clocks of products) and by what else a wavefront issues: spreading the loads over the products, one branch for all that
+// dense blocks need, and the fragments a whole k-tile ahead are worth 3 to 8 % each.
+template <int BT>
+__device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned char* smem, int m0, int n0, int klo, int nk,
+                                               f32x16 (&acc)[BT / 64][BT / 64]) {
+  constexpr int NSTAGE = 3, WT = BT / 2, FR = WT / 32;
+  constexpr int BLK = BT / 32, GROUP = 4096;                // 32 x 32 blocks of lo in a k-tile; bytes of lo2's place of 128 rows
+  constexpr int OPB = BT * 64, LOB = BT * 32;               // bytes of a k-tile of hi or X, and of lo1 or lo2
+  constexpr int STAGE_BYTES = 2 * OPB + 2 * LOB;            // hi, X, lo1, lo2 (with the positions of lo1)
+  constexpr int LPW = BT / 64, LPWL = LOB / 4096;           // 1 KB loads per wave and k-tile: of hi or X, of lo1 or lo2
+  constexpr int TL = 2 * LPW + LPWL + 1;                    // loads per k-tile per wave, load_dense apart
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  const GemmTerm& tm = P.term[0];
+  const int64_t kt0 = klo / kGemmBK, lokt = tm.ktl / 2;     // (elements of lo1, and of lo2, per k-tile)
+  // the positions that a wave fetches, 256 bytes of a group's 512 (with one group, two waves fetch the same)
+  auto pos_at = [](int w) { return (BT == 256 ? (w >> 1) * GROUP : 0) + 64 + (w & 1) * 256; };
+  if (nk <= 0) return;
+
+  const int ld_line = lane >> 4;                            // (tile format in LDS: see tile_loop)
+  const int ld_row = ld_line * 4 + ((lane & 15) >> 2);
+  const int ld_chunk = (lane & 3) ^ ld_line;
+  struct TileSrc {
+    const uint16_t *hi, *x, *lo, *lo2, *pos;
+    unsigned char* st;
+    int seq;
+  } c;
+  {
+    const int64_t row = wave * LPW * 16 + ld_row;
+    c.hi = tm.L[0] + (m0 + row) * tm.ldl + kt0 * tm.ktl + ld_chunk * 8;
+    c.x = tm.R[0] + (n0 + row) * tm.ldr + kt0 * tm.ktr + ld_chunk * 8;
+    const int64_t o = kt0 * lokt + (int64_t)m0 * 16;
+    c.lo = tm.L[1] + o + wave * (LPWL * 512) + lane * 8;
+    c.lo2 = tm.R[1] + o + wave * (LPWL * 512) + lane * 8;
+    c.pos = tm.R[1] + o + (pos_at(wave) >> 1) + lane * 2;
+    c.st = smem;
+    c.seq = 0;
+  }
+  const int64_t lstep = 16 * tm.ldl, rstep = 16 * tm.ldr;
+  auto next_tile = [&](int stage) {
+    ++c.seq;
+    c.st = smem + stage * STAGE_BYTES;
+    const bool more = c.seq < nk;
+    const int64_t ls = more ? tm.ktl : 0, rs = more ? tm.ktr : 0, os = more ? lokt : 0;
+    c.hi += ls;
+    c.x += rs;
+    c.lo += os;
+    c.lo2 += os;
+    c.pos += os;
+  };
+  auto to_lds = [&](const uint16_t* src, int off) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                     (__attribute__((address_space(3))) void*)(c.st + off), 16, 0, 0);
+  };
+  auto load_one = [&](int q) {
+    if (q < 2 * LPW) {
+      const int j = q >> 1;
+      if (q & 1) to_lds(c.x + j * rstep, OPB + (wave_s * LPW + j) * 1024);
+      else to_lds(c.hi + j * lstep, (wave_s * LPW + j) * 1024);
+    } else if (q < 2 * LPW + LPWL) {
+      const int p = q - 2 * LPW;
+      to_lds(c.lo + p * 512, 2 * OPB + (wave_s * LPWL + p) * 1024);
+    } else {
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)c.pos,
+                                       (__attribute__((address_space(3))) void*)(c.st + 2 * OPB + LOB + pos_at(wave_s)), 4, 0, 0);
+    }
+  };
+  // lo2's place of a tile with dense blocks: in front of its other loads, so that the counts the waits go by hold (more loads only
+  // make them longer)
+  auto load_dense = [&](int f) {
+    if (__builtin_expect(f == 0, 1)) return;
+#pragma unroll
+    for (int p = 0; p < LPWL; ++p) to_lds(c.lo2 + p * 512, 2 * OPB + LOB + (wave_s * LPWL + p) * 1024);
+  };
+
+  const int rl = lane & 31, half = lane >> 5;
+  const int fr_line = rl >> 2, fr_x = fr_line & 3, fr_hi = (rl & 3) << 2;
+  const int lo2_at = lane == 0 ? 0 : lane < 9 ? 64 + 16 * (lane - 1) : 576 + 16 * (lane - 9);
+  const int lo2_step = lane == 0 ? 16 : lane < 9 ? 128 : 880;
+  const int grp = 2 * OPB + LOB + (BT == 256 ? wm * GROUP : 0), blk0 = BT == 256 ? 0 : wm * FR;      // this wavefront's blocks of lo2
+  // the fragments of two k-tiles, the one that is multiplied and the one that is read meanwhile (by the parity of their number)
+  bf16x8 af[2][2][FR], bfr[2][2][FR], lo[2][FR];
+  u32x4 lo2[FR];
+  int pos[2][FR], mark;
+  auto frag = [&](const unsigned char* st, int kk, int i) {
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(st + i * 2048 + fr_line * 256 + ((fr_hi | ((kk * 2 + half) ^ fr_x)) << 4)));
+  };
+  constexpr int NREAD = 6 * FR;
+  auto read_one = [&](const unsigned char* st, int s, int r) {
+    const int i = r % FR, kk = r / FR & 1;
+    if (r < 4 * FR) {
+      if (r < 2 * FR) af[s][kk][i] = frag(st + wm * (WT * 64), kk, i);
+      else bfr[s][kk][i] = frag(st + OPB + wn * (WT * 64), kk, i);
+    } else if (r < 5 * FR) {
+      lo[s][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(st + 2 * OPB + (wm * FR + i) * 1024 + lane * 16));
+    } else {
+      pos[s][i] = *reinterpret_cast<const uint16_t*>(st + grp + 64 + (blk0 + i) * 128 + lane * 2);
+    }
+  };
+  auto blocks_of = [&](int f) { return (f >> (wave_s >> 1) * FR) & ((1 << FR) - 1); };      // this wavefront's
+  auto read_dense = [&](const unsigned char* st, int i) {
+    lo2[i] = *reinterpret_cast<const u32x4*>(st + grp + lo2_at + (blk0 + i) * lo2_step);
+  };
+  // a dense block's pairs that stand for positions: those to pos, zeros in their place
+  auto decode = [&](int s, int i, int dense) {
+    int p = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t x = lo2[i][e] ^ kPositionsMark;
+      const bool is = x < 0x10000u;
+      p |= is ? (int)x : 4 << (4 * e);
+      lo2[i][e] = is ? 0u : lo2[i][e];
+    }
+    if (dense >> i & 1) pos[s][i] = p;
+  };
+
+  // Pipeline: one barrier per k-tile `it`, behind which tile it is in registers (its stage is loaded again, with tile it + NSTAGE) and
+  // tile it + 1 in LDS: its fragments are read and tile it + NSTAGE is requested, one at a time, between the products of tile it.
+  constexpr int NM = FR * FR, NSLOT = 3 * NM, READ_SLOTS = NSLOT - NM / 2, LOAD_SLOTS = NSLOT - 4;
+#pragma unroll
+  for (int t = 0; t < NSTAGE; ++t) {
+    load_dense(1);                                          // (not known yet)
+#pragma unroll
+    for (int q = 0; q < TL; ++q) load_one(q);
+    next_tile((t + 1) % NSTAGE);
+  }
+  // which blocks of each k-tile are dense: a bit per block, from the marks in their places
+  unsigned char* flags = smem + NSTAGE * STAGE_BYTES;
+  for (int kt = tid; kt < nk; kt += 256) {
+    const uint32_t* mark = reinterpret_cast<const uint32_t*>(tm.R[1] + (kt0 + kt) * lokt + (int64_t)m0 * 16);
+    int f = 0;
+#pragma unroll
+    for (int b = 0; b < BLK; ++b) f |= mark[(b >> 2) * (GROUP / 4) + (b & 3) * 4] != kSparseMark ? 1 << b : 0;
+    flags[kt] = (unsigned char)f;
+  }
+  wait_vm_and_lds<0>();
+  wg_barrier();
+  int fl[NSTAGE];
+#pragma unroll
+  for (int t = 0; t < NSTAGE; ++t) fl[t] = t < nk ? __builtin_amdgcn_readfirstlane(flags[t]) : 0;
+  mark = flags[min(NSTAGE, nk - 1)];
+#pragma unroll
+  for (int r = 0; r < NREAD; ++r) read_one(smem, 0, r);
+#pragma unroll
+  for (int i = 0; i < FR; ++i) {
+    read_dense(smem, i);
+    decode(0, i, blocks_of(fl[0]));
+  }
+  for (int it0 = 0; it0 < nk; it0 += 2 * NSTAGE) {
+#pragma unroll
+    for (int u = 0; u < 2 * NSTAGE; ++u) {
+      if (__builtin_expect(it0 + u < nk, 1)) {
+        const int sg = u % NSTAGE, s = u & 1;
+        const unsigned char* nx = smem + (u + 1) % NSTAGE * STAGE_BYTES;
+        auto both = [&](int j) { return __builtin_shufflevector(bfr[s][0][j], bfr[s][1][j], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15); };
+        __builtin_amdgcn_sched_barrier(0);
+        wait_vm_and_lds<TL>();
+        wg_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        const int fl_now = fl[sg];
+#pragma unroll
+        for (int m = 0; m < NSLOT; ++m) {
+          const int i = m % NM / FR, j = m % FR;
+          __builtin_amdgcn_sched_barrier(0);
+          if (m < 2 * NM) dense_product(acc[i][j], af[s][m / NM % 2][i], bfr[s][m / NM % 2][j]);
+          else sparse_product(acc[i][j], lo[s][i], both(j), pos[s][i]);
+          __builtin_amdgcn_sched_barrier(0);
+          // (behind the last k-tile: a stale stage, not used)
+#pragma unroll
+          for (int r = m * NREAD / READ_SLOTS; r < (m + 1) * NREAD / READ_SLOTS && r < NREAD; ++r) read_one(nx, s ^ 1, r);
+          if (m == 1) {
+            fl[sg] = c.seq < nk ? __builtin_amdgcn_readfirstlane(mark) : 0;
+            load_dense(fl[sg]);
+          }
+          if (m == READ_SLOTS - 1) mark = flags[min(it0 + u + NSTAGE + 1, nk - 1)];
+          const int l = m - 2;
+#pragma unroll
+          for (int q = l * TL / LOAD_SLOTS; l >= 0 && l < LOAD_SLOTS && q < (l + 1) * TL / LOAD_SLOTS; ++q) load_one(q);
+          if (m == NSLOT - 2) next_tile((u + 1) % NSTAGE);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (__builtin_expect((fl_now | fl[(u + 1) % NSTAGE]) != 0, 0)) {       // (one branch for both: a taken one costs tens of clocks)
+          const int dense = blocks_of(fl_now), then = blocks_of(fl[(u + 1) % NSTAGE]);
+#pragma unroll
+          for (int i = 0; i < FR; ++i) {                    // lo2: positions 2, 3
+#pragma unroll
+            for (int j = 0; j < FR; j += 2)
+              sparse_products_if(dense >> i & 1, acc[i][j], acc[i][j + 1], __builtin_bit_cast(bf16x8, lo2[i]), both(j), both(j + 1), 0xEEEE);
+            __builtin_amdgcn_sched_barrier(0);
+            read_dense(nx, i);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i > 0) decode(s ^ 1, i - 1, then);
+          }
+          decode(s ^ 1, FR - 1, then);
+        }
+      }
+    }
+  }
+  wait_vm_and_lds<0>();   // the surplus loads past the last k-tile
+#pragma unroll
+  for (int i = 0; i < FR; ++i)
+#pragma unroll
+    for (int j = 0; j < FR; ++j) settle(acc[i][j]);
+}
+
 // A wave-uniform value that is to stay in scalar registers (the compiler would otherwise choose between the two problems of a
 // batch again at every use).
 __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
@@ -362,7 +590,7 @@ __device__ __forceinline__ void store_partial(float* dst, const f32x16 (&acc)[BT
 }
 
 // One BT x BT tile of C: tile number `wid` of the batch (see the numbering below).
-template <int BT, bool SPLIT>
+template <int BT, bool SPLIT, bool REMAINDER>
 __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* smem, int wid) {
   constexpr int WT = BT / 2;             // wave tile edge
   constexpr int FR = WT / 32;            // 32x32 MFMA blocks per wave tile edge
@@ -411,7 +639,10 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* sme
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  if (P.nterm > 1) {
+  if constexpr (REMAINDER) {
+    if (P.kind == 0) tile_loop<BT, 0, false>(P, smem, m0, n0, klo, nk, acc);
+    else remainder_loop<BT>(P, smem, m0, n0, klo, nk, acc);
+  } else if (P.nterm > 1) {
     if (P.kind == 0) tile_loop<BT, 0, true>(P, smem, m0, n0, klo, nk, acc);
     else if (P.kind == 1) tile_loop<BT, 1, true>(P, smem, m0, n0, klo, nk, acc);
     else tile_loop<BT, 2, true>(P, smem, m0, n0, klo, nk, acc);
@@ -483,16 +714,17 @@ __device__ __forceinline__ void diagonal_block(const GemmProblem& P, int block) 
 // CAPPED = false: one workgroup per tile.  CAPPED = true: a workgroup takes tiles blockIdx.x, blockIdx.x + gridDim.x,
 // ...: the caller caps the grid to leave compute units to a kernel running beside this one.  The grid is a multiple
 // of 8 then, so a workgroup's tiles all belong to its own XCD's share.
-template <int BT, bool CAPPED, bool SPLIT = false>
+// REMAINDER: a batch of kinds 3 and 0 (a kernel of its own: in one with the other loops theirs lost 5 %).
+template <int BT, bool CAPPED, bool SPLIT = false, bool REMAINDER = false>
 __global__ __launch_bounds__(256, BT == 128 ? 2 : 1) void gemm_nt_kernel(GemmBatch b) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if (!CAPPED) {
     if (SPLIT && (int)blockIdx.x < b.diag_wgs) { if (threadIdx.x < 64) diagonal_block(b.p[1], blockIdx.x); }
-    else gemm_tile<BT, SPLIT>(b, smem, blockIdx.x - (SPLIT ? b.diag_wgs : 0));
+    else gemm_tile<BT, SPLIT, REMAINDER>(b, smem, blockIdx.x - (SPLIT ? b.diag_wgs : 0));
   } else {
     const int total = b.ntiles[0] + b.ntiles[1];
     for (int wid = blockIdx.x; wid < total; wid += gridDim.x) {
-      gemm_tile<BT, false>(b, smem, wid);
+      gemm_tile<BT, false, false>(b, smem, wid);
       __syncthreads();                   // the last fragment reads of this tile before the next tile's loads land in LDS
     }
   }
@@ -537,15 +769,18 @@ __global__ __launch_bounds__(256) void add_parts_kernel(GemmBatch b) {
       if (row0 + 8 * v + q < P.M && col < P.N && !(pi && b.diag_wgs && row0 + 8 * v + q == col)) P.C[(int64_t)(row0 + 8 * v + q) * P.ldc + col] = c[v][q] + sum[v][q];
 }
 
-static LdsLimitOnce g_lds256, g_lds128, g_lds256c, g_lds128c, g_lds128s;
+static LdsLimitOnce g_lds256, g_lds128, g_lds256c, g_lds128c, g_lds128s, g_lds256r, g_lds128r;
 hipError_t launch_gemm(const GemmBatch& b, hipStream_t s) {
   GemmBatch bb = b;
   int total = 0, part_tiles = 0;
+  const bool remainder = b.p[0].kind == 3;
   for (int i = 0; i < 2; ++i) {
     const GemmProblem& q = bb.p[i];
     if (bb.p[i].split < 1) bb.p[i].split = 1;
     bb.ntiles[i] = i >= bb.nprob ? 0 : q.split * (q.tile_mode == 2 ? q.tiles_m * (q.tiles_m + 1) / 2 : q.tiles_m * q.tiles_n);
     if (q.split > 1 && (bb.tile != 128 || q.k_mode || q.store_mode || q.deal || !q.partial)) return hipErrorInvalidValue;
+    if (i < bb.nprob && q.kind == 3 && (q.nterm != 1 || q.K > kMaxRemainderK)) return hipErrorInvalidValue;
+    if (i < bb.nprob && remainder && (q.split > 1 || b.max_wgs > 0 || (q.kind != 3 && (q.kind != 0 || q.nterm != 1)))) return hipErrorInvalidValue;
     total += bb.ntiles[i];
     if (q.split > 1) part_tiles += bb.ntiles[i] / q.split;
   }
@@ -557,8 +792,13 @@ hipError_t launch_gemm(const GemmBatch& b, hipStream_t s) {
   if (e == hipSuccess) e = g_lds256c.ensure(reinterpret_cast<const void*>(&gemm_nt_kernel<256, true>), kLds256);
   if (e == hipSuccess) e = g_lds128c.ensure(reinterpret_cast<const void*>(&gemm_nt_kernel<128, true>), kLds128);
   if (e == hipSuccess) e = g_lds128s.ensure(reinterpret_cast<const void*>(&gemm_nt_kernel<128, false, true>), kLds128);
+  if (e == hipSuccess) e = g_lds256r.ensure(reinterpret_cast<const void*>(&gemm_nt_kernel<256, false, false, true>), kLds256);
+  if (e == hipSuccess) e = g_lds128r.ensure(reinterpret_cast<const void*>(&gemm_nt_kernel<128, false, false, true>), kLds128);
   if (e != hipSuccess) return e;
-  if (part_tiles) {
+  if (remainder) {
+    if (b.tile == 256) hipLaunchKernelGGL((gemm_nt_kernel<256, false, false, true>), dim3(total), dim3(256), kLds256, s, bb);
+    else hipLaunchKernelGGL((gemm_nt_kernel<128, false, false, true>), dim3(total), dim3(256), kLds128, s, bb);
+  } else if (part_tiles) {
     hipLaunchKernelGGL((gemm_nt_kernel<128, false, true>), dim3(bb.diag_wgs + total), dim3(256), kLds128, s, bb);
     hipLaunchKernelGGL(add_parts_kernel, dim3(4 * part_tiles), dim3(256), 0, s, bb);
   } else if (b.max_wgs > 0 && b.max_wgs < total) {

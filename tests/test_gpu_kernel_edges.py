@@ -431,3 +431,40 @@ def test_super_block_kernel_finds_its_operands_in_the_caches():
             times.append(1e3 * ms / launches)
         us[n] = min(times)
     assert us[8192] <= 1.4 * us[1024], us
+
+
+@pytest.mark.parametrize("n,tokens", [(1928, 1), (1928, 2080), (2048, 96), (2496, 97), (3848, 64), (4104, 500)])
+@pytest.mark.parametrize("kind", ["near", "far", "all", "rows"])
+def test_sparse_remainder_of_the_difference(n, tokens, kind):
+    """dXXT from remainders that few, some, all or the odd rows' entries have: the blocks of the sparse operand are of either form,
+    alone and side by side.  (n = 1928: the fewest columns that take it; 3848: 256-tiles with a ragged edge.)"""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + tokens)
+    X = torch.randn((tokens, n), device="cuda", generator=g)
+    e = torch.randn((tokens, n), device="cuda", generator=g)
+    if kind in ("all", "rows"):            # |X| far below |dX|: hardly an entry of dX fits 8 bits
+        small = torch.arange(n, device="cuda") % 2 if kind == "rows" else torch.ones(n, device="cuda")
+        X, Xt = torch.where(small > 0, X * 2.0 ** -7, X).to(torch.bfloat16), e.to(torch.bfloat16)
+    else:
+        X, Xt = X.to(torch.bfloat16), (X + {"near": 0.05, "far": 0.2}[kind] * e).to(torch.bfloat16)
+    H = torch.zeros((n, n), device="cuda")
+    A, Au = torch.zeros_like(H), torch.zeros_like(H)
+    ws = B.workspace(B.gptaq_accumulate_workspace_bytes(tokens, n))
+    ws.fill_(0xff)                         # (what the call does not write is not read as numbers)
+    B.gptaq_accumulate(X, Xt, H, A, ws)
+    B.gptaq_accumulate_upper(X, Xt, torch.zeros_like(H), Au, ws)
+    ref = (Xt.double() - X.double()).T @ X.double()
+    assert torch.equal(A.triu(), Au.triu())
+    # products are exact in fp32; the sum of a chain of tokens / 16 steps, three a k-tile, errs by about 2^-24 sqrt(steps) of itself
+    # (the remainders themselves are 5e-4 of dXXT and more)
+    bound = 2.0 ** -24 * max(4.0, (tokens / 8) ** 0.5)
+    err = float((A.double() - ref).norm() / ref.norm())
+    assert err <= bound, (err, bound)
+
+
+def test_sparse_remainder_where_nothing_differs():
+    X = torch.randn((300, 2056), device="cuda").to(torch.bfloat16)
+    H = torch.zeros((2056, 2056), device="cuda")
+    A = torch.zeros_like(H)
+    B.gptaq_accumulate(X, X.clone(), H, A, B.workspace(B.gptaq_accumulate_workspace_bytes(300, 2056)))
+    assert not bool(A.any()) and bool(H.any())
