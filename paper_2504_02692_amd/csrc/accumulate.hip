@@ -175,6 +175,16 @@ __global__ void invert_permutation_kernel(const int32_t* perm, int n, int32_t* i
 // Error of dXXT against 64 bits as before: 2.96e-7 / 2.91e-7 at 4104 columns and 6144 tokens.
 static bool sparse_remainder(int64_t n) { const int64_t t = (n + 127) / 128; return t * (t + 1) > 256; }
 
+// How many of H's last 256-tiles are taken as quarters: those past one tile for each of the 256 CUs, if they are few.  A tile of dXXT
+// takes 1.45 times as long as one of H, so most CUs are idle while a second tile of H runs on a few of them.  A quarter fetches twice
+// the bytes of its part of a tile: with many (56 at 4352 columns) the launch takes longer.  Measured, whole tiles / so, upper form, us: 3848
+// columns and 32768 tokens 1550 / 1487, 4096 1493 / 1440, 4096 and 2048 tokens 120 / 110; in the last of several rounds (6144 to 11008
+// columns) no difference.
+static int quartered_tiles(int64_t tiles, int64_t h, int64_t tokens) {
+  const int64_t more = tiles - 256;
+  return tokens >= 1024 && more > 0 && more <= 32 && more <= h ? (int)round_up(more, 2) : 0;
+}
+
 static int64_t padded_n(int64_t n) { return round_up(n, gemm_tile_for(n, n)); }
 
 // In how many parts of their tokens the sums of a pass are taken, and what the parts' sums need beside the operands.
@@ -243,6 +253,10 @@ static hipError_t launch_products(const uint16_t* oX, const uint16_t* oHi, const
   h = a;
   h.C = H; h.kind = 0; h.tile_mode = 2;
   h.term[0] = {{oX, oX}, {oX, oX}, 32, 32, np * 32, np * 32};
+  if (a.kind == 3 && tile == 256) {
+    const int64_t t = a.tiles_m, upper = t * (t + 1) / 2;
+    h.quartered = quartered_tiles((dxxt_upper ? upper : t * t) + upper, upper, cp);
+  }
   const int split = split_for(n, cp);
   if (split > 1 && operand_bytes + partial_bytes(n, split) <= ws_bytes) {      // (a smaller workspace: sums in one part)
     a.split = split;

@@ -62,6 +62,7 @@ struct GemmProblem {
                          // length); 1: dealt four tiles at a time (tile lengths that vary along the list: k_mode 1, 2)
   int32_t split;         // > 1 (128-tiles, k_mode 0, store_mode 0): K in so many parts, each summed by workgroups of its own into
   float* partial;        // `partial` (tiles * split * 128 * 128 floats), and added to C by a second kernel; 0 counts as 1
+  int32_t quartered;     // (256-tiles of kind 0 in a batch of kind 3, second problem) so many of its last tiles are taken as four of 128 x 128
   GemmTerm term[2];
 };
 

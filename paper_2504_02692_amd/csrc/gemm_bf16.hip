@@ -603,6 +603,29 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* sme
   int ntile = b.ntiles[0];
   if (id >= ntile) { pi = 1; id -= ntile; ntile = b.ntiles[1]; }
   const GemmProblem& P = b.p[pi];
+  // Quarters of the last tiles of the second problem, behind its whole ones: a CU that has nothing more to do takes one, and the launch
+  // ends sooner.  An element's products are added in the same order as in a whole tile.
+  if constexpr (REMAINDER && BT == 256) {
+    const int whole = ntile - 4 * P.quartered;
+    if (pi == 1) {
+      if (id >= whole) {
+        int q = id - whole, tm, tn;
+        q = (q & 7) * (P.quartered >> 1) + (q >> 3);                                  // (an even number: neighbours on one XCD)
+        tile_position(P, whole + (q >> 2), tm, tn);
+        const int m0 = uniform(tm * 256 + (q & 2) * 64), n0 = uniform(tn * 256 + (q & 1) * 128);
+        if (m0 > n0) return;                                                          // (below the diagonal)
+        f32x16 acc[2][2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[i >> 1][i & 1][v] = 0.f;
+        tile_loop<128, 0, false>(P, smem, m0, n0, 0, P.K / kGemmBK, acc);
+        store_tile<128>(P.C, uniform(P.ldc), uniform(P.M), uniform(P.N), uniform(P.store_mode), m0, n0, acc);
+        return;
+      }
+      ntile = whole;
+    }
+  }
   if (!P.deal) {
     const int per = ntile >> 3, rem = ntile & 7, xcd = id & 7, loc = id >> 3;
     id = xcd < rem ? xcd * (per + 1) + loc : rem * (per + 1) + (xcd - rem) * per + loc;
@@ -777,7 +800,8 @@ hipError_t launch_gemm(const GemmBatch& b, hipStream_t s) {
   for (int i = 0; i < 2; ++i) {
     const GemmProblem& q = bb.p[i];
     if (bb.p[i].split < 1) bb.p[i].split = 1;
-    bb.ntiles[i] = i >= bb.nprob ? 0 : q.split * (q.tile_mode == 2 ? q.tiles_m * (q.tiles_m + 1) / 2 : q.tiles_m * q.tiles_n);
+    if (i < bb.nprob && q.quartered && (!remainder || bb.tile != 256 || i != 1 || q.tile_mode != 2 || q.store_mode || q.deal || q.quartered % 2)) return hipErrorInvalidValue;
+    bb.ntiles[i] = i >= bb.nprob ? 0 : 3 * q.quartered + q.split * (q.tile_mode == 2 ? q.tiles_m * (q.tiles_m + 1) / 2 : q.tiles_m * q.tiles_n);
     if (q.split > 1 && (bb.tile != 128 || q.k_mode || q.store_mode || q.deal || !q.partial)) return hipErrorInvalidValue;
     if (i < bb.nprob && q.kind == 3 && (q.nterm != 1 || q.K > kMaxRemainderK)) return hipErrorInvalidValue;
     if (i < bb.nprob && remainder && (q.split > 1 || b.max_wgs > 0 || (q.kind != 3 && (q.kind != 0 || q.nterm != 1)))) return hipErrorInvalidValue;

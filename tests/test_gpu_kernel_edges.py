@@ -468,3 +468,18 @@ def test_sparse_remainder_where_nothing_differs():
     A = torch.zeros_like(H)
     B.gptaq_accumulate(X, X.clone(), H, A, B.workspace(B.gptaq_accumulate_workspace_bytes(300, 2056)))
     assert not bool(A.any()) and bool(H.any())
+
+
+@pytest.mark.parametrize("n,tokens", [(3848, 1024), (4096, 2100)])
+def test_quarters_of_the_last_tiles_have_the_bits_of_whole_ones(n, tokens):
+    """The upper form of 16 tile rows has 16 tiles more than the chip has CUs and takes them as quarters; the full form has them whole."""
+    X, Xt = synth.make_activations_device(tokens, n, 5, "x", "cuda")
+    ws = B.workspace(B.gptaq_accumulate_workspace_bytes(tokens, n))
+    Hf, Hu = torch.ones((n, n), device="cuda"), torch.ones((n, n), device="cuda")
+    Af, Au = torch.ones_like(Hf), torch.ones_like(Hf)
+    B.gptaq_accumulate(X, Xt, Hf, Af, ws)
+    B.gptaq_accumulate_upper(X, Xt, Hu, Au, ws)
+    assert torch.equal(Hf.triu(), Hu.triu()) and torch.equal(Af.triu(), Au.triu())
+    ref = X.double().T @ X.double() + 1.0
+    err = float((Hu.double() - ref).triu().norm() / ref.triu().norm())
+    assert err <= 2.0 ** -24 * (tokens / 8) ** 0.5, err        # (a chain of tokens / 16 steps)
