@@ -4,7 +4,8 @@
 // forms dX = X~ - X in fp32, splits it exactly into two bf16 terms (hi = rne(dX),
 // lo = dX - hi) and writes X, hi, lo transposed in k-tile-major order: [token tile of 32]
 // [neuron][32 tokens], the operand layout the MFMA GEMM wants (tokens are its K dimension and
-// a block of neurons x one token tile is a single contiguous run).
+// a block of neurons x one token tile is a single contiguous run).  From 1921 columns on lo is written as a sparse operand
+// (sparse_remainder, GemmTerm).
 // (2) One launch of the MFMA GEMM computes dXXT += hi X^T + lo X^T on all tiles and
 // H += X X^T on the tiles that touch the upper triangle.
 #include "common.h"
