@@ -15,7 +15,7 @@ namespace gptaq {
 
 // Workspace of gptaq_accumulate_noalloc: one copy per GPU, owned by the code object, never freed.
 constexpr size_t kScratchBytes = (size_t)32 << 20;
-constexpr int64_t kScratchMaxN = 16384;                   // 6 * 16384 * 320 tokens still fit
+constexpr int64_t kScratchMaxN = 16384;                   // the operands of 320 tokens of 16384 entries still fit, positions among them
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 __device__ __forceinline__ float bf16_to_f32(uint32_t h) { return __uint_as_float(h << 16); }
@@ -31,12 +31,20 @@ template <bool SPARSE>
 __global__ __launch_bounds__(256) void split_transpose_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ Xt, int64_t ldx,
     int tokens, int n, uint16_t* __restrict__ oX, uint16_t* __restrict__ oHi,
-    uint16_t* __restrict__ oLo, uint16_t* __restrict__ oLo2, int64_t ldo /* padded rows */, int tile0 /* first 64-token tile of the output */,
+    uint16_t* __restrict__ oLo, uint16_t* __restrict__ oLo2, uint16_t* __restrict__ oPos, uint8_t* __restrict__ oDense, int64_t ldo /* padded rows */, int tile0 /* first 64-token tile of the output */,
     const int32_t* __restrict__ row_of /* NULL, or operand row of input column j (a permutation of 0 .. n-1) */) {
   constexpr int LS = 72;                                  // padded LDS row, 144 bytes
-  __shared__ __attribute__((aligned(16))) uint16_t sx[64 * LS], sh[64 * LS], sl[64 * LS];
+  __shared__ __attribute__((aligned(16))) uint16_t sx[64 * LS], sh[64 * LS], sl[64 * LS], spos[SPARSE ? 64 * 4 : 4];
   const int n0 = blockIdx.x * 64, t0 = blockIdx.y * 64;
   const int tid = threadIdx.x, r = tid >> 3, c = tid & 7;
+  auto row_to = [&](int i) {                                // the operand row of input column n0 + i
+    int64_t row = n0 + i;                                   // (padding rows stay where they are)
+    if (row_of && row < n) {
+      const int32_t rr = row_of[row];
+      if (rr >= 0 && rr < n) row = rr;                      // (an entry out of range cannot send a write out of bounds)
+    }
+    return row;
+  };
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
     const int t = t0 + r + 32 * p, col = n0 + c * 8;
@@ -62,30 +70,21 @@ __global__ __launch_bounds__(256) void split_transpose_kernel(
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
     const int nl = r + 32 * p;
-    int64_t row = n0 + nl;                                  // (padding rows stay where they are)
-    if (row_of && row < n) {
-      const int32_t rr = row_of[row];
-      if (rr >= 0 && rr < n) row = rr;                      // (an entry out of range cannot send a write out of bounds)
-    }
-    const int64_t g = (((int64_t)(blockIdx.y + tile0) * 2 + (c >> 2)) * ldo + row) * 32 + (c & 3) * 8;   // k-tile-major
+    const int64_t g = (((int64_t)(blockIdx.y + tile0) * 2 + (c >> 2)) * ldo + row_to(nl)) * 32 + (c & 3) * 8;   // k-tile-major
     *reinterpret_cast<u32x4*>(oX + g) = *reinterpret_cast<const u32x4*>(sx + nl * LS + c * 8);
     *reinterpret_cast<u32x4*>(oHi + g) = *reinterpret_cast<const u32x4*>(sh + nl * LS + c * 8);
     if (!SPARSE) *reinterpret_cast<u32x4*>(oLo + g) = *reinterpret_cast<const u32x4*>(sl + nl * LS + c * 8);
   }
   if (!SPARSE) return;
   // lo, in the form that GemmTerm describes: a wavefront has a 32 x 32 block and a lane the 16 tokens of its row that it has there
-  const int lane = tid & 63, nl = (tid >> 7) * 32 + (lane & 31), k = tid >> 6 & 1;
-  int64_t row = n0 + nl;
-  if (row_of && row < n) {
-    const int32_t rr = row_of[row];
-    if (rr >= 0 && rr < n) row = rr;
-  }
+  const int lane = tid & 63, nl = (tid >> 7) * 32 + (lane & 31), k = tid >> 6 & 1, half = lane >> 5;
+  const int64_t row = row_to(nl);
   uint64_t q[4];
   int nz[4];
   bool more = row_of != nullptr;                            // (rows that go elsewhere: their blocks are not known here, and are dense)
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    const u32x4 x = *reinterpret_cast<const u32x4*>(sl + nl * LS + k * 32 + (lane >> 5) * 16 + h * 8);
+    const u32x4 x = *reinterpret_cast<const u32x4*>(sl + nl * LS + k * 32 + half * 16 + h * 8);
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
       const uint32_t a = x[2 * e], b = x[2 * e + 1];
@@ -103,20 +102,16 @@ __global__ __launch_bounds__(256) void split_transpose_kernel(
     // and (0,1) where two do not
     const uint32_t at = (uint32_t)(0x444E4DCE498E4DC4ull >> (4 * nz[e]) & 15);
     v[e] = (uint32_t)(q[e] >> (16 * (at & 3)) & 0xffff) | (uint32_t)(q[e] >> (16 * (at >> 2))) << 16;
-    v2[e] = __builtin_popcount(nz[e]) > 2 ? (uint32_t)(q[e] >> 32) : kPositionsMark | at << (4 * e);
+    v2[e] = __builtin_popcount(nz[e]) > 2 ? (uint32_t)(q[e] >> 32) : 0u;
     places |= at << (4 * e);
   }
-  const int64_t kt = (int64_t)(blockIdx.y + tile0) * 2 + k;
-  const int to = (int)(row & 31) + (lane & 32), blk = (int)(row & 127) >> 5;
-  *reinterpret_cast<u32x4*>(oLo + (kt * ldo + (row & ~31)) * 16 + to * 8) = u32x4{v[0], v[1], v[2], v[3]};
-  unsigned char* second = reinterpret_cast<unsigned char*>(oLo2 + (kt * ldo + (row & ~127)) * 16);
-  if (dense) {
-    unsigned char* dst = to == 0 ? second + 16 * blk : to < 9 ? second + 64 + 128 * blk + 16 * (to - 1) : second + 576 + 880 * blk + 16 * (to - 9);
-    *reinterpret_cast<u32x4*>(dst) = u32x4{v2[0], v2[1], v2[2], v2[3]};
-  } else {
-    *reinterpret_cast<uint16_t*>(second + 64 + 128 * blk + 2 * to) = (uint16_t)places;
-    if (to == 0) *reinterpret_cast<u32x4*>(second + 16 * blk) = u32x4{kSparseMark, kSparseMark, kSparseMark, kSparseMark};
-  }
+  const int64_t kt = (int64_t)(blockIdx.y + tile0) * 2 + k, to = kt * ldo + row;
+  spos[nl * 4 + half * 2 + k] = (uint16_t)places;
+  *reinterpret_cast<u32x4*>(oLo + to * 16 + half * 8) = u32x4{v[0], v[1], v[2], v[3]};
+  if (dense) *reinterpret_cast<u32x4*>(oLo2 + to * 16 + half * 8) = u32x4{v2[0], v2[1], v2[2], v2[3]};
+  if (lane == 0) oDense[(kt * ldo + n0 + nl) >> 5] = dense;
+  __syncthreads();
+  if (tid < 64) *reinterpret_cast<uint64_t*>(oPos + ((int64_t)(blockIdx.y + tile0) * ldo + row_to(tid)) * 4) = *reinterpret_cast<const uint64_t*>(spos + tid * 4);
 }
 
 __global__ void symmetrize_kernel(float* H, int n, int64_t ldh) {
@@ -165,15 +160,15 @@ __global__ void invert_permutation_kernel(const int32_t* perm, int n, int32_t* i
 }
 
 // Whether the remainder's products are taken as sparse ones (kind 3): from 1921 columns on, where the upper form has more tiles than the
-// chip has CUs.  dX does not fit a bf16 only where it is larger than the smaller of X and X~ (2.7 % of the entries where the two differ
-// by 5 % of a channel's deviation), so most of lo is zero.  Fewer matrix instructions and operand bytes (41 KB instead of 48 for
-// 32 tokens of a 256-tile, which is what bounds these launches).  By n alone: a staged call writes its operands before the number of
-// tokens is known, and the sums do not depend on the form of the call.  Measured, us per call, upper form, as
-// dense operands / so: 2048 columns and 32768 tokens 588 / 568, 2736 872 / 828 (full form 1275 / 1115), 2736 and 4096 tokens 115 / 104,
-// 3072 and 16384 588 / 490, 4096 and 2048 135 / 117, 4096 and 32768 1556 / 1453, 11008 and 32768 9330 / 8790.  With fewer columns a
-// workgroup has its CU to itself and the branches of the loop show: 512 and 4096 tokens 54 / 58, 1536 and 4096 58 / 66.  Where every
-// block is dense (X~ 20 % off X or more, or the call permutes) the second sparse product takes the time back: 11008 9370 / 9860.
-// Error of dXXT against 64 bits as before: 2.96e-7 / 2.91e-7 at 4104 columns and 6144 tokens.
+// chip has CUs.  dX does not fit a bf16 only where it is larger than the smaller of X and X~, so most of lo is zero: of its 32 x 32
+// blocks 2 % are dense where X and X~ differ by 5 % of a channel's deviation, 14 % at 10 %, 38 % at 15, 69 % at 20, 96 % at 30.  Fewer matrix
+// instructions and operand bytes (42 KB instead of 48 for 32 tokens of a 256-tile, which is what bounds these launches).  By n alone: a staged
+// call writes its operands before the number of tokens is known, and the sums do not depend on the form of the call.  Measured, us
+// per call, as dense operands / so, at differences of 5, 10, 20 and 50 %: 2048 columns and 32768 tokens 586 / 558, 585, 602, 608; 2736 full 1270 / 1093,
+// 1112, 1286, 1314; 3072 and 16384 590 / 483, 494, 534, 544; 4096 and 2048 138 / 106, 108, 117, 120; 4096 and 32768 1585 / 1365, 1413, 1578, 1616; 6144
+// and 16384 1590 / 1447, 1481, 1597, 1637; 11008 and 32768 9690 / 8820, 9010, 9730, 10050.  With fewer columns a workgroup has its CU to itself
+// and the loop's branches show: 512 and 4096 tokens 54 / 58, 1536 and 4096 58 / 66.  Error of dXXT against 64 bits 2.91e-7 (dense operands
+// 2.96e-7) at 4104 columns and 6144 tokens.
 static bool sparse_remainder(int64_t n) { const int64_t t = (n + 127) / 128; return t * (t + 1) > 256; }
 
 // How many of H's last 256-tiles are taken as quarters: those past one tile for each of the 256 CUs, if they are few.  A tile of dXXT
@@ -188,6 +183,29 @@ static int quartered_tiles(int64_t tiles, int64_t h, int64_t tokens) {
 
 static int64_t padded_n(int64_t n) { return round_up(n, gemm_tile_for(n, n)); }
 
+// The operands of `tokens` tokens (a multiple of 64) in a workspace: X, hi and lo of 2 bytes an entry; lo in the sparse form in two halves,
+// and behind them the positions (4 bytes per 32 entries) and the bytes that say which 32 x 32 blocks are dense.
+struct Operands {
+  uint16_t *X, *hi, *lo, *lo2, *positions;
+  uint8_t* dense;
+  size_t bytes;
+  bool sparse;
+};
+static Operands operands_at(void* ws, int64_t np, int64_t tokens, bool sparse) {
+  Operands o;
+  const int64_t all = np * tokens;
+  o.X = (uint16_t*)ws;
+  o.hi = o.X + all;
+  o.lo = o.hi + all;
+  o.lo2 = o.lo + all / 2;
+  o.positions = o.lo + all;
+  o.dense = (uint8_t*)(o.positions + all / 16);
+  o.bytes = (size_t)(6 * all) + (sparse ? (size_t)(all / 8 + all / 1024) : 0);
+  o.sparse = sparse;
+  return o;
+}
+static size_t operand_bytes(int64_t np, int64_t tokens, bool sparse) { return operands_at(nullptr, np, tokens, sparse).bytes; }
+
 // In how many parts of their tokens the sums of a pass are taken, and what the parts' sums need beside the operands.
 // With few columns the tiles of H and dXXT leave most of the chip idle (n = 1024: 72 or 100 of 512 places for 128-tiles).  dXXT's tiles,
 // of two products, are split in `split` parts and H's, of one, in half as many, so that all workgroups take the same time.  The number is
@@ -201,6 +219,7 @@ static int64_t padded_n(int64_t n) { return round_up(n, gemm_tile_for(n, n)); }
 // workgroups: 2048 594 / 511 (687 / 699), 2736 888 / 861 (1241 / 1277), 3072 and 8192 tokens 257 / 277 (352 / 384)).  Errors against 64 bits
 // fall with the length of the sums: dXXT 8.7e-7 to 2.4e-7 at n = 1024.
 static int split_for(int64_t n, int64_t tokens) {
+  if (sparse_remainder(n)) return 1;             // (remainder_loop takes all of K; the estimate promises less than 1.5 from there on)
   if (gemm_tile_for(n, n) != 128) return 1;      // (256-tiles: they fill the chip, and the power limit takes what a fuller last round gives)
   if (tokens < 8192) return 1;                   // (the workspace of a call with few samples stays that of its operands)
   const int64_t t = (n + 127) / 128, upper = t * (t + 1) / 2;
@@ -231,16 +250,26 @@ using namespace gptaq;
 extern "C" size_t gptaq_accumulate_workspace_bytes(int64_t tokens, int64_t n) {
   if (tokens <= 0 || n <= 0) return 0;
   const int64_t c = round_up(tokens < 32768 ? tokens : 32768, 64);
-  return (size_t)(3 * padded_n(n) * c * 2) + partial_bytes(n, split_for(n, c));
+  return operand_bytes(padded_n(n), c, sparse_remainder(n)) + partial_bytes(n, split_for(n, c));
+}
+
+// The operands of c tokens, from 64-token tile `tile0` of o on.
+static int launch_split(const Operands& o, const uint16_t* X, const uint16_t* Xtilde, int64_t ldx, int64_t c, int64_t n, int64_t np, int64_t tile0,
+                        const int32_t* row_of, hipStream_t s) {
+  ProfScope ps(kProfAccumSplit, s);
+  hipLaunchKernelGGL(o.sparse ? split_transpose_kernel<true> : split_transpose_kernel<false>,
+                     dim3((unsigned)(np / 64), (unsigned)((c + 63) / 64)), dim3(256), 0, s, X, Xtilde, ldx, (int)c, (int)n, o.X, o.hi, o.lo, o.lo2,
+                     o.positions, o.dense, np, (int)tile0, row_of);
+  GPTAQ_LAUNCH_CHECK();
+  return GPTAQ_OK;
 }
 
 // H += X X^T (upper tiles) and dXXT += (hi + lo) X^T over cp tokens of split operands, as one launch.
 // dxxt_upper: only the tiles of dXXT that touch its upper triangle.  Eq. 17 masks dXXT L to its strictly upper part and
 // L is lower triangular, so entry (i, k) of dXXT reaches P only through sums over k >= j > i: in the natural column
 // order nothing on or below the diagonal is ever read, and two fifths of the products of the launch can be left out.
-static hipError_t launch_products(const uint16_t* oX, const uint16_t* oHi, const uint16_t* oLo, const uint16_t* oLo2, int64_t np, int64_t cp,
-                                  int64_t n, float* H, float* dXXT, int64_t ldh, bool dxxt_upper, void* ws, size_t ws_bytes, size_t operand_bytes,
-                                  hipStream_t s) {
+static hipError_t launch_products(const Operands& o, int64_t np, int64_t cp, int64_t n, float* H, float* dXXT, int64_t ldh, bool dxxt_upper,
+                                  void* ws, size_t ws_bytes, hipStream_t s) {
   const int tile = gemm_tile_for(n, n);
   GemmBatch b{};
   b.nprob = 2;
@@ -248,20 +277,22 @@ static hipError_t launch_products(const uint16_t* oX, const uint16_t* oHi, const
   GemmProblem& a = b.p[0];
   a.C = dXXT; a.ldc = ldh; a.M = (int)n; a.N = (int)n; a.K = (int)cp;
   a.tiles_m = a.tiles_n = (int)(np / tile);
-  a.kind = sparse_remainder(n) ? 3 : 1; a.nterm = 1; a.tile_mode = dxxt_upper ? 2 : 0; a.k_mode = 0; a.store_mode = 0;
-  a.term[0] = {{oHi, oLo}, {oX, oLo2}, 32, 32, np * 32, np * 32};
+  a.kind = o.sparse ? 3 : 1; a.nterm = 1; a.tile_mode = dxxt_upper ? 2 : 0; a.k_mode = 0; a.store_mode = 0;
+  a.term[0] = {{o.hi, o.lo}, {o.X, o.lo2}, 32, 32, np * 32, np * 32};
+  a.positions = o.positions;
+  a.dense = o.dense;
   GemmProblem& h = b.p[1];
   h = a;
   h.C = H; h.kind = 0; h.tile_mode = 2;
-  h.term[0] = {{oX, oX}, {oX, oX}, 32, 32, np * 32, np * 32};
+  h.term[0] = {{o.X, o.X}, {o.X, o.X}, 32, 32, np * 32, np * 32};
   if (a.kind == 3 && tile == 256) {
     const int64_t t = a.tiles_m, upper = t * (t + 1) / 2;
     h.quartered = quartered_tiles((dxxt_upper ? upper : t * t) + upper, upper, cp);
   }
   const int split = split_for(n, cp);
-  if (split > 1 && operand_bytes + partial_bytes(n, split) <= ws_bytes) {      // (a smaller workspace: sums in one part)
+  if (split > 1 && o.bytes + partial_bytes(n, split) <= ws_bytes) {      // (a smaller workspace: sums in one part)
     a.split = split;
-    a.partial = (float*)((unsigned char*)ws + operand_bytes);
+    a.partial = (float*)((unsigned char*)ws + o.bytes);
     h.split = split / 2;
     h.partial = a.partial + (int64_t)a.tiles_m * a.tiles_m * split * (128 * 128);
   }
@@ -289,23 +320,28 @@ static int accumulate_impl(const uint16_t* X, const uint16_t* Xtilde, int64_t to
   if (tokens == 0) return GPTAQ_OK;
   hipStream_t s = (hipStream_t)stream;
   const int64_t np = padded_n(n);
-  int64_t cmax = (int64_t)(ws_bytes / (size_t)(6 * np)) / 64 * 64;
+  // tokens a pass: at most 32768, which keeps one fp32 running sum short (accuracy), and K in int32
+  auto pass_for = [&](bool sparse) {
+    const int64_t c = (int64_t)(ws_bytes / operand_bytes(np, 64, sparse)) * 64;
+    return c < 32768 ? c : (int64_t)32768;
+  };
+  int64_t cmax = pass_for(false);
   if (cmax < 64) return GPTAQ_EWORKSPACE;
-  if (cmax > 32768) cmax = 32768;    // keeps one fp32 running sum short (accuracy), and K in int32
+  bool sparse = sparse_remainder(n);
+  if (sparse) {
+    // Positions take an eighth of a byte an entry.  In a workspace without room for them lo is dense if they would cost more than a tenth of the
+    // passes, each of which reads and writes H and dXXT: two sparse passes take as long as a dense one of 2048 tokens (4096 columns: 134
+    // and 139 us), of fewer tokens longer.
+    const int64_t c = pass_for(true);
+    sparse = c > 0 && 10 * ((tokens + c - 1) / c) <= 11 * ((tokens + cmax - 1) / cmax);
+    if (sparse) cmax = c;
+  }
   for (int64_t t0 = 0; t0 < tokens; t0 += cmax) {
     const int64_t c = tokens - t0 < cmax ? tokens - t0 : cmax;
     const int64_t cp = round_up(c, 64);
-    uint16_t* oX = (uint16_t*)ws;
-    uint16_t* oHi = oX + np * cp;
-    uint16_t *oLo = oHi + np * cp, *oLo2 = oLo + np * cp / 2;
-    {
-      ProfScope ps(kProfAccumSplit, s);
-      hipLaunchKernelGGL(sparse_remainder(n) ? split_transpose_kernel<true> : split_transpose_kernel<false>, dim3((unsigned)(np / 64), (unsigned)(cp / 64)),
-                         dim3(256), 0, s, X + t0 * ldx, Xtilde + t0 * ldx, ldx, (int)c, (int)n,
-                         oX, oHi, oLo, oLo2, np, 0, row_of);
-    }
-    GPTAQ_LAUNCH_CHECK();
-    hipError_t e = launch_products(oX, oHi, oLo, oLo2, np, cp, n, H, dXXT, ldh, dxxt_upper, ws, ws_bytes, (size_t)(6 * np * cp), s);
+    const Operands o = operands_at(ws, np, cp, sparse);
+    if (const int rc = launch_split(o, X + t0 * ldx, Xtilde + t0 * ldx, ldx, c, n, np, 0, row_of, s)) return rc;
+    hipError_t e = launch_products(o, np, cp, n, H, dXXT, ldh, dxxt_upper, ws, ws_bytes, s);
     if (e != hipSuccess) { set_last_hip_error(e); return GPTAQ_ELAUNCH; }
   }
   return GPTAQ_OK;
@@ -389,19 +425,14 @@ static int accumulate_staged_impl(const uint16_t* X, const uint16_t* Xtilde, int
     return GPTAQ_EDIM;
   if (tokens > 0 && (((uintptr_t)X | (uintptr_t)Xtilde) & 15)) return GPTAQ_EDIM;
   const int64_t np = padded_n(n);
-  if (((uintptr_t)ws & 255) || ws_bytes < (size_t)(6 * np * CAP)) return GPTAQ_EWORKSPACE;
+  if (((uintptr_t)ws & 255) || ws_bytes < operand_bytes(np, CAP, false)) return GPTAQ_EWORKSPACE;
   hipStream_t s = (hipStream_t)stream;
-  uint16_t *oX = (uint16_t*)ws, *oHi = oX + np * CAP, *oLo = oHi + np * CAP, *oLo2 = oLo + np * CAP / 2;
-  auto products = [&](int64_t cp) { return launch_products(oX, oHi, oLo, oLo2, np, cp, n, H, dXXT, ldh, dxxt_upper, ws, ws_bytes, (size_t)(6 * np * CAP), s); };
+  const Operands o = operands_at(ws, np, CAP, sparse_remainder(n) && ws_bytes >= operand_bytes(np, CAP, true));
+  auto products = [&](int64_t cp) { return launch_products(o, np, cp, n, H, dXXT, ldh, dxxt_upper, ws, ws_bytes, s); };
   int64_t done = 0, pend = *pending;
   while (done < tokens) {
     const int64_t take = tokens - done < CAP - pend ? tokens - done : CAP - pend, cp = round_up(take, 64);
-    {
-      ProfScope ps(kProfAccumSplit, s);
-      hipLaunchKernelGGL(sparse_remainder(n) ? split_transpose_kernel<true> : split_transpose_kernel<false>, dim3((unsigned)(np / 64), (unsigned)(cp / 64)), dim3(256), 0, s,
-                         X + done * ldx, Xtilde + done * ldx, ldx, (int)take, (int)n, oX, oHi, oLo, oLo2, np, (int)(pend / 64), (const int32_t*)nullptr);
-    }
-    GPTAQ_LAUNCH_CHECK();
+    if (const int rc = launch_split(o, X + done * ldx, Xtilde + done * ldx, ldx, take, n, np, pend / 64, nullptr, s)) return rc;
     done += take;
     pend += cp;                                    // (only the chunk that comes with flush may be ragged: it is the last)
     if (pend >= CAP) {

@@ -31,18 +31,15 @@ struct GemmTerm {
   int64_t ktl, ktr;
 };
 
-// Kind 3: L[0] = hi and R[0] = X as above, k-tile-major.  Of lo, the remainder of hi, few entries are not zero, so it is stored by
-// 32 x 32 blocks (rows x tokens of one k-tile) in the form of v_smfmac_f32_32x32x32_bf16: two values of every four tokens, lane l the
-// values of row l % 32 and tokens 16 (l / 32) .. + 15, 16 bytes a lane.  L[1]: those values (lo1), block (k-tile, row / 32) after block.
-// R[1]: as many bytes again, 4 KB for the four blocks of 128 rows: four heads of 16 bytes, four position fields of 128 (16 bits a lane:
-// where among its four tokens each value sits), four tails of 880.  Where no four tokens of a row hold more than two values, a
-// block's head is kSparseMark and its tail is not used.  Else the block is dense: head, position field and tail, one after the other,
-// are 16 bytes a lane (lo2), a pair for every four tokens: where these hold more than two values, lo1 has those of tokens 0 and 1 and
-// the pair those of tokens 2 and 3; where not, the pair is kPositionsMark with the positions of lo1's values at their bits of the 16.
-// (So the order in which a row's products are added does not depend on the other rows of its block.  The marks are NaNs that no
-// remainder is: those that arithmetic makes are quiet.)
-constexpr uint32_t kSparseMark = 0x7f817f81u, kPositionsMark = 0x7f810000u;
-constexpr int kMaxRemainderK = 32768;      // K of a problem of kind 3
+// Kind 3: L[0] = hi and R[0] = X as above, k-tile-major.  Of lo, the remainder of hi, few entries are not zero, so it is stored in the
+// form of v_smfmac_f32_32x32x32_bf16: two values of every four tokens, 32 bytes for a row and k-tile of 32 tokens (the eight values of
+// tokens 0 .. 15, then those of 16 .. 31: the operands of two lanes).  L[1]: those values (lo1).  `positions`: where among its four tokens
+// each value sits, 16 bits an operand, for two k-tiles at a time: 8 bytes a row (tokens 0 .. 15 of the first and of the second k-tile, then
+// 16 .. 31 of each).  A 32 x 32 block (32 rows, one k-tile) in which some four tokens of a row hold more than two values is dense: `dense`
+// has a byte per block, k-tile by k-tile, and R[1] for these blocks as much as L[1] (lo2), the values of tokens 2 and 3 of such fours, of
+// which lo1 has those of tokens 0 and 1, and zeros for the others.  So the order in which a row's products are added does not depend
+// on the other rows of its block.  lo2 of a block that is not dense is not written and is not read as numbers.
+constexpr int kMaxRemainderK = 32768;      // K of a problem of kind 3 (a multiple of 64)
 
 // C (+)= sum_t sum_pairs L R^T.  kind 0: L0 R0.  kind 1: L0 R0 + L1 R0 (two left operands share the
 // right one).  kind 2: L0 R0 + L0 R1 + L1 R0 (hi/lo split of both sides, lo*lo dropped).  kind 3: (hi + lo) X^T (one term; see above).
@@ -63,6 +60,8 @@ struct GemmProblem {
   int32_t split;         // > 1 (128-tiles, k_mode 0, store_mode 0): K in so many parts, each summed by workgroups of its own into
   float* partial;        // `partial` (tiles * split * 128 * 128 floats), and added to C by a second kernel; 0 counts as 1
   int32_t quartered;     // (256-tiles of kind 0 in a batch of kind 3, second problem) so many of its last tiles are taken as four of 128 x 128
+  const uint16_t* positions;   // kind 3 (see above)
+  const uint8_t* dense;
   GemmTerm term[2];
 };
 

@@ -21,6 +21,7 @@
 // the MFMAs of an earlier k-tile, and the barriers carry no memory fence, so that loads stay in
 // flight across them (see wg_barrier).
 #include "common.h"
+#include <utility>
 
 namespace gptaq {
 
@@ -47,8 +48,8 @@ template <int N> __device__ __forceinline__ void wait_vm_and_lds() {
 }
 
 constexpr int kFlagBytes = kMaxRemainderK / kGemmBK;      // kind 3: a byte per k-tile
-constexpr int kLds256 = 3 * 3 * 256 * 64 + kFlagBytes;    // largest ring: kinds 1 and 3, 3 stages x 3 operand tiles (2 x 4 and 4 x 2 are smaller)
-constexpr int kLds128 = 3 * 3 * 128 * 64 + kFlagBytes;
+constexpr int kLds256 = 3 * 3 * 256 * 64 + 4 * 256 * 8 + kFlagBytes;    // kind 3: 3 stages x 3 operand tiles, positions of 4 pairs of k-tiles, flags (2 x 4 and 4 x 2 tiles are smaller)
+constexpr int kLds128 = 3 * 3 * 128 * 64 + 4 * 128 * 8 + kFlagBytes;
 
 template <int BT, int KIND, bool MULTI>
 __device__ __forceinline__ void tile_loop(const GemmProblem& P, unsigned char* smem, int m0, int n0, int klo, int nk,
@@ -220,229 +221,264 @@ __device__ __forceinline__ void tile_loop(const GemmProblem& P, unsigned char* s
 
 // The products of remainder_loop are assembly: v_smfmac's result is its accumulator, and from the builtins the compiler made copies of
 // accumulators, for which there are no registers (1.8 KB of scratch a lane).  It does not look into assembly: an operand must not have
-// been written by one of the two instructions before (a nop stands for them), and what reads the accumulators as registers waits for the
-// last of them (settle); that one product adds to what another has just written is the hardware's to order.
+// been written by a vector instruction less than two wait states before (a nop stands for them where positions are moved; hi comes
+// from LDS), and what reads the accumulators as registers waits for the last product (settle); that one product adds to what another
+// has just written is the hardware's to order.  tests/test_mfma_hazards.py looks at every build.
 __device__ __forceinline__ void dense_product(f32x16& acc, bf16x8 l, bf16x8 x) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(l), "v"(x));
 }
-__device__ __forceinline__ void sparse_product(f32x16& acc, bf16x8 lo, bf16x16 x, int pos) {      // 32 tokens
-  asm volatile("s_nop 1\n\tv_smfmac_f32_32x32x32_bf16 %0, %1, %2, %3" : "+a"(acc) : "v"(lo), "v"(x), "v"(pos));
+constexpr int kPositions23 = 0xEEEE;       // the last two of every four tokens
+// 32 tokens; WHICH: the low or the high 16 bits of pos
+template <int WHICH> __device__ __forceinline__ void sparse_product(f32x16& acc, bf16x8 lo, bf16x16 x, int pos) {
+  if (WHICH) asm volatile("s_nop 1\n\tv_smfmac_f32_32x32x32_bf16 %0, %1, %2, %3 abid:1" : "+a"(acc) : "v"(lo), "v"(x), "v"(pos));
+  else asm volatile("s_nop 1\n\tv_smfmac_f32_32x32x32_bf16 %0, %1, %2, %3" : "+a"(acc) : "v"(lo), "v"(x), "v"(pos));
 }
-// (two, if on != 0: the branch is inside, so that no accumulator has two ways to come from)
-__device__ __forceinline__ void sparse_products_if(int on, f32x16& a0, f32x16& a1, bf16x8 lo, bf16x16 x0, bf16x16 x1, int pos) {
+// lo2's products of a row of blocks, if on != 0 (the branch is inside, so that no accumulator has two ways to come from)
+__device__ __forceinline__ void sparse_products_if(int on, f32x16 (&a)[2], bf16x8 lo, const bf16x16 (&x)[2]) {
   asm volatile("s_cmp_eq_u32 %6, 0\n\ts_cbranch_scc1 .Lnone%=\n\ts_nop 1\n\t"
                "v_smfmac_f32_32x32x32_bf16 %0, %2, %3, %5\n\tv_smfmac_f32_32x32x32_bf16 %1, %2, %4, %5\n.Lnone%=:"
-               : "+a"(a0), "+a"(a1) : "v"(lo), "v"(x0), "v"(x1), "v"(pos), "s"(on) : "scc");
+               : "+a"(a[0]), "+a"(a[1]) : "v"(lo), "v"(x[0]), "v"(x[1]), "v"(kPositions23), "s"(on) : "scc");
+}
+__device__ __forceinline__ void sparse_products_if(int on, f32x16 (&a)[4], bf16x8 lo, const bf16x16 (&x)[4]) {
+  asm volatile("s_cmp_eq_u32 %10, 0\n\ts_cbranch_scc1 .Lnone%=\n\ts_nop 1\n\t"
+               "v_smfmac_f32_32x32x32_bf16 %0, %4, %5, %9\n\tv_smfmac_f32_32x32x32_bf16 %1, %4, %6, %9\n\t"
+               "v_smfmac_f32_32x32x32_bf16 %2, %4, %7, %9\n\tv_smfmac_f32_32x32x32_bf16 %3, %4, %8, %9\n.Lnone%=:"
+               : "+a"(a[0]), "+a"(a[1]), "+a"(a[2]), "+a"(a[3])
+               : "v"(lo), "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(kPositions23), "s"(on) : "scc");
 }
 __device__ __forceinline__ void settle(f32x16& acc) { asm volatile("s_nop 15\n\ts_nop 7" : "+a"(acc)); }
 
-// Kind 3: acc += (hi + lo) X^T, hi and X bf16 operands as above, lo the remainder of hi, of which few entries are not zero
-// (GemmTerm says how it is stored).  lo takes a v_smfmac_f32_32x32x32_bf16 per 32 x 32 block and k-tile, at twice the rate of a
-// dense product; a second one (lo2) where the block is marked as dense.  Bound by its operand bytes (41 KB per 32 tokens of a 256-tile, for
-// 1536 clocks of products) and by what else a wavefront issues: spreading the loads over the products, one branch for all that
-// dense blocks need, and the fragments a whole k-tile ahead are worth 3 to 8 % each.
+// f of the numbers 0 .. N - 1, as types
+template <class F, int... I> __device__ __forceinline__ void static_for_each(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F> __device__ __forceinline__ void static_for(F&& f) { static_for_each(f, std::make_integer_sequence<int, N>{}); }
+
+// 16 or 4 bytes a lane, one lane's behind the other's from dst on; OFFSET counts on both sides
+template <int OFFSET> __device__ __forceinline__ void load_to_lds16(const unsigned char* src, unsigned char* dst) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, OFFSET, 0);
+}
+__device__ __forceinline__ void load_to_lds4(const unsigned char* src, unsigned char* dst) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 4, 0, 0);
+}
+
+__device__ __align__(16) unsigned char zeros[2048];         // stands in for lo2 of a block that has none
+
+// Which of remainder_loop's two forms: dense 32 x 32 blocks per k-tile (of 8 and of 4) from which on lo2's products are taken with the
+// rest.  A k-tile of a workgroup alone on its CU waits for a branch that is not hidden by another workgroup: with 128-tiles that is from a
+// quarter on (2048 columns, 38 % dense: 627 us with branches, 583 without; with two workgroups a CU, 2736 columns full, 1245 / 1277).  With
+// 256-tiles almost all have to be (4096 columns, 69 %: 1555 / 1588, all: 1645 / 1598; 11008 9620 / 9950, 9980 / 10050).
+constexpr int kMany256 = 7, kMany128 = 1;
+
+// Kind 3: acc += (hi + lo) X^T, hi and X bf16 operands as above, lo the remainder of hi, of which few entries are not zero (GemmTerm says
+// how it is stored).  lo1 takes a v_smfmac_f32_32x32x32_bf16 per 32 x 32 block and k-tile, at twice the rate of a dense product; lo2 of
+// a dense block a second one.  Bound by its operand bytes (42 KB per 32 tokens of a 256-tile for 1536 clocks of products, 50 for 2048 where
+// all blocks are dense) and by the power-limited clock.  So what is done beside the products is little: positions come ready
+// to use and for two k-tiles at a time (taken apart here, from words of lo2, they cost 100 vector instructions a k-tile: 4096 columns and
+// 32768 tokens with all blocks dense 1946 us, so 1616; dense operands 1594), and a block's lo2 is fetched and multiplied behind a
+// branch of that block alone.
 template <int BT>
-__device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned char* smem, int m0, int n0, int klo, int nk,
-                                               f32x16 (&acc)[BT / 64][BT / 64]) {
+__device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned char* smem, int m0, int n0, int nk, f32x16 (&acc)[BT / 64][BT / 64]) {
   constexpr int NSTAGE = 3, WT = BT / 2, FR = WT / 32;
-  constexpr int BLK = BT / 32, GROUP = 4096;                // 32 x 32 blocks of lo in a k-tile; bytes of lo2's place of 128 rows
-  constexpr int OPB = BT * 64, LOB = BT * 32;               // bytes of a k-tile of hi or X, and of lo1 or lo2
-  constexpr int STAGE_BYTES = 2 * OPB + 2 * LOB;            // hi, X, lo1, lo2 (with the positions of lo1)
+  constexpr int OPB = BT * 64, LOB = BT * 32, POSB = BT * 8;          // bytes of a k-tile of hi or X, of lo1 or lo2; of the positions of two k-tiles
+  constexpr int LO1 = 2 * OPB, LO2 = LO1 + LOB, STAGE_BYTES = LO2 + LOB;
+  constexpr int POS = NSTAGE * STAGE_BYTES, FLAGS = POS + 4 * POSB;   // the positions of eight k-tiles, and a byte per k-tile
   constexpr int LPW = BT / 64, LPWL = LOB / 4096;           // 1 KB loads per wave and k-tile: of hi or X, of lo1 or lo2
-  constexpr int TL = 2 * LPW + LPWL + 1;                    // loads per k-tile per wave, load_dense apart
+  constexpr int POS_PARTS = BT / 128;                       // 1 KB parts of POSB
+  if (nk <= 0) return;                                      // (nk is even)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const GemmTerm& tm = P.term[0];
-  const int64_t kt0 = klo / kGemmBK, lokt = tm.ktl / 2;     // (elements of lo1, and of lo2, per k-tile)
-  // the positions that a wave fetches, 256 bytes of a group's 512 (with one group, two waves fetch the same)
-  auto pos_at = [](int w) { return (BT == 256 ? (w >> 1) * GROUP : 0) + 64 + (w & 1) * 256; };
-  if (nk <= 0) return;
+  typedef const unsigned char* Bytes;
+  const int64_t kt = tm.ktl * 2, pos2 = kt / 8;             // bytes per k-tile of hi or X, and per two of the positions
 
-  const int ld_line = lane >> 4;                            // (tile format in LDS: see tile_loop)
-  const int ld_row = ld_line * 4 + ((lane & 15) >> 2);
-  const int ld_chunk = (lane & 3) ^ ld_line;
+  // A source is a base that the wavefront shares and a lane's offset.  hi and X: the tile format of tile_loop.  lo1 and lo2: a block has 64
+  // slots of 16 bytes in LDS, those of row r at 2 r and 2 r + 1, exchanged in every other eight rows, so that 16 lanes that read one half of
+  // 16 rows meet 16 different slots of a 256-byte line.
+  const uint32_t at64 = ((lane >> 4) * 4 + ((lane & 15) >> 2)) * 64 + ((lane & 3) ^ (lane >> 4)) * 16;
+  const uint32_t at32 = (lane >> 1) * 32 + ((lane ^ lane >> 4) & 1) * 16;
   struct TileSrc {
-    const uint16_t *hi, *x, *lo, *lo2, *pos;
-    unsigned char* st;
-    int seq;
+    Bytes hi, x, lo, lo2;
+    int st, seq;                                            // where in LDS the tile goes, and its number in load order (not clamped)
   } c;
-  {
-    const int64_t row = wave * LPW * 16 + ld_row;
-    c.hi = tm.L[0] + (m0 + row) * tm.ldl + kt0 * tm.ktl + ld_chunk * 8;
-    c.x = tm.R[0] + (n0 + row) * tm.ldr + kt0 * tm.ktr + ld_chunk * 8;
-    const int64_t o = kt0 * lokt + (int64_t)m0 * 16;
-    c.lo = tm.L[1] + o + wave * (LPWL * 512) + lane * 8;
-    c.lo2 = tm.R[1] + o + wave * (LPWL * 512) + lane * 8;
-    c.pos = tm.R[1] + o + (pos_at(wave) >> 1) + lane * 2;
-    c.st = smem;
-    c.seq = 0;
-  }
-  const int64_t lstep = 16 * tm.ldl, rstep = 16 * tm.ldr;
-  auto next_tile = [&](int stage) {
+  c.hi = (Bytes)tm.L[0] + (int64_t)m0 * 64 + wave_s * (LPW * 1024);
+  c.x = (Bytes)tm.R[0] + (int64_t)n0 * 64 + wave_s * (LPW * 1024);
+  c.lo = (Bytes)tm.L[1] + (int64_t)m0 * 32 + wave_s * (LPWL * 1024);
+  c.lo2 = (Bytes)tm.R[1] + (int64_t)m0 * 32 + wave_s * (LPWL * 1024);
+  c.st = 0;
+  c.seq = 0;
+  auto next_tile = [&](int stage_at) {
     ++c.seq;
-    c.st = smem + stage * STAGE_BYTES;
-    const bool more = c.seq < nk;
-    const int64_t ls = more ? tm.ktl : 0, rs = more ? tm.ktr : 0, os = more ? lokt : 0;
-    c.hi += ls;
-    c.x += rs;
-    c.lo += os;
-    c.lo2 += os;
-    c.pos += os;
+    c.st = stage_at;
+    const int64_t step = c.seq < nk ? kt : 0;
+    c.hi += step;
+    c.x += step;
+    c.lo += step / 2;
+    c.lo2 += step / 2;
   };
-  auto to_lds = [&](const uint16_t* src, int off) {
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                     (__attribute__((address_space(3))) void*)(c.st + off), 16, 0, 0);
+  // 1 KB, number `slab` of those that a wavefront fetches of an operand
+  auto to_lds = [&](Bytes base, uint32_t at, int lds, auto slab) { load_to_lds16<decltype(slab)::value * 1024>(base + (uint64_t)at, smem + lds); };
+  auto load_hi_x = [&](auto number) {                       // (in turn)
+    constexpr int q = decltype(number)::value;
+    if constexpr (q & 1) to_lds(c.x, at64, c.st + OPB + wave_s * (LPW * 1024), std::integral_constant<int, q / 2>{});
+    else to_lds(c.hi, at64, c.st + wave_s * (LPW * 1024), std::integral_constant<int, q / 2>{});
   };
-  auto load_one = [&](int q) {
-    if (q < 2 * LPW) {
-      const int j = q >> 1;
-      if (q & 1) to_lds(c.x + j * rstep, OPB + (wave_s * LPW + j) * 1024);
-      else to_lds(c.hi + j * lstep, (wave_s * LPW + j) * 1024);
-    } else if (q < 2 * LPW + LPWL) {
-      const int p = q - 2 * LPW;
-      to_lds(c.lo + p * 512, 2 * OPB + (wave_s * LPWL + p) * 1024);
-    } else {
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)c.pos,
-                                       (__attribute__((address_space(3))) void*)(c.st + 2 * OPB + LOB + pos_at(wave_s)), 4, 0, 0);
-    }
-  };
-  // lo2's place of a tile with dense blocks: in front of its other loads, so that the counts the waits go by hold (more loads only
-  // make them longer)
-  auto load_dense = [&](int f) {
-    if (__builtin_expect(f == 0, 1)) return;
-#pragma unroll
-    for (int p = 0; p < LPWL; ++p) to_lds(c.lo2 + p * 512, 2 * OPB + LOB + (wave_s * LPWL + p) * 1024);
+  auto load_lo1 = [&](auto slab) { to_lds(c.lo, at32, c.st + LO1 + wave_s * (LPWL * 1024), slab); };
+  auto load_lo2 = [&](Bytes base, auto slab) { to_lds(base, at32, c.st + LO2 + wave_s * (LPWL * 1024), slab); };
+  auto load_positions = [&](int pair, int part) {           // 256 bytes of a part
+    const int at = part * 1024 + wave_s * 256;
+    load_to_lds4((Bytes)P.positions + (int64_t)m0 * 8 + min(pair, nk / 2 - 1) * pos2 + at + (uint64_t)(uint32_t)(lane * 4),
+                 smem + POS + (pair & 3) * POSB + at);
   };
 
   const int rl = lane & 31, half = lane >> 5;
   const int fr_line = rl >> 2, fr_x = fr_line & 3, fr_hi = (rl & 3) << 2;
-  const int lo2_at = lane == 0 ? 0 : lane < 9 ? 64 + 16 * (lane - 1) : 576 + 16 * (lane - 9);
-  const int lo2_step = lane == 0 ? 16 : lane < 9 ? 128 : 880;
-  const int grp = 2 * OPB + LOB + (BT == 256 ? wm * GROUP : 0), blk0 = BT == 256 ? 0 : wm * FR;      // this wavefront's blocks of lo2
-  // the fragments of two k-tiles, the one that is multiplied and the one that is read meanwhile (by the parity of their number)
-  bf16x8 af[2][2][FR], bfr[2][2][FR], lo[2][FR];
-  u32x4 lo2[FR];
-  int pos[2][FR], mark;
   auto frag = [&](const unsigned char* st, int kk, int i) {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(st + i * 2048 + fr_line * 256 + ((fr_hi | ((kk * 2 + half) ^ fr_x)) << 4)));
   };
-  constexpr int NREAD = 6 * FR;
-  auto read_one = [&](const unsigned char* st, int s, int r) {
-    const int i = r % FR, kk = r / FR & 1;
-    if (r < 4 * FR) {
-      if (r < 2 * FR) af[s][kk][i] = frag(st + wm * (WT * 64), kk, i);
-      else bfr[s][kk][i] = frag(st + OPB + wn * (WT * 64), kk, i);
-    } else if (r < 5 * FR) {
-      lo[s][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(st + 2 * OPB + (wm * FR + i) * 1024 + lane * 16));
-    } else {
-      pos[s][i] = *reinterpret_cast<const uint16_t*>(st + grp + 64 + (blk0 + i) * 128 + lane * 2);
-    }
-  };
+  const int lo_at = wm * (FR * 1024) + (2 * rl + (half ^ (rl >> 3 & 1))) * 16, pos_at = POS + wm * (FR * 256) + rl * 8 + half * 4;
+  auto lo_frag = [&](const unsigned char* st, int i) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(st + lo_at + i * 1024)); };
+  auto read_positions = [&](int pair, int i) { return *reinterpret_cast<const int*>(smem + pos_at + (pair & 3) * POSB + i * 256); };
+  unsigned char* flags = smem + FLAGS;
   auto blocks_of = [&](int f) { return (f >> (wave_s >> 1) * FR) & ((1 << FR) - 1); };      // this wavefront's
-  auto read_dense = [&](const unsigned char* st, int i) {
-    lo2[i] = *reinterpret_cast<const u32x4*>(st + grp + lo2_at + (blk0 + i) * lo2_step);
-  };
-  // a dense block's pairs that stand for positions: those to pos, zeros in their place
-  auto decode = [&](int s, int i, int dense) {
-    int p = 0;
+  int fl0, fl1, fl2, mark;                                  // the dense blocks of the k-tiles it, it + 1, it + 2, and of the one behind them
+
+  // Pipeline: one barrier per k-tile `it`, behind which tile it + 1 is in LDS and tile it in registers.  A 32-row block's products
+  // (hi in two k-steps, lo1, lo2) are taken one after the other.  Between them, one at a time, the fragments of tile it + 1 are read: with
+  // 256-tiles those of a block into its registers of tile it while the next block is multiplied (the last block's into two sets
+  // in turn), with 128-tiles there are two sets for all; and tile it + NSTAGE is requested.
+  // ALWAYS: lo2 is fetched (where a block has none, from zeros) and multiplied with the rest; else behind a branch per block.
+  auto run = [&](auto form) {
+    constexpr bool ALWAYS = decltype(form)::value;
+    constexpr int G = (ALWAYS ? 4 : 3) * FR, NSLOT = G * FR, LOADS = 2 * LPW + (ALWAYS ? 2 : 1) * LPWL, LOAD_SLOTS = NSLOT - 4;
+    constexpr bool TWO = FR == 2;                           // two whole sets
+    constexpr int SETS = TWO ? 2 * FR : FR + 1;
+    constexpr int PER = 6, ROUNDS = TWO ? 1 : FR, ROUND_SLOTS = NSLOT / ROUNDS;         // reads of a block (with those of X that come along)
+    constexpr int READS = PER * FR / ROUNDS, READ_SLOTS = TWO ? NSLOT * 3 / 4 : ROUND_SLOTS / 2;
+    bf16x8 a[SETS][2], b[2][2][FR], l1[SETS], l2[SETS];
+    int pos[FR], pos_next[FR];
+    auto set_of = [](int i, int s) { return TWO ? 2 * i + s : i < FR - 1 ? i : FR - 1 + s; };
+    // of block i of the k-tile at st, to set t
+    auto read_item = [&](const unsigned char* st, int i, int t, int item) {
+      if (item == 0) l1[t] = lo_frag(st + LO1, i);
+      else if (item == 1) l2[t] = lo_frag(st + LO2, i);
+      else a[t][item - 2] = frag(st + wm * (WT * 64), item - 2, i);
+    };
+    auto read_x = [&](const unsigned char* st, int s, int k) { b[s][k / FR][k % FR] = frag(st + OPB + wn * (WT * 64), k / FR, k % FR); };
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const uint32_t x = lo2[i][e] ^ kPositionsMark;
-      const bool is = x < 0x10000u;
-      p |= is ? (int)x : 4 << (4 * e);
-      lo2[i][e] = is ? 0u : lo2[i][e];
+    for (int i = 0; i < FR; ++i) {
+#pragma unroll
+      for (int item = 0; item < 4; ++item) read_item(smem, i, set_of(i, 0), item);
+      pos_next[i] = read_positions(0, i);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) read_x(smem, 0, 2 * i + k);
     }
-    if (dense >> i & 1) pos[s][i] = p;
+    int cur = 0;                                            // where the stage of this k-tile begins
+    for (int it0 = 0; it0 < nk; it0 += 2) {
+      static_for<2>([&](auto parity) {
+        constexpr int s = decltype(parity)::value;
+        const int it = it0 + s, nxt = cur == (NSTAGE - 1) * STAGE_BYTES ? 0 : cur + STAGE_BYTES;
+        const unsigned char* nx = smem + nxt;
+        auto both = [&](int j) { return __builtin_shufflevector(b[s][0][j], b[s][1][j], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15); };
+        __builtin_amdgcn_sched_barrier(0);
+        wait_vm_and_lds<LOADS + ((s ^ 1) < POS_PARTS)>();   // (all but what the k-tile before has requested: so many at least)
+        wg_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        const int now = blocks_of(fl0);
+        static_for<NSLOT>([&](auto slot) {
+          constexpr int m = decltype(slot)::value, i = m / G, q = m % G, ph = q / FR, j = m % FR;
+          const int t = set_of(i, s);
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (ph < 2) dense_product(acc[i][j], a[t][ph], b[s][ph][j]);
+          else if constexpr (ph == 2) sparse_product<s>(acc[i][j], l1[t], both(j), pos[i]);
+          else sparse_product<0>(acc[i][j], l2[t], both(j), kPositions23);
+          __builtin_amdgcn_sched_barrier(0);
+          if constexpr (s == 0 && m < FR) pos[m] = pos_next[m];
+          if constexpr (s == 1 && m < FR) pos_next[m] = read_positions(it0 / 2 + 1, m);
+          // (behind the last k-tile: a stale stage, not used)
+          constexpr int round = m / ROUND_SLOTS, rq = m % ROUND_SLOTS;
+          constexpr int r0 = (rq * READS + READ_SLOTS - 1) / READ_SLOTS, r1 = ((rq + 1) * READS + READ_SLOTS - 1) / READ_SLOTS;
+          static_for<(r0 < READS ? (r1 < READS ? r1 : READS) - r0 : 0)>([&](auto number) {
+            constexpr int n = r0 + decltype(number)::value, item = n % PER, x = item - (PER - 2);
+            constexpr int block = TWO ? n / PER : (round + FR - 1) % FR;
+            if constexpr (x < 0) read_item(nx, block, set_of(block, s ^ 1), item);
+            else read_x(nx, s ^ 1, 2 * (TWO ? block : round) + x);
+          });
+          if constexpr (m == 1) {
+            const int f = __builtin_amdgcn_readfirstlane(mark);
+            fl0 = fl1;
+            fl1 = fl2;
+            fl2 = c.seq < nk ? f : 0;
+            if constexpr (!ALWAYS) static_for<LPWL>([&](auto slab) { if (fl2 >> (wave_s * LPWL + decltype(slab)::value) & 1) load_lo2(c.lo2, slab); });
+          }
+          if constexpr (m == NSLOT / 2) mark = flags[min(it + NSTAGE + 1, nk - 1)];
+          constexpr int l = m - 2, ALL = LOADS + (s < POS_PARTS), q0 = l * ALL / LOAD_SLOTS;
+          if constexpr (l >= 0 && l < LOAD_SLOTS && q0 < (l + 1) * ALL / LOAD_SLOTS) {
+            constexpr int w = q0 - 2 * LPW, w2 = w - LPWL;
+            if constexpr (q0 == LOADS) load_positions(it0 / 2 + 2, s);
+            else if constexpr (w < 0) load_hi_x(std::integral_constant<int, q0>{});
+            else if constexpr (w2 < 0) load_lo1(std::integral_constant<int, w>{});
+            else load_lo2(fl2 >> (wave_s * LPWL + w2) & 1 ? c.lo2 : (Bytes)zeros, std::integral_constant<int, w2>{});
+          }
+          if constexpr (!ALWAYS && q == G - 1) {
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (FR == 4) sparse_products_if(now >> i & 1, acc[i], l2[t], {both(0), both(1), both(2), both(3)});
+            else sparse_products_if(now >> i & 1, acc[i], l2[t], {both(0), both(1)});
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          if constexpr (m == NSLOT - 1) { next_tile(nxt); cur = nxt; }
+        });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    }
+    wait_vm_and_lds<0>();   // the surplus loads past the last k-tile
+#pragma unroll
+    for (int i = 0; i < FR; ++i)
+#pragma unroll
+      for (int j = 0; j < FR; ++j) settle(acc[i][j]);
   };
 
-  // Pipeline: one barrier per k-tile `it`, behind which tile it is in registers (its stage is loaded again, with tile it + NSTAGE) and
-  // tile it + 1 in LDS: its fragments are read and tile it + NSTAGE is requested, one at a time, between the products of tile it.
-  constexpr int NM = FR * FR, NSLOT = 3 * NM, READ_SLOTS = NSLOT - NM / 2, LOAD_SLOTS = NSLOT - 4;
-#pragma unroll
-  for (int t = 0; t < NSTAGE; ++t) {
-    load_dense(1);                                          // (not known yet)
-#pragma unroll
-    for (int q = 0; q < TL; ++q) load_one(q);
-    next_tile((t + 1) % NSTAGE);
-  }
-  // which blocks of each k-tile are dense: a bit per block, from the marks in their places
-  unsigned char* flags = smem + NSTAGE * STAGE_BYTES;
-  for (int kt = tid; kt < nk; kt += 256) {
-    const uint32_t* mark = reinterpret_cast<const uint32_t*>(tm.R[1] + (kt0 + kt) * lokt + (int64_t)m0 * 16);
-    int f = 0;
-#pragma unroll
-    for (int b = 0; b < BLK; ++b) f |= mark[(b >> 2) * (GROUP / 4) + (b & 3) * 4] != kSparseMark ? 1 << b : 0;
-    flags[kt] = (unsigned char)f;
+  for (int p = 0; p < 2 * POS_PARTS; ++p) load_positions(p / POS_PARTS, p % POS_PARTS);
+  static_for<NSTAGE>([&](auto t) {                          // (lo2 too: which blocks are dense is not known yet)
+    static_for<2 * LPW>(load_hi_x);
+    static_for<LPWL>(load_lo1);
+    static_for<LPWL>([&](auto slab) { load_lo2(c.lo2, slab); });
+    next_tile((decltype(t)::value + 1) % NSTAGE * STAGE_BYTES);
+  });
+  // which blocks of each k-tile are dense: a bit per block
+  for (int k = tid; k < nk; k += 256) {
+    const uint32_t* d = reinterpret_cast<const uint32_t*>(P.dense + k * (kt / 2048) + (m0 >> 5));
+    int f = (int)(d[0] * 0x10204080u >> 28);                // (bytes of 0 or 1: their bits side by side)
+    if (BT == 256) f |= (int)(d[1] * 0x10204080u >> 28) << 4;
+    flags[k] = (unsigned char)f;
   }
   wait_vm_and_lds<0>();
   wg_barrier();
-  int fl[NSTAGE];
+  int marked = 0;                                           // dense blocks
+  for (int k = 0; k < nk; k += 64) {
+    const int f = k + lane < nk ? flags[k + lane] : 0;
 #pragma unroll
-  for (int t = 0; t < NSTAGE; ++t) fl[t] = t < nk ? __builtin_amdgcn_readfirstlane(flags[t]) : 0;
+    for (int b = 0; b < BT / 32; ++b) marked += __builtin_popcountll(__ballot(f >> b & 1));
+  }
+  fl0 = __builtin_amdgcn_readfirstlane(flags[0]);
+  fl1 = __builtin_amdgcn_readfirstlane(flags[1]);
+  fl2 = __builtin_amdgcn_readfirstlane(flags[min(2, nk - 1)]);
   mark = flags[min(NSTAGE, nk - 1)];
+  if (marked > nk * (BT == 256 ? kMany256 : kMany128)) {
+    // (the first k-tiles have been fetched as they are)
 #pragma unroll
-  for (int r = 0; r < NREAD; ++r) read_one(smem, 0, r);
+    for (int t = 0; t < NSTAGE; ++t)
 #pragma unroll
-  for (int i = 0; i < FR; ++i) {
-    read_dense(smem, i);
-    decode(0, i, blocks_of(fl[0]));
+      for (int p = 0; p < LPWL; ++p)
+        if (!((t == 0 ? fl0 : t == 1 ? fl1 : fl2) >> (wave_s * LPWL + p) & 1))
+          *reinterpret_cast<u32x4*>(smem + t * STAGE_BYTES + LO2 + (wave_s * LPWL + p) * 1024 + lane * 16) = u32x4{0, 0, 0, 0};
+    wait_vm_and_lds<0>();
+    wg_barrier();
+    run(std::true_type{});
+  } else {
+    run(std::false_type{});
   }
-  for (int it0 = 0; it0 < nk; it0 += 2 * NSTAGE) {
-#pragma unroll
-    for (int u = 0; u < 2 * NSTAGE; ++u) {
-      if (__builtin_expect(it0 + u < nk, 1)) {
-        const int sg = u % NSTAGE, s = u & 1;
-        const unsigned char* nx = smem + (u + 1) % NSTAGE * STAGE_BYTES;
-        auto both = [&](int j) { return __builtin_shufflevector(bfr[s][0][j], bfr[s][1][j], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15); };
-        __builtin_amdgcn_sched_barrier(0);
-        wait_vm_and_lds<TL>();
-        wg_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        const int fl_now = fl[sg];
-#pragma unroll
-        for (int m = 0; m < NSLOT; ++m) {
-          const int i = m % NM / FR, j = m % FR;
-          __builtin_amdgcn_sched_barrier(0);
-          if (m < 2 * NM) dense_product(acc[i][j], af[s][m / NM % 2][i], bfr[s][m / NM % 2][j]);
-          else sparse_product(acc[i][j], lo[s][i], both(j), pos[s][i]);
-          __builtin_amdgcn_sched_barrier(0);
-          // (behind the last k-tile: a stale stage, not used)
-#pragma unroll
-          for (int r = m * NREAD / READ_SLOTS; r < (m + 1) * NREAD / READ_SLOTS && r < NREAD; ++r) read_one(nx, s ^ 1, r);
-          if (m == 1) {
-            fl[sg] = c.seq < nk ? __builtin_amdgcn_readfirstlane(mark) : 0;
-            load_dense(fl[sg]);
-          }
-          if (m == READ_SLOTS - 1) mark = flags[min(it0 + u + NSTAGE + 1, nk - 1)];
-          const int l = m - 2;
-#pragma unroll
-          for (int q = l * TL / LOAD_SLOTS; l >= 0 && l < LOAD_SLOTS && q < (l + 1) * TL / LOAD_SLOTS; ++q) load_one(q);
-          if (m == NSLOT - 2) next_tile((u + 1) % NSTAGE);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (__builtin_expect((fl_now | fl[(u + 1) % NSTAGE]) != 0, 0)) {       // (one branch for both: a taken one costs tens of clocks)
-          const int dense = blocks_of(fl_now), then = blocks_of(fl[(u + 1) % NSTAGE]);
-#pragma unroll
-          for (int i = 0; i < FR; ++i) {                    // lo2: positions 2, 3
-#pragma unroll
-            for (int j = 0; j < FR; j += 2)
-              sparse_products_if(dense >> i & 1, acc[i][j], acc[i][j + 1], __builtin_bit_cast(bf16x8, lo2[i]), both(j), both(j + 1), 0xEEEE);
-            __builtin_amdgcn_sched_barrier(0);
-            read_dense(nx, i);
-            __builtin_amdgcn_sched_barrier(0);
-            if (i > 0) decode(s ^ 1, i - 1, then);
-          }
-          decode(s ^ 1, FR - 1, then);
-        }
-      }
-    }
-  }
-  wait_vm_and_lds<0>();   // the surplus loads past the last k-tile
-#pragma unroll
-  for (int i = 0; i < FR; ++i)
-#pragma unroll
-    for (int j = 0; j < FR; ++j) settle(acc[i][j]);
 }
 
 // A wave-uniform value that is to stay in scalar registers (the compiler would otherwise choose between the two problems of a
@@ -664,7 +700,7 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* sme
 
   if constexpr (REMAINDER) {
     if (P.kind == 0) tile_loop<BT, 0, false>(P, smem, m0, n0, klo, nk, acc);
-    else remainder_loop<BT>(P, smem, m0, n0, klo, nk, acc);
+    else remainder_loop<BT>(P, smem, m0, n0, nk, acc);
   } else if (P.nterm > 1) {
     if (P.kind == 0) tile_loop<BT, 0, true>(P, smem, m0, n0, klo, nk, acc);
     else if (P.kind == 1) tile_loop<BT, 1, true>(P, smem, m0, n0, klo, nk, acc);
@@ -803,7 +839,7 @@ hipError_t launch_gemm(const GemmBatch& b, hipStream_t s) {
     if (i < bb.nprob && q.quartered && (!remainder || bb.tile != 256 || i != 1 || q.tile_mode != 2 || q.store_mode || q.deal || q.quartered % 2)) return hipErrorInvalidValue;
     bb.ntiles[i] = i >= bb.nprob ? 0 : 3 * q.quartered + q.split * (q.tile_mode == 2 ? q.tiles_m * (q.tiles_m + 1) / 2 : q.tiles_m * q.tiles_n);
     if (q.split > 1 && (bb.tile != 128 || q.k_mode || q.store_mode || q.deal || !q.partial)) return hipErrorInvalidValue;
-    if (i < bb.nprob && q.kind == 3 && (q.nterm != 1 || q.K > kMaxRemainderK)) return hipErrorInvalidValue;
+    if (i < bb.nprob && q.kind == 3 && (q.nterm != 1 || q.k_mode || q.K % (2 * kGemmBK) || q.K > kMaxRemainderK)) return hipErrorInvalidValue;
     if (i < bb.nprob && remainder && (q.split > 1 || b.max_wgs > 0 || (q.kind != 3 && (q.kind != 0 || q.nterm != 1)))) return hipErrorInvalidValue;
     total += bb.ntiles[i];
     if (q.split > 1) part_tiles += bb.ntiles[i] / q.split;

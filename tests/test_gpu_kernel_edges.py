@@ -483,3 +483,70 @@ def test_quarters_of_the_last_tiles_have_the_bits_of_whole_ones(n, tokens):
     ref = X.double().T @ X.double() + 1.0
     err = float((Hu.double() - ref).triu().norm() / ref.triu().norm())
     assert err <= 2.0 ** -24 * (tokens / 8) ** 0.5, err        # (a chain of tokens / 16 steps)
+
+
+@pytest.mark.parametrize("n,tokens", [(1928, 96), (2496, 2080), (3848, 224), (4104, 512)])
+@pytest.mark.parametrize("one_in", [9, 3])
+def test_sparse_remainder_with_blocks_that_have_none_among_dense_ones(n, tokens, one_in):
+    """One 32 x 32 block in nine, or in three, has no difference at all and the others no entry that fits 8 bits: with one in nine lo2 is
+    taken for every block, with zeros in the place of those that have none; the first and the last k-tiles are among them."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    X = (2.0 ** -7 * torch.randn((tokens, n), device="cuda", generator=g)).to(torch.bfloat16)
+    e = torch.randn((tokens, n), device="cuda", generator=g).to(torch.bfloat16)
+    block = torch.arange(tokens, device="cuda")[:, None] // 32 + torch.arange(n, device="cuda")[None, :] // 32
+    Xt = torch.where(block % one_in == 0, X, e)
+    H = torch.zeros((n, n), device="cuda")
+    A, Au = torch.zeros_like(H), torch.zeros_like(H)
+    ws = B.workspace(B.gptaq_accumulate_workspace_bytes(tokens, n))
+    ws.fill_(0xff)                         # (what the call does not write is not read as numbers)
+    B.gptaq_accumulate(X, Xt, H, A, ws)
+    ws.fill_(0xff)
+    B.gptaq_accumulate_upper(X, Xt, torch.zeros_like(H), Au, ws)
+    assert torch.equal(A.triu(), Au.triu())
+    ref = (Xt.double() - X.double()).T @ X.double()
+    # (bound: see test_sparse_remainder_of_the_difference)
+    err = float((A.double() - ref).norm() / ref.norm())
+    assert err <= 2.0 ** -24 * max(4.0, (tokens / 8) ** 0.5), err
+
+
+@pytest.mark.parametrize("n", [1928, 3848])
+def test_workspace_without_room_for_positions(n):
+    """A workspace of 6 bytes an entry, which is what dense operands take, is enough, in one call as in staged ones."""
+    tokens, np_ = 200, {1928: 2048, 3848: 4096}[n]
+    X, Xt = synth.make_activations_device(tokens, n, 3, "x", "cuda")
+    refs = [S.double().T @ X.double() for S in (X, Xt.double() - X.double())]
+    bound = 2.0 ** -24 * max(4.0, (tokens / 8) ** 0.5)
+    for nb in (6 * np_ * 64, 6 * np_ * 256, B.gptaq_accumulate_workspace_bytes(64, n)):
+        H, A = torch.zeros((n, n), device="cuda"), torch.zeros((n, n), device="cuda")
+        B.gptaq_accumulate(X, Xt, H, A, B.workspace(nb))
+        for got, ref in zip((H.triu(), A), (refs[0].triu(), refs[1])):
+            assert float((got.double() - ref).norm() / ref.norm()) <= bound
+    H, A = torch.zeros((n, n), device="cuda"), torch.zeros((n, n), device="cuda")
+    ws = B.workspace(6 * np_ * 32768)
+    pending = B.gptaq_accumulate_staged(X[:128], Xt[:128], H, A, ws, 0, flush=False)
+    assert pending == 128 and B.gptaq_accumulate_staged(X[128:], Xt[128:], H, A, ws, pending, flush=True) == 0
+    for got, ref in zip((H.triu(), A), (refs[0].triu(), refs[1])):
+        assert float((got.double() - ref).norm() / ref.norm()) <= bound
+
+
+def _accumulate_us(call, n, tokens, noise, repeats=5):
+    X, Xt = synth.make_activations_device(tokens, n, 7, "x", "cuda", noise=noise)
+    H = torch.zeros((n, n), device="cuda")
+    A = torch.zeros_like(H)
+    ws = B.workspace(B.gptaq_accumulate_workspace_bytes(tokens, n))
+    times = []
+    for _ in range(repeats + 2):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        call(X, Xt, H, A, ws)
+        t1.record()
+        torch.cuda.synchronize()
+        times.append(1e3 * t0.elapsed_time(t1))
+    return min(times[2:])
+
+
+def test_dense_remainder_costs_what_its_products_cost():
+    """Where every block of the remainder is dense, a tile of dXXT takes 2 units of products instead of 1.5 and 50 KB instead of 42 per
+    k-tile, and H 1 and 32 either way: 1.2 times the time (1.19 measured).  What finds its positions costs nothing beside that
+    (taken from words of lo2 it was 1.5 times)."""
+    assert _accumulate_us(B.gptaq_accumulate_upper, 4096, 32768, 0.5) <= 1.3 * _accumulate_us(B.gptaq_accumulate_upper, 4096, 32768, 0.001)
