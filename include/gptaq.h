@@ -73,8 +73,7 @@ int gptaq_accumulate(const uint16_t* X, const uint16_t* Xtilde, int64_t tokens, 
  * split operands go to a 32 MiB scratch array that is part of the library's code object (one copy per GPU,
  * held until the process ends), and the call makes no hipMalloc, hipFree or other allocating call.
  * The chunk is processed in passes of as many tokens as fit:
- * 6 bytes for each of n (rounded up to the tile) entries of a token, about 6 1/8 from n = 1921 on, in multiples
- * of 64 tokens (1280 at n = 4096).
+ * floor(32 MiB / (6 * round_up(n, tile))) rounded down to 64 (1344 tokens at n = 4096).
  *   n > 16384 returns GPTAQ_ETOOLARGE before anything is launched; other argument errors as gptaq_accumulate.
  *   Every call on a GPU shares that GPU's array: calls that overlap in time on one GPU (two streams, two
  *   host threads) race.  Nothing in the array has to be cleared between calls. */

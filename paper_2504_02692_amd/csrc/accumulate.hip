@@ -15,7 +15,7 @@ namespace gptaq {
 
 // Workspace of gptaq_accumulate_noalloc: one copy per GPU, owned by the code object, never freed.
 constexpr size_t kScratchBytes = (size_t)32 << 20;
-constexpr int64_t kScratchMaxN = 16384;                   // the operands of 320 tokens of 16384 entries still fit, positions among them
+constexpr int64_t kScratchMaxN = 16384;                   // 6 * 16384 * 320 tokens still fit
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 __device__ __forceinline__ float bf16_to_f32(uint32_t h) { return __uint_as_float(h << 16); }
@@ -31,10 +31,10 @@ template <bool SPARSE>
 __global__ __launch_bounds__(256) void split_transpose_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ Xt, int64_t ldx,
     int tokens, int n, uint16_t* __restrict__ oX, uint16_t* __restrict__ oHi,
-    uint16_t* __restrict__ oLo, uint16_t* __restrict__ oLo2, uint16_t* __restrict__ oPos, uint8_t* __restrict__ oDense, int64_t ldo /* padded rows */, int tile0 /* first 64-token tile of the output */,
+    uint16_t* __restrict__ oLo, uint16_t* __restrict__ oLo2, int64_t ldo /* padded rows */, int tile0 /* first 64-token tile of the output */,
     const int32_t* __restrict__ row_of /* NULL, or operand row of input column j (a permutation of 0 .. n-1) */) {
   constexpr int LS = 72;                                  // padded LDS row, 144 bytes
-  __shared__ __attribute__((aligned(16))) uint16_t sx[64 * LS], sh[64 * LS], sl[64 * LS], spos[SPARSE ? 64 * 4 : 4];
+  __shared__ __attribute__((aligned(16))) uint16_t sx[64 * LS], sh[64 * LS], sl[64 * LS];
   const int n0 = blockIdx.x * 64, t0 = blockIdx.y * 64;
   const int tid = threadIdx.x, r = tid >> 3, c = tid & 7;
   auto row_to = [&](int i) {                                // the operand row of input column n0 + i
@@ -78,10 +78,9 @@ __global__ __launch_bounds__(256) void split_transpose_kernel(
   if (!SPARSE) return;
   // lo, in the form that GemmTerm describes: a wavefront has a 32 x 32 block and a lane the 16 tokens of its row that it has there
   const int lane = tid & 63, nl = (tid >> 7) * 32 + (lane & 31), k = tid >> 6 & 1, half = lane >> 5;
-  const int64_t row = row_to(nl);
   uint64_t q[4];
   int nz[4];
-  bool more = row_of != nullptr;                            // (rows that go elsewhere: their blocks are not known here, and are dense)
+  bool more = false;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const u32x4 x = *reinterpret_cast<const u32x4*>(sl + nl * LS + k * 32 + half * 16 + h * 8);
@@ -98,20 +97,37 @@ __global__ __launch_bounds__(256) void split_transpose_kernel(
   uint32_t v[4], v2[4], places = 0;
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    // places of two values that hold what is not zero: (0,1) (0,3) (1,3) (0,1) | (2,3) (0,2) (1,2) - | (2,3) (0,3) (1,3) - | (2,3) - - -,
-    // and (0,1) where two do not
-    const uint32_t at = (uint32_t)(0x444E4DCE498E4DC4ull >> (4 * nz[e]) & 15);
+    // places of two values that hold what is not zero: (0,1) (0,3) (1,3) (0,1) | (2,3) (0,2) (1,2) - | (2,3) (0,3) (1,3) - | (2,3) - - -
+    const uint32_t at = dense ? 4u : (uint32_t)(0x444E4DCE498E4DC4ull >> (4 * nz[e]) & 15);
     v[e] = (uint32_t)(q[e] >> (16 * (at & 3)) & 0xffff) | (uint32_t)(q[e] >> (16 * (at >> 2))) << 16;
-    v2[e] = __builtin_popcount(nz[e]) > 2 ? (uint32_t)(q[e] >> 32) : 0u;
+    v2[e] = dense ? (uint32_t)(q[e] >> 32) : e == 0 ? kRowMark : 0u;
     places |= at << (4 * e);
   }
-  const int64_t kt = (int64_t)(blockIdx.y + tile0) * 2 + k, to = kt * ldo + row;
-  spos[nl * 4 + half * 2 + k] = (uint16_t)places;
-  *reinterpret_cast<u32x4*>(oLo + to * 16 + half * 8) = u32x4{v[0], v[1], v[2], v[3]};
-  if (dense) *reinterpret_cast<u32x4*>(oLo2 + to * 16 + half * 8) = u32x4{v2[0], v2[1], v2[2], v2[3]};
-  if (lane == 0) oDense[(kt * ldo + n0 + nl) >> 5] = dense;
-  __syncthreads();
-  if (tid < 64) *reinterpret_cast<uint64_t*>(oPos + ((int64_t)(blockIdx.y + tile0) * ldo + row_to(tid)) * 4) = *reinterpret_cast<const uint64_t*>(spos + tid * 4);
+  const int64_t kt = (int64_t)(blockIdx.y + tile0) * 2 + k;
+  if (!row_of) {
+    const int64_t row = n0 + nl;
+    *reinterpret_cast<u32x4*>(oLo + (kt * ldo + row) * 16 + half * 8) = u32x4{v[0], v[1], v[2], v[3]};
+    const int blk = (int)(row & 127) >> 5, piece = 2 * (lane & 31) + half;
+    unsigned char* group = reinterpret_cast<unsigned char*>(oLo2 + (kt * ldo + (row & ~127)) * 16);
+    places |= __shfl_down(places, 32) << 16;
+    if (dense) {
+      unsigned char* dst = piece == 0 ? group + 16 * blk : piece < 9 ? group + 64 + 128 * blk + 16 * (piece - 1) : group + 576 + 880 * blk + 16 * (piece - 9);
+      *reinterpret_cast<u32x4*>(dst) = u32x4{v2[0], v2[1], v2[2], v2[3]};
+    } else {
+      if (half == 0) *reinterpret_cast<uint32_t*>(group + 64 + 128 * blk + 4 * lane) = places;
+      if (lane == 0) *reinterpret_cast<uint32_t*>(group + 16 * blk) = kSparseMark;
+    }
+    return;
+  }
+  // by rows, in runs of 64 bytes as of hi and X  (a wavefront's rows are read and written by it alone)
+  if (!dense) v2[0] |= places;
+  *reinterpret_cast<u32x4*>(sl + nl * LS + k * 32 + half * 8) = u32x4{v[0], v[1], v[2], v[3]};
+  *reinterpret_cast<u32x4*>(sl + nl * LS + k * 32 + 16 + half * 8) = u32x4{v2[0], v2[1], v2[2], v2[3]};
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const int w = (tid >> 7) * 32 + (lane >> 2) + 16 * p;
+    *reinterpret_cast<u32x4*>(oLo + (kt * ldo + row_to(w)) * 32 + (lane & 3) * 8) = *reinterpret_cast<const u32x4*>(sl + w * LS + k * 32 + (lane & 3) * 8);
+  }
 }
 
 __global__ void symmetrize_kernel(float* H, int n, int64_t ldh) {
@@ -161,14 +177,15 @@ __global__ void invert_permutation_kernel(const int32_t* perm, int n, int32_t* i
 
 // Whether the remainder's products are taken as sparse ones (kind 3): from 1921 columns on, where the upper form has more tiles than the
 // chip has CUs.  dX does not fit a bf16 only where it is larger than the smaller of X and X~, so most of lo is zero: of its 32 x 32
-// blocks 2 % are dense where X and X~ differ by 5 % of a channel's deviation, 14 % at 10 %, 38 % at 15, 69 % at 20, 96 % at 30.  Fewer matrix
-// instructions and operand bytes (42 KB instead of 48 for 32 tokens of a 256-tile, which is what bounds these launches).  By n alone: a staged
+// blocks 2 % are dense where X and X~ differ by 5 % of a channel's deviation, 14 % at 10 %, 38 % at 15, 69 % at 20, 96 % at 30, all at 50.  Fewer matrix
+// instructions and operand bytes (41 KB instead of 48 for 32 tokens of a 256-tile, which is what bounds these launches).  By n alone: a staged
 // call writes its operands before the number of tokens is known, and the sums do not depend on the form of the call.  Measured, us
-// per call, as dense operands / so, at differences of 5, 10, 20 and 50 %: 2048 columns and 32768 tokens 586 / 558, 585, 602, 608; 2736 full 1270 / 1093,
-// 1112, 1286, 1314; 3072 and 16384 590 / 483, 494, 534, 544; 4096 and 2048 138 / 106, 108, 117, 120; 4096 and 32768 1585 / 1365, 1413, 1578, 1616; 6144
-// and 16384 1590 / 1447, 1481, 1597, 1637; 11008 and 32768 9690 / 8820, 9010, 9730, 10050.  With fewer columns a workgroup has its CU to itself
-// and the loop's branches show: 512 and 4096 tokens 54 / 58, 1536 and 4096 58 / 66.  Error of dXXT against 64 bits 2.91e-7 (dense operands
-// 2.96e-7) at 4104 columns and 6144 tokens.
+// per call, dense operands / so, at differences of 5, 10, 20 and 50 %: 2048 columns and 32768 tokens 596 / 576, 599, 612, 617; 2736
+// full 1285 / 1126, 1167, 1331, 1341; 3072 and 16384 592 / 492, 499, 550, 552; 4096 and 2048 138 / 106, 109, 117, 120; 4096 and 32768 1585 / 1384, 1420,
+// 1591, 1638; 6144 and 16384 1586 / 1447, 1477, 1583, 1644; 11008 and 32768 9800 / 8930, 9080, 9860, 10170.  So where X~ is off by 20 % and more this is up to
+// 4 % slower than dense operands (the sparse instruction draws more power, and positions are 2 % more bytes).  With fewer columns a
+// workgroup has its CU to itself and the loop's branches show: 512 and 4096 tokens 54 / 58, 1536 and 4096 58 / 66.  Error of dXXT against 64
+// bits 2.91e-7 (dense operands 2.96e-7) at 4104 columns and 6144 tokens.
 static bool sparse_remainder(int64_t n) { const int64_t t = (n + 127) / 128; return t * (t + 1) > 256; }
 
 // How many of H's last 256-tiles are taken as quarters: those past one tile for each of the 256 CUs, if they are few.  A tile of dXXT
@@ -183,28 +200,17 @@ static int quartered_tiles(int64_t tiles, int64_t h, int64_t tokens) {
 
 static int64_t padded_n(int64_t n) { return round_up(n, gemm_tile_for(n, n)); }
 
-// The operands of `tokens` tokens (a multiple of 64) in a workspace: X, hi and lo of 2 bytes an entry; lo in the sparse form in two halves,
-// and behind them the positions (4 bytes per 32 entries) and the bytes that say which 32 x 32 blocks are dense.
+// The operands of `tokens` tokens (a multiple of 64) in a workspace: X, hi and lo of 2 bytes an entry, lo in the sparse form in two halves.
 struct Operands {
-  uint16_t *X, *hi, *lo, *lo2, *positions;
-  uint8_t* dense;
+  uint16_t *X, *hi, *lo, *lo2;
   size_t bytes;
-  bool sparse;
+  bool rows;               // lo by rows
 };
-static Operands operands_at(void* ws, int64_t np, int64_t tokens, bool sparse) {
-  Operands o;
+static Operands operands_at(void* ws, int64_t np, int64_t tokens, bool rows) {
   const int64_t all = np * tokens;
-  o.X = (uint16_t*)ws;
-  o.hi = o.X + all;
-  o.lo = o.hi + all;
-  o.lo2 = o.lo + all / 2;
-  o.positions = o.lo + all;
-  o.dense = (uint8_t*)(o.positions + all / 16);
-  o.bytes = (size_t)(6 * all) + (sparse ? (size_t)(all / 8 + all / 1024) : 0);
-  o.sparse = sparse;
-  return o;
+  uint16_t* X = (uint16_t*)ws;
+  return {X, X + all, X + 2 * all, X + 2 * all + all / 2, (size_t)(6 * all), rows};
 }
-static size_t operand_bytes(int64_t np, int64_t tokens, bool sparse) { return operands_at(nullptr, np, tokens, sparse).bytes; }
 
 // In how many parts of their tokens the sums of a pass are taken, and what the parts' sums need beside the operands.
 // With few columns the tiles of H and dXXT leave most of the chip idle (n = 1024: 72 or 100 of 512 places for 128-tiles).  dXXT's tiles,
@@ -250,16 +256,16 @@ using namespace gptaq;
 extern "C" size_t gptaq_accumulate_workspace_bytes(int64_t tokens, int64_t n) {
   if (tokens <= 0 || n <= 0) return 0;
   const int64_t c = round_up(tokens < 32768 ? tokens : 32768, 64);
-  return operand_bytes(padded_n(n), c, sparse_remainder(n)) + partial_bytes(n, split_for(n, c));
+  return (size_t)(3 * padded_n(n) * c * 2) + partial_bytes(n, split_for(n, c));
 }
 
 // The operands of c tokens, from 64-token tile `tile0` of o on.
 static int launch_split(const Operands& o, const uint16_t* X, const uint16_t* Xtilde, int64_t ldx, int64_t c, int64_t n, int64_t np, int64_t tile0,
                         const int32_t* row_of, hipStream_t s) {
   ProfScope ps(kProfAccumSplit, s);
-  hipLaunchKernelGGL(o.sparse ? split_transpose_kernel<true> : split_transpose_kernel<false>,
+  hipLaunchKernelGGL(sparse_remainder(n) ? split_transpose_kernel<true> : split_transpose_kernel<false>,
                      dim3((unsigned)(np / 64), (unsigned)((c + 63) / 64)), dim3(256), 0, s, X, Xtilde, ldx, (int)c, (int)n, o.X, o.hi, o.lo, o.lo2,
-                     o.positions, o.dense, np, (int)tile0, row_of);
+                     np, (int)tile0, row_of);
   GPTAQ_LAUNCH_CHECK();
   return GPTAQ_OK;
 }
@@ -277,10 +283,9 @@ static hipError_t launch_products(const Operands& o, int64_t np, int64_t cp, int
   GemmProblem& a = b.p[0];
   a.C = dXXT; a.ldc = ldh; a.M = (int)n; a.N = (int)n; a.K = (int)cp;
   a.tiles_m = a.tiles_n = (int)(np / tile);
-  a.kind = o.sparse ? 3 : 1; a.nterm = 1; a.tile_mode = dxxt_upper ? 2 : 0; a.k_mode = 0; a.store_mode = 0;
+  a.kind = sparse_remainder(n) ? 3 : 1; a.nterm = 1; a.tile_mode = dxxt_upper ? 2 : 0; a.k_mode = 0; a.store_mode = 0;
   a.term[0] = {{o.hi, o.lo}, {o.X, o.lo2}, 32, 32, np * 32, np * 32};
-  a.positions = o.positions;
-  a.dense = o.dense;
+  a.lo_rows = o.rows;
   GemmProblem& h = b.p[1];
   h = a;
   h.C = H; h.kind = 0; h.tile_mode = 2;
@@ -320,26 +325,13 @@ static int accumulate_impl(const uint16_t* X, const uint16_t* Xtilde, int64_t to
   if (tokens == 0) return GPTAQ_OK;
   hipStream_t s = (hipStream_t)stream;
   const int64_t np = padded_n(n);
-  // tokens a pass: at most 32768, which keeps one fp32 running sum short (accuracy), and K in int32
-  auto pass_for = [&](bool sparse) {
-    const int64_t c = (int64_t)(ws_bytes / operand_bytes(np, 64, sparse)) * 64;
-    return c < 32768 ? c : (int64_t)32768;
-  };
-  int64_t cmax = pass_for(false);
+  int64_t cmax = (int64_t)(ws_bytes / (size_t)(6 * np)) / 64 * 64;
   if (cmax < 64) return GPTAQ_EWORKSPACE;
-  bool sparse = sparse_remainder(n);
-  if (sparse) {
-    // Positions take an eighth of a byte an entry.  In a workspace without room for them lo is dense if they would cost more than a tenth of the
-    // passes, each of which reads and writes H and dXXT: two sparse passes take as long as a dense one of 2048 tokens (4096 columns: 134
-    // and 139 us), of fewer tokens longer.
-    const int64_t c = pass_for(true);
-    sparse = c > 0 && 10 * ((tokens + c - 1) / c) <= 11 * ((tokens + cmax - 1) / cmax);
-    if (sparse) cmax = c;
-  }
+  if (cmax > 32768) cmax = 32768;    // keeps one fp32 running sum short (accuracy), and K in int32
   for (int64_t t0 = 0; t0 < tokens; t0 += cmax) {
     const int64_t c = tokens - t0 < cmax ? tokens - t0 : cmax;
     const int64_t cp = round_up(c, 64);
-    const Operands o = operands_at(ws, np, cp, sparse);
+    const Operands o = operands_at(ws, np, cp, row_of != nullptr);
     if (const int rc = launch_split(o, X + t0 * ldx, Xtilde + t0 * ldx, ldx, c, n, np, 0, row_of, s)) return rc;
     hipError_t e = launch_products(o, np, cp, n, H, dXXT, ldh, dxxt_upper, ws, ws_bytes, s);
     if (e != hipSuccess) { set_last_hip_error(e); return GPTAQ_ELAUNCH; }
@@ -425,9 +417,9 @@ static int accumulate_staged_impl(const uint16_t* X, const uint16_t* Xtilde, int
     return GPTAQ_EDIM;
   if (tokens > 0 && (((uintptr_t)X | (uintptr_t)Xtilde) & 15)) return GPTAQ_EDIM;
   const int64_t np = padded_n(n);
-  if (((uintptr_t)ws & 255) || ws_bytes < operand_bytes(np, CAP, false)) return GPTAQ_EWORKSPACE;
+  if (((uintptr_t)ws & 255) || ws_bytes < (size_t)(6 * np * CAP)) return GPTAQ_EWORKSPACE;
   hipStream_t s = (hipStream_t)stream;
-  const Operands o = operands_at(ws, np, CAP, sparse_remainder(n) && ws_bytes >= operand_bytes(np, CAP, true));
+  const Operands o = operands_at(ws, np, CAP, false);
   auto products = [&](int64_t cp) { return launch_products(o, np, cp, n, H, dXXT, ldh, dxxt_upper, ws, ws_bytes, s); };
   int64_t done = 0, pend = *pending;
   while (done < tokens) {

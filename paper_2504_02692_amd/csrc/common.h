@@ -31,14 +31,18 @@ struct GemmTerm {
   int64_t ktl, ktr;
 };
 
-// Kind 3: L[0] = hi and R[0] = X as above, k-tile-major.  Of lo, the remainder of hi, few entries are not zero, so it is stored in the
-// form of v_smfmac_f32_32x32x32_bf16: two values of every four tokens, 32 bytes for a row and k-tile of 32 tokens (the eight values of
-// tokens 0 .. 15, then those of 16 .. 31: the operands of two lanes).  L[1]: those values (lo1).  `positions`: where among its four tokens
-// each value sits, 16 bits an operand, for two k-tiles at a time: 8 bytes a row (tokens 0 .. 15 of the first and of the second k-tile, then
-// 16 .. 31 of each).  A 32 x 32 block (32 rows, one k-tile) in which some four tokens of a row hold more than two values is dense: `dense`
-// has a byte per block, k-tile by k-tile, and R[1] for these blocks as much as L[1] (lo2), the values of tokens 2 and 3 of such fours, of
-// which lo1 has those of tokens 0 and 1, and zeros for the others.  So the order in which a row's products are added does not depend
-// on the other rows of its block.  lo2 of a block that is not dense is not written and is not read as numbers.
+// Kind 3: L[0] = hi and R[0] = X as above, k-tile-major.  Of lo, the remainder of hi, few entries are not zero.  It is taken by 32 x 32 blocks
+// (32 columns of the caller's X, one k-tile) in one or two v_smfmac_f32_32x32x32_bf16, whose left operand is two values of every four
+// tokens and 16 bits that say which: 16 bytes for tokens 0 .. 15 of a row and 16 for 16 .. 31.
+// Sparse block, no four tokens of a row hold more than two values that are not zero: lo1 has these values, and positions say where they sit.
+// Dense block: lo1 has the values of tokens 0 and 1 of every four, lo2 those of 2 and 3, positions are the same for all.
+// By blocks (lo_rows = 0): L[1] is lo1, 32 bytes a row and k-tile.  R[1] has as many bytes again, 4 KB for the four blocks of 128 rows:
+// four heads of 16 bytes, four position fields of 128, four tails of 880.  A sparse block has kSparseMark in its head and 4 bytes a row in
+// its position field, and its tail is not used; head, position field and tail of a dense one, one after the other, are lo2.
+// By rows (lo_rows = 1), for rows in another order than the columns of X, so that the two kinds lie among each other: L[1] is 64
+// bytes a row and k-tile, lo1 and then lo2; of a sparse block's rows each 16 bytes of lo2 are kRowMark with the positions in its low half, and zeros.
+// The marks are NaNs that no remainder is: those that arithmetic makes are quiet.
+constexpr uint32_t kSparseMark = 0x7f817f81u, kRowMark = 0x7f810000u;
 constexpr int kMaxRemainderK = 32768;      // K of a problem of kind 3 (a multiple of 64)
 
 // C (+)= sum_t sum_pairs L R^T.  kind 0: L0 R0.  kind 1: L0 R0 + L1 R0 (two left operands share the
@@ -60,8 +64,7 @@ struct GemmProblem {
   int32_t split;         // > 1 (128-tiles, k_mode 0, store_mode 0): K in so many parts, each summed by workgroups of its own into
   float* partial;        // `partial` (tiles * split * 128 * 128 floats), and added to C by a second kernel; 0 counts as 1
   int32_t quartered;     // (256-tiles of kind 0 in a batch of kind 3, second problem) so many of its last tiles are taken as four of 128 x 128
-  const uint16_t* positions;   // kind 3 (see above)
-  const uint8_t* dense;
+  int32_t lo_rows;       // kind 3: how lo lies (see above)
   GemmTerm term[2];
 };
 

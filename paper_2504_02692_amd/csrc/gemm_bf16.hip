@@ -48,8 +48,8 @@ template <int N> __device__ __forceinline__ void wait_vm_and_lds() {
 }
 
 constexpr int kFlagBytes = kMaxRemainderK / kGemmBK;      // kind 3: a byte per k-tile
-constexpr int kLds256 = 3 * 3 * 256 * 64 + 4 * 256 * 8 + kFlagBytes;    // kind 3: 3 stages x 3 operand tiles, positions of 4 pairs of k-tiles, flags (2 x 4 and 4 x 2 tiles are smaller)
-constexpr int kLds128 = 3 * 3 * 128 * 64 + 4 * 128 * 8 + kFlagBytes;
+constexpr int kLds256 = 3 * (3 * 256 * 64 + 256 * 4) + kFlagBytes;    // kind 3: 3 stages x (3 operand tiles, positions), flags (2 x 4 and 4 x 2 tiles are smaller)
+constexpr int kLds128 = 3 * (3 * 128 * 64 + 128 * 4) + kFlagBytes;
 
 template <int BT, int KIND, bool MULTI>
 __device__ __forceinline__ void tile_loop(const GemmProblem& P, unsigned char* smem, int m0, int n0, int klo, int nk,
@@ -227,11 +227,9 @@ __device__ __forceinline__ void tile_loop(const GemmProblem& P, unsigned char* s
 __device__ __forceinline__ void dense_product(f32x16& acc, bf16x8 l, bf16x8 x) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(l), "v"(x));
 }
-constexpr int kPositions23 = 0xEEEE;       // the last two of every four tokens
-// 32 tokens; WHICH: the low or the high 16 bits of pos
-template <int WHICH> __device__ __forceinline__ void sparse_product(f32x16& acc, bf16x8 lo, bf16x16 x, int pos) {
-  if (WHICH) asm volatile("s_nop 1\n\tv_smfmac_f32_32x32x32_bf16 %0, %1, %2, %3 abid:1" : "+a"(acc) : "v"(lo), "v"(x), "v"(pos));
-  else asm volatile("s_nop 1\n\tv_smfmac_f32_32x32x32_bf16 %0, %1, %2, %3" : "+a"(acc) : "v"(lo), "v"(x), "v"(pos));
+constexpr uint16_t kPositions01 = 0x4444, kPositions23 = 0xEEEE;          // the first two of every four tokens, and the last two
+__device__ __forceinline__ void sparse_product(f32x16& acc, bf16x8 lo, bf16x16 x, uint16_t pos) {      // 32 tokens
+  asm volatile("s_nop 1\n\tv_smfmac_f32_32x32x32_bf16 %0, %1, %2, %3" : "+a"(acc) : "v"(lo), "v"(x), "v"(pos));
 }
 // lo2's products of a row of blocks, if on != 0 (the branch is inside, so that no accumulator has two ways to come from)
 __device__ __forceinline__ void sparse_products_if(int on, f32x16 (&a)[2], bf16x8 lo, const bf16x16 (&x)[2]) {
@@ -262,50 +260,54 @@ __device__ __forceinline__ void load_to_lds4(const unsigned char* src, unsigned 
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 4, 0, 0);
 }
 
-__device__ __align__(16) unsigned char zeros[2048];         // stands in for lo2 of a block that has none
+__device__ __align__(16) unsigned char zeros[4096];         // stands in for lo2 of a block that has none
 
-// Which of remainder_loop's two forms: dense 32 x 32 blocks per k-tile (of 8 and of 4) from which on lo2's products are taken with the
-// rest.  A k-tile of a workgroup alone on its CU waits for a branch that is not hidden by another workgroup: with 128-tiles that is from a
-// quarter on (2048 columns, 38 % dense: 627 us with branches, 583 without; with two workgroups a CU, 2736 columns full, 1245 / 1277).  With
-// 256-tiles almost all have to be (4096 columns, 69 %: 1555 / 1588, all: 1645 / 1598; 11008 9620 / 9950, 9980 / 10050).
+// Which of remainder_loop's two forms by blocks: from so many dense 32 x 32 blocks per k-tile on (of 8 and of 4, the mean over the k-tiles of a
+// tile) lo2's products are taken with the rest.  Us with branches / without, of 32768 tokens, upper form: 4096 columns, 69 % dense: 1550 / 1606, 96 %: 1629 /
+// 1605; 11008 columns 9695 / 9980, 10030 / 9960.  A workgroup alone on its CU waits for the branches, which another one does not hide: with
+// 128-tiles 2048 columns, 14 %: 596 / 600, 38 %: 644 / 598 (and, with two to a CU, 2736 columns in the full form 1249 / 1295).
 constexpr int kMany256 = 7, kMany128 = 1;
 
 // Kind 3: acc += (hi + lo) X^T, hi and X bf16 operands as above, lo the remainder of hi, of which few entries are not zero (GemmTerm says
 // how it is stored).  lo1 takes a v_smfmac_f32_32x32x32_bf16 per 32 x 32 block and k-tile, at twice the rate of a dense product; lo2 of
-// a dense block a second one.  Bound by its operand bytes (42 KB per 32 tokens of a 256-tile for 1536 clocks of products, 50 for 2048 where
-// all blocks are dense) and by the power-limited clock.  So what is done beside the products is little: positions come ready
-// to use and for two k-tiles at a time (taken apart here, from words of lo2, they cost 100 vector instructions a k-tile: 4096 columns and
-// 32768 tokens with all blocks dense 1946 us, so 1616; dense operands 1594), and a block's lo2 is fetched and multiplied behind a
-// branch of that block alone.
+// a dense block a second one.  Bound by its operand bytes (41 KB per 32 tokens of a 256-tile for 1536 clocks of products, 49 for 2048 where
+// all blocks are dense) and by the power-limited clock, so little is done beside the products: a block's positions are ready to use, and
+// its lo2 is fetched and multiplied behind a branch of that block alone.  (With the positions of a dense block's values among the words of
+// lo2, a word of two for each four tokens, taking them out was 100 vector instructions a k-tile: 4096 columns and 32768 tokens 1950 us where all blocks are
+// dense, so 1610; dense operands 1580.)
 template <int BT>
 __device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned char* smem, int m0, int n0, int nk, f32x16 (&acc)[BT / 64][BT / 64]) {
   constexpr int NSTAGE = 3, WT = BT / 2, FR = WT / 32;
-  constexpr int OPB = BT * 64, LOB = BT * 32, POSB = BT * 8;          // bytes of a k-tile of hi or X, of lo1 or lo2; of the positions of two k-tiles
-  constexpr int LO1 = 2 * OPB, LO2 = LO1 + LOB, STAGE_BYTES = LO2 + LOB;
-  constexpr int POS = NSTAGE * STAGE_BYTES, FLAGS = POS + 4 * POSB;   // the positions of eight k-tiles, and a byte per k-tile
+  constexpr int OPB = BT * 64, LOB = BT * 32, GROUP = 4096;            // bytes of a k-tile of hi or X, of lo1 or lo2; of 128 rows of R[1]
+  constexpr int LO1 = 2 * OPB, LO2 = LO1 + LOB, POS = LO2 + LOB, STAGE_BYTES = POS + BT * 4, FLAGS = NSTAGE * STAGE_BYTES;
   constexpr int LPW = BT / 64, LPWL = LOB / 4096;           // 1 KB loads per wave and k-tile: of hi or X, of lo1 or lo2
-  constexpr int POS_PARTS = BT / 128;                       // 1 KB parts of POSB
   if (nk <= 0) return;                                      // (nk is even)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const GemmTerm& tm = P.term[0];
   typedef const unsigned char* Bytes;
-  const int64_t kt = tm.ktl * 2, pos2 = kt / 8;             // bytes per k-tile of hi or X, and per two of the positions
+  const bool rows = P.lo_rows != 0;
+  const int64_t kt = tm.ktl * 2;                            // bytes per k-tile of hi or X
 
-  // A source is a base that the wavefront shares and a lane's offset.  hi and X: the tile format of tile_loop.  lo1 and lo2: a block has 64
+  // A source is a base that the wavefront shares and a lane's offset.  hi, X and lo by rows: the tile format of tile_loop.  lo1 and lo2: a block has 64
   // slots of 16 bytes in LDS, those of row r at 2 r and 2 r + 1, exchanged in every other eight rows, so that 16 lanes that read one half of
   // 16 rows meet 16 different slots of a 256-byte line.
   const uint32_t at64 = ((lane >> 4) * 4 + ((lane & 15) >> 2)) * 64 + ((lane & 3) ^ (lane >> 4)) * 16;
-  const uint32_t at32 = (lane >> 1) * 32 + ((lane ^ lane >> 4) & 1) * 16;
+  const int piece = lane ^ (lane >> 4 & 1);                 // of a block's 64 times 16 bytes
+  const uint32_t at32 = piece * 16;
+  const uint32_t lo2_step = piece == 0 ? 16 : piece < 9 ? 128 : 880;      // from block to block of R[1]
+  const uint32_t at_lo2 = (piece == 0 ? 0 : piece < 9 ? 48 + 16 * piece : 432 + 16 * piece) + (wave & (4 / LPWL - 1)) * LPWL * lo2_step;
+  // the positions that a wavefront fetches, 256 bytes of a group's 512 (with 128 rows two fetch the same)
+  const int pos_part = BT == 256 ? wave_s : wave_s & 1;
   struct TileSrc {
     Bytes hi, x, lo, lo2;
     int st, seq;                                            // where in LDS the tile goes, and its number in load order (not clamped)
   } c;
   c.hi = (Bytes)tm.L[0] + (int64_t)m0 * 64 + wave_s * (LPW * 1024);
   c.x = (Bytes)tm.R[0] + (int64_t)n0 * 64 + wave_s * (LPW * 1024);
-  c.lo = (Bytes)tm.L[1] + (int64_t)m0 * 32 + wave_s * (LPWL * 1024);
-  c.lo2 = (Bytes)tm.R[1] + (int64_t)m0 * 32 + wave_s * (LPWL * 1024);
+  c.lo = (Bytes)tm.L[1] + (rows ? (int64_t)m0 * 64 + wave_s * (LPW * 1024) : (int64_t)m0 * 32 + wave_s * (LPWL * 1024));
+  c.lo2 = (Bytes)tm.R[1] + (int64_t)m0 * 32;
   c.st = 0;
   c.seq = 0;
   auto next_tile = [&](int stage_at) {
@@ -314,7 +316,7 @@ __device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned ch
     const int64_t step = c.seq < nk ? kt : 0;
     c.hi += step;
     c.x += step;
-    c.lo += step / 2;
+    c.lo += rows ? step : step / 2;
     c.lo2 += step / 2;
   };
   // 1 KB, number `slab` of those that a wavefront fetches of an operand
@@ -324,12 +326,15 @@ __device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned ch
     if constexpr (q & 1) to_lds(c.x, at64, c.st + OPB + wave_s * (LPW * 1024), std::integral_constant<int, q / 2>{});
     else to_lds(c.hi, at64, c.st + wave_s * (LPW * 1024), std::integral_constant<int, q / 2>{});
   };
+  auto load_lo_rows = [&](auto slab) { to_lds(c.lo, at64, c.st + LO1 + wave_s * (LPW * 1024), slab); };
   auto load_lo1 = [&](auto slab) { to_lds(c.lo, at32, c.st + LO1 + wave_s * (LPWL * 1024), slab); };
-  auto load_lo2 = [&](Bytes base, auto slab) { to_lds(base, at32, c.st + LO2 + wave_s * (LPWL * 1024), slab); };
-  auto load_positions = [&](int pair, int part) {           // 256 bytes of a part
-    const int at = part * 1024 + wave_s * 256;
-    load_to_lds4((Bytes)P.positions + (int64_t)m0 * 8 + min(pair, nk / 2 - 1) * pos2 + at + (uint64_t)(uint32_t)(lane * 4),
-                 smem + POS + (pair & 3) * POSB + at);
+  auto load_lo2 = [&](Bytes base, auto number) {            // of block `number` of the wavefront's LPWL
+    constexpr int p = decltype(number)::value;
+    to_lds(base, at_lo2 + p * lo2_step, c.st + LO2 + (wave_s * LPWL + p) * 1024, std::integral_constant<int, 0>{});
+  };
+  auto lo2_of_wave = [&]() { return c.lo2 + (wave_s * LPWL >> 2) * GROUP; };
+  auto load_positions = [&]() {
+    load_to_lds4(c.lo2 + (pos_part >> 1) * GROUP + 64 + (pos_part & 1) * 256 + (uint64_t)(uint32_t)(lane * 4), smem + c.st + POS + pos_part * 256);
   };
 
   const int rl = lane & 31, half = lane >> 5;
@@ -337,40 +342,42 @@ __device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned ch
   auto frag = [&](const unsigned char* st, int kk, int i) {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(st + i * 2048 + fr_line * 256 + ((fr_hi | ((kk * 2 + half) ^ fr_x)) << 4)));
   };
-  const int lo_at = wm * (FR * 1024) + (2 * rl + (half ^ (rl >> 3 & 1))) * 16, pos_at = POS + wm * (FR * 256) + rl * 8 + half * 4;
+  const int lo_at = wm * (FR * 1024) + (2 * rl + (half ^ (rl >> 3 & 1))) * 16, pos_at = POS + wm * (FR * 128) + rl * 4 + half * 2;
   auto lo_frag = [&](const unsigned char* st, int i) { return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(st + lo_at + i * 1024)); };
-  auto read_positions = [&](int pair, int i) { return *reinterpret_cast<const int*>(smem + pos_at + (pair & 3) * POSB + i * 256); };
   unsigned char* flags = smem + FLAGS;
   auto blocks_of = [&](int f) { return (f >> (wave_s >> 1) * FR) & ((1 << FR) - 1); };      // this wavefront's
-  int fl0, fl1, fl2, mark;                                  // the dense blocks of the k-tiles it, it + 1, it + 2, and of the one behind them
+  int fl0 = 0, fl1 = 0, fl2 = 0, mark = 0;                                  // the dense blocks of the k-tiles it, it + 1, it + 2, and of the one behind them
 
   // Pipeline: one barrier per k-tile `it`, behind which tile it + 1 is in LDS and tile it in registers.  A 32-row block's products
   // (hi in two k-steps, lo1, lo2) are taken one after the other.  Between them, one at a time, the fragments of tile it + 1 are read: with
   // 256-tiles those of a block into its registers of tile it while the next block is multiplied (the last block's into two sets
   // in turn), with 128-tiles there are two sets for all; and tile it + NSTAGE is requested.
   // ALWAYS: lo2 is fetched (where a block has none, from zeros) and multiplied with the rest; else behind a branch per block.
-  auto run = [&](auto form) {
-    constexpr bool ALWAYS = decltype(form)::value;
-    constexpr int G = (ALWAYS ? 4 : 3) * FR, NSLOT = G * FR, LOADS = 2 * LPW + (ALWAYS ? 2 : 1) * LPWL, LOAD_SLOTS = NSLOT - 4;
+  // ROWS: lo by rows.  Whether a row is one of a sparse block, and its positions then, come out of the first words of its lo2; lo2 is multiplied
+  // where one of the 32 rows is not.
+  auto run = [&](auto layout, auto form) {
+    constexpr bool ROWS = decltype(layout)::value, ALWAYS = decltype(form)::value;
+    constexpr int G = (ALWAYS ? 4 : 3) * FR, NSLOT = G * FR, LOADS = 2 * LPW + (ROWS ? LPW : LPWL + 1 + (ALWAYS ? LPWL : 0)), LOAD_SLOTS = NSLOT - 4;
     constexpr bool TWO = FR == 2;                           // two whole sets
     constexpr int SETS = TWO ? 2 * FR : FR + 1;
-    constexpr int PER = 6, ROUNDS = TWO ? 1 : FR, ROUND_SLOTS = NSLOT / ROUNDS;         // reads of a block (with those of X that come along)
+    constexpr int PER = ROWS ? 6 : 7, ROUNDS = TWO ? 1 : FR, ROUND_SLOTS = NSLOT / ROUNDS;         // reads of a block (with those of X that come along)
     constexpr int READS = PER * FR / ROUNDS, READ_SLOTS = TWO ? NSLOT * 3 / 4 : ROUND_SLOTS / 2;
     bf16x8 a[SETS][2], b[2][2][FR], l1[SETS], l2[SETS];
-    int pos[FR], pos_next[FR];
+    uint16_t pos[SETS], p = 0;                              // (16 bits: the compiler would clear the others otherwise)
+    int on = 0;                                             // whether the block that is multiplied is dense; p: its positions
     auto set_of = [](int i, int s) { return TWO ? 2 * i + s : i < FR - 1 ? i : FR - 1 + s; };
     // of block i of the k-tile at st, to set t
     auto read_item = [&](const unsigned char* st, int i, int t, int item) {
-      if (item == 0) l1[t] = lo_frag(st + LO1, i);
-      else if (item == 1) l2[t] = lo_frag(st + LO2, i);
-      else a[t][item - 2] = frag(st + wm * (WT * 64), item - 2, i);
+      if (item == 0) l1[t] = ROWS ? frag(st + LO1 + wm * (WT * 64), 0, i) : lo_frag(st + LO1, i);
+      else if (item == 1) l2[t] = ROWS ? frag(st + LO1 + wm * (WT * 64), 1, i) : lo_frag(st + LO2, i);
+      else if (item < 4) a[t][item - 2] = frag(st + wm * (WT * 64), item - 2, i);
+      else pos[t] = *reinterpret_cast<const uint16_t*>(st + pos_at + i * 128);
     };
     auto read_x = [&](const unsigned char* st, int s, int k) { b[s][k / FR][k % FR] = frag(st + OPB + wn * (WT * 64), k / FR, k % FR); };
 #pragma unroll
     for (int i = 0; i < FR; ++i) {
 #pragma unroll
-      for (int item = 0; item < 4; ++item) read_item(smem, i, set_of(i, 0), item);
-      pos_next[i] = read_positions(0, i);
+      for (int item = 0; item < PER - 2; ++item) read_item(smem, i, set_of(i, 0), item);
 #pragma unroll
       for (int k = 0; k < 2; ++k) read_x(smem, 0, 2 * i + k);
     }
@@ -382,7 +389,7 @@ __device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned ch
         const unsigned char* nx = smem + nxt;
         auto both = [&](int j) { return __builtin_shufflevector(b[s][0][j], b[s][1][j], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15); };
         __builtin_amdgcn_sched_barrier(0);
-        wait_vm_and_lds<LOADS + ((s ^ 1) < POS_PARTS)>();   // (all but what the k-tile before has requested: so many at least)
+        wait_vm_and_lds<LOADS>();                           // (all but what the k-tile before has requested: so many at least)
         wg_barrier();
         __builtin_amdgcn_sched_barrier(0);
         const int now = blocks_of(fl0);
@@ -391,11 +398,24 @@ __device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned ch
           const int t = set_of(i, s);
           __builtin_amdgcn_sched_barrier(0);
           if constexpr (ph < 2) dense_product(acc[i][j], a[t][ph], b[s][ph][j]);
-          else if constexpr (ph == 2) sparse_product<s>(acc[i][j], l1[t], both(j), pos[i]);
-          else sparse_product<0>(acc[i][j], l2[t], both(j), kPositions23);
+          else if constexpr (ph == 2) sparse_product(acc[i][j], l1[t], both(j), p);
+          else sparse_product(acc[i][j], l2[t], both(j), kPositions23);
           __builtin_amdgcn_sched_barrier(0);
-          if constexpr (s == 0 && m < FR) pos[m] = pos_next[m];
-          if constexpr (s == 1 && m < FR) pos_next[m] = read_positions(it0 / 2 + 1, m);
+          if constexpr (q == FR) {
+            if constexpr (ROWS) {
+              u32x4 w = __builtin_bit_cast(u32x4, l2[t]);
+              const uint32_t x = w[0] ^ kRowMark;
+              const bool mark = x < 0x10000u;
+              p = mark ? (uint16_t)x : kPositions01;
+              w[0] = mark ? 0u : w[0];
+              l2[t] = __builtin_bit_cast(bf16x8, w);
+              const uint64_t those = __ballot(!mark);
+              on = __builtin_amdgcn_readfirstlane((uint32_t)those | (uint32_t)(those >> 32));
+            } else {
+              on = now >> i & 1;
+              p = on ? kPositions01 : pos[t];
+            }
+          }
           // (behind the last k-tile: a stale stage, not used)
           constexpr int round = m / ROUND_SLOTS, rq = m % ROUND_SLOTS;
           constexpr int r0 = (rq * READS + READ_SLOTS - 1) / READ_SLOTS, r1 = ((rq + 1) * READS + READ_SLOTS - 1) / READ_SLOTS;
@@ -405,26 +425,27 @@ __device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned ch
             if constexpr (x < 0) read_item(nx, block, set_of(block, s ^ 1), item);
             else read_x(nx, s ^ 1, 2 * (TWO ? block : round) + x);
           });
-          if constexpr (m == 1) {
+          if constexpr (!ROWS && m == 1) {
             const int f = __builtin_amdgcn_readfirstlane(mark);
             fl0 = fl1;
             fl1 = fl2;
             fl2 = c.seq < nk ? f : 0;
-            if constexpr (!ALWAYS) static_for<LPWL>([&](auto slab) { if (fl2 >> (wave_s * LPWL + decltype(slab)::value) & 1) load_lo2(c.lo2, slab); });
+            if constexpr (!ALWAYS) static_for<LPWL>([&](auto slab) { if (fl2 >> (wave_s * LPWL + decltype(slab)::value) & 1) load_lo2(lo2_of_wave(), slab); });
           }
-          if constexpr (m == NSLOT / 2) mark = flags[min(it + NSTAGE + 1, nk - 1)];
-          constexpr int l = m - 2, ALL = LOADS + (s < POS_PARTS), q0 = l * ALL / LOAD_SLOTS;
-          if constexpr (l >= 0 && l < LOAD_SLOTS && q0 < (l + 1) * ALL / LOAD_SLOTS) {
+          if constexpr (!ROWS && m == NSLOT / 2) mark = flags[min(it + NSTAGE + 1, nk - 1)];
+          constexpr int l = m - 2, q0 = l * LOADS / LOAD_SLOTS;
+          if constexpr (l >= 0 && l < LOAD_SLOTS && q0 < (l + 1) * LOADS / LOAD_SLOTS) {
             constexpr int w = q0 - 2 * LPW, w2 = w - LPWL;
-            if constexpr (q0 == LOADS) load_positions(it0 / 2 + 2, s);
-            else if constexpr (w < 0) load_hi_x(std::integral_constant<int, q0>{});
+            if constexpr (w < 0) load_hi_x(std::integral_constant<int, q0>{});
+            else if constexpr (ROWS) load_lo_rows(std::integral_constant<int, w>{});
+            else if constexpr (q0 == LOADS - 1) load_positions();
             else if constexpr (w2 < 0) load_lo1(std::integral_constant<int, w>{});
-            else load_lo2(fl2 >> (wave_s * LPWL + w2) & 1 ? c.lo2 : (Bytes)zeros, std::integral_constant<int, w2>{});
+            else load_lo2(fl2 >> (wave_s * LPWL + w2) & 1 ? lo2_of_wave() : (Bytes)zeros, std::integral_constant<int, w2>{});
           }
           if constexpr (!ALWAYS && q == G - 1) {
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (FR == 4) sparse_products_if(now >> i & 1, acc[i], l2[t], {both(0), both(1), both(2), both(3)});
-            else sparse_products_if(now >> i & 1, acc[i], l2[t], {both(0), both(1)});
+            if constexpr (FR == 4) sparse_products_if(on, acc[i], l2[t], {both(0), both(1), both(2), both(3)});
+            else sparse_products_if(on, acc[i], l2[t], {both(0), both(1)});
             __builtin_amdgcn_sched_barrier(0);
           }
           if constexpr (m == NSLOT - 1) { next_tile(nxt); cur = nxt; }
@@ -439,18 +460,29 @@ __device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned ch
       for (int j = 0; j < FR; ++j) settle(acc[i][j]);
   };
 
-  for (int p = 0; p < 2 * POS_PARTS; ++p) load_positions(p / POS_PARTS, p % POS_PARTS);
   static_for<NSTAGE>([&](auto t) {                          // (lo2 too: which blocks are dense is not known yet)
     static_for<2 * LPW>(load_hi_x);
-    static_for<LPWL>(load_lo1);
-    static_for<LPWL>([&](auto slab) { load_lo2(c.lo2, slab); });
+    if (rows) {
+      static_for<LPW>(load_lo_rows);
+    } else {
+      static_for<LPWL>(load_lo1);
+      static_for<LPWL>([&](auto number) { load_lo2(lo2_of_wave(), number); });
+      load_positions();
+    }
     next_tile((decltype(t)::value + 1) % NSTAGE * STAGE_BYTES);
   });
-  // which blocks of each k-tile are dense: a bit per block
+  if (rows) {
+    wait_vm_and_lds<0>();
+    wg_barrier();
+    run(std::true_type{}, std::false_type{});
+    return;
+  }
+  // which blocks of each k-tile are dense, from their heads: a bit per block
   for (int k = tid; k < nk; k += 256) {
-    const uint32_t* d = reinterpret_cast<const uint32_t*>(P.dense + k * (kt / 2048) + (m0 >> 5));
-    int f = (int)(d[0] * 0x10204080u >> 28);                // (bytes of 0 or 1: their bits side by side)
-    if (BT == 256) f |= (int)(d[1] * 0x10204080u >> 28) << 4;
+    const uint32_t* head = reinterpret_cast<const uint32_t*>((Bytes)tm.R[1] + (int64_t)k * (kt / 2) + (int64_t)m0 * 32);
+    int f = 0;
+#pragma unroll
+    for (int b = 0; b < BT / 32; ++b) f |= head[(b >> 2) * (GROUP / 4) + (b & 3) * 4] != kSparseMark ? 1 << b : 0;
     flags[k] = (unsigned char)f;
   }
   wait_vm_and_lds<0>();
@@ -475,9 +507,9 @@ __device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned ch
           *reinterpret_cast<u32x4*>(smem + t * STAGE_BYTES + LO2 + (wave_s * LPWL + p) * 1024 + lane * 16) = u32x4{0, 0, 0, 0};
     wait_vm_and_lds<0>();
     wg_barrier();
-    run(std::true_type{});
+    run(std::false_type{}, std::true_type{});
   } else {
-    run(std::false_type{});
+    run(std::false_type{}, std::false_type{});
   }
 }
 
