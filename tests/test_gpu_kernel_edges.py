@@ -561,3 +561,61 @@ def test_sparse_remainder_of_reordered_inputs(n, tokens, kind):
     B.gptaq_accumulate_upper_permuted(X, Xt, inv, Hp, Ap, ws)
     H = torch.triu(H) + torch.triu(H, 1).T
     assert torch.equal(Hp.triu(), H[perm][:, perm].triu()) and torch.equal(Ap.triu(), A[perm][:, perm].triu())
+
+
+@pytest.mark.parametrize("n", [1928, 3848])
+@pytest.mark.parametrize("upper", [False, True])
+def test_staged_sums_with_the_sparse_remainder(n, upper):
+    """Small chunks, the last one ragged, are the sums of one call, bit for bit; then another series in the same workspace, whose dense blocks are
+    others."""
+    ws = B.workspace(B.gptaq_accumulate_workspace_bytes(32768, n))
+    call = B.gptaq_accumulate_upper if upper else B.gptaq_accumulate
+    for seed, noise in ((1, 0.5), (2, 0.05)):
+        cuts = [0, 128, 192, 384, 461]
+        X, Xt = synth.make_activations_device(cuts[-1], n, seed, "x", "cuda", noise=noise)
+        H, A, Hs, As = (torch.zeros((n, n), device="cuda") for _ in range(4))
+        call(X, Xt, H, A, B.workspace(B.gptaq_accumulate_workspace_bytes(cuts[-1], n)))
+        pending = 0
+        for t0, t1 in zip(cuts, cuts[1:]):
+            pending = B.gptaq_accumulate_staged(X[t0:t1], Xt[t0:t1], Hs, As, ws, pending, flush=t1 == cuts[-1], upper=upper)
+        assert pending == 0
+        assert torch.equal(H.triu(), Hs.triu())
+        assert torch.equal(A.triu(), As.triu()) and (upper or torch.equal(A, As))
+
+
+@pytest.mark.parametrize("n,tokens", [(1928, 700), (3848, 1500)])
+def test_sums_in_the_library_s_own_workspace_with_the_sparse_remainder(n, tokens):
+    X, Xt = synth.make_activations_device(tokens, n, 4, "x", "cuda", noise=0.1)
+    H, A, Hn, An = (torch.zeros((n, n), device="cuda") for _ in range(4))
+    B.gptaq_accumulate(X, Xt, H, A, B.workspace(32 << 20))
+    B.gptaq_accumulate_noalloc(X, Xt, Hn, An)
+    assert torch.equal(H.triu(), Hn.triu()) and torch.equal(A, An)
+
+
+@pytest.mark.parametrize("n", [1928, 3848])
+@pytest.mark.parametrize("noise", [0.05, 0.5])
+def test_sparse_remainder_of_what_is_not_finite(n, noise):
+    """An infinity in X, one in X~ and a NaN in X~: the entries that are not finite are those of the exact sums, in every form, and the others are
+    what they should be.  (An entry is infinite or NaN as the products come: zeros of the remainder are not multiplied.)"""
+    tokens = 200
+    X, Xt = synth.make_activations_device(tokens, n, 6, "x", "cuda", noise=noise)
+    X[70, 40], Xt[71, 130], Xt[3, 1500] = float("inf"), float("-inf"), float("nan")
+    Xd, Dd = X.double(), Xt.double() - X.double()
+    refs = (Xd.T.contiguous() @ Xd, Dd.T.contiguous() @ Xd)
+    bound = 2.0 ** -24 * max(4.0, (tokens / 8) ** 0.5)
+    ws = B.workspace(B.gptaq_accumulate_workspace_bytes(tokens, n))
+    inv = torch.randperm(n, device="cuda", generator=torch.Generator(device="cuda").manual_seed(n)).int()
+    perm = torch.argsort(inv)
+    for form in ("full", "upper", "permuted"):
+        H, A = torch.zeros((n, n), device="cuda"), torch.zeros((n, n), device="cuda")
+        if form == "permuted":
+            B.gptaq_accumulate_upper_permuted(X, Xt, inv, H, A, ws)
+        else:
+            (B.gptaq_accumulate if form == "full" else B.gptaq_accumulate_upper)(X, Xt, H, A, ws)
+        for got, ref, tri in ((H, refs[0], True), (A, refs[1], form != "full")):
+            if form == "permuted":
+                ref = ref[perm][:, perm]
+            keep = torch.ones_like(got, dtype=torch.bool).triu() if tri else torch.ones_like(got, dtype=torch.bool)
+            assert torch.equal(got.isfinite() & keep, ref.isfinite() & keep)
+            keep &= ref.isfinite()
+            assert float((got[keep].double() - ref[keep]).norm() / ref[keep].norm()) <= bound
