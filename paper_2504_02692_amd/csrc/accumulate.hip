@@ -190,12 +190,12 @@ static bool sparse_remainder(int64_t n) { const int64_t t = (n + 127) / 128; ret
 
 // How many of H's last 256-tiles are taken as quarters: those past one tile for each of the 256 CUs, if they are few.  A tile of dXXT
 // takes 1.45 times as long as one of H, so most CUs are idle while a second tile of H runs on a few of them.  A quarter fetches twice
-// the bytes of its part of a tile: with many (56 at 4352 columns) the launch takes longer.  Measured, whole tiles / so, upper form, us: 3848
-// columns and 32768 tokens 1550 / 1487, 4096 1493 / 1440, 4096 and 2048 tokens 120 / 110; in the last of several rounds (6144 to 11008
-// columns) no difference.
-static int quartered_tiles(int64_t tiles, int64_t h, int64_t tokens) {
+// the bytes of its part of a tile: with many the launch takes longer (50 at 4352 columns: 1588 us to 1660).  Of the launches of 256-tiles only the upper
+// form of 16 tile rows has few, 272 tiles (3841 to 4096 columns): 15 rows have 240, 17 306, and the full form 345 and more.  Measured, whole
+// tiles / so, us: 4096 columns and 64 tokens 38 / 32, 512 53 / 45, 2048 118 / 101, 32768 1512 / 1390, 3848 and 32768 1485 / 1338.
+static int quartered_tiles(int64_t tiles) {
   const int64_t more = tiles - 256;
-  return tokens >= 1024 && more > 0 && more <= 32 && more <= h ? (int)round_up(more, 2) : 0;
+  return more > 0 && more <= 32 ? (int)more : 0;
 }
 
 static int64_t padded_n(int64_t n) { return round_up(n, gemm_tile_for(n, n)); }
@@ -292,7 +292,7 @@ static hipError_t launch_products(const Operands& o, int64_t np, int64_t cp, int
   h.term[0] = {{o.X, o.X}, {o.X, o.X}, 32, 32, np * 32, np * 32};
   if (a.kind == 3 && tile == 256) {
     const int64_t t = a.tiles_m, upper = t * (t + 1) / 2;
-    h.quartered = quartered_tiles((dxxt_upper ? upper : t * t) + upper, upper, cp);
+    h.quartered = quartered_tiles((dxxt_upper ? upper : t * t) + upper);
   }
   const int split = split_for(n, cp);
   if (split > 1 && o.bytes + partial_bytes(n, split) <= ws_bytes) {      // (a smaller workspace: sums in one part)

@@ -619,3 +619,13 @@ def test_sparse_remainder_of_what_is_not_finite(n, noise):
             assert torch.equal(got.isfinite() & keep, ref.isfinite() & keep)
             keep &= ref.isfinite()
             assert float((got[keep].double() - ref[keep]).norm() / ref[keep].norm()) <= bound
+
+
+@pytest.mark.parametrize("n,tokens", [(3848, 1), (4096, 64), (3976, 200)])
+def test_quarters_of_the_last_tiles_with_few_tokens(n, tokens):
+    X, Xt = synth.make_activations_device(tokens, n, 5, "x", "cuda")
+    ws = B.workspace(B.gptaq_accumulate_workspace_bytes(tokens, n))
+    Hf, Hu, Af, Au = (torch.ones((n, n), device="cuda") for _ in range(4))
+    B.gptaq_accumulate(X, Xt, Hf, Af, ws)
+    B.gptaq_accumulate_upper(X, Xt, Hu, Au, ws)
+    assert torch.equal(Hf.triu(), Hu.triu()) and torch.equal(Af.triu(), Au.triu())
