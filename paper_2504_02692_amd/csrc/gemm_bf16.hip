@@ -658,7 +658,7 @@ __device__ __forceinline__ void store_partial(float* dst, const f32x16 (&acc)[BT
 }
 
 // One BT x BT tile of C: tile number `wid` of the batch (see the numbering below).
-template <int BT, bool SPLIT, bool REMAINDER>
+template <int BT, bool CAPPED, bool SPLIT, bool REMAINDER>
 __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* smem, int wid) {
   constexpr int WT = BT / 2;             // wave tile edge
   constexpr int FR = WT / 32;            // 32x32 MFMA blocks per wave tile edge
@@ -733,6 +733,11 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* sme
   if constexpr (REMAINDER) {
     if (P.kind == 0) tile_loop<BT, 0, false>(P, smem, m0, n0, klo, nk, acc);
     else remainder_loop<BT>(P, smem, m0, n0, nk, acc);
+  } else if constexpr (CAPPED) {       // (kind 2 alone: launch_gemm refuses others)
+    if (P.nterm > 1) tile_loop<BT, 2, true>(P, smem, m0, n0, klo, nk, acc);
+    else tile_loop<BT, 2, false>(P, smem, m0, n0, klo, nk, acc);
+  // (No batch has kinds 0 and 1 with several terms, nor as 256-tiles here, but the code that the compiler makes for kind 2 is better with them in
+  // the kernel: without, two halves of 22016 x 4096 weights take 2551 us instead of 2522, and a solve with 1024 columns 977 instead of 967.)
   } else if (P.nterm > 1) {
     if (P.kind == 0) tile_loop<BT, 0, true>(P, smem, m0, n0, klo, nk, acc);
     else if (P.kind == 1) tile_loop<BT, 1, true>(P, smem, m0, n0, klo, nk, acc);
@@ -811,11 +816,11 @@ __global__ __launch_bounds__(256, BT == 128 ? 2 : 1) void gemm_nt_kernel(GemmBat
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if (!CAPPED) {
     if (SPLIT && (int)blockIdx.x < b.diag_wgs) { if (threadIdx.x < 64) diagonal_block(b.p[1], blockIdx.x); }
-    else gemm_tile<BT, SPLIT, REMAINDER>(b, smem, blockIdx.x - (SPLIT ? b.diag_wgs : 0));
+    else gemm_tile<BT, false, SPLIT, REMAINDER>(b, smem, blockIdx.x - (SPLIT ? b.diag_wgs : 0));
   } else {
     const int total = b.ntiles[0] + b.ntiles[1];
     for (int wid = blockIdx.x; wid < total; wid += gridDim.x) {
-      gemm_tile<BT, false, false>(b, smem, wid);
+      gemm_tile<BT, true, false, false>(b, smem, wid);
       __syncthreads();                   // the last fragment reads of this tile before the next tile's loads land in LDS
     }
   }
@@ -873,6 +878,7 @@ hipError_t launch_gemm(const GemmBatch& b, hipStream_t s) {
     if (q.split > 1 && (bb.tile != 128 || q.k_mode || q.store_mode || q.deal || !q.partial)) return hipErrorInvalidValue;
     if (i < bb.nprob && q.kind == 3 && (q.nterm != 1 || q.k_mode || q.K % (2 * kGemmBK) || q.K > kMaxRemainderK)) return hipErrorInvalidValue;
     if (i < bb.nprob && remainder && (q.split > 1 || b.max_wgs > 0 || (q.kind != 3 && (q.kind != 0 || q.nterm != 1)))) return hipErrorInvalidValue;
+    if (i < bb.nprob && b.max_wgs > 0 && q.kind != 2) return hipErrorInvalidValue;
     total += bb.ntiles[i];
     if (q.split > 1) part_tiles += bb.ntiles[i] / q.split;
   }
