@@ -361,7 +361,7 @@ __device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned ch
     constexpr bool TWO = FR == 2;                           // two whole sets
     constexpr int SETS = TWO ? 2 * FR : FR + 1;
     constexpr int PER = ROWS ? 6 : 7, ROUNDS = TWO ? 1 : FR, ROUND_SLOTS = NSLOT / ROUNDS;         // reads of a block (with those of X that come along)
-    constexpr int READS = PER * FR / ROUNDS, READ_SLOTS = TWO ? NSLOT * 3 / 4 : ROUND_SLOTS / 2;
+    constexpr int READS = PER * FR / ROUNDS, READ_SLOTS = TWO ? NSLOT - 1 : ROUND_SLOTS - 2;
     bf16x8 a[SETS][2], b[2][2][FR], l1[SETS], l2[SETS];
     uint16_t pos[SETS], p = 0;                              // (16 bits: the compiler would clear the others otherwise)
     int on = 0;                                             // whether the block that is multiplied is dense; p: its positions
