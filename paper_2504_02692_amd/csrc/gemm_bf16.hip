@@ -755,6 +755,7 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* sme
     store_partial<BT>(P.partial + (int64_t)(part * nt + id) * (BT * BT), acc);
     return;
   }
+  wait_vm_and_lds<0>();      // (said here again, where all loops meet: else the compiler counts their loads among the tile's and waits for all of these)
   store_tile<BT>(P.C, uniform(P.ldc), uniform(P.M), uniform(P.N), uniform(P.store_mode), m0, n0, acc);
 }
 
