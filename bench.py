@@ -314,13 +314,14 @@ def main() -> int:
                                   "note": "2 m n^2 algorithmic flop over super-block kernel + far GEMM time"},
     }
     # HBM-side bytes per launch of the dominant kernel come from two separate rocprofv3 --pmc runs of this same command
-    # (FETCH_SIZE, WRITE_SIZE); they are quoted only when the committed summary is for this workload and chunk size
+    # (FETCH_SIZE, WRITE_SIZE); they are quoted only when the committed summary is for this workload, chunk size and kernel
+    kernel = "gemm_nt_kernel<256, false, false, true>" if sparse else "gemm_nt_kernel<256, false>"
     traffic, traffic_src = None, None
     tpath = os.path.join(ROOT, "profiles", f"{wl.name}_block_hbm_traffic.json")
     if os.path.exists(tpath):
         tj = json.load(open(tpath))
         if tj.get("workload") == wl.name and tj.get("chunk", 32768) == args.chunk and not args.staged \
-                and tj.get("dxxt", "full") == ("upper" if upper else "full"):
+                and tj.get("dxxt", "full") == ("upper" if upper else "full") and tj.get("kernel", "").startswith(kernel + " "):
             traffic, traffic_src = tj.get("bytes_per_launch_avg"), "profiles/" + os.path.basename(tpath)
     out = {
         "metric": "ms_per_layer_solve", "value": ms_per_step / n_layers, "unit": "ms/layer",
@@ -333,7 +334,7 @@ def main() -> int:
                                f"dXXT: {'entries with col >= row (all that Eq. 17 reads in natural column order)' if upper else 'all entries'}; "
                                f"layers with a common input (q/k/v, gate/up) quantised as one stacked matrix",
                    "layers_per_step": n_layers},
-        "roofline": {"bound": "mfma", "kernel": "gemm_nt_kernel<256> (accumulate: H and dXXT)",
+        "roofline": {"bound": "mfma", "kernel": kernel + " (accumulate: H and dXXT)",
                      "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_BF16_TFLOPS, "traffic": traffic, "traffic_source": traffic_src,
                      "launches": launches, "avg_launch_ms": gemm_ms / max(1, launches),

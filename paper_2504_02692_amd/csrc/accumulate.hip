@@ -180,10 +180,10 @@ __global__ void invert_permutation_kernel(const int32_t* perm, int n, int32_t* i
 // blocks 2 % are dense where X and X~ differ by 5 % of a channel's deviation, 14 % at 10 %, 38 % at 15, 69 % at 20, 96 % at 30, all at 50.  Fewer matrix
 // instructions and operand bytes (41 KB instead of 48 for 32 tokens of a 256-tile, which is what bounds these launches).  By n alone: a staged
 // call writes its operands before the number of tokens is known, and the sums do not depend on the form of the call.  Measured, us
-// per call, dense operands / so, at differences of 5, 10, 20 and 50 %: 2048 columns and 32768 tokens 596 / 576, 599, 612, 617; 2736
-// full 1285 / 1126, 1167, 1331, 1341; 3072 and 16384 592 / 492, 499, 550, 552; 4096 and 2048 138 / 106, 109, 117, 120; 4096 and 32768 1585 / 1384, 1420,
-// 1591, 1638; 6144 and 16384 1586 / 1447, 1477, 1583, 1644; 11008 and 32768 9800 / 8930, 9080, 9860, 10170.  So where X~ is off by 20 % and more this is up to
-// 4 % slower than dense operands (the sparse instruction draws more power, and positions are 2 % more bytes).  With fewer columns a
+// per call, dense operands / so, at differences of 5, 10, 20 and 50 %: 2048 columns and 32768 tokens 592 / 571, 597, 609, 627; 2736
+// full 1275 / 1136, 1152, 1324, 1338; 3072 and 16384 594 / 487, 495, 547, 549; 4096 and 2048 138 / 105, 108, 117, 120; 4096 and 32768 1605 / 1383, 1431,
+// 1576, 1640; 6144 and 16384 1600 / 1455, 1479, 1579, 1646; 11008 and 32768 9710 / 8803, 9032, 9699, 10081.  So where X~ is off by more than 20 % (with
+// 128-tiles by more than 10) this is up to 5 % slower than dense operands: the sparse instruction draws more power, and positions are 2 % more bytes.  With fewer columns a
 // workgroup has its CU to itself and the loop's branches show: 512 and 4096 tokens 54 / 58, 1536 and 4096 58 / 66.  Error of dXXT against 64
 // bits 2.91e-7 (dense operands 2.96e-7) at 4104 columns and 6144 tokens.
 static bool sparse_remainder(int64_t n) { const int64_t t = (n + 127) / 128; return t * (t + 1) > 256; }

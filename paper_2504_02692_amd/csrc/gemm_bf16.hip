@@ -273,8 +273,8 @@ constexpr int kMany256 = 7, kMany128 = 1;
 // a dense block a second one.  Bound by its operand bytes (41 KB per 32 tokens of a 256-tile for 1536 clocks of products, 49 for 2048 where
 // all blocks are dense) and by the power-limited clock, so little is done beside the products: a block's positions are ready to use, and
 // its lo2 is fetched and multiplied behind a branch of that block alone.  (With the positions of a dense block's values among the words of
-// lo2, a word of two for each four tokens, taking them out was 100 vector instructions a k-tile: 4096 columns and 32768 tokens 1950 us where all blocks are
-// dense, so 1610; dense operands 1580.)
+// lo2, a word of two for each four tokens, taking them out was 100 vector instructions a k-tile: 4096 columns and 32768 tokens 1974 us where all blocks are
+// dense, so 1640; dense operands 1620.)
 template <int BT>
 __device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned char* smem, int m0, int n0, int nk, f32x16 (&acc)[BT / 64][BT / 64]) {
   constexpr int NSTAGE = 3, WT = BT / 2, FR = WT / 32;
@@ -537,7 +537,8 @@ struct TileBuffer {
 // An element is addressed as (lane offset) + (scalar offset of its row) + (immediate), one instruction each; at the edge of the
 // matrix, where a row or a column lies outside, its load reads the tile's first element instead and its store is masked.  With a
 // branch per element and 64-bit products per address, ~35 instructions each, a 256-tile took ~45 us here: accumulate_upper at
-// n = 4096, where 16 of the 256 CUs have two tiles, took 115 us for 64 tokens and 197 us for 2048; now 56 and 136.
+// n = 4096, where 16 of the 256 CUs have two tiles, took 115 us for 64 tokens and 197 us for 2048; so 56 and 136 (with the sparse remainder and
+// H's last tiles as quarters 32 and 105).
 // For C += acc the loads run two pieces (of eight rows per half wave) ahead of the stores.  Rows so far apart that a tile is
 // out of reach of 32-bit offsets take 64-bit addresses (WIDE).
 template <int BT, int MODE, bool EDGE, bool WIDE>
