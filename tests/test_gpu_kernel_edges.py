@@ -527,17 +527,17 @@ def _accumulate_us(call, n, tokens, noise, repeats=5):
 
 def test_dense_remainder_costs_what_its_products_cost():
     """Where every block of the remainder is dense, a tile of dXXT takes 2 units of products instead of 1.5 and 50 KB instead of 42 per
-    k-tile, and H 1 and 32 either way: 1.2 times the time (1.19 measured).  What finds its positions costs nothing beside that
+    k-tile, and H 1 and 32 either way: 1.2 times the time, as measured.  What finds its positions costs nothing beside that
     (taken from words of lo2 it was 1.5 times)."""
     assert _accumulate_us(B.gptaq_accumulate_upper, 4096, 32768, 0.5) <= 1.3 * _accumulate_us(B.gptaq_accumulate_upper, 4096, 32768, 0.001)
 
 
 def test_reordered_inputs_cost_what_others_do():
-    """gptaq_accumulate_upper_permuted writes its operands to scattered rows and fetches all of lo (1.04 times gptaq_accumulate_upper; with
-    every block taken as a dense one it was 1.45 times)."""
+    """gptaq_accumulate_upper_permuted fetches all of lo, 48 KB a k-tile of a tile of dXXT instead of 41, which is 1.17 times, and writes
+    its operands to scattered rows, 5 % more (1.13 measured; with every block taken as a dense one it was 1.45 times)."""
     inv = torch.randperm(4096, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1)).int()
     permuted = lambda X, Xt, H, A, ws: B.gptaq_accumulate_upper_permuted(X, Xt, inv, H, A, ws)
-    assert _accumulate_us(permuted, 4096, 32768, 0.05) <= 1.2 * _accumulate_us(B.gptaq_accumulate_upper, 4096, 32768, 0.05)
+    assert _accumulate_us(permuted, 4096, 32768, 0.05) <= 1.3 * _accumulate_us(B.gptaq_accumulate_upper, 4096, 32768, 0.05)
 
 
 @pytest.mark.parametrize("n,tokens", [(1928, 96), (2496, 2080), (3848, 224)])
