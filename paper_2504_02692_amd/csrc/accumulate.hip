@@ -181,7 +181,7 @@ __global__ void invert_permutation_kernel(const int32_t* perm, int n, int32_t* i
 // instructions and operand bytes (41 KB instead of 48 for 32 tokens of a 256-tile, which is what bounds these launches).  By n alone: a staged
 // call writes its operands before the number of tokens is known, and the sums do not depend on the form of the call.  Measured, us
 // per call, dense operands / so, at differences of 5, 10, 20 and 50 %: 2048 columns and 32768 tokens 592 / 571, 597, 609, 627; 2736
-// full 1275 / 1136, 1152, 1324, 1338; 3072 and 16384 594 / 487, 495, 547, 549; 4096 and 2048 138 / 105, 108, 117, 120; 4096 and 32768 1605 / 1383, 1431,
+// full 1275 / 1108, 1138, 1317, 1332; 3072 and 16384 594 / 487, 495, 547, 549; 4096 and 2048 138 / 105, 108, 117, 120; 4096 and 32768 1605 / 1383, 1431,
 // 1576, 1640; 6144 and 16384 1600 / 1455, 1479, 1579, 1646; 11008 and 32768 9710 / 8803, 9032, 9699, 10081.  So where X~ is off by more than 20 % (with
 // 128-tiles by more than 10) this is up to 5 % slower than dense operands: the sparse instruction draws more power, and positions are 2 % more bytes.  With fewer columns a
 // workgroup has its CU to itself and the loop's branches show: 512 and 4096 tokens 54 / 58, 1536 and 4096 58 / 66.  Error of dXXT against 64

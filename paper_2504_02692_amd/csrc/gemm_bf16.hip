@@ -272,7 +272,7 @@ constexpr int kMany256 = 7, kMany128 = 1;
 // how it is stored).  lo1 takes a v_smfmac_f32_32x32x32_bf16 per 32 x 32 block and k-tile, at twice the rate of a dense product; lo2 of
 // a dense block a second one.  Bound by its operand bytes (41 KB per 32 tokens of a 256-tile for 1536 clocks of products, 49 for 2048 where
 // all blocks are dense) and by the power-limited clock, so little is done beside the products: a block's positions are ready to use, and
-// its lo2 is fetched and multiplied behind a branch of that block alone.  (With the positions of a dense block's values among the words of
+// its lo2 is fetched, and with 256-tiles multiplied, behind a branch of that block alone.  (With the positions of a dense block's values among the words of
 // lo2, a word of two for each four tokens, taking them out was 100 vector instructions a k-tile: 4096 columns and 32768 tokens 1974 us where all blocks are
 // dense, so 1640; dense operands 1620.)
 template <int BT>
@@ -359,6 +359,8 @@ __device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned ch
     constexpr bool ROWS = decltype(layout)::value, ALWAYS = decltype(form)::value;
     constexpr int G = (ALWAYS ? 4 : 3) * FR, NSLOT = G * FR, LOADS = 2 * LPW + (ROWS ? LPW : LPWL + 1 + (ALWAYS ? LPWL : 0)), LOAD_SLOTS = NSLOT - 4;
     constexpr bool TWO = FR == 2;                           // two whole sets
+    // lo2 of a k-tile's two blocks behind them, with one branch for both where it is rare (2736 columns full 1145 us, so 1108)
+    constexpr bool LAST = TWO && !ROWS && !ALWAYS;
     constexpr int SETS = TWO ? 2 * FR : FR + 1;
     constexpr int PER = ROWS ? 6 : 7, ROUNDS = TWO ? 1 : FR, ROUND_SLOTS = NSLOT / ROUNDS;         // reads of a block (with those of X that come along)
     constexpr int READS = PER * FR / ROUNDS, READ_SLOTS = TWO ? NSLOT - 1 : ROUND_SLOTS - 2;
@@ -442,7 +444,7 @@ __device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned ch
             else if constexpr (w2 < 0) load_lo1(std::integral_constant<int, w>{});
             else load_lo2(fl2 >> (wave_s * LPWL + w2) & 1 ? lo2_of_wave() : (Bytes)zeros, std::integral_constant<int, w2>{});
           }
-          if constexpr (!ALWAYS && q == G - 1) {
+          if constexpr (!ALWAYS && !LAST && q == G - 1) {
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (FR == 4) sparse_products_if(on, acc[i], l2[t], {both(0), both(1), both(2), both(3)});
             else sparse_products_if(on, acc[i], l2[t], {both(0), both(1)});
@@ -451,6 +453,12 @@ __device__ __forceinline__ void remainder_loop(const GemmProblem& P, unsigned ch
           if constexpr (m == NSLOT - 1) { next_tile(nxt); cur = nxt; }
         });
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (LAST) {
+          if (__builtin_expect(now != 0, 0)) {
+#pragma unroll
+            for (int i = 0; i < FR; ++i) sparse_products_if(now >> i & 1, acc[i], l2[set_of(i, s)], {both(0), both(1)});
+          }
+        }
       });
     }
     wait_vm_and_lds<0>();   // the surplus loads past the last k-tile
