@@ -87,7 +87,7 @@ inline int gemm_tile_for(int64_t M, int64_t N) {
   return (M >= 1024 && N >= 1024 && t256 >= 224) ? 256 : 128;
 }
 
-// fp64-grade rank-k products through digit-sliced int8 MFMA (gemm_i8s.hip).  A sliced operand holds
+// fp64-grade rank-k products through digit-sliced int8 MFMA (gemm_i8s.h).  A sliced operand holds
 // kI8Planes digit planes of rows_pad x kI8MaxK signed bytes (rows_pad a multiple of 128; rows and k beyond the
 // source are zero) and one power-of-two scale (its exponent) per row.
 constexpr int kI8Planes = 6;
@@ -104,34 +104,27 @@ struct I8Gemm {
   const uint8_t* A; int64_t a_plane, a_chunk; const int32_t* sa;
   const uint8_t* B; int64_t b_plane, b_chunk; const int32_t* sb;
   double* C; int64_t ldc;
-  int32_t M, N, nchunk, beta, upper_only, tiles_m, tiles_n, ntile;
+  int32_t M, N, nchunk, beta, upper_only, tiles_m, tiles_n, tile0, ntile;      // tiles tile0 .. tile0 + ntile - 1 of the list
   double alpha;
 };
-// Slices the R x K matrix with element (r, k) at src[r * sr + k * sk] (one stride must be 1, K <= kI8MaxK).
-hipError_t launch_slice_i8(const double* src, int64_t sr, int64_t sk, int R, int K, const I8Operand& o, hipStream_t s);
-// C = beta C + alpha A B^T over rows [a_row0, a_row0 + M) of A and [b_row0, b_row0 + N) of B (offsets multiples
-// of 128 and 64); upper_only skips the tiles entirely below the diagonal of C.
-hipError_t launch_gemm_i8s(const I8Operand& A, int a_row0, const I8Operand& B, int b_row0, double* C, int64_t ldc, int M,
-                           int N, int K, double alpha, int beta, int upper_only, hipStream_t s);
-
 // The fp64 part of the factor sweep, one outer block of kFactorBlock columns [o0, o0 + kFactorBlock) at a time (o0 a multiple of
-// it; the block may reach past n).  V holds the block's factor as 16 x 16 tiles, (k, a) at (16 k + a) * 256 doubles.
+// it; the block may reach past n).  V holds the block's factor as 16 x 16 tiles, (k, a) at (16 k + a) * 256 doubles; T the second
+// half's own block after the first half's update, as tiles (a, b), a >= b, at (a (a + 1) / 2 + b) * 256.
 constexpr int kFactorBlock = 256;
-constexpr size_t kFactorTileBytes = (size_t)kFactorBlock * kFactorBlock * 8;
+constexpr size_t kFactorTileBytes = (size_t)kFactorBlock * kFactorBlock * 8, kHalfTileBytes = (size_t)36 * 256 * 8;
+constexpr size_t kBlockSyncBytes = 512;
 struct BlockFactor {
   const double* F; int64_t ldf; int n, o0;
   int32_t* info;                     // set to 1 + index of the first pivot that is not positive, unless set already
-  double* V;
+  double *V, *T;
+  int32_t* sync;                     // kBlockSyncBytes, zeros
 };
 struct BlockPanel {
-  double* F; int64_t ldf; int n, o0;
-  const double* V;
   I8Operand Vs;                      // out: digits of V_I,OB, rows I = 0 .. o0 - 1
   I8Operand Ucol;                    // out: digits of the columns of U_OB,OB
-  double* Uob;                       // out: U_OB,OB, kFactorBlock x kFactorBlock, zeros below the diagonal; the upper part also to F
+  double* Uob;                       // out: U_OB,OB, kFactorBlock x kFactorBlock by columns, zeros below the diagonal;
+  double* Uout;                      // its upper part also to F_OB,OB
 };
-hipError_t launch_block_factor(const BlockFactor& a, hipStream_t s);
-hipError_t launch_block_panel(const BlockPanel& a, hipStream_t s);
 
 // Column loop + in-super-block updates of a whole super-block in one launch (quantize_sb.hip).
 constexpr int kSbCols = 1024;       // columns per super-block

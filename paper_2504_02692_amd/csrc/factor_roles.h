@@ -1,9 +1,10 @@
-// The fp64 part of the factor sweep (Algorithm 1, line 3): one 256-column outer block OB at a time,
-//   block_factor_kernel : F_OB,OB = V V^T, V upper triangular, in one workgroup;
-//   block_panel_kernel  : V_I,OB = F_I,OB V_OB,OB^-T for the rows I above OB, and U_OB,OB = V_OB,OB^-1, written as the digit
-//                         operands of the rank-256 products (gemm_i8s.hip).
+// The fp64 part of the factor sweep (Algorithm 1, line 3), as parts of the sweep's launches (factor_sweep.hip).  One 256-column outer
+// block OB at a time:
+//   factor_role   : F_OB,OB = V V^T, V upper triangular, in one workgroup;
+//   panel_role    : V_I,OB = F_I,OB V_OB,OB^-T for the rows I above OB, and U_OB,OB = V_OB,OB^-1, written as the digit
+//                   operands of the rank-256 products (gemm_i8s.h).
 //
-// Both count indices of the block from its end, r -> 255 - r, which turns the factorisation "from the last column to the
+// All count indices of the block from its end, r -> 255 - r, which turns the factorisation "from the last column to the
 // first" into the usual one: S = V V^T with V lower triangular, columns 0, 1, ... (S, V, W = V^-1 below are in this order;
 // where the matrix ends the block is filled up with the identity, which then comes first and couples to nothing).
 //
@@ -14,17 +15,17 @@
 // so  T_ab^T -= X_b X_a^T  and  X_a^T = W_k T_ak^T  chain from accumulator to operand without a shuffle.  In memory and
 // LDS a tile is two runs of 64 x 16 bytes: registers 0, 1 of every lane, then 2, 3.
 //
-// What bounds them: the factorisation is a chain of 256 column steps (each a reciprocal, its Newton steps and an update,
-// ~100 clocks) on one CU beside 680 tile products of 256 clocks on three of its SIMDs; the panel kernel is a chain of 16 tile
-// columns.  An f64 MFMA (64 clocks for 1024 products) is no faster than v_fma_f64, but its operands are one register a lane,
-// where fp64 FMAs on 64 x 64 tiles were bound by their LDS reads and by solves of one wavefront.  Measured per block of 256
-// columns: factorisation 152 -> 47 us alone (113K clocks; the MFMAs keep the matrix pipes of their three SIMDs busy for 68K of them,
-// most of that in the first half; the second half is the column steps, 3.0K clocks per tile), in gptaq_prepare beside the other
-// chain's products 54 on average at n = 4096 and 76 at n = 11008; panel 50 -> 15 us alone (35K clocks, of which a wavefront issues 21 %
-// and waits for loads 34 %), 20 and 81 in gptaq_prepare, with the digits (8 us) and the inverse (a kernel of 46 us on the other
-// chain) in it.  gptaq_prepare 4.41 -> 2.04 ms at n = 4096, 22.5 -> 18.2 at n = 11008.
+// What bounds them: one chain.  A block of 256 columns of a small matrix, in us: 2.8 until the first tiles are there, 14 for each half
+// (a tile 1.7 to 1.9: 1.28 of its 16 column steps, each a reciprocal, its Newton steps and an update; 0.5 until the next diagonal tile is
+// updated and handed over), 1.5 + 1.7 + 3.5 between them for the second half's rows (the last column, the rows from the other workgroups, the
+// update and its way back), 1.5 for the last column of the panel and 4.6 for its digits and their way to memory: 47 in all, and no more
+// than 55 beside products.  As launches of their own, the factorisation in one workgroup of eight wavefronts, panel and products on two
+// streams, it was 48 + 16 and 15 to 20 of events; with a launch for each half, the rows and the update between them 16 + 7 + 6 + 16.
+// An f64 MFMA (64 clocks for 1024 products) is no faster than v_fma_f64, but its operands are one register a lane.
+// gptaq_prepare at n = 512 / 4096 / 11008: 243 / 1976 / 18100 us -> 166 / 1620 / 17000.
+#pragma once
 #include "common.h"
-#include "i8_digits.h"
+#include "gemm_i8s.h"
 #include <utility>
 
 namespace gptaq {
@@ -34,6 +35,7 @@ typedef __attribute__((ext_vector_type(4))) double f64x4;
 
 namespace {
 constexpr int NT = kFactorBlock / 16;             // tiles per side of the block
+constexpr int NH = NT / 2;                        // and of a half
 constexpr int TILE = 256;                         // doubles of a tile
 
 __device__ __forceinline__ f64x4 load_tile(const double* t, int lane) {
@@ -43,6 +45,11 @@ __device__ __forceinline__ f64x4 load_tile(const double* t, int lane) {
 __device__ __forceinline__ void store_tile(double* t, int lane, f64x4 x) {
   *reinterpret_cast<f64x2*>(t + 2 * lane) = f64x2{x[0], x[1]};
   *reinterpret_cast<f64x2*>(t + 128 + 2 * lane) = f64x2{x[2], x[3]};
+}
+// the same for a reader on another CU in the same launch: written through to where all XCDs see it (see BlockSync)
+__device__ __forceinline__ void publish_tile(double* t, int lane, f64x4 x) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) __hip_atomic_store(t + (v >> 1) * 128 + 2 * lane + (v & 1), x[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // lane whose part of a stored tile is the A operand of lane l
 __device__ __forceinline__ int operand_lane(int lane) { return (lane & 48) | (4 * (lane & 3)) | ((lane >> 2) & 3); }
@@ -98,8 +105,48 @@ __device__ __forceinline__ double rsqrt_of(double x) {
   return fma(r * e, fma(e, 0.375, 0.5), r);
 }
 
+// ---- several workgroups of one launch work on a block: one factors it, others follow it tile column by tile column.  A workgroup
+// draws a number when it starts, and the parts are dealt in the order of the numbers, so that whoever waits does so for workgroups that
+// are running already, whatever the order in which the hardware starts them; and nobody waits for the workgroups that do products.
+// What one writes for another goes past its XCD's L2 (publish_tile), and a flag behind it once the stores have been acknowledged.  The
+// reader's own L2 cannot hold an older copy: nothing reads these lines earlier in the launch, and a launch starts with clean caches.
+// All words are 0 before the call's first launch.
+struct BlockSync {
+  static constexpr int kTicket = 56, kWords = 128;
+  static constexpr int column(int k, int w) { return 3 * k + w; }          // W_kk and the rows of wavefront w + 1 of tile column k
+  static constexpr int row(int m) { return 48 + m; }                       // tile row NH + m on the first half's columns
+  static constexpr int tile(int m, int w) { return 64 + 4 * m + w; }       // tiles w, w + 4 of row m of the second half's updated block
+};
+__device__ __forceinline__ void set_flag(int32_t* sync, int word, int lane) {      // (behind a wait for the stores it stands for)
+  if (lane == 0) __hip_atomic_store(sync + word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <int N> __device__ __forceinline__ void wait_stores() {           // all but the last N memory accesses of the wavefront are done
+  asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
+}
+struct Flags {
+  int32_t* words;                                // 64 of them, one a lane
+  int32_t* info;
+  int give_up;                                   // what info says if nothing comes
+  int lane;
+  uint64_t seen = 0;
+  __device__ __forceinline__ bool ready(uint64_t need) const { return (seen & need) == need; }
+  // Waits until the flags of `need` are set.  (Two seconds are a hundred thousand times what it takes: only where something else writes
+  // into the workspace meanwhile does it end without them, and says so.)
+  __device__ __forceinline__ void wait(uint64_t need) {
+    for (int i = 0; !ready(need); ++i) {
+      seen = __ballot(__hip_atomic_load(words + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0);
+      if (!ready(need)) __builtin_amdgcn_s_sleep(2);
+      if (i == 1 << 20) {
+        if (lane == 0) atomicCAS(info, 0, give_up);
+        seen = ~0ull;
+      }
+    }
+    asm volatile("" ::: "memory");
+  }
+};
+
 struct FactorShared {
-  double x[NT][TILE];        // V_ak of the current tile column k
+  double x[NH][TILE];        // V_ak of the current tile column k
   double diag[TILE];         // tile (k, k) before its factorisation, entry (row, column) at 16 column + row
   double w[TILE];            // W_kk, as a stored tile
 };
@@ -185,46 +232,49 @@ __device__ __forceinline__ void factor_diag(FactorShared& sh, int32_t* info, int
   }
 }
 
-// ---- the tile rows.  Wavefront 0 factors the diagonal tiles and has its SIMD to itself but for wavefront 4, which moves results
-// to memory: an f64 MFMA holds the pipe that f64 VALU instructions need for 64 clocks, and the chain of column steps must not
-// wait for it.  The other six hold the tiles (a, 0 .. a) of these rows a, a SIMD's two about as many as another's at every step:
+// entry block (a, b) of OB, a >= b, as a tile: both halves of a diagonal one from the upper triangle of F, the identity past column n
+__device__ __forceinline__ f64x4 load_block_tile(const BlockFactor& a, int ta, int tb, int r, int g) {
+  const int last = a.o0 + kFactorBlock - 1, row = 16 * ta + r;
+  if (tb < ta) return load_row4(a.F, a.ldf, a.n, last - row, last - 3 - 16 * tb - 4 * g);
+  f64x4 d;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int col = 16 * tb + 4 * g + v, fi = last - max(row, col), fj = last - min(row, col);
+    const double x = a.F[(int64_t)min(fi, a.n - 1) * a.ldf + min(fj, a.n - 1)];
+    d[v] = fj < a.n ? x : (fi == fj ? 1.0 : 0.0);
+  }
+  return d;
+}
+// tile (a, b) of the second half's own block after the first half's update, a >= b
+__device__ __forceinline__ double* half_tile(const BlockFactor& a, int ta, int tb) { return a.T + (ta * (ta + 1) / 2 + tb) * TILE; }
+__device__ __forceinline__ double* factor_tile(double* V, int k, int a) { return V + ((int64_t)k * NT + a) * TILE; }
+
+// ---- the block's factorisation, one workgroup, a half after the other.  Wavefront 0 factors the diagonal tiles; the other three hold
+// the tiles (a, 0 .. a) of these rows a of the half in registers from load to end, about as many products each:
 __host__ __device__ constexpr int tile_row(int w, int i) {
-  constexpr int8_t rows[8][4] = {{-1, -1, -1, -1}, {15, 4, 3, -1}, {14, 5, 2, -1}, {13, 6, 1, 0},
-                                 {-1, -1, -1, -1}, {10, 9, -1, -1}, {11, 8, -1, -1}, {12, 7, -1, -1}};
+  constexpr int8_t rows[4][3] = {{-1, -1, -1}, {7, 1, 0}, {6, 3, -1}, {5, 4, 2}};
   return rows[w][i];
 }
-__host__ __device__ constexpr int tile_rows(int w) { int n = 0; while (n < 4 && tile_row(w, n) >= 0) ++n; return n; }
+__host__ __device__ constexpr int tile_rows(int w) { int n = 0; while (n < 3 && tile_row(w, n) >= 0) ++n; return n; }
 __host__ __device__ constexpr int tile_base(int w, int i) { int b = 0; for (int q = 0; q < i; ++q) b += tile_row(w, q) + 1; return b; }
 
-template <int W>
+template <int W, int HALF>
 __device__ __forceinline__ void factor_rows(const BlockFactor& a, FactorShared& sh) {
-  constexpr int NR = tile_rows(W);
+  constexpr int NR = tile_rows(W), first = NH * HALF;
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, ol = operand_lane(lane);
   f64x4 t[tile_base(W, NR)];
-  // A CU takes ~14 bytes per clock of what other CUs have just written, 20K clocks for the whole block: so only two tile columns
-  // are waited for at the start, and the others are requested kAhead columns ahead of their first update (step 0)
-  constexpr int kAhead = 4;
-  const int last = a.o0 + kFactorBlock - 1;
-  auto load_column = [&](int b) {
+  if (HALF) {
+    Flags f{a.sync + 64, a.info, a.o0 + kFactorBlock / 2, lane};
+    f.wait(0xffffffffull);
+  }
 #pragma unroll
-    for (int i = NR - 1; i >= 0; --i) {
-      if (b > tile_row(W, i)) continue;
-      const int row = 16 * tile_row(W, i) + r;
-      f64x4& d = t[tile_base(W, i) + b];
-      if (b < tile_row(W, i)) {
-        d = load_row4(a.F, a.ldf, a.n, last - row, last - 3 - 16 * b - 4 * g);
-      } else {
+  for (int b = 0; b < NH; ++b) {                               // (in the order in which they are needed)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {                                            // both halves from the upper triangle of F
-          const int col = 16 * b + 4 * g + v, fi = last - max(row, col), fj = last - min(row, col);
-          const double x = a.F[(int64_t)min(fi, a.n - 1) * a.ldf + min(fj, a.n - 1)];
-          d[v] = fj < a.n ? x : (fi == fj ? 1.0 : 0.0);
-        }
-      }
-    }
+    for (int i = NR - 1; i >= 0; --i)
+      if (b <= tile_row(W, i))
+        t[tile_base(W, i) + b] = HALF ? load_tile(half_tile(a, tile_row(W, i), b), lane) : load_block_tile(a, tile_row(W, i), b, r, g);
     __builtin_amdgcn_sched_barrier(0);
-  };
-  load_column(0);
+  }
   auto put_diag = [&](const f64x4& d) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) sh.diag[16 * (4 * g + v) + r] = d[v];
@@ -233,23 +283,25 @@ __device__ __forceinline__ void factor_rows(const BlockFactor& a, FactorShared& 
   for (int i = 0; i < NR; ++i)
     if (tile_row(W, i) == 0) put_diag(t[tile_base(W, i)]);
   lds_barrier();
-#pragma unroll
-  for (int b = 1; b <= kAhead; ++b) load_column(b);
 #pragma clang loop unroll(full)
-  for (int k = 0; k < NT; ++k) {
+  for (int k = 0; k < NH; ++k) {
     lds_barrier();                                             // W_kk is in LDS; every wavefront is done with column k - 1
-    if (k == NT - 1) break;
+    if (W == 1) publish_tile(factor_tile(a.V, first + k, first + k), lane, load_tile(sh.w, lane));
+    if (k == NH - 1) break;
     f64x4 nx[NR];
     const f64x4 wk = load_tile(sh.w, ol);
     auto column = [&](int i) {                                 // V_ak of the wavefront's i-th row
       const f64x4 x = tile_product(wk, t[tile_base(W, i) + k], f64x4{0.0, 0.0, 0.0, 0.0});
       store_tile(sh.x[tile_row(W, i)], lane, x);
+      publish_tile(factor_tile(a.V, first + k, first + tile_row(W, i)), lane, x);
       nx[i] = -x;
     };
     // the diagonal tile that the next factorisation waits for comes first
+    bool own = false;
 #pragma unroll
     for (int i = 0; i < NR; ++i)
       if (tile_row(W, i) == k + 1) {
+        own = true;
         __builtin_amdgcn_s_setprio(2);
         column(i);
         wave_publish();
@@ -258,14 +310,20 @@ __device__ __forceinline__ void factor_rows(const BlockFactor& a, FactorShared& 
         put_diag(d);
         __builtin_amdgcn_s_setprio(0);
       }
+    // the stores of column k - 1 are a step old and have arrived
+    if (k > 0) {
+      if (W == 1) { if (own) wait_stores<8>(); else wait_stores<4>(); }
+      else if (own) wait_stores<4>();
+      else wait_stores<0>();
+      set_flag(a.sync, BlockSync::column(first + k - 1, W - 1), lane);
+    }
 #pragma unroll
     for (int i = 0; i < NR; ++i)
       if (tile_row(W, i) > k + 1) column(i);
     lds_barrier();                                             // column k of V and the next diagonal tile are in LDS
 #pragma unroll
-    for (int b = k + 1; b < NT; ++b) {
+    for (int b = k + 1; b < NH; ++b) {
       if (b > tile_row(W, 0)) continue;
-      if (k == 0 && b + kAhead < NT) load_column(b + kAhead);
       const f64x4 xb = load_tile(sh.x[b], ol);
 #pragma unroll
       for (int i = 0; i < NR; ++i)
@@ -275,52 +333,118 @@ __device__ __forceinline__ void factor_rows(const BlockFactor& a, FactorShared& 
         }
     }
   }
+  wait_stores<0>();
+  set_flag(a.sync, BlockSync::column(first + NH - 2, W - 1), lane);
+  set_flag(a.sync, BlockSync::column(first + NH - 1, W - 1), lane);
 }
 
-__global__ __launch_bounds__(512) void block_factor_kernel(BlockFactor a) {
-  __shared__ __attribute__((aligned(16))) FactorShared sh;
-  const int lane = threadIdx.x & 63;
-  switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
-    case 0:
-      lds_barrier();                                           // tile (0, 0) is in LDS
-      for (int k = 0; k < NT; ++k) {
-        factor_diag(sh, a.info, a.o0 + kFactorBlock - 16 * k);
-        lds_barrier();
-        if (k == NT - 1) break;
-        lds_barrier();
-      }
-      break;
-    case 4:
-      lds_barrier();
-      for (int k = 0; k < NT; ++k) {
-        lds_barrier();
-        double* col = a.V + (int64_t)k * NT * TILE;
-        store_tile(col + k * TILE, lane, load_tile(sh.w, lane));
-        if (k == NT - 1) break;
-        lds_barrier();
-        for (int i = k + 1; i < NT; ++i) store_tile(col + i * TILE, lane, load_tile(sh.x[i], lane));
-      }
-      break;
-    case 1: factor_rows<1>(a, sh); break;
-    case 2: factor_rows<2>(a, sh); break;
-    case 3: factor_rows<3>(a, sh); break;
-    case 5: factor_rows<5>(a, sh); break;
-    case 6: factor_rows<6>(a, sh); break;
-    default: factor_rows<7>(a, sh); break;
+template <int HALF>
+__device__ __forceinline__ void factor_diagonal(const BlockFactor& a, FactorShared& sh) {
+  lds_barrier();                                               // the first diagonal tile is in LDS
+  for (int k = 0; k < NH; ++k) {
+    factor_diag(sh, a.info, a.o0 + kFactorBlock - 16 * (NH * HALF + k));
+    lds_barrier();
+    if (k == NH - 1) break;
+    lds_barrier();
   }
 }
 
-// ---- the rows above the block, and the inverse.  One workgroup per 16 rows; wavefront w holds tile columns w, w + 4, ...
+__device__ __forceinline__ void factor_role(const BlockFactor& a, FactorShared& sh) {
+  switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
+    case 0: __builtin_amdgcn_s_setprio(3); factor_diagonal<0>(a, sh); factor_diagonal<1>(a, sh); break;
+    case 1: factor_rows<1, 0>(a, sh); factor_rows<1, 1>(a, sh); break;
+    case 2: factor_rows<2, 0>(a, sh); factor_rows<2, 1>(a, sh); break;
+    default: factor_rows<3, 0>(a, sh); factor_rows<3, 1>(a, sh); break;
+  }
+}
+
+// ---- a panel: 16 rows, one workgroup; wavefront w holds tile columns w, w + 4, ...
 // Step k: their owner turns tile column k into V_ik = F_ik W_kk^T and publishes it in LDS; all update their later columns.
-// Workgroups 0 .. 15 take 16 rows of the identity through the same steps, which makes them rows of V^-T, i.e. columns of
-// U_OB,OB.  The digit operands keep the matrix's own order of columns: k = 255 - (column counted from the end).
-__global__ __launch_bounds__(256) void block_panel_kernel(BlockPanel a) {
-  __shared__ __attribute__((aligned(16))) double xs[2][TILE];
-  __shared__ double rowmax[4][16];
+struct PanelShared {
+  double x[2][TILE];
+  double rowmax[4][16];
+};
+// The left operands (W_kk for its owner, V_bk of the wavefront's later columns b) are fetched a step ahead if they are there.
+template <int STEPS>
+__device__ __forceinline__ void panel_steps(const double* V, f64x4 (&t)[STEPS / 4], int wave, int lane, PanelShared& sh, Flags& flags) {
+  constexpr int NQ = STEPS / 4;
+  const int ol = operand_lane(lane);
+  auto tile_of = [&](int k, int b) { return V + ((int64_t)k * NT + b) * TILE; };
+  auto need = [&](int k) { return 7ull << (3 * k) | (STEPS == NT ? 0xffull << BlockSync::row(0) : 0ull); };
+  f64x4 wk[2], vb[2][NQ];
+  auto fetch = [&](int k) {
+    if (wave == (k & 3)) wk[k & 1] = load_tile(tile_of(k, k), ol);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+      if (4 * q + 3 > k) vb[k & 1][q] = load_tile(tile_of(k, max(wave + 4 * q, k)), ol);
+  };
+  bool have = false;
+#pragma clang loop unroll(full)
+  for (int k = 0; k < STEPS; ++k) {
+    if (!have) {
+      flags.wait(need(k));
+      fetch(k);
+    }
+    have = k + 1 < STEPS && flags.ready(need(k + 1));
+    if (have) fetch(k + 1);
+    const int q0 = k >> 2;
+    if (wave == (k & 3)) {
+      t[q0] = tile_product(wk[k & 1], t[q0], f64x4{0.0, 0.0, 0.0, 0.0});
+      store_tile(sh.x[k & 1], lane, -t[q0]);
+    }
+    if (k == STEPS - 1) break;
+    lds_barrier();
+    const f64x4 nx = load_tile(sh.x[k & 1], lane);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+      if (4 * q + 3 > k && wave + 4 * q > k) t[q] = tile_product(vb[k & 1][q], nx, t[q]);
+  }
+}
+
+// Tile row m of OB's second half: V on the first half's columns, then the row's part of the second half's own block less the product
+// of these rows.
+__device__ __forceinline__ void half_row_role(const BlockFactor& a, int m, PanelShared& sh) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r = lane & 15, g = lane >> 4, ol = operand_lane(lane);
-  const bool inverse = blockIdx.x < NT;
-  const int row0 = inverse ? 16 * (int)blockIdx.x : 16 * ((int)blockIdx.x - NT);
+  f64x4 x[NH / 4], t[2];
+#pragma unroll
+  for (int q = 0; q < NH / 4; ++q) x[q] = load_block_tile(a, NH + m, wave + 4 * q, r, g);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) t[q] = load_block_tile(a, NH + m, NH + min(wave + 4 * q, m), r, g);
+  Flags flags{a.sync, a.info, a.o0 + kFactorBlock, lane};
+  panel_steps<NH>(a.V, x, wave, lane, sh, flags);
+#pragma unroll
+  for (int q = 0; q < NH / 4; ++q) publish_tile(factor_tile(a.V, wave + 4 * q, NH + m), lane, x[q]);
+  wait_stores<0>();
+  lds_barrier();
+  if (wave == 0) set_flag(a.sync, BlockSync::row(m), lane);
+  flags.wait(((2ull << m) - 1) << BlockSync::row(0));
+  f64x4 xa[NH], xb[2][NH];
+#pragma unroll
+  for (int k = 0; k < NH; ++k) {
+    xa[k] = load_tile(factor_tile(a.V, k, NH + m), lane);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) xb[q][k] = load_tile(factor_tile(a.V, k, NH + min(wave + 4 * q, m)), ol);
+  }
+#pragma unroll
+  for (int k = 0; k < NH; ++k)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) t[q] = tile_product(xb[q][k], -xa[k], t[q]);
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+    if (wave + 4 * q <= m) publish_tile(half_tile(a, m, wave + 4 * q), lane, t[q]);
+  wait_stores<0>();
+  set_flag(a.sync, BlockSync::tile(m, wave), lane);
+}
+
+// The rows above the block, and the inverse: workgroups 0 .. 15 take 16 rows of the identity through the same steps, which makes
+// them rows of V^-T, i.e. columns of U_OB,OB.  The digit operands keep the matrix's own order of columns: k = 255 - (column counted
+// from the end).
+__device__ __forceinline__ void panel_role(const BlockFactor& f, const BlockPanel& a, int wg, PanelShared& sh) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = lane & 15, g = lane >> 4;
+  const bool inverse = wg < NT;
+  const int row0 = inverse ? 16 * wg : 16 * (wg - NT);
   f64x4 t[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q)
@@ -332,37 +456,10 @@ __global__ __launch_bounds__(256) void block_panel_kernel(BlockPanel a) {
   if (!inverse) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      t[q] = load_row4(a.F, a.ldf, a.n, row0 + r, a.o0 + kFactorBlock - 4 - 16 * (wave + 4 * q) - 4 * g);
+      t[q] = load_row4(f.F, f.ldf, f.n, row0 + r, f.o0 + kFactorBlock - 4 - 16 * (wave + 4 * q) - 4 * g);
   }
-  auto tile_of = [&](int k, int b) { return a.V + ((int64_t)k * NT + b) * TILE; };
-  // left operands of a step, fetched during the step before: W_kk for its owner, V_bk of the wavefront's later columns b
-  f64x4 wk, vb[4], wn, vn[4];
-  auto fetch = [&](int k, f64x4& w, f64x4 (&v)[4]) {
-    if (k >= NT) return;
-    if (wave == (k & 3)) w = load_tile(tile_of(k, k), ol);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (4 * q + 3 > k) v[q] = load_tile(tile_of(k, max(wave + 4 * q, k)), ol);
-  };
-  fetch(0, wk, vb);
-#pragma clang loop unroll(full)
-  for (int k = 0; k < NT; ++k) {
-    fetch(k + 1, wn, vn);
-    const int q0 = k >> 2;
-    if (wave == (k & 3)) {
-      t[q0] = tile_product(wk, t[q0], f64x4{0.0, 0.0, 0.0, 0.0});
-      store_tile(xs[k & 1], lane, -t[q0]);
-    }
-    if (k == NT - 1) break;
-    lds_barrier();
-    const f64x4 nx = load_tile(xs[k & 1], lane);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (4 * q + 3 > k && wave + 4 * q > k) t[q] = tile_product(vb[q], nx, t[q]);
-    wk = wn;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) vb[q] = vn[q];
-  }
+  Flags flags{f.sync, f.info, f.o0 + kFactorBlock, lane};
+  panel_steps<NT>(f.V, t, wave, lane, sh, flags);
   // ---- digits: one scale per row, the row's 256 entries are in the four wavefronts
   double mx = 0.0;
 #pragma unroll
@@ -371,10 +468,10 @@ __global__ __launch_bounds__(256) void block_panel_kernel(BlockPanel a) {
     for (int v = 0; v < 4; ++v) mx = fmax(mx, fabs(t[q][v]));
   mx = fmax(mx, __shfl_xor(mx, 16, 64));
   mx = fmax(mx, __shfl_xor(mx, 32, 64));
-  if (lane < 16) rowmax[wave][lane] = mx;
+  if (lane < 16) sh.rowmax[wave][lane] = mx;
   lds_barrier();
 #pragma unroll
-  for (int q = 0; q < 4; ++q) mx = fmax(mx, rowmax[q][r]);
+  for (int q = 0; q < 4; ++q) mx = fmax(mx, sh.rowmax[q][r]);
   const int e = digit_exponent(mx);
   const double sc = digit_scale(e);
   const I8Operand& o = inverse ? a.Ucol : a.Vs;
@@ -399,21 +496,10 @@ __global__ __launch_bounds__(256) void block_panel_kernel(BlockPanel a) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int i = kFactorBlock - 1 - (16 * (wave + 4 * q) + 4 * g + v);
-        a.Uob[(int64_t)i * kFactorBlock + j] = t[q][v];
-        if (i <= j && a.o0 + j < a.n) a.F[(int64_t)(a.o0 + i) * a.ldf + a.o0 + j] = t[q][v];
+        a.Uob[j * kFactorBlock + i] = t[q][v];
+        if (i <= j && f.o0 + j < f.n) a.Uout[(int64_t)i * f.ldf + j] = t[q][v];
       }
   }
 }
 }  // namespace
-
-hipError_t launch_block_factor(const BlockFactor& a, hipStream_t s) {
-  hipLaunchKernelGGL(block_factor_kernel, dim3(1), dim3(512), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_block_panel(const BlockPanel& a, hipStream_t s) {
-  hipLaunchKernelGGL(block_panel_kernel, dim3((unsigned)(NT + a.o0 / 16)), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
 }  // namespace gptaq

@@ -12,11 +12,12 @@
 // normwise bound of the same kind as a floating-point product's, ~2^7 coarser than native fp64 and far
 // below what the fp32 outputs of the solve resolve.
 //
-// Layout of a sliced operand (written by slice_i8_kernel, consumed by gemm_i8s_kernel): digit plane i,
+// Layout of a sliced operand (written by slice_i8, consumed by multiply_i8): digit plane i,
 // k-chunk c (32 digits), row slab (32 rows) form one 1 KB block, stored in exactly the order the block has
 // in LDS, so a wavefront moves it with one global -> LDS load of 16 bytes per lane.  Inside the block, row
 // r and 16-byte half h sit at 256 (r / 8) + 16 (2 (r % 8) + (h ^ ((r / 8) & 1))): the 16 rows that one
 // clock of a ds_read_b128 serves fall into 16 different 16-byte slots of a 256-byte LDS line pair.
+#pragma once
 #include "common.h"
 #include "i8_digits.h"
 
@@ -67,14 +68,15 @@ template <int LPW, int EPI> __device__ __forceinline__ void wait_vm_lds_for(int 
 // One workgroup slices one slab of 32 rows: thread t owns 32 consecutive k of one row (one k-chunk).
 // Rows >= R of the last slab and k >= K are written as zeros; slabs past the last row are left alone (a
 // product only stores the rows it was asked for, whatever digits the padding holds).
-__global__ __launch_bounds__(256) void slice_i8_kernel(const double* src, int64_t sr, int64_t sk, int R, int K,
-                                                       uint8_t* planes, int64_t plane_stride, int64_t chunk_stride,
-                                                       int32_t* scale) {
-  __shared__ double smax[32][9];
-  const int t = threadIdx.x;
+struct I8Slice { const double* src; int64_t sr, sk; int32_t R, K; I8Operand o; };
+struct SliceShared { double max[32][9]; };
+__device__ __forceinline__ void slice_i8(const I8Slice& a, int slab, SliceShared& sh) {
+  const int64_t sr = a.sr, sk = a.sk;
+  const int R = a.R, K = a.K, t = threadIdx.x;
+  const double* src = a.src;
   const bool kmajor = sr == 1;                   // consecutive threads along the contiguous direction
   const int rl = kmajor ? (t & 31) : (t >> 3), c = kmajor ? (t >> 5) : (t & 7);
-  const int r = blockIdx.x * 32 + rl;
+  const int r = slab * 32 + rl;
   // (clamped addresses instead of a branch per load, which would wait for each; 64-bit shifts and conversions per digit took
   // longer than the loads: prepare at n = 11008: 127 launches, 1.53 -> 1.26 ms)
   const int64_t row = (int64_t)min(r, R - 1) * sr;
@@ -87,12 +89,12 @@ __global__ __launch_bounds__(256) void slice_i8_kernel(const double* src, int64_
     if (r >= R || c * KC + q >= K) v[q] = 0.0;
     mx = fmax(mx, fabs(v[q]));
   }
-  smax[rl][c] = mx;
+  sh.max[rl][c] = mx;
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 8; ++q) mx = fmax(mx, smax[rl][q]);
+  for (int q = 0; q < 8; ++q) mx = fmax(mx, sh.max[rl][q]);
   const int e = digit_exponent(mx);               // mx = f * 2^e, f in [0.5, 1)
-  if (c == 0) scale[r] = e - 26;                  // the product of two scaled rows carries 2^-52: see the epilogue
+  if (c == 0) a.o.scale[r] = e - 26;                  // the product of two scaled rows carries 2^-52: see the epilogue
   const double sc = digit_scale(e);
   uint32_t w[NP][8];
 #pragma unroll
@@ -103,14 +105,155 @@ __global__ __launch_bounds__(256) void slice_i8_kernel(const double* src, int64_
     for (int i = 0; i < NP; ++i) w[i][q] = d[i];
   }
   const int line = rl >> 3;
-  uint8_t* blk = planes + (int64_t)c * chunk_stride + (int64_t)blockIdx.x * 1024 + line * 256;
+  uint8_t* blk = a.o.planes + (int64_t)c * a.o.chunk_stride() + (int64_t)slab * 1024 + line * 256;
 #pragma unroll
   for (int i = 0; i < NP; ++i)
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int slot = ((rl & 7) << 1) | (h ^ (line & 1));
-      *reinterpret_cast<u32x4*>(blk + (int64_t)i * plane_stride + slot * 16) =
+      *reinterpret_cast<u32x4*>(blk + (int64_t)i * a.o.plane_stride() + slot * 16) =
           u32x4{w[i][4 * h], w[i][4 * h + 1], w[i][4 * h + 2], w[i][4 * h + 3]};
+    }
+}
+
+// ------------------------------------------------------------------------------------------------ row block
+// U_OB,J = U_OB,OB R_OB,J over R_OB,J in place, and the digits of its columns (one scale per column of the matrix): 32 columns,
+// one workgroup.  The columns' own digits are made in LDS; those of the rows of U_OB,OB come from memory straight into the lanes that need
+// them.  U_OB,OB is upper triangular, so a block of 32 rows begins at its own k-chunk; a wavefront takes blocks w and 7 - w.
+// A chain of loads, 9 k-chunks and stores: 20 us alone, hidden beside the next block's factorisation but for the last.  (As three launches,
+// digits, product, digits, it was 5 + 10 + 5 us and three steps of the chain of launches.)
+struct I8RowBlock {
+  double* R; int64_t ldf;            // R_OB,J, wo x J
+  int32_t J, wo;
+  I8Operand Urow, out;
+};
+struct RowBlockShared {
+  uint8_t digits[NP * (kI8MaxK / KC)][1024];     // [plane][k-chunk]
+  SliceShared s;
+  double colmax[4][32];
+  int32_t exponent[32];
+};
+__device__ __forceinline__ void row_block_i8(const I8RowBlock& a, int wg, RowBlockShared& sh) {
+  constexpr int NC = kI8MaxK / KC;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int rl = lane & 31, line = rl >> 3, col = wg * 32 + rl;
+  const int lane_off = line * 256 + ((((rl & 7) << 1) | ((lane >> 5) ^ (line & 1))) << 4);
+  const int nc = (a.wo + KC - 1) / KC;
+  // digits of U_OB,OB, AHEAD chunks before they are multiplied: they come from another XCD's panel
+  constexpr int AHEAD = 2;
+  i32x4 x[AHEAD + 1][NP];
+  auto load = [&](int ib, int d, i32x4 (&to)[NP]) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+      to[i] = *reinterpret_cast<const i32x4*>(a.Urow.planes + (int64_t)i * a.Urow.plane_stride() + (int64_t)min(ib + d, NC - 1) * a.Urow.chunk_stride() +
+                                              ib * 1024 + lane_off);
+  };
+#pragma unroll
+  for (int d = 0; d < AHEAD; ++d) load(wave, d, x[d]);
+  {
+    const int c = t >> 5;
+    const double* src = a.R + min(wg * 32 + rl, a.J - 1);
+    double v[KC], mx = 0.0;
+#pragma unroll
+    for (int q = 0; q < KC; ++q) v[q] = src[(int64_t)min(c * KC + q, a.wo - 1) * a.ldf];
+#pragma unroll
+    for (int q = 0; q < KC; ++q) {
+      if (wg * 32 + rl >= a.J || c * KC + q >= a.wo) v[q] = 0.0;
+      mx = fmax(mx, fabs(v[q]));
+    }
+    sh.s.max[rl][c] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) mx = fmax(mx, sh.s.max[rl][q]);
+    const int e = digit_exponent(mx);
+    if (c == 0) sh.exponent[rl] = e - 26;
+    const double sc = digit_scale(e);
+    uint32_t w[NP][8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      uint32_t d[NP];
+      pack_digits(digits_of(v[4 * q], sc), digits_of(v[4 * q + 1], sc), digits_of(v[4 * q + 2], sc), digits_of(v[4 * q + 3], sc), d);
+#pragma unroll
+      for (int i = 0; i < NP; ++i) w[i][q] = d[i];
+    }
+#pragma unroll
+    for (int i = 0; i < NP; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        *reinterpret_cast<u32x4*>(&sh.digits[i * NC + c][line * 256 + ((((rl & 7) << 1) | (h ^ (line & 1))) << 4)]) =
+            u32x4{w[i][4 * h], w[i][4 * h + 1], w[i][4 * h + 2], w[i][4 * h + 3]};
+  }
+  __syncthreads();
+  const int eb = sh.exponent[rl];
+  double res[2][16];
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    const int ib = half ? NC - 1 - wave : wave;              // block of 32 rows
+    i32x16 acc[NP];
+#pragma unroll
+    for (int s = 0; s < NP; ++s)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[s][v] = 0;
+    if (half) {
+#pragma unroll
+      for (int d = 0; d < AHEAD; ++d) load(ib, d, x[d]);
+    }
+#pragma unroll
+    for (int d = 0; d < NC; ++d) {                           // chunk ib + d
+      if (ib + d >= nc) break;
+      if (d + AHEAD < NC) load(ib, d + AHEAD, x[(d + AHEAD) % (AHEAD + 1)]);
+      __builtin_amdgcn_sched_barrier(0);
+      const i32x4 (&xa)[NP] = x[d % (AHEAD + 1)];
+      i32x4 y[NP];
+#pragma unroll
+      for (int i = 0; i < NP; ++i) y[i] = *reinterpret_cast<const i32x4*>(&sh.digits[i * NC + ib + d][lane_off]);
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int q = 0; q <= p; ++q) {
+          if (p + q >= NP) continue;
+          acc[p + q] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xa[q], y[p], acc[p + q], 0, 0, 0);
+          if (q < p) acc[p + q] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xa[p], y[q], acc[p + q], 0, 0, 0);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int row = 32 * ib + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+      double r = (double)acc[0][v];
+#pragma unroll
+      for (int s = 1; s < NP; ++s) r = fma(r, 256.0, (double)acc[s][v]);
+      const bool in = row < a.wo && col < a.J;
+      r = in ? ldexp(r, a.Urow.scale[row] + eb) : 0.0;
+      res[half][v] = r;
+      if (in) a.R[(int64_t)row * a.ldf + col] = r;
+    }
+  }
+  double mx = 0.0;
+#pragma unroll
+  for (int half = 0; half < 2; ++half)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) mx = fmax(mx, fabs(res[half][v]));
+  mx = fmax(mx, __shfl_xor(mx, 32, 64));
+  if (lane < 32) sh.colmax[wave][lane] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) mx = fmax(mx, sh.colmax[q][rl]);
+  const int e = digit_exponent(mx);
+  if (t < 32) a.out.scale[col] = e - 26;
+  const double sc = digit_scale(e);
+  uint8_t* slab = a.out.planes + (int64_t)wg * 1024 + 256 * line;
+#pragma unroll
+  for (int half = 0; half < 2; ++half)
+#pragma unroll
+    for (int v = 0; v < 16; v += 4) {
+      const int k0 = 32 * (half ? NC - 1 - wave : wave) + 2 * v + 4 * (lane >> 5);
+      uint32_t w[NP];
+      pack_digits(digits_of(res[half][v], sc), digits_of(res[half][v + 1], sc), digits_of(res[half][v + 2], sc), digits_of(res[half][v + 3], sc), w);
+      const int slot = ((rl & 7) << 1) | (((k0 >> 4) & 1) ^ (line & 1));
+      uint8_t* dst = slab + (int64_t)(k0 >> 5) * a.out.chunk_stride() + slot * 16 + (k0 & 15);
+#pragma unroll
+      for (int i = 0; i < NP; ++i) *reinterpret_cast<uint32_t*>(dst + (int64_t)i * a.out.plane_stride()) = w[i];
     }
 }
 
@@ -119,10 +262,9 @@ __global__ __launch_bounds__(256) void slice_i8_kernel(const double* src, int64_
 // consecutive tiles form one stream through the LDS ring, so the first chunks of the next tile arrive while the current one is
 // finished and written out.
 template <int BM>
-__global__ __launch_bounds__(256, BM == 128 ? 1 : 2) void gemm_i8s_kernel(I8Gemm g) {
+__device__ __forceinline__ void multiply_i8(const I8Gemm& g, int wg, int nwg, unsigned char* smem) {
   using S = Shape<BM>;
   constexpr int SLABS_A = S::SLABS_A, FRM = S::FRM, STAGE = S::STAGE, NSTAGE = S::NSTAGE, AHEAD = S::AHEAD, LPW = S::LPW;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 
@@ -132,9 +274,9 @@ __global__ __launch_bounds__(256, BM == 128 ? 1 : 2) void gemm_i8s_kernel(I8Gemm
   // (1.5 MB) stay in that XCD's L2.
   int t_next, t_end, t_step;
   {
-    const int nwg = gridDim.x, xcd = blockIdx.x & 7, loc = blockIdx.x >> 3;
+    const int xcd = wg & 7, loc = wg >> 3;
     const int per = g.ntile >> 3, rem = g.ntile & 7;
-    t_next = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + loc;
+    t_next = g.tile0 + (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + loc;
     t_end = t_next - loc + per + (xcd < rem ? 1 : 0);
     t_step = (nwg >> 3) + (xcd < (nwg & 7) ? 1 : 0);
   }
@@ -325,68 +467,6 @@ __global__ __launch_bounds__(256, BM == 128 ? 1 : 2) void gemm_i8s_kernel(I8Gemm
     cur = nxt;
     nxt = advance();
   }
-}
-
-hipError_t launch_slice_i8(const double* src, int64_t sr, int64_t sk, int R, int K, const I8Operand& o, hipStream_t s) {
-  if (R <= 0) return hipSuccess;
-  if (K > kI8MaxK || (sr != 1 && sk != 1) || R > o.rows_pad) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(slice_i8_kernel, dim3((unsigned)((R + 31) / 32)), dim3(256), 0, s, src, sr, sk, R, K, o.planes,
-                     o.plane_stride(), o.chunk_stride(), o.scale);
-  return hipGetLastError();
-}
-
-// Workgroups per launch, at most (for BM = 128; twice as many of the half-size ones).  A workgroup fills a CU or
-// half of one, and the products run beside the small sequential kernels of the other chain of the sweep, which
-// can only start on a CU that a workgroup has left: with one workgroup per CU for the whole launch those kernels
-// waited (n = 11008: 32.6 ms per prepare; 31.5 with 512, 30.7 with 1024, 30.6 with one tile per workgroup).  1024
-// keeps the workgroups of the sweep's products short and still lets very large products (n >= 28672) run tens of
-// tiles per workgroup.
-constexpr int kI8Workgroups = 1024;
-
-template <int BM>
-static hipError_t launch_shape(const I8Operand& A, int a_row0, const I8Operand& B, int b_row0, double* C, int64_t ldc, int M,
-                               int N, int K, double alpha, int beta, int upper_only, hipStream_t s) {
-  using S = Shape<BM>;
-  static LdsLimitOnce lds_once;                  // per instantiation
-  I8Gemm g;
-  g.tiles_m = (M + BM - 1) / BM;
-  g.tiles_n = (N + BN - 1) / BN;
-  if (a_row0 + g.tiles_m * BM > A.rows_pad || b_row0 + g.tiles_n * BN > B.rows_pad) return hipErrorInvalidValue;
-  {
-    const hipError_t e = lds_once.ensure((const void*)&gemm_i8s_kernel<BM>, S::NSTAGE * S::STAGE);
-    if (e != hipSuccess) return e;
-  }
-  g.A = A.planes + (int64_t)a_row0 * KC; g.a_plane = A.plane_stride(); g.a_chunk = A.chunk_stride(); g.sa = A.scale + a_row0;
-  g.B = B.planes + (int64_t)b_row0 * KC; g.b_plane = B.plane_stride(); g.b_chunk = B.chunk_stride(); g.sb = B.scale + b_row0;
-  g.C = C; g.ldc = ldc; g.M = M; g.N = N; g.beta = beta; g.upper_only = upper_only;
-  const int nch = (K + KC - 1) / KC;               // (a sliced operand is zero past its K)
-  g.nchunk = nch < S::AHEAD ? S::AHEAD : nch;
-  g.alpha = alpha;
-  int total = 0;
-  for (int first = 0; first < g.tiles_m; first += 4) {
-    const int gsz = g.tiles_m - first < 4 ? g.tiles_m - first : 4;
-    const int c0 = upper_only ? (first * (BM / BN) < g.tiles_n ? first * (BM / BN) : g.tiles_n) : 0;
-    total += gsz * (g.tiles_n - c0);
-  }
-  if (total == 0) return hipSuccess;
-  g.ntile = total;
-  const int cap = kI8Workgroups * (128 / BM);
-  hipLaunchKernelGGL(gemm_i8s_kernel<BM>, dim3((unsigned)(total < cap ? total : cap)), dim3(256), S::NSTAGE * S::STAGE, s, g);
-  return hipGetLastError();
-}
-
-// Which shape: measured with K = 256, 64-row tiles against 128-row tiles: 25.7 / 32.7 us for a 10752 x 256 update,
-// 193 / 220 for 5376^2, 461 / 505 for the upper half of 10752^2, 3040 / 3038 for the upper half of 26624^2,
-// 3245 / 3046 for 40960 x 8192.  The small tiles win while latencies matter and lose a little once the product is
-// large enough to be bound by its traffic.
-constexpr int64_t kI8SmallProduct = (int64_t)1 << 28;     // M * N up to here: 64-row tiles
-
-hipError_t launch_gemm_i8s(const I8Operand& A, int a_row0, const I8Operand& B, int b_row0, double* C, int64_t ldc, int M,
-                           int N, int K, double alpha, int beta, int upper_only, hipStream_t s) {
-  if (M <= 0 || N <= 0 || K <= 0) return hipSuccess;
-  if (K > kI8MaxK || (a_row0 % 128) || (b_row0 % BN)) return hipErrorInvalidValue;
-  return (int64_t)M * N <= kI8SmallProduct ? launch_shape<64>(A, a_row0, B, b_row0, C, ldc, M, N, K, alpha, beta, upper_only, s)
-                                           : launch_shape<128>(A, a_row0, B, b_row0, C, ldc, M, N, K, alpha, beta, upper_only, s);
 }
 
 }  // namespace gptaq

@@ -1,4 +1,4 @@
-// Six signed 8-bit digits of a scaled double (the operand format of gemm_i8s.hip), without 64-bit conversions or shifts:
+// Six signed 8-bit digits of a scaled double (the operand format of gemm_i8s.h), without 64-bit conversions or shifts:
 // adding 1.5 * 2^52 rounds the scaled value (|n| <= 2^46) to an integer in the low bits of the sum, half to even; 128 added to
 // each of the five low bytes makes the borrows of signed digits, and flipping their top bits makes the bytes signed.
 #pragma once

@@ -9,27 +9,28 @@
 // right-hand side R of the solve V U = I afterwards:
 //
 //   for every outer block OB of 256 columns, last to first      (I: rows above OB, J: columns right of OB)
-//     factor : F_OB,OB = V_OB,OB V_OB,OB^T             one workgroup          } fp64 (block_factor.hip)
+//     factor : F_OB,OB = V_OB,OB V_OB,OB^T                                    } fp64 (factor_roles.h)
 //     panel  : V_I,OB = F_I,OB V_OB,OB^-T and U_OB,OB = V_OB,OB^-1, as digits }
 //     syrk   : F_II  -= V_I,OB V_I,OB^T                (rank 256)  } the n^3 * 2/3 bulk: digit-sliced operands,
 //     rowblk : U_OB,J  = U_OB,OB R_OB,J                            } exact int8 MFMA products,
-//     rupd   : R_I,J  -= V_I,OB U_OB,J                 (rank 256)  } fp64 recombination (gemm_i8s.hip)
+//     rupd   : R_I,J  -= V_I,OB U_OB,J                 (rank 256)  } fp64 recombination (gemm_i8s.h)
 //     close  : R_I,OB  = -V_I,OB U_OB,OB
 //
 // Theorem 4.2's two products then run on the bf16 MFMA GEMM with fp32 operands split into
 // bf16 hi+lo (three cross products per term).
 #include "common.h"
-#include <mutex>
-#include <vector>
+#include "factor_sweep.h"
 
 namespace gptaq {
 
 constexpr int NBO = kFactorBlock;             // outer block (columns per rank-256 update)
 
 // ----------------------------------------------------------------------------- statistics
-// One workgroup: dead inputs, lambda = damp * mean(diag), info words.
+// One workgroup: dead inputs, lambda = damp * mean(diag), info words; the factor sweep's flags are cleared.
 __global__ __launch_bounds__(1024) void diag_stats_kernel(const float* H, int64_t ldh, int n, float damp,
-                                                          uint8_t* dead, double* lam_out, int32_t* info) {
+                                                          uint8_t* dead, double* lam_out, int32_t* info, int32_t* sync,
+                                                          int nsync) {
+  for (int i = threadIdx.x; i < nsync; i += 1024) sync[i] = 0;
   __shared__ double ssum[1024];
   __shared__ int scnt[1024];
   double s = 0.0;
@@ -68,20 +69,6 @@ __global__ void build_F_kernel(const float* H, int64_t ldh, int n, const double*
 }
 
 // --------------------------------------------------------------- extraction and splits
-__device__ __forceinline__ uint16_t bf16_rne(float f) {
-  __bf16 b = (__bf16)f;
-  return __builtin_bit_cast(uint16_t, b);
-}
-__device__ __forceinline__ float bf16_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
-// The two products of Theorem 4.2 only read the operand blocks of kSplitBlock^2 on and above the diagonal (their tiles start
-// and their k ranges begin at multiples of a tile edge that divides it), so the others are not written: a third of
-// extract_U_kernel's bytes and two thirds of split_rows_kernel's.
-constexpr int kSplitBlock = 256;
-// The operands are k-tile-major: a tile's rows of 32 k are one run, not 64 bytes of every row (whose stride is a power of two at
-// n = 4096): 147 -> 118 us per product at n = 4096, 1.32 -> 1.10 ms at n = 11008.
-__device__ __forceinline__ int64_t operand_at(int64_t row, int64_t k, int64_t np) { return (k >> 5) * np * 32 + row * 32 + (k & 31); }
-
 // U (fp32, upper, zeros below) from F; its bf16 hi/lo split row-major (Uh, Ul) and
 // transposed (Uth, Utl), zero-padded to np x np.   grid (np/64, np/64), 256 threads.
 __global__ __launch_bounds__(256) void extract_U_kernel(const double* F, int64_t ldf, int n, float* U, int64_t ldu,
@@ -122,26 +109,7 @@ __global__ __launch_bounds__(256) void extract_U_kernel(const double* F, int64_t
   }
 }
 
-// bf16 hi/lo split of the strictly upper triangle of an fp32 matrix (rows flagged in `zero_rows` read as 0), padded
-// to np x np; entries on and below the diagonal are not read and come out as 0.  Both uses want exactly that: Eq. 17
-// masks dXXT L to its strictly upper part and L is lower triangular, so entry (i, k) of dXXT only ever meets a
-// non-zero of L when k > i, and the masked product itself is strictly upper.
-// `info` (may be NULL): a NaN or Inf among the entries read is reported as info[0] = -(1 + row of the entry).
-__global__ __launch_bounds__(256) void split_rows_kernel(const float* A, int64_t lda, int n, const uint8_t* zero_rows,
-                                                         uint16_t* Ah, uint16_t* Al, int64_t np, int32_t* info) {
-  const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x, r0 = 4 * (int64_t)blockIdx.y;      // four rows: 256 bytes of a k-tile
-  if (c >= np || c / kSplitBlock < r0 / kSplitBlock) return;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int64_t r = r0 + i, o = operand_at(r, c, np);
-    float v = 0.f;
-    if (r < n && c < n && c > r && !(zero_rows && zero_rows[r])) v = A[r * lda + c];
-    if (info && !__builtin_isfinite(v)) atomicMin(info, -(1 + (int)r));
-    const uint16_t h = bf16_rne(v);
-    Ah[o] = h;
-    Al[o] = bf16_rne(v - bf16_f32(h));
-  }
-}
+__global__ __launch_bounds__(256) void split_rows_kernel(SplitRows a) { split_rows(a, blockIdx.x, blockIdx.y); }
 
 }  // namespace gptaq
 
@@ -151,7 +119,7 @@ namespace {
 struct PrepLayout {
   int64_t np;
   int64_t rp;                      // rows of a sliced operand that spans the whole matrix
-  size_t off_F, off_lam, off_dead, off_O, off_b[6], off_Uob[2], off_V, off_pl[6], off_sc[6], total;
+  size_t off_F, off_lam, off_dead, off_O, off_b[6], off_Uob, off_V, off_T, off_sync, off_pl[8], off_sc[8], total;
 };
 PrepLayout prep_layout(int64_t n) {
   PrepLayout L;
@@ -164,13 +132,15 @@ PrepLayout prep_layout(int64_t n) {
   L.off_dead = take((size_t)n);
   L.off_O = take((size_t)L.np * L.np * 4);
   for (int i = 0; i < 6; ++i) L.off_b[i] = take((size_t)L.np * L.np * 2);
-  for (int i = 0; i < 2; ++i) L.off_Uob[i] = take((size_t)NBO * NBO * 8);
+  L.off_Uob = take((size_t)NBO * NBO * 8);
   L.off_V = take(kFactorTileBytes);
-  // sliced operands of the rank-256 products: V_I,OB (two: the helper stream reads one while the next is
-  // written), R_OB,J / U_OB,J, and U_OB,OB by columns (two) and by rows
+  L.off_T = take(kHalfTileBytes);
+  L.off_sync = take((size_t)((n + NBO - 1) / NBO) * kBlockSyncBytes);
+  // sliced operands of the rank-256 products: V_I,OB (three blocks' in turn), U_OB,J (two blocks'), and U_OB,OB by columns (two) and
+  // by rows
   L.rp = round_up(n, 128);
-  for (int i = 0; i < 6; ++i) {
-    const int64_t rows = i < 3 ? L.rp : NBO;
+  for (int i = 0; i < 8; ++i) {
+    const int64_t rows = i < 5 ? L.rp : NBO;
     L.off_pl[i] = take(I8Operand::plane_bytes(rows));
     L.off_sc[i] = take((size_t)rows * 4);
   }
@@ -199,9 +169,9 @@ extern "C" int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, floa
   double* F = (double*)(base + L.off_F);
   uint8_t* deadbuf = dead ? dead : (uint8_t*)(base + L.off_dead);
   float* Obuf = (float*)(base + L.off_O);
-  I8Operand sl[6];
-  for (int i = 0; i < 6; ++i) sl[i] = I8Operand{base + L.off_pl[i], (int32_t*)(base + L.off_sc[i]), i < 3 ? L.rp : (int64_t)NBO};
-  const I8Operand &RJs = sl[2], &Urow = sl[5];
+  int32_t* sync = (int32_t*)(base + L.off_sync);
+  I8Operand sl[8];
+  for (int i = 0; i < 8; ++i) sl[i] = I8Operand{base + L.off_pl[i], (int32_t*)(base + L.off_sc[i]), i < 5 ? L.rp : (int64_t)NBO};
   const int64_t ldf = round_up(n, 16);
   uint16_t* bb[6];
   for (int i = 0; i < 6; ++i) bb[i] = (uint16_t*)(base + L.off_b[i]);
@@ -209,78 +179,20 @@ extern "C" int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, floa
   uint16_t *Uh = bb[0], *Ul = bb[1], *Uth = bb[2], *Utl = bb[3], *Ah = bb[4], *Al = bb[5];
   const int ni = (int)n;
 
-  hipLaunchKernelGGL(diag_stats_kernel, dim3(1), dim3(1024), 0, s, H, ldh, ni, damp, deadbuf, lam, info);
+  hipLaunchKernelGGL(diag_stats_kernel, dim3(1), dim3(1024), 0, s, H, ldh, ni, damp, deadbuf, lam, info, sync,
+                     (int)((n + NBO - 1) / NBO * (kBlockSyncBytes / 4)));
   GPTAQ_LAUNCH_CHECK();
   hipLaunchKernelGGL(build_F_kernel, dim3((unsigned)((n + 255) / 256), (unsigned)n), dim3(256), 0, s, H, ldh, ni,
                      lam, F, ldf, info);
   GPTAQ_LAUNCH_CHECK();
 
-  // The sweep is two chains of kernels over the outer blocks OB = nob-1 .. 0 (I: rows above, J: columns right):
-  //   factor chain (caller's stream): factorisation of block column OB, digits of V_I,OB and of U_OB,OB, Schur update
-  //                                   of the next block column;
-  //   inverse chain (helper stream):  Schur update of the rest of F_II, then U_OB,J = U_OB,OB R_OB,J,
-  //                                   R_I,J -= V_I,OB U_OB,J, R_I,OB = -V_I,OB U_OB,OB.
-  // The rank-256 products run on the int8 matrix cores from digit-sliced operands (gemm_i8s.hip).
-  // The inverse chain of a block needs that block's V_I,OB and U_OB,OB and nothing later from the
-  // factor chain, and it only writes columns >= o0 of F while the factor chain has moved on to columns < o0,
-  // so the two overlap: the small sequential kernels of one hide behind the rank-256 products of the other.
-  // What it reads alternates between two sets of buffers; an event per block and direction orders the streams.
-  std::lock_guard<std::mutex> side_lock(side_stream_mutex());
-  const int nob = (int)((n + NBO - 1) / NBO);
-  SideStream* side = side_stream(3 * nob + 2);
-  if (!side) { set_last_hip_error(hipGetLastError()); return GPTAQ_ELAUNCH; }
-  hipStream_t sb = side->stream;
   {
     ProfScope sweep_scope(kProfFactor, s);
-    bool ok = true;
-    auto chk = [&](hipError_t e) { if (e != hipSuccess && ok) { ok = false; set_last_hip_error(e); } };
-    hipEvent_t ev_fork = side->events[3 * nob];
-    chk(hipEventRecord(ev_fork, s));                          // the helper stream starts behind build_F
-    chk(hipStreamWaitEvent(sb, ev_fork, 0));
-    // dXXT (dead rows zeroed) split for the products at the end: it depends on nothing here and runs beside the first block
-    hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)((np + 255) / 256), (unsigned)(np / 4)), dim3(256), 0, sb, dXXT, ldh, ni,
-                       deadbuf, Ah, Al, np, info);
-    chk(hipGetLastError());
-    for (int ob = nob - 1; ob >= 0 && ok; --ob) {
-      const int o0 = ob * NBO, o1 = (int)(n < o0 + NBO ? n : o0 + NBO), wo = o1 - o0;
-      const I8Operand &Vs = sl[ob & 1], &Ucol = sl[3 + (ob & 1)];
-      double* Uob = (double*)(base + L.off_Uob[ob & 1]);
-      hipEvent_t ev_factored = side->events[2 * ob], ev_inverted = side->events[2 * ob + 1];
-      // ---- factor chain
-      double* V = (double*)(base + L.off_V);
-      chk(launch_block_factor(BlockFactor{F, ldf, ni, o0, info, V}, s));
-      // the digit buffers of this block were last read by the inverse chain of block ob + 2
-      if (ob + 2 <= nob - 1) chk(hipStreamWaitEvent(s, side->events[2 * (ob + 2) + 1], 0));
-      chk(launch_block_panel(BlockPanel{F, ldf, ni, o0, V, Vs, Ucol, Uob}, s));
-      chk(hipEventRecord(ev_factored, s));
-      // Schur complement of everything above/left of the outer block, F_II -= V_I,OB V_I,OB^T, in two parts:
-      // the block column the next outer block factors (here, it is on the critical path) and the rest (upper
-      // tiles, on the helper stream).  The next block's part-one update overlaps this block's part two in
-      // memory, so it waits for it.
-      const int c_lo = o0 > NBO ? o0 - NBO : 0;
-      if (ob + 1 <= nob - 1) chk(hipStreamWaitEvent(s, side->events[2 * nob + ob + 1], 0));
-      chk(launch_gemm_i8s(Vs, 0, Vs, c_lo, F + c_lo, ldf, o0, o0 - c_lo, wo, -1.0, 1, 0, s));
-      // ---- inverse chain
-      chk(hipStreamWaitEvent(sb, ev_factored, 0));
-      chk(launch_gemm_i8s(Vs, 0, Vs, 0, F, ldf, c_lo, c_lo, wo, -1.0, 1, 1, sb));
-      if (ob >= 1) chk(hipEventRecord(side->events[2 * nob + ob], sb));
-      double* FJ = F + (int64_t)o0 * ldf + o1;                  // block row OB right of the diagonal block
-      chk(launch_slice_i8(FJ, 1, ldf, ni - o1, wo, RJs, sb));   // R_OB,J (digits per column of it)
-      chk(launch_slice_i8(Uob, NBO, 1, wo, wo, Urow, sb));
-      chk(launch_gemm_i8s(Urow, 0, RJs, 0, FJ, ldf, wo, ni - o1, wo, 1.0, 0, 0, sb));           // U_OB,J = U_OB,OB R_OB,J
-      chk(launch_slice_i8(FJ, 1, ldf, ni - o1, wo, RJs, sb));                                    // now U_OB,J
-      chk(launch_gemm_i8s(Vs, 0, RJs, 0, F + o1, ldf, o0, ni - o1, wo, -1.0, 1, 0, sb));         // R_I,J -= V_I,OB U_OB,J
-      chk(launch_gemm_i8s(Vs, 0, Ucol, 0, F + o0, ldf, o0, wo, wo, -1.0, 0, 0, sb));             // R_I,OB = -V_I,OB U_OB,OB
-      chk(hipGetLastError());
-      if (ob >= 2) chk(hipEventRecord(ev_inverted, sb));       // (the join is behind the last two)
-    }
-    // join: everything after the sweep runs on the caller's stream, and whatever the helper stream was given is behind it when
-    // the call returns, also if a launch or an event call failed part-way
-    hipEvent_t ev_join = side->events[3 * nob + 1];
-    hipError_t joined = hipEventRecord(ev_join, sb);
-    if (joined == hipSuccess) joined = hipStreamWaitEvent(s, ev_join, 0);
-    chk(joined);
-    if (!ok) return GPTAQ_ELAUNCH;
+    // (dXXT, dead rows zeroed, is split for the products at the end on the way)
+    const hipError_t swept = launch_factor_sweep(
+        FactorSweep{F, ldf, ni, info, (double*)(base + L.off_V), (double*)(base + L.off_T), (double*)(base + L.off_Uob), sync,
+                    {sl[0], sl[1], sl[2]}, {sl[3], sl[4]}, {sl[5], sl[6]}, sl[7], SplitRows{dXXT, ldh, ni, deadbuf, Ah, Al, np, info}}, s);
+    if (swept != hipSuccess) { set_last_hip_error(swept); return GPTAQ_ELAUNCH; }
   }
   // U -> H (fp32) and the bf16 splits.
   hipLaunchKernelGGL(extract_U_kernel, dim3((unsigned)(np / 64), (unsigned)(np / 64)), dim3(256), 0, s, F, ldf, ni, H,
@@ -306,8 +218,8 @@ extern "C" int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, floa
   }
   if (e != hipSuccess) { set_last_hip_error(e); return GPTAQ_ELAUNCH; }
   // split O (reuses the dXXT split buffers), then P = O U: P[i][j] = sum_{i < a <= j} O[i][a] U[a][j]
-  hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)((np + 255) / 256), (unsigned)(np / 4)), dim3(256), 0, s, Obuf, np,
-                     ni, (const uint8_t*)nullptr, Ah, Al, np, (int32_t*)nullptr);
+  hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)((np + 255) / 256), (unsigned)(np / kSplitRowsPerWg)), dim3(256), 0, s,
+                     SplitRows{Obuf, np, ni, nullptr, Ah, Al, np, nullptr});
   GPTAQ_LAUNCH_CHECK();
   g.C = dXXT; g.ldc = ldh; g.k_mode = 2;
   g.term[0] = {{Ah, Al}, {Uth, Utl}, 32, 32, np * 32, np * 32};

@@ -87,6 +87,51 @@ def test_factor_and_inverse_at_tile_edges(n):
         assert PU.rel_fro(Ad.cpu().numpy(), P) <= 5e-5
 
 
+# Blocks whose buffers take turns (three of V, two of U's rows), ragged first blocks that end in either half, rows of dXXT that are not
+# 16-byte aligned.  U against H itself: |U^T U (H + lambda I) - I|; the tolerances of test_factor_and_inverse_at_tile_edges.
+@pytest.mark.parametrize("n,ld", [(1152, 1152), (1281, 1281), (1409, 1411), (1790, 1792), (2049, 2056)])
+def test_factor_sweep_over_many_blocks(n, ld):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    X = torch.randn((4 * n, n), device="cuda", generator=g).double()
+    H = X.T.contiguous() @ X
+    A = ((0.1 * torch.randn((4 * n, n), device="cuda", generator=g)).double().T.contiguous() @ X).float()
+    Hd, Ad = torch.full((n, ld), 7.0, device="cuda"), torch.full((n, ld), 7.0, device="cuda")
+    Hd[:, :n], Ad[:, :n] = H.float(), A
+    ws = B.workspace(B.gptaq_prepare_workspace_bytes(n)).fill_(255)
+    dead, info = torch.empty(n, dtype=torch.uint8, device="cuda"), torch.empty(2, dtype=torch.int32, device="cuda")
+    assert B.load().gptaq_prepare(Hd.data_ptr(), Ad.data_ptr(), n, ld, 0.01, dead.data_ptr(), info.data_ptr(), ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream) == 0
+    assert info.tolist() == [0, 0] and bool((Hd[:, n:] == 7).all()) and bool((Ad[:, n:] == 7).all())
+    Hl = H.float().double().triu()
+    Hl = (Hl + Hl.triu(1).T).cpu()
+    Hl += 0.01 * Hl.diagonal().mean() * torch.eye(n, dtype=torch.float64)
+    V = torch.linalg.cholesky(Hl.flip(0, 1)).flip(0, 1)              # H + lambda I = V V^T, V upper
+    U = torch.linalg.inv(V)
+    P = ((A.double().cpu() @ U.T.contiguous()).triu(1) @ U)
+    assert PU.rel_fro(Hd[:, :n].cpu().numpy(), U.numpy()) <= 1e-6
+    assert PU.rel_fro(Ad[:, :n].cpu().numpy(), P.numpy()) <= 5e-5
+
+
+def test_two_factor_sweeps_beside_each_other():
+    """Workgroups of a block wait for others of the same launch: two calls on two streams, each with its own buffers, both end, with the
+    bits of a call alone."""
+    n = 2304
+    g = torch.Generator(device="cuda").manual_seed(5)
+    X = torch.randn((2 * n, n), device="cuda", generator=g)
+    H0, A0 = X.T.contiguous() @ X, (0.1 * torch.randn((2 * n, n), device="cuda", generator=g)).T.contiguous() @ X
+    sets = [(H0.clone(), A0.clone(), B.workspace(B.gptaq_prepare_workspace_bytes(n)), torch.cuda.Stream()) for _ in range(2)]
+    Ha, Aa = H0.clone(), A0.clone()
+    B.gptaq_prepare(Ha, Aa, 0.01, sets[0][2])
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for H, A, ws, s in sets:
+            with torch.cuda.stream(s):
+                H.copy_(H0), A.copy_(A0)
+                B.gptaq_prepare(H, A, 0.01, ws)
+    torch.cuda.synchronize()
+    for H, A, _, _ in sets:
+        assert torch.equal(H, Ha) and torch.equal(A, Aa)
+
+
 # The tile store of the bf16 product: inside the matrix, at its edges, rows farther apart than n, and so far apart that a tile is
 # out of reach of 32-bit offsets; 128-tiles and (from 224 of them) 256-tiles.
 @pytest.mark.parametrize("n,ld,tokens", [(8, 8, 40), (128, 128, 33), (136, 140, 64), (1032, 1032, 96), (3608, 3616, 64), (3840, 3840, 32),
