@@ -219,26 +219,30 @@ static Operands operands_at(void* ws, int64_t np, int64_t tokens, bool rows) {
 // full one where it is defined), from: 18 ns per token in a round of more than 256 workgroups (two to a CU), 11 in one of fewer; 5 us per
 // round; parts written and read at 4 TB/s, and a launch for them.  (Four workgroups a tile row sum H's diagonal in one part: see
 // diagonal_block.)
-// Measured, one part / so many, us per call of 32768 tokens, upper form (full): n = 256 313 / 78 (311 / 79), 512 321 / 94 (312 / 106), 768
-// 335 / 133 (327 / 153), 1024 383 / 197 (386 / 240), 1280 491 / 262 (489 / 354), 1536 536 / 342 (541 / 442); of 8192 tokens 512 92 / 39, 1024
-// 98 / 56 (99 / 73).  Where the estimate promises less than a factor of 1.5 there was little to be had (without the diagonal's
-// workgroups: 2048 594 / 511 (687 / 699), 2736 888 / 861 (1241 / 1277), 3072 and 8192 tokens 257 / 277 (352 / 384)).  Errors against 64 bits
-// fall with the length of the sums: dXXT 8.7e-7 to 2.4e-7 at n = 1024.
+// Measured, one part / so many, us per call of 32768 tokens, upper form (full): n = 256 302 / 75 (312 / 75), 512 317 / 88 (316 / 91), 768
+// 331 / 129 (321 / 147), 1024 370 / 194 (372 / 231), 1280 482 / 257 (481 / 349), 1536 534 / 342 (531 / 433); of 8192 tokens 512 91 / 40, 1024
+// 96 / 55 (97 / 73); of 4096 256 51 / 28, 512 54 / 34, 768 54 / 33 (55 / 34), 1024 54 / 36 (54 / 46), 1280 57 / 47 (59 / 53); of 2048 512 32 / 25,
+// 1024 34 / 28 (33 / 33); of 1024 there is nothing to be had (512 20.6 / 21.4).  Where the estimate promises less than a factor of 1.5 there was
+// little to be had with many tokens and more than 640 columns (without the diagonal's workgroups: 2048 594 / 511 (687 / 699), 2736 888 / 861 (1241 /
+// 1277), 3072 and 8192 tokens 257 / 277 (352 / 384); 1536 and 16384 188 / 163 (206 / 228)); with less than 8192 tokens, or up to 640
+// columns, a factor of 1.1 is kept, and more than eight parts never were the best.  Errors against 64 bits fall with the length of the
+// sums: dXXT 8.7e-7 to 2.4e-7 at n = 1024.
 static int split_for(int64_t n, int64_t tokens) {
   if (sparse_remainder(n)) return 1;             // (remainder_loop takes all of K; the estimate promises less than 1.5 from there on)
   if (gemm_tile_for(n, n) != 128) return 1;      // (256-tiles: they fill the chip, and the power limit takes what a fuller last round gives)
-  if (tokens < 8192) return 1;                   // (the workspace of a call with few samples stays that of its operands)
   const int64_t t = (n + 127) / 128, upper = t * (t + 1) / 2;
+  const bool small = tokens < 8192 || t <= 5;
   int best = 1;
   double least = 0.;
   for (int split : {1, 2, 4, 6, 8, 12, 16}) {
+    if (small && split > 8) break;
     double us = 0.;
     for (int64_t dxxt : {upper, t * t}) {
       const int64_t wgs = dxxt * split + upper * ((split + 1) / 2) + (split > 1 ? 4 * t : 0), rounds = wgs / 512, rest = wgs % 512;
       us += (0.018 * (double)rounds + (rest == 0 ? 0. : rest <= 256 ? 0.0112 : 0.018)) * (double)tokens / split;
-      us += 5. * (double)(rounds + (rest > 0)) + (split > 1 ? (double)wgs * 0.033 + 6. : 0.);
+      us += 5. * (double)(rounds + (rest > 0)) + (split > 1 ? (double)wgs * 0.033 + 6. + (small ? 0.5 * split : 0.) : 0.);
     }
-    if (split == 1) least = us / 1.5;
+    if (split == 1) least = us / (small ? 1.1 : 1.5);
     else if (us < least) { best = split; least = us; }
   }
   return best;

@@ -364,6 +364,12 @@ def test_sums_in_parts_are_the_sums(n, ld, tokens):
             assert float((got.double() - ref).norm() / ref.norm()) <= 3e-6
 
 
+# The same with few tokens: the fewest of a size that are taken in parts, k-tiles that do not divide over them, a part of few k-tiles.
+@pytest.mark.parametrize("n,ld,tokens", [(8, 8, 2048), (264, 264, 2080), (512, 520, 4096), (776, 776, 4100), (1280, 1280, 6000)])
+def test_sums_in_parts_of_few_tokens(n, ld, tokens):
+    test_sums_in_parts_are_the_sums(n, ld, tokens)
+
+
 @pytest.mark.parametrize("n,tokens", [(264, 8192), (520, 16448), (1032, 32768)])
 def test_sums_in_parts_round_the_total_once(n, tokens):
     """Whole numbers, whose sums are exact in fp32 in any order, on totals of 2^25 (steps of 2 and 4): what a call leaves is the exact
