@@ -14,6 +14,7 @@
 // Trailing update (lines 11-12, Eq. 18):  W[:, i+B:] += [-E | V] [U; P][i:i+B, i+B:] on the
 // MFMA GEMM with three bf16 cross products per term (operands carried to about 2^-17 relative, fp32 sums).
 #include "common.h"
+#include "near_operands.h"
 #include "row_halves.h"
 #include <mutex>
 
@@ -84,34 +85,40 @@ struct ClipSearch {
   }
 };
 
-// One wavefront per row: range of the whole (original) row -> one (scale, zero) per row.
-__global__ __launch_bounds__(256) void row_params_kernel(const float* W, int64_t ldw, int m, int n, float maxq, int sym,
-                                                         int mse_grid, int mse_steps, float* scales, float* zeros) {
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (row >= m) return;
+// One wavefront per row: range of the whole (original) row -> one (scale, zero) per row.  Columns of dead inputs count as 0.
+struct RowParams {
+  const float* W; int64_t ldw; int m, n; const uint8_t* dead;
+  float maxq; int sym, mse_grid, mse_steps;
+  float *scales, *zeros;
+};
+__device__ __forceinline__ void row_params(const RowParams& a, int wg) {
+  const int row = wg * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (row >= a.m) return;
+  const float* w = a.W + (int64_t)row * a.ldw;
+  auto weight = [&](int c) { return a.dead && a.dead[c] ? 0.f : w[c]; };
   float mn = 0.f, mx = 0.f;
-  for (int c = lane; c < n; c += 64) {
-    const float v = W[(int64_t)row * ldw + c];
+  for (int c = lane; c < a.n; c += 64) {
+    const float v = weight(c);
     mn = fminf(mn, v);
     mx = fmaxf(mx, v);
   }
   mn = wave_min(mn);
   mx = wave_max(mx);
   float sc, zr;
-  grid_params(mn, mx, maxq, sym, sc, zr);
-  if (mse_steps > 0) {
+  grid_params(mn, mx, a.maxq, a.sym, sc, zr);
+  if (a.mse_steps > 0) {
     ClipSearch cs;
-    cs.begin(mn, mx, maxq, sym);
-    for (int i = 0; i < mse_steps; ++i) {
-      const float si = cs.scale_of(i, mse_grid), isi = 1.f / si;
+    cs.begin(mn, mx, a.maxq, a.sym);
+    for (int i = 0; i < a.mse_steps; ++i) {
+      const float si = cs.scale_of(i, a.mse_grid), isi = 1.f / si;
       float e = 0.f;
-      for (int c = lane; c < n; c += 64) e += cs.err_of(W[(int64_t)row * ldw + c], si, isi);
+      for (int c = lane; c < a.n; c += 64) e += cs.err_of(weight(c), si, isi);
       cs.offer(wave_sum(e), si);
     }
     sc = cs.best_scale;
     zr = cs.zero;
   }
-  if (lane == 0) { scales[row] = sc; zeros[row] = zr; }
+  if (lane == 0) { a.scales[row] = sc; a.zeros[row] = zr; }
 }
 
 struct QuantArgs {
@@ -422,10 +429,9 @@ extern "C" size_t gptaq_quantize_workspace_bytes(int64_t m, int64_t n) {
 
 namespace gptaq {
 // Dead inputs (zero Hessian diagonal): their columns of W count as 0 (GPTQ's rule, which the paper defers to).
-// grid: one workgroup per 64 columns; it returns at once unless one of its columns is dead.
-__global__ __launch_bounds__(256) void zero_dead_columns_kernel(float* W, int64_t ldw, int m, int n, const uint8_t* dead) {
-  __shared__ int any;
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63);
+// One workgroup per 64 columns; it returns at once unless one of its columns is dead.
+__device__ __forceinline__ void zero_dead_columns(float* W, int64_t ldw, int m, int n, const uint8_t* dead, int wg, int& any) {
+  const int c = wg * 64 + (threadIdx.x & 63);
   const bool d = c < n && dead[c];
   if (threadIdx.x == 0) any = 0;
   __syncthreads();
@@ -434,6 +440,27 @@ __global__ __launch_bounds__(256) void zero_dead_columns_kernel(float* W, int64_
   if (!any) return;
   for (int r = threadIdx.x >> 6; r < m; r += 4)
     if (d) W[(int64_t)r * ldw + c] = 0.f;
+}
+
+// What comes before the first super-block, in one launch: its operands, the rows' ranges, the dead columns (in this order of workgroups).
+// (As launches of their own they took 2 to 5 us each: a solve of 512 x 512, 283 -> 281 us, 4096 x 4096 with the waits saved below 850 -> 816.)
+struct BeginLayer {
+  const float *U, *P; int64_t ldh; SbNear near;
+  RowParams rows;
+  float* W;
+  int near_wgs, row_wgs, dead_wgs;
+};
+__global__ __launch_bounds__(256) void begin_layer_kernel(BeginLayer a) {
+  __shared__ float t[kSub][65];
+  __shared__ int any;
+  int wg = blockIdx.x;
+  if (wg < a.near_wgs) {
+    near_operands(a.U, a.P, a.ldh, a.rows.n, 0, a.near, wg % kNearTiles, wg / kNearTiles % kNearEvents, wg / (kNearTiles * kNearEvents), t);
+    return;
+  }
+  wg -= a.near_wgs;
+  if (wg < a.row_wgs) row_params(a.rows, wg);
+  else zero_dead_columns(a.W, a.rows.ldw, a.rows.m, a.rows.n, a.rows.dead, wg - a.row_wgs, any);
 }
 }  // namespace gptaq
 
@@ -456,10 +483,6 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
                              int mse_grid, int mse_steps, bool may_use_helper = true, bool make_farop = true, bool near_made = false,
                              hipEvent_t operands_made = nullptr) {
   const int64_t ev_kt = round_up(m, 256) * 32;   // a k-tile of the -E / V buffers, in elements
-  if (dead) {
-    hipLaunchKernelGGL(zero_dead_columns_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, s, W, ldw, (int)m, (int)n, dead);
-    GPTAQ_LAUNCH_CHECK();
-  }
   SbArgs a;
   a.W = W; a.ldw = ldw; a.m = (int)m; a.n = (int)n;
   a.maxq = (float)((1 << bits) - 1); a.group = group; a.sym = sym; a.terms = terms;
@@ -468,11 +491,6 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
   a.evkt = ev_kt;
   a.clip_grid = mse_grid; a.clip_steps = group > 0 ? mse_steps : 0;
   a.fast_rows = (ldw % 4 == 0) && (((uintptr_t)W & 15) == 0) && (n % 16 == 0) && (((uintptr_t)codes & 15) == 0);
-  if (group <= 0) {
-    hipLaunchKernelGGL(row_params_kernel, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, W, ldw, (int)m, (int)n,
-                       a.maxq, sym, mse_grid, mse_steps, scales, zeros);
-    GPTAQ_LAUNCH_CHECK();
-  }
   const int nsb = (int)((n + kSbCols - 1) / kSbCols);
   // (with one or two super-blocks there is no far2; it pays when the super-block kernel leaves most of the chip free.  One chain / two,
   // ms: 4096 rows: 3072 columns 0.56 / 0.56, 4096 0.86 / 0.83, 5120 1.27 / 1.18; 3072 rows: 4096 0.81 / 0.76, 8192 2.47 / 2.28, 11008
@@ -547,6 +565,17 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     ProfScope ps(kProfTrailGemm, st);
     chk(launch_gemm(b, st));
   };
+  {
+    BeginLayer f{U, (terms & 2) ? P : U, ldh, near, RowParams{W, ldw, (int)m, (int)n, dead, a.maxq, sym, mse_grid, mse_steps, scales, zeros}, W, 0, 0, 0};
+    if (terms != 0 && !near_made) f.near_wgs = kNearTiles * kNearEvents * 2;
+    if (group <= 0) f.row_wgs = (int)((m + 3) / 4);
+    if (dead) f.dead_wgs = (int)((n + 63) / 64);
+    if (f.near_wgs + f.row_wgs + f.dead_wgs > 0) {
+      ProfScope ps(kProfTrailSplit, s);
+      hipLaunchKernelGGL(begin_layer_kernel, dim3((unsigned)(f.near_wgs + f.row_wgs + f.dead_wgs)), dim3(256), 0, s, f);
+      chk(hipGetLastError());
+    }
+  }
   for (int k = 0; k < nsb && ok; ++k) {
     const int64_t sb0 = (int64_t)k * kSbCols;
     const int64_t sb_end = n < sb0 + kSbCols ? n : sb0 + kSbCols;
@@ -555,11 +584,11 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     uint16_t* const* ev = buf + (set ? 12 : 0);
     a.sb0 = (int)sb0; a.sbw = (int)(sb_end - sb0);
     a.EV = far ? ev[0] : nullptr; a.evstride = ev[1] - ev[0];
-    // this super-block's columns must have every earlier update, and its buffer set must be free again
-    if (two_chains && k >= 2) chk(hipStreamWaitEvent(s, ev_far2(k - 2), 0));
+    // (with two chains this super-block's columns have every earlier update and its buffer set is free again: far1(k - 1) has waited for
+    // far2(k - 2), and another wait for it costs the stream some 9 us)
     if (k == 0 && far_operands && !two_chains) make_far_operands();
     a.near = near_in_front ? near : near.at(k);
-    if (terms != 0 && (near_in_front || (k == 0 && !near_made))) {
+    if (terms != 0 && near_in_front && k > 0) {
       ProfScope ps(kProfTrailSplit, s);
       chk(launch_near_operands(U, (terms & 2) ? P : U, ldh, (int)n, k, 1, a.near, s));
     }
