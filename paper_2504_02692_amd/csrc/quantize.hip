@@ -492,14 +492,15 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
   a.clip_grid = mse_grid; a.clip_steps = group > 0 ? mse_steps : 0;
   a.fast_rows = (ldw % 4 == 0) && (((uintptr_t)W & 15) == 0) && (n % 16 == 0) && (((uintptr_t)codes & 15) == 0);
   const int nsb = (int)((n + kSbCols - 1) / kSbCols);
-  // (with one or two super-blocks there is no far2; it pays when the super-block kernel leaves most of the chip free.  One chain / two,
-  // ms: 4096 rows: 3072 columns 0.56 / 0.56, 4096 0.86 / 0.83, 5120 1.27 / 1.18; 3072 rows: 4096 0.81 / 0.76, 8192 2.47 / 2.28, 11008
-  // 3.82 / 3.51; fewer rows lose: 1024 of 3072 0.52 / 0.55, of 4096 0.70 / 0.73, of 5120 0.91 / 0.94.  More rows, and most matrices of
+  // (with one or two super-blocks there is no far2; it pays when the super-block kernel leaves most of the chip free, and the far updates of
+  // so many rows take longer than the events between the streams.  One chain / two, us: 1024 rows: 3072 columns 509 / 517, 4096 693 / 700,
+  // 6144 1129 / 1172; 256 rows: 4096 689 / 698, 6144 1087 / 1143, 8192 1610 / 1720; 1536: 3072 510 / 515, 4096 714 / 705, 5120 954 / 928; 2560: 3072
+  // 534 / 519, 4096 768 / 724, 8192 2152 / 1945; 4096: 2560 475 / 458, 4096 864 / 775, 5120 1202 / 1122.  More rows, and most matrices of
   // more columns, go through as row halves: see first_row_half)
   int cus = 256, dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
   const int sbk_wgs = (int)((m + 63) / 64);
-  const bool two_chains = may_use_helper && terms != 0 && nsb >= 3 && sbk_wgs <= cus / 4;
+  const bool two_chains = may_use_helper && terms != 0 && nsb >= 3 && m > 1024 && sbk_wgs <= cus / 4;
   std::unique_lock<std::mutex> side_lock(side_stream_mutex(), std::defer_lock);
   SideStream* side = nullptr;
   if (two_chains) {
