@@ -58,13 +58,14 @@ struct GemmProblem {
   int32_t tile_mode;     // 0: all tiles; 1: tiles entirely below the diagonal do no work (but store);
                          // 2: square problem, only tiles with tile column >= tile row are scheduled
   int32_t k_mode;        // 0: all k; 1: k >= first column of the tile; 2: tile row0 <= k < tile col end
-  int32_t store_mode;    // 0: C += acc; 1: C = acc; 2: C = acc where col > row, else 0
+  int32_t store_mode;    // 0: C += acc; 1: C = acc; 2: C = acc where col > row, else 0; 3: as 2, in out_hi and out_lo instead of C
   int32_t deal;          // how the tile list is shared out to the 8 XCDs: 0: one contiguous run each (tiles of equal
                          // length); 1: dealt four tiles at a time (tile lengths that vary along the list: k_mode 1, 2)
   int32_t split;         // > 1 (128-tiles, k_mode 0, store_mode 0): K in so many parts, each summed by workgroups of its own into
   float* partial;        // `partial` (tiles * split * 128 * 128 floats), and added to C by a second kernel; 0 counts as 1
   int32_t quartered;     // (256-tiles of kind 0 in a batch of kind 3, second problem) so many of its last tiles are taken as four of 128 x 128
   int32_t lo_rows;       // kind 3: how lo lies (see above)
+  uint16_t *out_hi, *out_lo;      // store_mode 3: k-tile-major with ldc rows, the tiles that have work
   GemmTerm term[2];
 };
 

@@ -613,6 +613,37 @@ __device__ __forceinline__ void store_tile(float* C, int64_t ldc, int M, int N, 
   else store_tile_as<BT, 2, false, false>(C, ldc, M, N, store_mode, m0, n0, acc);
 }
 
+// What lies above the diagonal of C = acc, 0 elsewhere, split into bf16 hi and lo as the left operand of another product (k-tile-major, a
+// multiple of the tile in rows and columns), instead of C: entries past the matrix are zeros already.
+// Saves a pass over the result: 5 / 17 / 90 us at n = 512 / 4096 / 11008.  (Addressed as in store_tile.)
+template <int BT>
+__device__ __forceinline__ void store_operand(const GemmProblem& P, int m0, int n0, const f32x16 (&acc)[BT / 64][BT / 64]) {
+  constexpr int WT = BT / 2, FR = WT / 32;
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int row0 = m0 + (wave >> 1) * WT, col0 = n0 + (wave & 1) * WT;               // the wavefront's first element
+  const int64_t first = uniform((int64_t)(col0 >> 5) * P.ldc * 32 + (int64_t)row0 * 32);
+  const TileBuffer hi(reinterpret_cast<float*>(P.out_hi + first)), lo(reinterpret_cast<float*>(P.out_lo + first));
+  const int lrow = 4 * (lane >> 5), above = row0 + lrow - col0 - (lane & 31);
+  const uint32_t at = (uint32_t)(lrow * 64 + (lane & 31) * 2), kt = (uint32_t)uniform(P.ldc) * 64u;
+#pragma unroll
+  for (int i = 0; i < FR; ++i)
+#pragma unroll
+    for (int j = 0; j < FR; ++j) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int r = 32 * i + 8 * (v >> 2) + (v & 3);
+        const float x = 32 * j - r > above ? acc[i][j][v] : 0.f;
+        const __bf16 h = (__bf16)x;
+        const __bf16 l = (__bf16)(x - (float)h);
+        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, h), hi.rsrc, at, j * kt + 64 * r, 0);
+        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, l), lo.rsrc, at, j * kt + 64 * r, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 // Tile row and column of tile number `id` of a problem.
 __device__ __forceinline__ void tile_position(const GemmProblem& P, int id, int& tm, int& tn) {
   // Tiles are numbered in groups of GROUP tile rows, column by column inside a group, so the workgroups
@@ -667,7 +698,7 @@ __device__ __forceinline__ void store_partial(float* dst, const f32x16 (&acc)[BT
 }
 
 // One BT x BT tile of C: tile number `wid` of the batch (see the numbering below).
-template <int BT, bool CAPPED, bool SPLIT, bool REMAINDER>
+template <int BT, bool CAPPED, bool SPLIT, bool REMAINDER, bool OPERAND>
 __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* smem, int wid) {
   constexpr int WT = BT / 2;             // wave tile edge
   constexpr int FR = WT / 32;            // 32x32 MFMA blocks per wave tile edge
@@ -745,6 +776,7 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* sme
   } else if constexpr (CAPPED) {       // (kind 2 alone: launch_gemm refuses others)
     if (P.nterm > 1) tile_loop<BT, 2, true>(P, smem, m0, n0, klo, nk, acc);
     else tile_loop<BT, 2, false>(P, smem, m0, n0, klo, nk, acc);
+  // (The same holds where the result becomes an operand: with kind 2's loop alone the 256-tile's accumulators were spilled, 3.1 ms instead of 1.1.)
   // (No batch has kinds 0 and 1 with several terms, nor as 256-tiles here, but the code that the compiler makes for kind 2 is better with them in
   // the kernel: without, two halves of 22016 x 4096 weights take 2551 us instead of 2522, and a solve with 1024 columns 977 instead of 967.)
   } else if (P.nterm > 1) {
@@ -764,8 +796,10 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* sme
     store_partial<BT>(P.partial + (int64_t)(part * nt + id) * (BT * BT), acc);
     return;
   }
+  if (OPERAND && skipped) return;      // (the blocks below the diagonal are never read)
   wait_vm_and_lds<0>();      // (said here again, where all loops meet: else the compiler counts their loads among the tile's and waits for all of these)
-  store_tile<BT>(P.C, uniform(P.ldc), uniform(P.M), uniform(P.N), uniform(P.store_mode), m0, n0, acc);
+  if constexpr (OPERAND) store_operand<BT>(P, m0, n0, acc);
+  else store_tile<BT>(P.C, uniform(P.ldc), uniform(P.M), uniform(P.N), uniform(P.store_mode), m0, n0, acc);
 }
 
 // C[i][i] += sum_k L0[i][k]^2 over all of K, of a problem whose other sums are taken in parts: a workgroup's first wavefront per 32 rows, which takes the
@@ -821,16 +855,17 @@ __device__ __forceinline__ void diagonal_block(const GemmProblem& P, int block) 
 // ...: the caller caps the grid to leave compute units to a kernel running beside this one.  The grid is a multiple
 // of 8 then, so a workgroup's tiles all belong to its own XCD's share.
 // REMAINDER: a batch of kinds 3 and 0 (a kernel of its own: in one with the other loops theirs lost 5 %).
-template <int BT, bool CAPPED, bool SPLIT = false, bool REMAINDER = false>
+// OPERAND: the result as an operand of another product (store_mode 3).
+template <int BT, bool CAPPED, bool SPLIT = false, bool REMAINDER = false, bool OPERAND = false>
 __global__ __launch_bounds__(256, BT == 128 ? 2 : 1) void gemm_nt_kernel(GemmBatch b) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if (!CAPPED) {
     if (SPLIT && (int)blockIdx.x < b.diag_wgs) { if (threadIdx.x < 64) diagonal_block(b.p[1], blockIdx.x); }
-    else gemm_tile<BT, false, SPLIT, REMAINDER>(b, smem, blockIdx.x - (SPLIT ? b.diag_wgs : 0));
+    else gemm_tile<BT, false, SPLIT, REMAINDER, OPERAND>(b, smem, blockIdx.x - (SPLIT ? b.diag_wgs : 0));
   } else {
     const int total = b.ntiles[0] + b.ntiles[1];
     for (int wid = blockIdx.x; wid < total; wid += gridDim.x) {
-      gemm_tile<BT, true, false, false>(b, smem, wid);
+      gemm_tile<BT, true, false, false, false>(b, smem, wid);
       __syncthreads();                   // the last fragment reads of this tile before the next tile's loads land in LDS
     }
   }
@@ -875,7 +910,7 @@ __global__ __launch_bounds__(256) void add_parts_kernel(GemmBatch b) {
       if (row0 + 8 * v + q < P.M && col < P.N && !(pi && b.diag_wgs && row0 + 8 * v + q == col)) P.C[(int64_t)(row0 + 8 * v + q) * P.ldc + col] = c[v][q] + sum[v][q];
 }
 
-static LdsLimitOnce g_lds256, g_lds128, g_lds256c, g_lds128c, g_lds128s, g_lds256r, g_lds128r;
+static LdsLimitOnce g_lds256, g_lds128, g_lds256c, g_lds128c, g_lds128s, g_lds256r, g_lds128r, g_lds256o, g_lds128o;
 hipError_t launch_gemm(const GemmBatch& b, hipStream_t s) {
   GemmBatch bb = b;
   int total = 0, part_tiles = 0;
@@ -889,6 +924,7 @@ hipError_t launch_gemm(const GemmBatch& b, hipStream_t s) {
     if (i < bb.nprob && q.kind == 3 && (q.nterm != 1 || q.k_mode || q.K % (2 * kGemmBK) || q.K > kMaxRemainderK)) return hipErrorInvalidValue;
     if (i < bb.nprob && remainder && (q.split > 1 || b.max_wgs > 0 || (q.kind != 3 && (q.kind != 0 || q.nterm != 1)))) return hipErrorInvalidValue;
     if (i < bb.nprob && b.max_wgs > 0 && q.kind != 2) return hipErrorInvalidValue;
+    if (i < bb.nprob && q.store_mode == 3 && (bb.nprob != 1 || q.kind != 2 || q.nterm != 1 || q.split > 1 || b.max_wgs > 0 || !q.out_hi || !q.out_lo)) return hipErrorInvalidValue;
     total += bb.ntiles[i];
     if (q.split > 1) part_tiles += bb.ntiles[i] / q.split;
   }
@@ -902,8 +938,13 @@ hipError_t launch_gemm(const GemmBatch& b, hipStream_t s) {
   if (e == hipSuccess) e = g_lds128s.ensure(reinterpret_cast<const void*>(&gemm_nt_kernel<128, false, true>), kLds128);
   if (e == hipSuccess) e = g_lds256r.ensure(reinterpret_cast<const void*>(&gemm_nt_kernel<256, false, false, true>), kLds256);
   if (e == hipSuccess) e = g_lds128r.ensure(reinterpret_cast<const void*>(&gemm_nt_kernel<128, false, false, true>), kLds128);
+  if (e == hipSuccess) e = g_lds256o.ensure(reinterpret_cast<const void*>(&gemm_nt_kernel<256, false, false, false, true>), kLds256);
+  if (e == hipSuccess) e = g_lds128o.ensure(reinterpret_cast<const void*>(&gemm_nt_kernel<128, false, false, false, true>), kLds128);
   if (e != hipSuccess) return e;
-  if (remainder) {
+  if (b.p[0].store_mode == 3) {
+    if (b.tile == 256) hipLaunchKernelGGL((gemm_nt_kernel<256, false, false, false, true>), dim3(total), dim3(256), kLds256, s, bb);
+    else hipLaunchKernelGGL((gemm_nt_kernel<128, false, false, false, true>), dim3(total), dim3(256), kLds128, s, bb);
+  } else if (remainder) {
     if (b.tile == 256) hipLaunchKernelGGL((gemm_nt_kernel<256, false, false, true>), dim3(total), dim3(256), kLds256, s, bb);
     else hipLaunchKernelGGL((gemm_nt_kernel<128, false, false, true>), dim3(total), dim3(256), kLds128, s, bb);
   } else if (part_tiles) {

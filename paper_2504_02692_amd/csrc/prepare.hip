@@ -58,40 +58,75 @@ __global__ __launch_bounds__(1024) void diag_stats_kernel(const float* H, int64_
 
 // F (upper triangle, fp64) = H + lambda I with the dead-input rule applied.
 // A NaN or Inf in the upper triangle of H is reported as info[0] = -(1 + row of the entry) (smallest row wins).
-__global__ void build_F_kernel(const float* H, int64_t ldh, int n, const double* lam, double* F, int64_t ldf, int32_t* info) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x, i = blockIdx.y;
-  if (j >= n || j < i) return;
-  const float h = H[(int64_t)i * ldh + j];
-  if (!__builtin_isfinite(h)) atomicMin(info, -(1 + i));
-  double v = (double)h;
-  if (i == j) { if (v == 0.0) v = 1.0; v += *lam; }
-  F[(int64_t)i * ldf + j] = v;
+// 256 columns of 16 rows, one workgroup: a wavefront four rows, four columns a lane.  Bound by memory: 30 us at n = 4096, 139 at
+// 11008 (one entry a thread: 36 and 205).
+constexpr int kBuildRows = 16;
+__global__ __launch_bounds__(256) void build_F_kernel(const float* H, int64_t ldh, int n, const double* lam, double* F, int64_t ldf, int32_t* info) {
+  typedef __attribute__((ext_vector_type(2))) double f64x2;
+  const int j = blockIdx.x * 256 + 4 * (threadIdx.x & 63), r0 = kBuildRows * blockIdx.y + 4 * (threadIdx.x >> 6);
+  if (blockIdx.x * 256 + 256 <= kBuildRows * blockIdx.y || j >= n) return;
+  const bool wide = ((uintptr_t)H & 15) == 0 && ldh % 4 == 0 && j + 4 <= n;
+  float h[4][4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float* src = H + (int64_t)min(r0 + q, n - 1) * ldh;
+    if (wide) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(src + j);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) h[q][e] = x[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) h[q][e] = src[min(j + e, n - 1)];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int i = r0 + q;
+    if (i >= n || j + 3 < i) continue;
+    double v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = (double)h[q][e];
+      if (j + e >= i && j + e < n && !__builtin_isfinite(h[q][e])) atomicMin(info, -(1 + i));
+      if (j + e == i) {
+        if (v[e] == 0.0) v[e] = 1.0;
+        v[e] += *lam;
+      }
+    }
+    // (what lies below the diagonal or past column n in a row of F is not read, and F's rows are a multiple of 16 long)
+    double* dst = F + (int64_t)i * ldf + j;
+    *reinterpret_cast<f64x2*>(dst) = f64x2{v[0], v[1]};
+    *reinterpret_cast<f64x2*>(dst + 2) = f64x2{v[2], v[3]};
+  }
 }
 
 // --------------------------------------------------------------- extraction and splits
 // U (fp32, upper, zeros below) from F; its bf16 hi/lo split row-major (Uh, Ul) and
-// transposed (Uth, Utl), zero-padded to np x np.   grid (np/64, np/64), 256 threads.
-__global__ __launch_bounds__(256) void extract_U_kernel(const double* F, int64_t ldf, int n, float* U, int64_t ldu,
-                                                        uint16_t* Uh, uint16_t* Ul, uint16_t* Uth, uint16_t* Utl,
-                                                        int64_t np) {
+// transposed (Uth, Utl), zero-padded to np x np.   grid (np/64, np/64).
+// Bound by memory at large n, by the latency of its loads at small: with 256 threads, 16 rows each in turn, 9 / 41 / 297 us at
+// n = 512 / 4096 / 11008; 5 / 38 / 257.
+constexpr int kExtractThreads = 1024, kExtractStep = kExtractThreads / 64;
+__global__ __launch_bounds__(kExtractThreads) void extract_U_kernel(const double* F, int64_t ldf, int n, float* U, int64_t ldu, uint16_t* Uh,
+                                                                    uint16_t* Ul, uint16_t* Uth, uint16_t* Utl, int64_t np) {
   __shared__ uint16_t th[64][66], tl[64][66];
   const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-  const int c = threadIdx.x & 63, rb = threadIdx.x >> 6;
+  const int c = threadIdx.x & 63, rb = threadIdx.x >> 6, gc = c0 + c;
   if (c0 / kSplitBlock < r0 / kSplitBlock) {
-    for (int p = 0; p < 16; ++p) {
-      const int gr = r0 + rb + 4 * p, gc = c0 + c;
+#pragma unroll
+    for (int p = 0; p < 64 / kExtractStep; ++p) {
+      const int gr = r0 + rb + kExtractStep * p;
       if (gr < n && gc < n) U[(int64_t)gr * ldu + gc] = 0.f;
     }
     return;
   }
-#pragma unroll 4
-  for (int p = 0; p < 16; ++p) {
-    const int r = rb + 4 * p, gr = r0 + r, gc = c0 + c;
-    float u = 0.f;
-    if (gr < n && gc < n) {
-      if (gc >= gr) u = (float)F[(int64_t)gr * ldf + gc];
-      U[(int64_t)gr * ldu + gc] = u;
-    }
+  double f[64 / kExtractStep];
+#pragma unroll
+  for (int p = 0; p < 64 / kExtractStep; ++p) f[p] = F[(int64_t)min(r0 + rb + kExtractStep * p, n - 1) * ldf + min(gc, n - 1)];
+#pragma unroll
+  for (int p = 0; p < 64 / kExtractStep; ++p) {
+    const int r = rb + kExtractStep * p, gr = r0 + r;
+    const float u = gr < n && gc < n && gc >= gr ? (float)f[p] : 0.f;
+    if (gr < n && gc < n) U[(int64_t)gr * ldu + gc] = u;
     const uint16_t h = bf16_rne(u);
     const uint16_t l = bf16_rne(u - bf16_f32(h));
     const int64_t o = operand_at(gr, gc, np);
@@ -101,15 +136,14 @@ __global__ __launch_bounds__(256) void extract_U_kernel(const double* F, int64_t
     tl[r][c] = l;
   }
   __syncthreads();
-  for (int p = 0; p < 16; ++p) {
-    const int r = rb + 4 * p;            // r: column of U inside the tile, c: row of U
+#pragma unroll
+  for (int p = 0; p < 64 / kExtractStep; ++p) {
+    const int r = rb + kExtractStep * p;            // r: column of U inside the tile, c: row of U
     const int64_t o = operand_at(c0 + r, r0 + c, np);
     Uth[o] = th[c][r];
     Utl[o] = tl[c][r];
   }
 }
-
-__global__ __launch_bounds__(256) void split_rows_kernel(SplitRows a) { split_rows(a, blockIdx.x, blockIdx.y); }
 
 }  // namespace gptaq
 
@@ -168,7 +202,7 @@ extern "C" int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, floa
   double* lam = (double*)(base + L.off_lam);
   double* F = (double*)(base + L.off_F);
   uint8_t* deadbuf = dead ? dead : (uint8_t*)(base + L.off_dead);
-  float* Obuf = (float*)(base + L.off_O);
+  uint16_t *Oh = (uint16_t*)(base + L.off_O), *Ol = Oh + L.np * L.np;      // O as the left operand of the last product
   int32_t* sync = (int32_t*)(base + L.off_sync);
   I8Operand sl[8];
   for (int i = 0; i < 8; ++i) sl[i] = I8Operand{base + L.off_pl[i], (int32_t*)(base + L.off_sc[i]), i < 5 ? L.rp : (int64_t)NBO};
@@ -182,7 +216,7 @@ extern "C" int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, floa
   hipLaunchKernelGGL(diag_stats_kernel, dim3(1), dim3(1024), 0, s, H, ldh, ni, damp, deadbuf, lam, info, sync,
                      (int)((n + NBO - 1) / NBO * (kBlockSyncBytes / 4)));
   GPTAQ_LAUNCH_CHECK();
-  hipLaunchKernelGGL(build_F_kernel, dim3((unsigned)((n + 255) / 256), (unsigned)n), dim3(256), 0, s, H, ldh, ni,
+  hipLaunchKernelGGL(build_F_kernel, dim3((unsigned)((n + 255) / 256), (unsigned)((n + kBuildRows - 1) / kBuildRows)), dim3(256), 0, s, H, ldh, ni,
                      lam, F, ldf, info);
   GPTAQ_LAUNCH_CHECK();
 
@@ -195,7 +229,7 @@ extern "C" int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, floa
     if (swept != hipSuccess) { set_last_hip_error(swept); return GPTAQ_ELAUNCH; }
   }
   // U -> H (fp32) and the bf16 splits.
-  hipLaunchKernelGGL(extract_U_kernel, dim3((unsigned)(np / 64), (unsigned)(np / 64)), dim3(256), 0, s, F, ldf, ni, H,
+  hipLaunchKernelGGL(extract_U_kernel, dim3((unsigned)(np / 64), (unsigned)(np / 64)), dim3(kExtractThreads), 0, s, F, ldf, ni, H,
                      ldh, Uh, Ul, Uth, Utl, np);
   GPTAQ_LAUNCH_CHECK();
   // The K ranges of these two products are triangular, so tiles differ in length by the whole of K: the tile list is
@@ -207,9 +241,9 @@ extern "C" int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, floa
   b.nprob = 1; b.tile = tile;
   GemmProblem& g = b.p[0];
   // O = triu(dXXT U^T, 1): O[i][a] = sum_{b >= a} dXXT[i][b] U[a][b]
-  g.C = Obuf; g.ldc = np; g.M = ni; g.N = ni; g.K = (int)np;
+  g.C = nullptr; g.ldc = np; g.M = ni; g.N = ni; g.K = (int)np;
   g.tiles_m = g.tiles_n = (int)(np / tile);
-  g.kind = 2; g.nterm = 1; g.tile_mode = 1; g.k_mode = 1; g.store_mode = 2; g.deal = 1;
+  g.kind = 2; g.nterm = 1; g.tile_mode = 1; g.k_mode = 1; g.store_mode = 3; g.out_hi = Oh; g.out_lo = Ol; g.deal = 1;
   g.term[0] = {{Ah, Al}, {Uh, Ul}, 32, 32, np * 32, np * 32};
   hipError_t e;
   {
@@ -217,12 +251,9 @@ extern "C" int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, floa
     e = launch_gemm(b, s);
   }
   if (e != hipSuccess) { set_last_hip_error(e); return GPTAQ_ELAUNCH; }
-  // split O (reuses the dXXT split buffers), then P = O U: P[i][j] = sum_{i < a <= j} O[i][a] U[a][j]
-  hipLaunchKernelGGL(split_rows_kernel, dim3((unsigned)((np + 255) / 256), (unsigned)(np / kSplitRowsPerWg)), dim3(256), 0, s,
-                     SplitRows{Obuf, np, ni, nullptr, Ah, Al, np, nullptr});
-  GPTAQ_LAUNCH_CHECK();
-  g.C = dXXT; g.ldc = ldh; g.k_mode = 2;
-  g.term[0] = {{Ah, Al}, {Uth, Utl}, 32, 32, np * 32, np * 32};
+  // P = O U: P[i][j] = sum_{i < a <= j} O[i][a] U[a][j]
+  g.C = dXXT; g.ldc = ldh; g.k_mode = 2; g.store_mode = 2;
+  g.term[0] = {{Oh, Ol}, {Uth, Utl}, 32, 32, np * 32, np * 32};
   {
     ProfScope ps(kProfPGemm, s);
     e = launch_gemm(b, s);

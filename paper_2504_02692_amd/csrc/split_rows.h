@@ -1,5 +1,5 @@
-// bf16 hi/lo split of the strictly upper triangle of an fp32 matrix, the left operand of Theorem 4.2's products (prepare.hip); of
-// dXXT it is made beside the first block of the factor sweep (factor_sweep.hip).
+// bf16 hi/lo split of the strictly upper triangle of an fp32 matrix, dXXT as the left operand of Theorem 4.2's first product (prepare.hip),
+// made beside the first block of the factor sweep (factor_sweep.hip).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -20,14 +20,14 @@ constexpr int kSplitBlock = 256;
 // n = 4096): 147 -> 118 us per product at n = 4096, 1.32 -> 1.10 ms at n = 11008.
 __device__ __forceinline__ int64_t operand_at(int64_t row, int64_t k, int64_t np) { return (k >> 5) * np * 32 + row * 32 + (k & 31); }
 
-// Rows flagged in `zero_rows` read as 0; padded to np x np; entries on and below the diagonal are not read and come out as 0.  Both
-// uses want exactly that: Eq. 17 masks dXXT L to its strictly upper part and L is lower triangular, so entry (i, k) of dXXT only
-// ever meets a non-zero of L when k > i, and the masked product itself is strictly upper.
+// Rows flagged in `zero_rows` count as 0; padded to np x np; entries on and below the diagonal come out as 0, whatever they are: Eq. 17
+// masks dXXT L to its strictly upper part and L is lower triangular, so entry (i, k) of dXXT only ever meets a non-zero of L when k > i.
 // `info` (may be NULL): a NaN or Inf among the entries read is reported as info[0] = -(1 + row of the entry).
 struct SplitRows { const float* A; int64_t lda; int n; const uint8_t* zero_rows; uint16_t *Ah, *Al; int64_t np; int32_t* info; };
 // Columns cx * 256 .. + 255 of 32 rows, one workgroup of 256; ceil(np / 256) times np / 32 of them.  Eight columns of a row per thread and
-// four rows in turn: a wavefront reads 128 bytes of each of 16 rows and writes 1 KB runs of a k-tile.  Bound by memory: 23 -> 17 us at
-// n = 4096, 129 -> 90 at 11008 (a column of four rows per thread before); rows that are not 16-byte aligned are read entry by entry.
+// four rows in turn: a wavefront reads 128 bytes of each of 16 rows and writes 1 KB runs of a k-tile.  Bound by memory: as a launch
+// of its own 17 us at n = 4096, 90 at 11008 (a column of four rows per thread: 23 and 129); rows that are not 16-byte aligned are read entry
+// by entry.
 constexpr int kSplitRowsPerWg = 32;
 __device__ __forceinline__ void split_rows(const SplitRows& a, int64_t cx, int64_t ry) {
   typedef __attribute__((ext_vector_type(4))) float f4;
