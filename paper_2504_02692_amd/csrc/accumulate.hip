@@ -212,6 +212,16 @@ static Operands operands_at(void* ws, int64_t np, int64_t tokens, bool rows) {
   return {X, X + all, X + 2 * all, X + 2 * all + all / 2, (size_t)(6 * all), rows};
 }
 
+// Whether the sums of a pass are taken in blocks of 32 x 64, a workgroup's wavefronts an eighth of the tokens each (launch_narrow_sums): up to
+// 4096 tokens, where the full form has no more blocks than the chip has CUs (576 columns).  Measured, 128-tiles in one part or in parts
+// (with a workspace for them) / so, us per call: n = 512 and 1024 tokens 21 / 16, 2048 25 / 21, 4096 53 or 32 / 32 (full form 53 or 32 / 29); 256 and 1024
+// 19 / 15, 4096 50 or 27 / 28; with more tokens parts are the better (512 and 8192 40 / 47), and with a second block to a CU (640 and
+// 4096, full form 33 / 45).  (By the full form alone: the upper form is bit for bit the full one where it is defined.)
+static bool few_blocks(int64_t n, int64_t tokens) {
+  const int64_t rows = (n + 31) / 32, cols = (n + 63) / 64;
+  return tokens <= 4096 && rows * cols + cols * (cols + 1) <= 256;
+}
+
 // In how many parts of their tokens the sums of a pass are taken, and what the parts' sums need beside the operands.
 // With few columns the tiles of H and dXXT leave most of the chip idle (n = 1024: 72 or 100 of 512 places for 128-tiles).  dXXT's tiles,
 // of two products, are split in `split` parts and H's, of one, in half as many, so that all workgroups take the same time.  The number is
@@ -221,8 +231,8 @@ static Operands operands_at(void* ws, int64_t np, int64_t tokens, bool rows) {
 // diagonal_block.)
 // Measured, one part / so many, us per call of 32768 tokens, upper form (full): n = 256 302 / 75 (312 / 75), 512 317 / 88 (316 / 91), 768
 // 331 / 129 (321 / 147), 1024 370 / 194 (372 / 231), 1280 482 / 257 (481 / 349), 1536 534 / 342 (531 / 433); of 8192 tokens 512 91 / 40, 1024
-// 96 / 55 (97 / 73); of 4096 256 51 / 28, 512 54 / 34, 768 54 / 33 (55 / 34), 1024 54 / 36 (54 / 46), 1280 57 / 47 (59 / 53); of 2048 512 32 / 25,
-// 1024 34 / 28 (33 / 33); of 1024 there is nothing to be had (512 20.6 / 21.4).  Where the estimate promises less than a factor of 1.5 there was
+// 96 / 55 (97 / 73); of 4096 768 54 / 33 (55 / 34), 1024 54 / 36 (54 / 46), 1280 57 / 47 (59 / 53); of 2048
+// 1024 34 / 28 (33 / 33); of 1024 there is nothing to be had.  Where the estimate promises less than a factor of 1.5 there was
 // little to be had with many tokens and more than 640 columns (without the diagonal's workgroups: 2048 594 / 511 (687 / 699), 2736 888 / 861 (1241 /
 // 1277), 3072 and 8192 tokens 257 / 277 (352 / 384); 1536 and 16384 188 / 163 (206 / 228)); with less than 8192 tokens, or up to 640
 // columns, a factor of 1.1 is kept, and more than eight parts never were the best.  Errors against 64 bits fall with the length of the
@@ -230,6 +240,7 @@ static Operands operands_at(void* ws, int64_t np, int64_t tokens, bool rows) {
 static int split_for(int64_t n, int64_t tokens) {
   if (sparse_remainder(n)) return 1;             // (remainder_loop takes all of K; the estimate promises less than 1.5 from there on)
   if (gemm_tile_for(n, n) != 128) return 1;      // (256-tiles: they fill the chip, and the power limit takes what a fuller last round gives)
+  if (few_blocks(n, tokens)) return 1;
   const int64_t t = (n + 127) / 128, upper = t * (t + 1) / 2;
   const bool small = tokens < 8192 || t <= 5;
   int best = 1;
@@ -298,6 +309,8 @@ static hipError_t launch_products(const Operands& o, int64_t np, int64_t cp, int
     const int64_t t = a.tiles_m, upper = t * (t + 1) / 2;
     h.quartered = quartered_tiles((dxxt_upper ? upper : t * t) + upper);
   }
+  ProfScope ps(kProfAccumGemm, s);
+  if (few_blocks(n, cp)) return launch_narrow_sums(b, s);
   const int split = split_for(n, cp);
   if (split > 1 && o.bytes + partial_bytes(n, split) <= ws_bytes) {      // (a smaller workspace: sums in one part)
     a.split = split;
@@ -305,7 +318,6 @@ static hipError_t launch_products(const Operands& o, int64_t np, int64_t cp, int
     h.split = split / 2;
     h.partial = a.partial + (int64_t)a.tiles_m * a.tiles_m * split * (128 * 128);
   }
-  ProfScope ps(kProfAccumGemm, s);
   return launch_gemm(b, s);
 }
 

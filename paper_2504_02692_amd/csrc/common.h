@@ -80,6 +80,8 @@ struct GemmBatch {
 
 // Enqueue the batch; problems are scheduled in order (put the heavier one first).
 hipError_t launch_gemm(const GemmBatch& b, hipStream_t s);
+// The same for the sums of a narrow input: kind 1 first, kind 0 of the upper triangle second (tiles_m and tiles_n are filled in).
+hipError_t launch_narrow_sums(const GemmBatch& b, hipStream_t s);
 // Row padding the GEMM expects from an operand with `rows` logical rows.
 inline int gemm_tile_for(int64_t M, int64_t N) {
   // 256 x 256 tiles move the fewest bytes per flop but one workgroup fills a CU; use them only when they

@@ -910,6 +910,113 @@ __global__ __launch_bounds__(256) void add_parts_kernel(GemmBatch b) {
       if (row0 + 8 * v + q < P.M && col < P.N && !(pi && b.diag_wgs && row0 + 8 * v + q == col)) P.C[(int64_t)(row0 + 8 * v + q) * P.ldc + col] = c[v][q] + sum[v][q];
 }
 
+// C += L R^T for the two problems of a batch whose tiles are few: one workgroup per 32 x 64 block of C, its eight wavefronts take an eighth
+// of K each and add their sums up through LDS, in order, before C is rounded once.  So nothing but C is written, and a CU for every 128-tile
+// becomes one for each of its eight blocks.  Operand fragments come straight from memory, kNarrowAhead k-tiles ahead, 8 KB a k-tile for 16
+// MFMAs.  Bound by what a CU is given: a workgroup alone gets 35 bytes a clock (8 columns and 32768 tokens, 8 MB in 110 us), 200 of them 20
+// each (512 columns and 4096 tokens, full form, 1 MB in 23 us).  H's diagonal is left to diagonal_block.
+constexpr int kNarrowRows = 32, kNarrowCols = 64, kNarrowAhead = 4;
+template <int NL>
+__device__ __forceinline__ void narrow_loop(const GemmTerm& tm, int row0, int col0, int k0, int k1, f32x4 (&acc)[2][4]) {
+  // (16 rows of a k-tile are 1 KB in a row, and one load: with 32 x 32 products a load takes half of each of twice as many lines)
+  const int lane = threadIdx.x & 63, in_tile = (lane & 15) * 32 + 8 * (lane >> 4);
+  const int64_t row_at = (int64_t)row0 * 32 + in_tile, col_at = (int64_t)col0 * 32 + in_tile, step = tm.ktl;
+  u32x4 l[kNarrowAhead][NL][2], r[kNarrowAhead][4];
+  auto load = [&](int set, int k) {
+    const int64_t at = (int64_t)min(k, k1 - 1) * step;
+#pragma unroll
+    for (int o = 0; o < NL; ++o)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) l[set][o][i] = *reinterpret_cast<const u32x4*>(tm.L[o] + at + row_at + 512 * i);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r[set][j] = *reinterpret_cast<const u32x4*>(tm.R[0] + at + col_at + 512 * j);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if (k1 <= k0) return;
+#pragma unroll
+  for (int a = 0; a < kNarrowAhead; ++a) load(a, k0 + a);
+  auto multiply = [&](int a) {
+#pragma unroll
+    for (int o = 0; o < NL; ++o)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, l[a][o][i]), __builtin_bit_cast(bf16x8, r[a][j]), acc[i][j], 0, 0, 0);
+  };
+  int k = k0;                       // (no branch between the loads of a round: the compiler would wait for all of them)
+  for (; k + kNarrowAhead <= k1; k += kNarrowAhead)
+#pragma unroll
+    for (int a = 0; a < kNarrowAhead; ++a) {
+      multiply(a);
+      load(a, k + a + kNarrowAhead);
+    }
+#pragma unroll
+  for (int a = 0; a < kNarrowAhead - 1; ++a)
+    if (k + a < k1) multiply(a);
+}
+__global__ __launch_bounds__(512, 2) void narrow_kernel(GemmBatch b) {
+  __shared__ __attribute__((aligned(16))) f32x4 sums[8][8][64];          // by wavefront and piece of four rows
+  if ((int)blockIdx.x < b.diag_wgs) {
+    if (threadIdx.x < 64) diagonal_block(b.p[1], blockIdx.x);
+    return;
+  }
+  int id = blockIdx.x - b.diag_wgs, pi = 0, ntile = b.ntiles[0];
+  if (id >= ntile) { pi = 1; id -= ntile; ntile = b.ntiles[1]; }
+  const GemmProblem& P = b.p[pi];
+  {                                                                      // one run of blocks per XCD: they share their rows
+    const int per = ntile >> 3, rem = ntile & 7, xcd = id & 7, loc = id >> 3;
+    id = xcd < rem ? xcd * (per + 1) + loc : rem * (per + 1) + (xcd - rem) * per + loc;
+  }
+  int tr = 0, tc;
+  if (P.tile_mode == 2) {                                                // block rows 2 t and 2 t + 1 begin at block column t
+    for (int in_row = P.tiles_n; id >= in_row; ++tr) { id -= in_row; in_row = P.tiles_n - ((tr + 1) >> 1); }
+    tc = (tr >> 1) + id;
+  } else {
+    tr = id / P.tiles_n;
+    tc = id - tr * P.tiles_n;
+  }
+  const int row0 = uniform(tr * kNarrowRows), col0 = uniform(tc * kNarrowCols);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, nk = P.K / kGemmBK;
+  f32x4 acc[2][4];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[i >> 2][i & 3] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int k0 = (int)((int64_t)nk * wave / 8), k1 = (int)((int64_t)nk * (wave + 1) / 8);
+  if (P.kind == 0) narrow_loop<1>(P.term[0], row0, col0, k0, k1, acc);
+  else narrow_loop<2>(P.term[0], row0, col0, k0, k1, acc);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) sums[wave][i][lane] = acc[i >> 2][i & 3];
+  // wavefront w adds piece w up, 16 x 16 of C (a lane holds rows 4 (lane / 16) + 0 .. 3)
+  const int row = row0 + 16 * (wave >> 2) + 4 * (lane >> 4), col = col0 + 16 * (wave & 3) + (lane & 15);
+  float c[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) c[q] = P.C[(int64_t)min(row + q, P.M - 1) * P.ldc + min(col, P.N - 1)];
+  __syncthreads();
+  f32x4 sum = sums[0][wave][lane];
+#pragma unroll
+  for (int w = 1; w < 8; ++w) sum += sums[w][wave][lane];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (row + q < P.M && col < P.N && !(pi && row + q == col)) P.C[(int64_t)(row + q) * P.ldc + col] = c[q] + sum[q];
+}
+hipError_t launch_narrow_sums(const GemmBatch& b, hipStream_t s) {
+  GemmBatch bb = b;
+  if (b.nprob != 2) return hipErrorInvalidValue;
+  int total = 0;
+  for (int i = 0; i < 2; ++i) {
+    GemmProblem& q = bb.p[i];
+    if (q.kind != 1 - i || q.nterm != 1 || q.k_mode || q.store_mode || q.M != q.N || q.K <= 0 || q.K % kGemmBK || (i == 1 && q.tile_mode != 2)) return hipErrorInvalidValue;
+    q.tiles_m = (q.M + kNarrowRows - 1) / kNarrowRows;
+    q.tiles_n = (q.N + kNarrowCols - 1) / kNarrowCols;
+    bb.ntiles[i] = 0;
+    for (int r = 0; r < q.tiles_m; ++r) bb.ntiles[i] += q.tiles_n - (q.tile_mode == 2 ? r >> 1 : 0);
+    total += bb.ntiles[i];
+  }
+  bb.diag_wgs = (bb.p[1].tiles_m + 7) / 8 * 8;                            // (a multiple of 8, which leaves the blocks on their XCDs)
+  hipLaunchKernelGGL(narrow_kernel, dim3(bb.diag_wgs + total), dim3(512), 0, s, bb);
+  return hipGetLastError();
+}
+
 static LdsLimitOnce g_lds256, g_lds128, g_lds256c, g_lds128c, g_lds128s, g_lds256r, g_lds128r, g_lds256o, g_lds128o;
 hipError_t launch_gemm(const GemmBatch& b, hipStream_t s) {
   GemmBatch bb = b;

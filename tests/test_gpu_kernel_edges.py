@@ -365,9 +365,35 @@ def test_sums_in_parts_are_the_sums(n, ld, tokens):
 
 
 # The same with few tokens: the fewest of a size that are taken in parts, k-tiles that do not divide over them, a part of few k-tiles.
-@pytest.mark.parametrize("n,ld,tokens", [(8, 8, 2048), (264, 264, 2080), (512, 520, 4096), (776, 776, 4100), (1280, 1280, 6000)])
+@pytest.mark.parametrize("n,ld,tokens", [(8, 8, 4160), (584, 592, 2080), (512, 520, 6000), (776, 776, 4100), (1280, 1280, 6000)])
 def test_sums_in_parts_of_few_tokens(n, ld, tokens):
     test_sums_in_parts_are_the_sums(n, ld, tokens)
+
+
+# Blocks of 32 x 64 with an eighth of the tokens to a wavefront: one block and its edges, an odd number of block rows, the most columns; k-tiles for a
+# few wavefronts only, that do not divide over them, the most.  They need the operands' workspace and no more.
+@pytest.mark.parametrize("n,ld,tokens", [(8, 8, 1), (40, 48, 64), (72, 72, 200), (136, 140, 1100), (264, 264, 330), (512, 512, 4096), (552, 560, 2048), (576, 576, 4090)])
+def test_sums_of_narrow_inputs(n, ld, tokens):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    X = torch.randn((tokens, n), device="cuda", generator=g).bfloat16()
+    Xt = (X.float() + 0.05 * torch.randn((tokens, n), device="cuda", generator=g)).bfloat16()
+    start = torch.randn((n, n), device="cuda", generator=g)
+    size = B.gptaq_accumulate_workspace_bytes(tokens, n)
+    assert size == 6 * -(-n // 128) * 128 * (-(-tokens // 64) * 64)
+    Xd, Dd = X.double(), Xt.double() - X.double()
+    refs = ((start.double() + Xd.T.contiguous() @ Xd).triu(), start.double() + Dd.T.contiguous() @ Xd)
+    out = []
+    for call in (B.gptaq_accumulate, B.gptaq_accumulate_upper):
+        whole = [torch.full((n + 1, ld), -7.0, device="cuda") for _ in range(2)]
+        H, A = whole[0][:n, :n], whole[1][:n, :n]
+        H.copy_(start)
+        A.copy_(start)
+        call(X, Xt, H, A, B.workspace(size))
+        assert all((w[n:] == -7.0).all() and (w[:, n:] == -7.0).all() for w in whole)
+        out.append((H.triu(), A.clone()))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1].triu(), out[1][1].triu())
+    for got, ref in zip(out[0], refs):
+        assert float((got.double() - ref).norm() / ref.norm()) <= 3e-6          # (as in test_sums_in_parts_are_the_sums)
 
 
 @pytest.mark.parametrize("n,tokens", [(264, 8192), (520, 16448), (1032, 32768)])
