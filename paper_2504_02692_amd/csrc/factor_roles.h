@@ -263,26 +263,34 @@ __device__ __forceinline__ void factor_rows(const BlockFactor& a, FactorShared& 
   constexpr int NR = tile_rows(W), first = NH * HALF;
   const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4, ol = operand_lane(lane);
   f64x4 t[tile_base(W, NR)];
+  auto put_diag = [&](const f64x4& d) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sh.diag[16 * (4 * g + v) + r] = d[v];
+  };
+  // The second half's first tile is there before its others (half_row_role), and its factorisation takes the time in which they come.
+  Flags f{a.sync + 64, a.info, a.o0 + kFactorBlock / 2, lane};
   if (HALF) {
-    Flags f{a.sync + 64, a.info, a.o0 + kFactorBlock / 2, lane};
+    if (W == 1) {
+      f.wait(1ull);
+      put_diag(load_tile(half_tile(a, 0, 0), lane));
+    }
+    lds_barrier();
     f.wait(0xffffffffull);
   }
 #pragma unroll
   for (int b = 0; b < NH; ++b) {                               // (in the order in which they are needed)
 #pragma unroll
     for (int i = NR - 1; i >= 0; --i)
-      if (b <= tile_row(W, i))
+      if (b <= tile_row(W, i) && (!HALF || tile_row(W, i) > 0))
         t[tile_base(W, i) + b] = HALF ? load_tile(half_tile(a, tile_row(W, i), b), lane) : load_block_tile(a, tile_row(W, i), b, r, g);
     __builtin_amdgcn_sched_barrier(0);
   }
-  auto put_diag = [&](const f64x4& d) {
+  if (!HALF) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) sh.diag[16 * (4 * g + v) + r] = d[v];
-  };
-#pragma unroll
-  for (int i = 0; i < NR; ++i)
-    if (tile_row(W, i) == 0) put_diag(t[tile_base(W, i)]);
-  lds_barrier();
+    for (int i = 0; i < NR; ++i)
+      if (tile_row(W, i) == 0) put_diag(t[tile_base(W, i)]);
+    lds_barrier();
+  }
 #pragma clang loop unroll(full)
   for (int k = 0; k < NH; ++k) {
     lds_barrier();                                             // W_kk is in LDS; every wavefront is done with column k - 1
@@ -365,8 +373,9 @@ struct PanelShared {
   double rowmax[4][16];
 };
 // The left operands (W_kk for its owner, V_bk of the wavefront's later columns b) are fetched a step ahead if they are there.
-template <int STEPS>
-__device__ __forceinline__ void panel_steps(const double* V, f64x4 (&t)[STEPS / 4], int wave, int lane, PanelShared& sh, Flags& flags) {
+// after(k, V_ik negated): called by every wavefront at the end of each step but the last.
+template <int STEPS, class After>
+__device__ __forceinline__ void panel_steps(const double* V, f64x4 (&t)[STEPS / 4], int wave, int lane, PanelShared& sh, Flags& flags, After after) {
   constexpr int NQ = STEPS / 4;
   const int ol = operand_lane(lane);
   auto tile_of = [&](int k, int b) { return V + ((int64_t)k * NT + b) * TILE; };
@@ -398,6 +407,7 @@ __device__ __forceinline__ void panel_steps(const double* V, f64x4 (&t)[STEPS / 
 #pragma unroll
     for (int q = 0; q < NQ; ++q)
       if (4 * q + 3 > k && wave + 4 * q > k) t[q] = tile_product(vb[k & 1][q], nx, t[q]);
+    after(k, nx);
   }
 }
 
@@ -412,12 +422,23 @@ __device__ __forceinline__ void half_row_role(const BlockFactor& a, int m, Panel
 #pragma unroll
   for (int q = 0; q < 2; ++q) t[q] = load_block_tile(a, NH + m, NH + min(wave + 4 * q, m), r, g);
   Flags flags{a.sync, a.info, a.o0 + kFactorBlock, lane};
-  panel_steps<NH>(a.V, x, wave, lane, sh, flags);
+  // The first row's tile, which the factorisation goes on with, needs nothing of the other rows: wavefront 0 updates it column by column.
+  auto first_tile = [&](int k, const f64x4& nx) {
+    if (m == 0 && wave == 0) t[0] = tile_product(-load_tile(sh.x[k & 1], ol), nx, t[0]);
+  };
+  panel_steps<NH>(a.V, x, wave, lane, sh, flags, first_tile);
 #pragma unroll
   for (int q = 0; q < NH / 4; ++q) publish_tile(factor_tile(a.V, wave + 4 * q, NH + m), lane, x[q]);
+  if (m == 0) {
+    lds_barrier();
+    first_tile(NH - 1, load_tile(sh.x[(NH - 1) & 1], lane));
+    if (wave == 0) publish_tile(half_tile(a, 0, 0), lane, t[0]);
+  }
   wait_stores<0>();
+  if (m == 0) set_flag(a.sync, BlockSync::tile(0, wave), lane);
   lds_barrier();
   if (wave == 0) set_flag(a.sync, BlockSync::row(m), lane);
+  if (m == 0) return;
   flags.wait(((2ull << m) - 1) << BlockSync::row(0));
   f64x4 xa[NH], xb[2][NH];
 #pragma unroll
@@ -459,7 +480,7 @@ __device__ __forceinline__ void panel_role(const BlockFactor& f, const BlockPane
       t[q] = load_row4(f.F, f.ldf, f.n, row0 + r, f.o0 + kFactorBlock - 4 - 16 * (wave + 4 * q) - 4 * g);
   }
   Flags flags{f.sync, f.info, f.o0 + kFactorBlock, lane};
-  panel_steps<NT>(f.V, t, wave, lane, sh, flags);
+  panel_steps<NT>(f.V, t, wave, lane, sh, flags, [](int, const f64x4&) {});
   // ---- digits: one scale per row, the row's 256 entries are in the four wavefronts
   double mx = 0.0;
 #pragma unroll
