@@ -115,7 +115,7 @@ struct I8Gemm {
 // half's own block after the first half's update, as tiles (a, b), a >= b, at (a (a + 1) / 2 + b) * 256.
 constexpr int kFactorBlock = 256;
 constexpr size_t kFactorTileBytes = (size_t)kFactorBlock * kFactorBlock * 8, kHalfTileBytes = (size_t)36 * 256 * 8;
-constexpr size_t kBlockSyncBytes = 512;
+constexpr size_t kBlockSyncBytes = 768;
 struct BlockFactor {
   const double* F; int64_t ldf; int n, o0;
   int32_t* info;                     // set to 1 + index of the first pivot that is not positive, unless set already

@@ -112,10 +112,11 @@ __device__ __forceinline__ double rsqrt_of(double x) {
 // reader's own L2 cannot hold an older copy: nothing reads these lines earlier in the launch, and a launch starts with clean caches.
 // All words are 0 before the call's first launch.
 struct BlockSync {
-  static constexpr int kTicket = 56, kWords = 128;
+  static constexpr int kTicket = 56, kWords = kBlockSyncBytes / 4;
   static constexpr int column(int k, int w) { return 3 * k + w; }          // W_kk and the rows of wavefront w + 1 of tile column k
   static constexpr int row(int m) { return 48 + m; }                       // tile row NH + m on the first half's columns
   static constexpr int tile(int m, int w) { return 64 + 4 * m + w; }       // tiles w, w + 4 of row m of the second half's updated block
+  static constexpr int cell(int m, int k) { return 128 + 8 * m + k; }      // tile row NH + m on tile column k < NH
 };
 __device__ __forceinline__ void set_flag(int32_t* sync, int word, int lane) {      // (behind a wait for the stores it stands for)
   if (lane == 0) __hip_atomic_store(sync + word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -422,35 +423,57 @@ __device__ __forceinline__ void half_row_role(const BlockFactor& a, int m, Panel
 #pragma unroll
   for (int q = 0; q < 2; ++q) t[q] = load_block_tile(a, NH + m, NH + min(wave + 4 * q, m), r, g);
   Flags flags{a.sync, a.info, a.o0 + kFactorBlock, lane};
-  // The first row's tile, which the factorisation goes on with, needs nothing of the other rows: wavefront 0 updates it column by column.
-  auto first_tile = [&](int k, const f64x4& nx) {
-    if (m == 0 && wave == 0) t[0] = tile_product(-load_tile(sh.x[k & 1], ol), nx, t[0]);
-  };
-  panel_steps<NH>(a.V, x, wave, lane, sh, flags, first_tile);
+  // The update follows the columns, three steps behind: a row publishes a column at its step, its flag a step later, its rows are fetched by the
+  // others in the step after that and multiplied in the next.  What is left behind the last column is a product of three.
+  // (Row 0's one tile, which the factorisation goes on with first, needs nothing of other rows: wavefront 0 updates it from LDS, at once.)
+  Flags cells{a.sync + BlockSync::cell(0, 0), a.info, a.o0 + kFactorBlock, lane};
+  const uint64_t rows = m == NH - 1 ? ~0ull : (1ull << (8 * (m + 1))) - 1;
+  f64x4 nx[NH], xb[3][2];
+  auto fetch = [&](int k, int set) {
 #pragma unroll
-  for (int q = 0; q < NH / 4; ++q) publish_tile(factor_tile(a.V, wave + 4 * q, NH + m), lane, x[q]);
-  if (m == 0) {
-    lds_barrier();
-    first_tile(NH - 1, load_tile(sh.x[(NH - 1) & 1], lane));
-    if (wave == 0) publish_tile(half_tile(a, 0, 0), lane, t[0]);
+    for (int q = 0; q < 2; ++q) xb[set][q] = load_tile(factor_tile(a.V, k, NH + min(wave + 4 * q, m)), ol);
+  };
+  auto apply = [&](int k, int set) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) t[q] = tile_product(xb[set][q], nx[k], t[q]);
+  };
+  auto after = [&](int k, const f64x4& negated) {
+    nx[k] = negated;
+    if (wave == (k & 3)) publish_tile(factor_tile(a.V, k, NH + m), lane, x[k >> 2]);
+    if (m == 0) {
+      if (wave == 0) t[0] = tile_product(-load_tile(sh.x[k & 1], ol), negated, t[0]);
+    } else {
+      if (k >= 3) apply(k - 3, (k - 3) & 1);
+      if (k >= 2) {
+        cells.wait(rows & 0x0101010101010101ull << (k - 2));
+        fetch(k - 2, k & 1);
+      }
+    }
+    if (k > 0 && wave == ((k - 1) & 3)) {
+      wait_stores<0>();
+      set_flag(a.sync, BlockSync::cell(m, k - 1), lane);
+    }
+  };
+  panel_steps<NH>(a.V, x, wave, lane, sh, flags, after);
+  if (wave == 3) publish_tile(factor_tile(a.V, NH - 1, NH + m), lane, x[1]);
+  lds_barrier();
+  nx[NH - 1] = load_tile(sh.x[(NH - 1) & 1], lane);
+  if (m == 0 && wave == 0) {
+    t[0] = tile_product(-load_tile(sh.x[(NH - 1) & 1], ol), nx[NH - 1], t[0]);
+    publish_tile(half_tile(a, 0, 0), lane, t[0]);
   }
   wait_stores<0>();
   if (m == 0) set_flag(a.sync, BlockSync::tile(0, wave), lane);
+  if (wave >= 2) set_flag(a.sync, BlockSync::cell(m, wave + 4), lane);
   lds_barrier();
   if (wave == 0) set_flag(a.sync, BlockSync::row(m), lane);
   if (m == 0) return;
-  flags.wait(((2ull << m) - 1) << BlockSync::row(0));
-  f64x4 xa[NH], xb[2][NH];
+  apply(NH - 4, (NH - 4) & 1);
+  cells.wait(rows & 0xe0e0e0e0e0e0e0e0ull);
 #pragma unroll
-  for (int k = 0; k < NH; ++k) {
-    xa[k] = load_tile(factor_tile(a.V, k, NH + m), lane);
+  for (int k = NH - 3; k < NH; ++k) fetch(k, k - (NH - 3));
 #pragma unroll
-    for (int q = 0; q < 2; ++q) xb[q][k] = load_tile(factor_tile(a.V, k, NH + min(wave + 4 * q, m)), ol);
-  }
-#pragma unroll
-  for (int k = 0; k < NH; ++k)
-#pragma unroll
-    for (int q = 0; q < 2; ++q) t[q] = tile_product(xb[q][k], -xa[k], t[q]);
+  for (int k = NH - 3; k < NH; ++k) apply(k, k - (NH - 3));
 #pragma unroll
   for (int q = 0; q < 2; ++q)
     if (wave + 4 * q <= m) publish_tile(half_tile(a, m, wave + 4 * q), lane, t[q]);
