@@ -17,12 +17,12 @@
 //
 // What bounds them: one chain.  A block of 256 columns of a small matrix, in us: 2.8 until the first tiles are there, 14 for each half
 // (a tile 1.7 to 1.9: 1.28 of its 16 column steps, each a reciprocal, its Newton steps and an update; 0.5 until the next diagonal tile is
-// updated and handed over), 1.5 + 1.7 + 3.5 between them for the second half's rows (the last column, the rows from the other workgroups, the
-// update and its way back), 1.5 for the last column of the panel and 4.6 for its digits and their way to memory: 47 in all, and no more
-// than 55 beside products.  As launches of their own, the factorisation in one workgroup of eight wavefronts, panel and products on two
-// streams, it was 48 + 16 and 15 to 20 of events; with a launch for each half, the rows and the update between them 16 + 7 + 6 + 16.
+// updated and handed over), about 4 between them (the last column, the rows from the other workgroups, the rest of the update and its way
+// back, less the first tile's factorisation), 1.5 for the last column of the panel and 3 for its digits and their way to memory: 43 in
+// all, and about 50 beside products.  As launches of their own, the factorisation in one workgroup of eight wavefronts, panel and products
+// on two streams, it was 48 + 16 and 15 to 20 of events; with a launch for each half, the rows and the update between them 16 + 7 + 6 + 16.
 // An f64 MFMA (64 clocks for 1024 products) is no faster than v_fma_f64, but its operands are one register a lane.
-// gptaq_prepare at n = 512 / 4096 / 11008: 243 / 1976 / 18100 us -> 166 / 1620 / 17000.
+// gptaq_prepare at n = 512 / 4096 / 11008: 243 / 1976 / 18100 us -> 158 / 1545 / 16600.
 #pragma once
 #include "common.h"
 #include "gemm_i8s.h"
@@ -503,7 +503,19 @@ __device__ __forceinline__ void panel_role(const BlockFactor& f, const BlockPane
       t[q] = load_row4(f.F, f.ldf, f.n, row0 + r, f.o0 + kFactorBlock - 4 - 16 * (wave + 4 * q) - 4 * g);
   }
   Flags flags{f.sync, f.info, f.o0 + kFactorBlock, lane};
-  panel_steps<NT>(f.V, t, wave, lane, sh, flags, [](int, const f64x4&) {});
+  // (U's own entries go to memory as the columns come: all of them behind the last one took 1.3 us more)
+  const int j = kFactorBlock - 1 - (row0 + r);
+  auto store_u = [&](int q) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = kFactorBlock - 1 - (16 * (wave + 4 * q) + 4 * g + v);
+      a.Uob[j * kFactorBlock + i] = t[q][v];
+      if (i <= j && f.o0 + j < f.n) a.Uout[(int64_t)i * f.ldf + j] = t[q][v];
+    }
+  };
+  panel_steps<NT>(f.V, t, wave, lane, sh, flags, [&](int k, const f64x4&) {
+    if (inverse && wave == (k & 3)) store_u(k >> 2);
+  });
   // ---- digits: one scale per row, the row's 256 entries are in the four wavefronts
   double mx = 0.0;
 #pragma unroll
@@ -533,17 +545,7 @@ __device__ __forceinline__ void panel_role(const BlockFactor& f, const BlockPane
 #pragma unroll
     for (int i = 0; i < kI8Planes; ++i) *reinterpret_cast<uint32_t*>(dst + (int64_t)i * o.plane_stride()) = w[i];
   }
-  if (inverse) {
-    const int j = kFactorBlock - 1 - (row0 + r);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int i = kFactorBlock - 1 - (16 * (wave + 4 * q) + 4 * g + v);
-        a.Uob[j * kFactorBlock + i] = t[q][v];
-        if (i <= j && f.o0 + j < f.n) a.Uout[(int64_t)i * f.ldf + j] = t[q][v];
-      }
-  }
+  if (inverse && wave == 3) store_u(NT / 4 - 1);
 }
 }  // namespace
 }  // namespace gptaq
