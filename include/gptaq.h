@@ -136,10 +136,7 @@ int gptaq_symmetrize(float* H, int64_t n, int64_t ldh, void* stream);
  *          are garbage);
  *          info[1] = number of dead inputs.
  *   n    : at most 65280.
- * Streams: part of the factor sweep runs on a helper stream that the library creates once per device
- * (default priority, kept until the process ends) and ties to `stream` with events on both ends, so to
- * the caller the call is still one asynchronous operation on `stream`.  Host-side the call takes a
- * library lock: concurrent calls from several host threads are serialised while they enqueue.
+ * Streams: one asynchronous operation on `stream`; the call uses no other stream and no library lock.
  */
 size_t gptaq_prepare_workspace_bytes(int64_t n);
 int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, float damp,

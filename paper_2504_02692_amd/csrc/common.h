@@ -160,8 +160,8 @@ hipError_t launch_quant_sb(const SbArgs& a, hipStream_t s);
 
 void set_last_hip_error(hipError_t e);
 
-// Helper stream of the library: entry points that run two chains of kernels side by side (the factor sweep of
-// gptaq_prepare, the far updates of gptaq_quantize_layer) put one chain on the caller's stream and the other on this
+// Helper stream of the library: entry points that run two chains of kernels side by side (the far updates of
+// gptaq_quantize_layer, its row halves) put one chain on the caller's stream and the other on this
 // stream, tied together with events on both ends, so that to the caller the call is still one asynchronous
 // operation on its own stream.  One stream (default priority) and one growing pool of events per device, created on
 // first use and kept until the process ends.  The mutex serialises the host threads that enqueue through it.

@@ -109,11 +109,25 @@ __device__ __forceinline__ void row_params(const RowParams& a, int wg) {
   if (a.mse_steps > 0) {
     ClipSearch cs;
     cs.begin(mn, mx, a.maxq, a.sym);
-    for (int i = 0; i < a.mse_steps; ++i) {
-      const float si = cs.scale_of(i, a.mse_grid), isi = 1.f / si;
-      float e = 0.f;
-      for (int c = lane; c < a.n; c += 64) e += cs.err_of(weight(c), si, isi);
-      cs.offer(wave_sum(e), si);
+    // kTogether candidates to a pass over the row, each summed in the order of the columns: a pass for each waits for the row (and for
+    // what is dead in it) every time.  80 candidates, one / so many to a pass, us: 4096 x 640 227 / 198, 1031 x 1480 568 / 443, 4096 x 2136 1400 / 830.
+    constexpr int kTogether = 8;
+    for (int i0 = 0; i0 < a.mse_steps; i0 += kTogether) {
+      float si[kTogether], isi[kTogether], e[kTogether];
+#pragma unroll
+      for (int i = 0; i < kTogether; ++i) {
+        si[i] = cs.scale_of(min(i0 + i, a.mse_steps - 1), a.mse_grid);
+        isi[i] = 1.f / si[i];
+        e[i] = 0.f;
+      }
+      for (int c = lane; c < a.n; c += 64) {
+        const float v = weight(c);
+#pragma unroll
+        for (int i = 0; i < kTogether; ++i) e[i] += cs.err_of(v, si[i], isi[i]);
+      }
+#pragma unroll
+      for (int i = 0; i < kTogether; ++i)
+        if (i0 + i < a.mse_steps) cs.offer(wave_sum(e[i]), si[i]);
     }
     sc = cs.best_scale;
     zr = cs.zero;

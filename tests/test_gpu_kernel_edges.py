@@ -370,6 +370,35 @@ def test_sums_in_parts_of_few_tokens(n, ld, tokens):
     test_sums_in_parts_are_the_sums(n, ld, tokens)
 
 
+# The range of a whole row: candidates go through it eight at a time.  One, a few, a whole number of eights and a remainder; rows shorter than a
+# wavefront and not a multiple of one; dead columns, which count as 0 whatever they hold.
+@pytest.mark.parametrize("m,n,grid,steps,sym", [(3, 40, 100, 1, False), (65, 72, 100, 7, True), (130, 200, 100, 16, False), (31, 264, 60, 45, False), (200, 520, 100, 80, True)])
+def test_row_range_search(m, n, grid, steps, sym):
+    rng = np.random.default_rng(n)
+    W = rng.standard_normal((m, n)).astype(np.float32)
+    dead = np.zeros(n, np.uint8)
+    dead[5::37] = 1
+    alive = np.where(dead, np.float32(0), W)
+    W[:, dead == 1] = 9.0
+    got = PU.gpu_quantize(W, dev(np.eye(n)), None, 4, 0, sym, 128, dead=dev(dead).to(torch.uint8), terms=0, mse=(grid, steps))
+    rows = torch.from_numpy(alive).double().numpy()
+    lo, hi = np.minimum(rows.min(1), 0), np.maximum(rows.max(1), 0)
+    if sym:
+        hi = np.maximum(-lo, hi)
+        lo = -hi
+    base = (hi - lo) / 15
+    zero = np.full(m, 8.0) if sym else np.rint(-lo / base.astype(np.float32))
+    scale = np.stack([((1 - i / grid) * base).astype(np.float32) for i in range(steps)])            # (steps, m)
+    q = np.clip(np.rint(rows[None] / scale[:, :, None].astype(np.float64)) + zero[None, :, None], 0, 15)
+    err = (((q - zero[None, :, None]) * scale[:, :, None] - rows[None]) ** 2).sum(2)
+    mine = got["scales"].reshape(m)
+    at = np.abs(scale - mine[None]).argmin(0)
+    assert np.array_equal(scale[at, np.arange(m)], mine) and np.array_equal(got["zeros"].reshape(m), zero)
+    # an fp32 sum of n squares against the exact one: n 2^-24 at most of each of the two compared, and x / scale by a reciprocal may take an entry on a
+    # boundary the other way, which changes nothing to first order
+    assert (err[at, np.arange(m)] <= err.min(0) * (1 + 2 * n * 2.0 ** -24 + 1e-6)).all()
+
+
 # Blocks of 32 x 64 with an eighth of the tokens to a wavefront: one block and its edges, an odd number of block rows, the most columns; k-tiles for a
 # few wavefronts only, that do not divide over them, the most.  They need the operands' workspace and no more.
 @pytest.mark.parametrize("n,ld,tokens", [(8, 8, 1), (40, 48, 64), (72, 72, 200), (136, 140, 1100), (264, 264, 330), (512, 512, 4096), (552, 560, 2048), (576, 576, 4090)])
