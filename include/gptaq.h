@@ -39,6 +39,9 @@ extern "C" {
 #define GPTAQ_ELAUNCH       -5   /* the HIP runtime refused a launch; see gptaq_last_hip_error */
 #define GPTAQ_ETOOLARGE     -6   /* beyond the fixed capacity of an entry point that allocates nothing */
 
+/* info[0] of gptaq_prepare: the call's workgroups lost each other, see there. */
+#define GPTAQ_INFO_STALLED   (-2147483647 - 1)
+
 /* Human-readable text for a status code. */
 const char* gptaq_status_string(int status);
 /* hipError_t of the most recent failed launch on this thread (0 if none). */
@@ -133,7 +136,9 @@ int gptaq_symmetrize(float* H, int64_t n, int64_t ldh, void* stream);
  *   dead : n bytes, out: 1 for dead inputs else 0.  May be NULL.
  *   info : 2 x int32, out: info[0] = 0, or 1 + index of the first non-positive pivot, or -(1 + row) of a
  *          NaN/Inf entry found in H (upper triangle) or dXXT (strictly upper triangle) (in both cases U and P
- *          are garbage);
+ *          are garbage), or GPTAQ_INFO_STALLED: workgroups of the call waited in vain for what others of it hand them,
+ *          which only happens where something else writes into `ws` while the call runs, or kernels of other streams
+ *          keep part of them off the GPU for minutes (U and P are garbage; H is not at fault: call again);
  *          info[1] = number of dead inputs.
  *   n    : at most 65280.
  * Streams: one asynchronous operation on `stream`; the call uses no other stream and no library lock.

@@ -79,6 +79,9 @@ PROFILE_TAGS = ("accumulate_gemm", "accumulate_split", "factor_sweep", "p_gemm",
                 "trailing_split")
 
 
+INFO_STALLED = -2 ** 31                          # info[0] of gptaq_prepare: its workgroups lost each other
+
+
 class GptaqError(RuntimeError):
     pass
 

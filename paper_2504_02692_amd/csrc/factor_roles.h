@@ -26,6 +26,7 @@
 #pragma once
 #include "common.h"
 #include "gemm_i8s.h"
+#include "patience.h"
 #include <utility>
 
 namespace gptaq {
@@ -106,8 +107,9 @@ __device__ __forceinline__ double rsqrt_of(double x) {
 }
 
 // ---- several workgroups of one launch work on a block: one factors it, others follow it tile column by tile column.  A workgroup
-// draws a number when it starts, and the parts are dealt in the order of the numbers, so that whoever waits does so for workgroups that
-// are running already, whatever the order in which the hardware starts them; and nobody waits for the workgroups that do products.
+// draws a number when it starts, and the parts are dealt in the order of the numbers: the nine that factor the block and wait for one
+// another come first, and a panel, which waits for these, starts when they are running, whatever the order in which the hardware starts
+// them; and nobody waits for the workgroups that do products.
 // What one writes for another goes past its XCD's L2 (publish_tile), and a flag behind it once the stores have been acknowledged.  The
 // reader's own L2 cannot hold an older copy: nothing reads these lines earlier in the launch, and a launch starts with clean caches.
 // All words are 0 before the call's first launch.
@@ -124,21 +126,23 @@ __device__ __forceinline__ void set_flag(int32_t* sync, int word, int lane) {   
 template <int N> __device__ __forceinline__ void wait_stores() {           // all but the last N memory accesses of the wavefront are done
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
 }
+constexpr int kFactorTeam = 1 + NH;               // workgroups that factor a block
+static_assert(GPTAQ_INFO_STALLED < -(1 + (1 << 24)), "no row's code");
 struct Flags {
   int32_t* words;                                // 64 of them, one a lane
-  int32_t* info;
-  int give_up;                                   // what info says if nothing comes
+  const BlockFactor& f;
   int lane;
   uint64_t seen = 0;
   __device__ __forceinline__ bool ready(uint64_t need) const { return (seen & need) == need; }
-  // Waits until the flags of `need` are set.  (Two seconds are a hundred thousand times what it takes: only where something else writes
-  // into the workspace meanwhile does it end without them, and says so.)
+  // Waits until the flags of `need` are set, or for as long as Patience has: then info says so.
   __device__ __forceinline__ void wait(uint64_t need) {
-    for (int i = 0; !ready(need); ++i) {
+    Patience patience;
+    while (!ready(need)) {
       seen = __ballot(__hip_atomic_load(words + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0);
-      if (!ready(need)) __builtin_amdgcn_s_sleep(2);
-      if (i == 1 << 20) {
-        if (lane == 0) atomicCAS(info, 0, give_up);
+      if (ready(need)) break;
+      __builtin_amdgcn_s_sleep(2);
+      if (patience.over([&]() { return __hip_atomic_load(f.sync + BlockSync::kTicket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= kFactorTeam; })) {
+        if (lane == 0) atomicMin(f.info, GPTAQ_INFO_STALLED);
         seen = ~0ull;
       }
     }
@@ -269,7 +273,7 @@ __device__ __forceinline__ void factor_rows(const BlockFactor& a, FactorShared& 
     for (int v = 0; v < 4; ++v) sh.diag[16 * (4 * g + v) + r] = d[v];
   };
   // The second half's first tile is there before its others (half_row_role), and its factorisation takes the time in which they come.
-  Flags f{a.sync + 64, a.info, a.o0 + kFactorBlock / 2, lane};
+  Flags f{a.sync + 64, a, lane};
   if (HALF) {
     if (W == 1) {
       f.wait(1ull);
@@ -422,11 +426,11 @@ __device__ __forceinline__ void half_row_role(const BlockFactor& a, int m, Panel
   for (int q = 0; q < NH / 4; ++q) x[q] = load_block_tile(a, NH + m, wave + 4 * q, r, g);
 #pragma unroll
   for (int q = 0; q < 2; ++q) t[q] = load_block_tile(a, NH + m, NH + min(wave + 4 * q, m), r, g);
-  Flags flags{a.sync, a.info, a.o0 + kFactorBlock, lane};
+  Flags flags{a.sync, a, lane};
   // The update follows the columns, three steps behind: a row publishes a column at its step, its flag a step later, its rows are fetched by the
   // others in the step after that and multiplied in the next.  What is left behind the last column is a product of three.
   // (Row 0's one tile, which the factorisation goes on with first, needs nothing of other rows: wavefront 0 updates it from LDS, at once.)
-  Flags cells{a.sync + BlockSync::cell(0, 0), a.info, a.o0 + kFactorBlock, lane};
+  Flags cells{a.sync + BlockSync::cell(0, 0), a, lane};
   const uint64_t rows = m == NH - 1 ? ~0ull : (1ull << (8 * (m + 1))) - 1;
   f64x4 nx[NH], xb[3][2];
   auto fetch = [&](int k, int set) {
@@ -502,7 +506,7 @@ __device__ __forceinline__ void panel_role(const BlockFactor& f, const BlockPane
     for (int q = 0; q < 4; ++q)
       t[q] = load_row4(f.F, f.ldf, f.n, row0 + r, f.o0 + kFactorBlock - 4 - 16 * (wave + 4 * q) - 4 * g);
   }
-  Flags flags{f.sync, f.info, f.o0 + kFactorBlock, lane};
+  Flags flags{f.sync, f, lane};
   // (U's own entries go to memory as the columns come: all of them behind the last one took 1.3 us more)
   const int j = kFactorBlock - 1 - (row0 + r);
   auto store_u = [&](int q) {

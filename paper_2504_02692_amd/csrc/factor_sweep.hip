@@ -23,7 +23,6 @@ namespace gptaq {
 
 namespace {
 constexpr int kSweepProducts = 4;
-constexpr int kFactorTeam = 1 + NH;              // workgroups that factor a block
 struct SweepLaunch {
   BlockFactor f;
   BlockPanel p;

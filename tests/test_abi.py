@@ -141,3 +141,35 @@ int main() {
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
     assert int(r.stdout) > 1000000
+
+
+def test_waits_end_and_wait_for_those_that_have_not_started(tmp_path):
+    """A workgroup that waits for others of its launch does not give up while some of them have no place on the GPU yet, gives up when all
+    have been running for a while, and ends in any case; what it reports then is no pivot's and no row's code."""
+    from paper_2504_02692_amd import binding
+    src = tmp_path / "check.cpp"
+    src.write_text("""#include "gptaq.h"
+#include "patience.h"
+#include <cstdio>
+using gptaq::Patience;
+// spells until a wait ends whose team has started by the end of spell `from`
+static int spells(int from) {
+  Patience p;
+  for (long polls = 1;; ++polls)
+    if (p.over([&]() { return polls / Patience::kPolls >= from; })) return polls % Patience::kPolls ? -1 : (int)(polls / Patience::kPolls);
+}
+int main() {
+  static_assert(Patience::kPolls >= 1 << 20 && Patience::kLongest >= 32, "a minute of other streams' kernels");
+  Patience gap;                                    // (a counter that something else clears meanwhile)
+  int flips = 0, asked = 0;
+  while (!gap.over([&]() { ++asked; return flips++ % 2 == 0; })) {}
+  std::printf("%d %d %d %d %d\\n", spells(1), spells(7), spells(1 << 20), asked, GPTAQ_INFO_STALLED);
+}
+""")
+    exe = tmp_path / "check"
+    subprocess.run(["g++", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2504_02692_amd", "csrc"), "-I", os.path.join(ROOT, "include"),
+                    str(src), "-o", str(exe)], check=True)
+    longest = 64
+    assert subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split() == [
+        "2", "8", str(longest), str(longest), str(binding.INFO_STALLED)]
+    assert not -65280 - 1 <= binding.INFO_STALLED <= 65280
