@@ -224,39 +224,48 @@ static bool few_blocks(int64_t n, int64_t tokens) {
 
 // In how many parts of their tokens the sums of a pass are taken, and what the parts' sums need beside the operands.
 // With few columns the tiles of H and dXXT leave most of the chip idle (n = 1024: 72 or 100 of 512 places for 128-tiles).  dXXT's tiles,
-// of two products, are split in `split` parts and H's, of one, in half as many, so that all workgroups take the same time.  The number is
-// the one with the least time for both forms of the call together (it must not depend on the form: the upper form is bit for bit the
-// full one where it is defined), from: 18 ns per token in a round of more than 256 workgroups (two to a CU), 11 in one of fewer; 5 us per
-// round; parts written and read at 4 TB/s, and a launch for them.  (Four workgroups a tile row sum H's diagonal in one part: see
-// diagonal_block.)
-// Measured, one part / so many, us per call of 32768 tokens, upper form (full): n = 256 302 / 75 (312 / 75), 512 317 / 88 (316 / 91), 768
-// 331 / 129 (321 / 147), 1024 370 / 194 (372 / 231), 1280 482 / 257 (481 / 349), 1536 534 / 342 (531 / 433); of 8192 tokens 512 91 / 40, 1024
-// 96 / 55 (97 / 73); of 4096 768 54 / 33 (55 / 34), 1024 54 / 36 (54 / 46), 1280 57 / 47 (59 / 53); of 2048
-// 1024 34 / 28 (33 / 33); of 1024 there is nothing to be had.  Where the estimate promises less than a factor of 1.5 there was
-// little to be had with many tokens and more than 640 columns (without the diagonal's workgroups: 2048 594 / 511 (687 / 699), 2736 888 / 861 (1241 /
-// 1277), 3072 and 8192 tokens 257 / 277 (352 / 384); 1536 and 16384 188 / 163 (206 / 228)); with less than 8192 tokens, or up to 640
-// columns, a factor of 1.1 is kept, and more than eight parts never were the best.  Errors against 64 bits fall with the length of the
-// sums: dXXT 8.7e-7 to 2.4e-7 at n = 1024.
+// of two products, are split in so many parts and H's, of one, in half as many, so that all workgroups take the same time.  (Four
+// workgroups a tile row sum H's diagonal in one part: see diagonal_block.)  How many parts pay depends on how full the last round of 512
+// workgroups is, which goes up and down with the tile rows: a line for each number of them.  Both forms of the call take the same
+// number (the upper form is bit for bit the full one where it is defined), and there are more only with more tokens, so that the workspace of
+// a call has room for every shorter one.  Measured, one part / so many, us per call, upper form (full):
+//   columns  tokens
+//    256      6144  72 / 33 (72 / 33)     32768  301 / 77 (314 / 77);  more parts than 8: the same
+//    640      1536  28 / 26 (28 / 27)      2048  35 / 28 (35 / 28)     8192  93 / 42 (93 / 43)     32768  326 / 105 (331 / 110)
+//    768      2048  36 / 29 (36 / 29)      8192  92 / 44 (92 / 55)    16384  172 / 76 (169 / 80)   32768  335 / 133 (326 / 153)
+//    896      2048  36 / 30 (35 / 32)      6144  76 / 45 (76 / 50)    16384  178 / 87 (179 / 98)   32768  347 / 159 (349 / 180)
+//   1024      1536  31 / 29 (30 / 31)      2048  35 / 29 (34 / 33)     8192  95 / 56 (94 / 75)     32768  384 / 196 (384 / 238)
+//   1152      2048  37 / 34 (36 / 36)      6144  77 / 60 (78 / 65)    16384  184 / 106 (185 / 140) 32768  442 / 239 (436 / 302)
+//   1280      4096  57 / 48 (57 / 54)      8192  97 / 76 (99 / 89)    16384  184 / 134 (183 / 163) 32768  487 / 261 (488 / 353)
+//   1408      6144  80 / 66 (83 / 96)     16384  190 / 148 (196 / 202) 20480  240 / 174 (248 / 240)   32768  523 / 327 (519 / 388)
+//   1536     16384  196 / 166 (214 / 230) 28672  468 / 309 (469 / 391) 32768  537 / 341 (536 / 444)
+//   1664      6144  83 / 96 (116 / 105)   12288  153 / 150 (217 / 207) 23040  348 / 292 (379 / 373) 32768  546 / 410 (557 / 530)
+//   1920     24576  432 / 361 (464 / 506) 32768  566 / 467 (626 / 661)
+// One part stays where the best number makes one of the forms slower or gives little (in this list 1408 columns and 6144 or 16384 tokens, 1536 and
+// 16384, 1664 and 6144 or 12288, 1920); at 1792 columns two would pay from 24576 tokens on (410 / 344 and 439 /
+// 418).  Between two numbers of parts, where one form gains what the other loses (768 columns and 12288 tokens, 6 / 8 parts: 55 / 62 (73 / 64)),
+// the line is where the sum of both does not care.  Errors against 64 bits fall with the length of the sums: dXXT 8.7e-7 to 2.4e-7 at n = 1024.
 static int split_for(int64_t n, int64_t tokens) {
-  if (sparse_remainder(n)) return 1;             // (remainder_loop takes all of K; the estimate promises less than 1.5 from there on)
-  if (gemm_tile_for(n, n) != 128) return 1;      // (256-tiles: they fill the chip, and the power limit takes what a fuller last round gives)
+  if (sparse_remainder(n)) return 1;             // (remainder_loop takes all of K)
   if (few_blocks(n, tokens)) return 1;
-  const int64_t t = (n + 127) / 128, upper = t * (t + 1) / 2;
-  const bool small = tokens < 8192 || t <= 5;
-  int best = 1;
-  double least = 0.;
-  for (int split : {1, 2, 4, 6, 8, 12, 16}) {
-    if (small && split > 8) break;
-    double us = 0.;
-    for (int64_t dxxt : {upper, t * t}) {
-      const int64_t wgs = dxxt * split + upper * ((split + 1) / 2) + (split > 1 ? 4 * t : 0), rounds = wgs / 512, rest = wgs % 512;
-      us += (0.018 * (double)rounds + (rest == 0 ? 0. : rest <= 256 ? 0.0112 : 0.018)) * (double)tokens / split;
-      us += 5. * (double)(rounds + (rest > 0)) + (split > 1 ? (double)wgs * 0.033 + 6. + (small ? 0.5 * split : 0.) : 0.);
-    }
-    if (split == 1) least = us / (small ? 1.1 : 1.5);
-    else if (us < least) { best = split; least = us; }
-  }
-  return best;
+  const int64_t t = (n + 127) / 128;
+  if (t <= 4) return 8;                          // (more than 4096 tokens)
+  static constexpr struct { int tokens, parts; } lines[][4] = {
+      {{1792, 4}, {3072, 6}},                                    // 5 tile rows, up to 640 columns
+      {{1792, 4}, {8192, 6}, {14080, 8}, {27008, 12}},           // 768
+      {{2048, 4}, {6912, 6}},                                    // 896
+      {{2048, 4}, {16384, 8}},                                   // 1024
+      {{2048, 2}, {4096, 4}, {14336, 6}},                        // 1152
+      {{3072, 2}, {16768, 8}},                                   // 1280
+      {{18112, 4}, {23296, 6}},                                  // 1408
+      {{28672, 8}},                                              // 1536
+      {{23040, 6}},                                              // 1664
+  };
+  int parts = 1;
+  if (t - 5 < (int64_t)(sizeof(lines) / sizeof(lines[0])))
+    for (const auto& line : lines[t - 5])
+      if (line.parts && tokens >= line.tokens) parts = line.parts;
+  return parts;
 }
 static size_t partial_bytes(int64_t n, int split) {
   if (split <= 1) return 0;

@@ -56,6 +56,22 @@ def test_workspace_queries(lib):
     assert lib.gptaq_status_string(0) == b"ok"
 
 
+def test_a_workspace_for_more_tokens_has_room_for_fewer(lib):
+    """Sums taken in parts of the tokens need room for the parts: more of it only with more tokens, so that the workspace of a series' largest
+    call serves the others.  And where the rule's measurements lie: parts of 1024 columns and 2048 tokens and of 1280 columns from 4096 to
+    16384, none where one form of the call is the slower for it."""
+    size = lib.gptaq_accumulate_workspace_bytes
+    operands = lambda tokens, n: 6 * -(-n // 128) * 128 * tokens
+    for n in [8, 520, *range(576, 2060, 8)]:
+        sizes = [size(tokens, n) for tokens in range(64, 32769, 64)]
+        assert sizes == sorted(sizes), n
+        assert all(s >= operands(64 * (i + 1), n) for i, s in enumerate(sizes))
+    for n, tokens in [(1024, 2048), (1280, 4096), (1280, 8192), (1280, 12288), (640, 2048)]:
+        assert size(tokens, n) > operands(tokens, n), (n, tokens)
+    for n, tokens in [(1408, 6144), (1408, 8192), (1664, 6144), (1664, 8128), (1536, 16384), (1920, 32768), (640, 1024)]:
+        assert size(tokens, n) == operands(tokens, n), (n, tokens)
+
+
 def test_argument_errors_are_reported_before_any_launch(lib):
     one = ctypes.c_void_p(256)      # a non-null, aligned, never dereferenced address
     null = ctypes.c_void_p(0)
