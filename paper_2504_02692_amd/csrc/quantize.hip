@@ -476,7 +476,8 @@ __device__ __forceinline__ void zero_dead_columns(float* W, int64_t ldw, int m, 
     if (d) W[(int64_t)r * ldw + c] = 0.f;
 }
 
-// What comes before the first super-block, in one launch: its operands, the rows' ranges, the dead columns (in this order of workgroups).
+// What comes before the first super-block, in one launch: the rows' ranges, the dead columns, its operands (in this order of workgroups: the
+// ranges read all of W, and the operands are to be in the caches when the super-block kernel reads them).
 // (As launches of their own they took 2 to 5 us each: a solve of 512 x 512, 283 -> 281 us, 4096 x 4096 with the waits saved below 850 -> 816.)
 struct BeginLayer {
   const float *U, *P; int64_t ldh; SbNear near;
@@ -488,13 +489,17 @@ __global__ __launch_bounds__(256) void begin_layer_kernel(BeginLayer a) {
   __shared__ float t[kSub][65];
   __shared__ int any;
   int wg = blockIdx.x;
-  if (wg < a.near_wgs) {
-    near_operands(a.U, a.P, a.ldh, a.rows.n, 0, a.near, wg % kNearTiles, wg / kNearTiles % kNearEvents, wg / (kNearTiles * kNearEvents), t);
+  if (wg < a.row_wgs) {
+    row_params(a.rows, wg);
     return;
   }
-  wg -= a.near_wgs;
-  if (wg < a.row_wgs) row_params(a.rows, wg);
-  else zero_dead_columns(a.W, a.rows.ldw, a.rows.m, a.rows.n, a.rows.dead, wg - a.row_wgs, any);
+  wg -= a.row_wgs;
+  if (wg < a.dead_wgs) {
+    zero_dead_columns(a.W, a.rows.ldw, a.rows.m, a.rows.n, a.rows.dead, wg, any);
+    return;
+  }
+  wg -= a.dead_wgs;
+  near_operands(a.U, a.P, a.ldh, a.rows.n, 0, a.near, wg % kNearTiles, wg / kNearTiles % kNearEvents, wg / (kNearTiles * kNearEvents), t);
 }
 }  // namespace gptaq
 
@@ -600,6 +605,9 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     ProfScope ps(kProfTrailGemm, st);
     chk(launch_gemm(b, st));
   };
+  // (in front of the first super-block's own operands, which are in the caches then when its kernel reads them: behind them, 8192 x 8192 with the
+  // E term alone took 2658 us instead of 2592, per channel 2676 instead of 2608)
+  if (far_operands && !two_chains) make_far_operands();
   {
     BeginLayer f{U, (terms & 2) ? P : U, ldh, near, RowParams{W, ldw, (int)m, (int)n, dead, a.maxq, sym, mse_grid, mse_steps, scales, zeros}, W, 0, 0, 0};
     if (terms != 0 && !near_made) f.near_wgs = kNearTiles * kNearEvents * 2;
@@ -621,7 +629,6 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     a.EV = far ? ev[0] : nullptr; a.evstride = ev[1] - ev[0];
     // (with two chains this super-block's columns have every earlier update and its buffer set is free again: far1(k - 1) has waited for
     // far2(k - 2), and another wait for it costs the stream some 9 us)
-    if (k == 0 && far_operands && !two_chains) make_far_operands();
     a.near = near_in_front ? near : near.at(k);
     if (terms != 0 && near_in_front && k > 0) {
       ProfScope ps(kProfTrailSplit, s);
