@@ -272,7 +272,8 @@ int gptaq_pack_codes(const uint8_t* codes, int64_t m, int64_t n, int64_t ldc, in
  *   0 accumulate MFMA GEMM (H and dXXT, one launch per pass)   1 accumulate split/transpose pass
  *   2 factorisation + triangular inverse sweep (whole sweep)    3 the two Theorem-4.2 GEMMs
  *   4 column-loop kernel (one per 1024 columns)                 5 trailing-update GEMM (one or two per 1024 columns)
- *   6 trailing operand split/transpose
+ *   6 operands of the column-loop kernel and of the trailing update (with per-channel ranges without those of the first 1024 columns, which
+ *     are made in one launch with the ranges)
  * gptaq_profile_enable(mask) clears the records and records the tags whose bit (1 << tag) is set
  * in `mask`; 0 stops recording.
  * gptaq_profile_read waits for the recorded events and returns the number of bracketed

@@ -186,12 +186,12 @@ struct LdsLimitOnce {
 
 // Optional per-kernel timing with HIP events (gptaq_profile_* in the public header).
 enum ProfTag { kProfAccumGemm = 0, kProfAccumSplit = 1, kProfFactor = 2, kProfPGemm = 3, kProfColumnLoop = 4,
-               kProfTrailGemm = 5, kProfTrailSplit = 6, kProfTags = 7 };
+               kProfTrailGemm = 5, kProfTrailSplit = 6, kProfTags = 7, kProfNone = -1 };
 bool prof_enabled(int tag);
 void prof_mark(int tag, hipStream_t s, bool begin);
 struct ProfScope {
   int tag; hipStream_t s; bool on;
-  ProfScope(int t, hipStream_t st) : tag(t), s(st), on(prof_enabled(t)) { if (on) prof_mark(tag, s, true); }
+  ProfScope(int t, hipStream_t st) : tag(t), s(st), on(t != kProfNone && prof_enabled(t)) { if (on) prof_mark(tag, s, true); }
   ~ProfScope() { if (on) prof_mark(tag, s, false); }
 };
 

@@ -614,7 +614,8 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     if (group <= 0) f.row_wgs = (int)((m + 3) / 4);
     if (dead) f.dead_wgs = (int)((n + 63) / 64);
     if (f.near_wgs + f.row_wgs + f.dead_wgs > 0) {
-      ProfScope ps(kProfTrailSplit, s);
+      // (no part of the trailing update where there are no operands, nor where the ranges, which may be searched, are most of it)
+      ProfScope ps(f.near_wgs && !f.row_wgs ? kProfTrailSplit : kProfNone, s);
       hipLaunchKernelGGL(begin_layer_kernel, dim3((unsigned)(f.near_wgs + f.row_wgs + f.dead_wgs)), dim3(256), 0, s, f);
       chk(hipGetLastError());
     }

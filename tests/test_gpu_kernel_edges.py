@@ -560,6 +560,21 @@ def test_first_super_block_finds_its_operands_in_the_caches():
     assert us[8192] <= 1.28 * us[1024], us
 
 
+# A launch of operands for each super-block and one for the far updates; a layer's first launch counts among them where it makes operands and
+# nothing else that matters.
+@pytest.mark.parametrize("n,group,terms,steps,launches", [(512, 128, 3, 0, 1), (2048, 128, 1, 0, 3), (2048, 0, 3, 0, 2), (512, 0, 3, 80, 0), (512, 0, 0, 0, 0), (512, 128, 0, 0, 0)])
+def test_operands_are_timed_without_the_ranges(n, group, terms, steps, launches):
+    m = 64
+    W, ws = torch.randn((m, n), device="cuda"), B.workspace(B.gptaq_quantize_workspace_bytes(m, n))
+    dead = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    B.gptaq_profile_enable(1 << B.PROFILE_TAGS.index("trailing_split"))
+    B.gptaq_quantize_layer(W, torch.eye(n, device="cuda"), torch.zeros((n, n), device="cuda"), 4, group, False, 128, ws, dead=dead, terms=terms,
+                           mse_grid=100 if steps else 0, mse_steps=steps)
+    got = B.gptaq_profile_read(B.PROFILE_TAGS.index("trailing_split"))[0]
+    B.gptaq_profile_enable(0)
+    assert got == launches
+
+
 @pytest.mark.parametrize("n,tokens", [(1928, 1), (1928, 2080), (2048, 96), (2496, 97), (3848, 64), (4104, 500)])
 @pytest.mark.parametrize("kind", ["near", "far", "all", "rows"])
 def test_sparse_remainder_of_the_difference(n, tokens, kind):
