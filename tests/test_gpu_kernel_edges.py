@@ -192,10 +192,11 @@ def test_clip_search_in_the_block_kernel(group, blocksize, m, n):
                             label=f"clip g{group} blocks of {blocksize} {m}x{n}", mse=(100, 80))
 
 
+@pytest.mark.parametrize("m", [40, 1030])
 @pytest.mark.parametrize("group", [32, 128])
-def test_clip_search_beside_the_far_update(group):
-    """Three super-blocks: the columns after the next one are updated on the helper stream."""
-    m, n = 40, 2304
+def test_clip_search_beside_the_far_update(group, m):
+    """Three super-blocks: from 1025 rows on the columns after the next one are updated on the helper stream."""
+    n = 2304
     Xb, Xtb = synth.make_activations(3500, n, 43, "clip2", 2, 20.0)
     H, A = O.accumulate(Xb, Xtb)
     U, P, _ = O.prepare(H, A, 0.01)
@@ -289,10 +290,12 @@ def test_activation_quantiser_rows(n, bits, clip):
     assert np.array_equal(ref, got)
 
 
-def test_a_solve_can_be_captured():
-    """gptaq_prepare (three outer blocks) and gptaq_quantize_layer (three super-blocks) put work on the helper stream; it joins the
-    caller's stream in front of the end of the call, also in a capture.  Every replay is checked, with other work in between."""
-    m, n = 33, 2064
+@pytest.mark.parametrize("m", [33, 1030])
+def test_a_solve_can_be_captured(m):
+    """gptaq_prepare (nine outer blocks) clears the flags of its workgroups in every replay.  gptaq_quantize_layer (three super-blocks) puts
+    work on the helper stream from 1025 rows on; it joins the caller's stream in front of the end of the call, also in a capture.  Every replay is
+    checked, with other work in between."""
+    n = 2064
     g = torch.Generator(device="cuda").manual_seed(3)
     X = torch.randn((2 * n, n), device="cuda", generator=g)
     H0, A0 = X.T.contiguous() @ X, (0.1 * torch.randn((2 * n, n), device="cuda", generator=g)).T.contiguous() @ X
@@ -425,6 +428,46 @@ def test_sums_of_narrow_inputs(n, ld, tokens):
         assert float((got.double() - ref).norm() / ref.norm()) <= 3e-6          # (as in test_sums_in_parts_are_the_sums)
 
 
+@pytest.mark.parametrize("n", [40, 328, 576])
+@pytest.mark.parametrize("upper", [False, True])
+def test_staged_sums_of_narrow_inputs(n, upper):
+    """Small chunks, the last one ragged, are the sums of one call, bit for bit, and so are those in the library's own workspace."""
+    ws = B.workspace(B.gptaq_accumulate_workspace_bytes(32768, n))
+    ws.fill_(0xff)                         # (what the calls do not write is not read as numbers)
+    cuts = [0, 64, 192, 1216, 1301]
+    X, Xt = synth.make_activations_device(cuts[-1], n, 1, "x", "cuda", noise=0.2)
+    H, A, Hs, As, Hn, An = (torch.ones((n, n), device="cuda") for _ in range(6))
+    (B.gptaq_accumulate_upper if upper else B.gptaq_accumulate)(X, Xt, H, A, B.workspace(B.gptaq_accumulate_workspace_bytes(cuts[-1], n)))
+    pending = 0
+    for t0, t1 in zip(cuts, cuts[1:]):
+        pending = B.gptaq_accumulate_staged(X[t0:t1], Xt[t0:t1], Hs, As, ws, pending, flush=t1 == cuts[-1], upper=upper)
+    assert pending == 0
+    assert torch.equal(H.triu(), Hs.triu())
+    assert torch.equal(A.triu(), As.triu()) and (upper or torch.equal(A, As))
+    B.gptaq_accumulate_noalloc(X, Xt, Hn, An)
+    assert torch.equal(H.triu(), Hn.triu()) and torch.equal(A.triu(), An.triu()) and (upper or torch.equal(A, An))
+
+
+@pytest.mark.parametrize("n", [40, 328, 576])
+def test_sums_of_narrow_inputs_that_are_not_finite(n):
+    """An infinity in X, one in X~ and a NaN in X~: the entries that are not finite are those of the exact sums, and the others are what they should be."""
+    tokens = 300
+    X, Xt = synth.make_activations_device(tokens, n, 6, "x", "cuda", noise=0.2)
+    X[70, 4], Xt[271, 21], Xt[3, n - 1] = float("inf"), float("-inf"), float("nan")
+    Xd, Dd = X.double(), Xt.double() - X.double()
+    refs = (Xd.T.contiguous() @ Xd, Dd.T.contiguous() @ Xd)
+    ws = B.workspace(B.gptaq_accumulate_workspace_bytes(tokens, n))
+    for upper in (False, True):
+        H, A = torch.zeros((n, n), device="cuda"), torch.zeros((n, n), device="cuda")
+        (B.gptaq_accumulate_upper if upper else B.gptaq_accumulate)(X, Xt, H, A, ws)
+        for got, ref, tri in ((H, refs[0], True), (A, refs[1], upper)):
+            keep = torch.ones_like(got, dtype=torch.bool).triu() if tri else torch.ones_like(got, dtype=torch.bool)
+            assert torch.equal(got.isfinite() & keep, ref.isfinite() & keep)
+            keep &= ref.isfinite()
+            # (fp32 sums of 300 exact products: sqrt(300) 2^-24 if every addition rounded the whole sum alike)
+            assert float((got[keep].double() - ref[keep]).norm() / ref[keep].norm()) <= 2.0 ** -24 * tokens ** 0.5
+
+
 @pytest.mark.parametrize("n,tokens", [(264, 8192), (520, 16448), (1032, 32768)])
 def test_sums_in_parts_round_the_total_once(n, tokens):
     """Whole numbers, whose sums are exact in fp32 in any order, on totals of 2^25 (steps of 2 and 4): what a call leaves is the exact
@@ -496,7 +539,37 @@ def test_few_rows_of_a_wide_matrix(m, n):
         assert torch.equal(got, torch.cat([p[i] for p in parts]))
 
 
-# Row halves that make the super-block kernel's operands for themselves, against calls on 600 rows at a time (one chain, and two).
+# Two chains (1025 to 4096 rows): the fewest super-blocks and the fewest rows; both sets of the -E / V buffers taken again; each term alone; the columns left
+# where the second chain starts at once; and one row fewer, which is one chain.
+@pytest.mark.parametrize("m,n,group,terms,far_updates", [(1025, 2064, 0, 3, 3), (1024, 3088, 16, 3, 3), (1025, 3088, 16, 3, 5), (2100, 4112, 0, 1, 7), (2100, 4112, 16, 2, 7),
+                                                         (2100, 4112, 16, 3, 7), (2500, 9232, 0, 3, 17), (4096, 5120, 128, 3, 7)])
+def test_two_chains_equal_one(m, n, group, terms, far_updates):
+    """The result is bit for bit that of calls on 700 rows at a time, which go through as one chain; columns of dead inputs are among them."""
+    g = torch.Generator(device="cuda").manual_seed(m)
+    U, P = (torch.randn((n, n), device="cuda", generator=g).mul_(f * n ** -0.5).triu_(1) for f in (1.0, 0.1))
+    U.diagonal().copy_(0.5 + torch.rand(n, device="cuda", generator=g))
+    W0 = 0.02 * torch.randn((m, n), device="cuda", generator=g)
+    dead = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    dead[7::501] = 1
+    W0[:, 7::501] = 5.0
+    tag = B.PROFILE_TAGS.index("trailing_gemm")
+
+    def quantize(W, launches):
+        W = W.clone()
+        B.gptaq_profile_enable(1 << tag)
+        out = B.gptaq_quantize_layer(W, U, P, 4, group, False, 128, B.workspace(B.gptaq_quantize_workspace_bytes(W.shape[0], n)), dead=dead, terms=terms)
+        assert B.gptaq_profile_read(tag)[0] == launches
+        B.gptaq_profile_enable(0)
+        torch.cuda.synchronize()
+        return (W, *out)
+
+    whole = quantize(W0, far_updates)
+    parts = [quantize(W0[r:r + 700], (n - 1) // 1024) for r in range(0, m, 700)]
+    for i, got in enumerate(whole):
+        assert torch.equal(got, torch.cat([p[i].reshape(-1, got.shape[1]) for p in parts]))
+
+
+# Row halves that make the super-block kernel's operands for themselves, against calls on 600 rows at a time, which are one chain.
 @pytest.mark.parametrize("n,terms,steps", [(2064, 1, 0), (3200, 2, 0), (3072, 3, 5)])
 def test_row_halves_with_operands_of_their_own(n, terms, steps):
     m, group = 10300, 64 if steps else 0
