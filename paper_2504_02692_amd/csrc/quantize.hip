@@ -533,9 +533,9 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
   const int nsb = (int)((n + kSbCols - 1) / kSbCols);
   // (with one or two super-blocks there is no far2; it pays when the super-block kernel leaves most of the chip free, and the far updates of
   // so many rows take longer than the events between the streams.  One chain / two, us: 1024 rows: 3072 columns 509 / 517, 4096 693 / 700,
-  // 6144 1129 / 1172; 256 rows: 4096 689 / 698, 6144 1087 / 1143, 8192 1610 / 1720; 1536: 3072 510 / 515, 4096 714 / 705, 5120 954 / 928; 2560: 3072
-  // 534 / 519, 4096 768 / 724, 8192 2152 / 1945; 4096: 2560 475 / 458, 4096 864 / 775, 5120 1202 / 1122.  More rows, and most matrices of
-  // more columns, go through as row halves: see first_row_half)
+  // 6144 1116 / 1163; 257 rows: 8192 1584 / 1616; 512: 6144 1083 / 1151, 8192 1593 / 1728; 1100: 4096 702 / 706, 8192 1666 / 1696; 1536: 3072 505 / 511,
+  // 4096 710 / 697, 5120 944 / 919, 8192 1765 / 1766; 2560: 3072 527 / 512, 4096 756 / 715, 8192 2111 / 1933; 4096: 2560 475 / 458, 4096 842 / 772, 5120 1176 /
+  // 1103, 11008 4256 / 3736.  More rows, and some few of many columns, go through as row halves: see first_row_half)
   int cus = 256, dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
   const int sbk_wgs = (int)((m + 63) / 64);
@@ -578,8 +578,8 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
   // the kernel takes 175 instead of 123 us), against 7 us of the chain.  With two chains, which have fewer rows, the helper stream
   // makes them beside the first super-block, and that is the better side.  In front of each / beside the first, ms: one chain, E term
   // alone: 4608 x 4096 0.66 / 0.67, 6144 x 4096 0.75 / 0.81, 9984 x 4096 0.91 / 1.03, 8192 x 8192 2.56 / 2.96, 8192 x 11008 4.23 / 4.56;
-  // both terms and 80 candidates: 6144 x 4096 1.74 / 1.81, 8192 x 8192 5.13 / 5.49; two chains: 1024 x 4096 0.75 / 0.73, 4096 x 4096
-  // 0.84 / 0.82, with 80 candidates 1.53 / 1.50, 3072 x 8192 2.30 / 2.28, 3072 x 11008 3.50 / 3.47.  (Row halves: see there.)
+  // both terms and 80 candidates: 6144 x 4096 1.74 / 1.81, 8192 x 8192 5.13 / 5.49; two chains: 1536 x 4096 0.71 / 0.70, 2048 x 8192 1.88 / 1.80, 4096 x 4096
+  // 0.81 / 0.77, with 80 candidates 1.53 / 1.50, 3072 x 8192 2.14 / 2.07, 3072 x 11008 3.28 / 3.20, 4096 x 11008 3.73 / 3.74.  (Row halves: see there.)
   const bool near_in_front = !two_chains && !near_made;
   const bool far_operands = make_farop && terms != 0 && nsb >= 2;
   auto ev_sbk = [&](int k) { return side->events[2 * k]; };       // super-block k's kernel has finished
@@ -646,8 +646,8 @@ static int quantize_layer_sb(float* W, int64_t m, int64_t n, int64_t ldw, const 
     // While far2 is long (many columns left) it sets the pace and starts at once, sharing the chip with far1; once it
     // is shorter than a super-block it only slows far1 down, which the next super-block waits for: then it starts
     // when far1 is done.
-    // (measured with the switch at 6 / 3 / 2 / 1 super-blocks of columns left, ms: 3072 x 5504 1.28 / 1.37 / 1.39 / 1.39; 3072 x 8192 2.28 /
-    // 2.30 / 2.32 / 2.35; 3072 x 11008 3.51 / 3.47 / 3.48 / 3.50)
+    // (measured with the switch at 6 / 3 / 2 / 1 super-blocks of columns left, ms: 3072 x 5504 1.19 / 1.27 / 1.33 / 1.36; 3072 x 8192 2.06 /
+    // 2.17 / 2.23 / 2.29; 4096 x 8192 2.26 / 2.21 / 2.30 / 2.38; 3072 x 11008 3.19 / 3.29 / 3.34 / 3.41; 4096 x 11008 3.62 / 3.57 / 3.66 / 3.71)
     constexpr int kFar2LateCols = 6 * kSbCols;
     const bool far2_late = has_far2 && (n - next_end) <= kFar2LateCols;
     auto launch_far2 = [&]() {
@@ -716,9 +716,9 @@ static int quantize_layer_impl(float* W, int64_t m, int64_t n, int64_t ldw, cons
       // The far operands serve both halves: made in front of the second half, beside the first half's first super-block.  So do, with
       // both terms and no search, those of the super-block kernel (the first one's are made before the streams fork); otherwise each half
       // makes its own in front of each of its super-blocks.  The latter / the former, ms: E term alone 16640 x 2048 0.50 / 0.53, 22016 x
-      // 4096 1.63 / 1.68; 80 candidates, 22016 x 4096 3.36 / 3.50; both terms 12288 x 2048 0.48 / 0.47, 16640 x 2048 0.70 / 0.71, 9216 x
-      // 3072 0.79 / 0.78, 22016 x 4096 2.46 / 2.40, 4096 x 11008 3.81 / 3.74, 8192 x 11008 6.04 / 6.04.  (The line is not the best one:
-      // 9984 x 4096 1.27 / 1.34, 4096 x 8192 2.38 / 2.46, 8192 x 8192 3.55 / 3.68, 1024 x 11008 2.36 / 2.43.)
+      // 4096 1.63 / 1.68; 80 candidates, 22016 x 4096 3.36 / 3.50; both terms 12288 x 2048 0.48 / 0.47, 16640 x 2048 0.67 / 0.66, 8192 x
+      // 3072 0.73 / 0.71, 4352 x 4096 0.88 / 0.87, 22016 x 4096 2.43 / 2.38, 1536 x 11008 2.55 / 2.54, 8192 x 11008 6.11 / 6.11.  (The line is not the best
+      // one: 9984 x 4096 1.28 / 1.31, 8192 x 8192 3.58 / 3.69, 1024 x 11008 2.35 / 2.38.)
       const float* Pt = (terms & 2) ? P : U;
       const bool near_once = terms == 3 && !(group > 0 && mse_steps > 0);
       hipError_t e = hipSuccess;

@@ -189,3 +189,28 @@ int main() {
     assert subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split() == [
         "2", "8", str(longest), str(longest), str(binding.INFO_STALLED)]
     assert not -65280 - 1 <= binding.INFO_STALLED <= 65280
+
+
+def test_row_halves_where_they_are_the_faster(tmp_path):
+    """The lines of the rule, both terms, no search: what has been measured on either side of them (against one chain up to 1024 rows and from 4097 on,
+    against two between)."""
+    src = tmp_path / "check.cpp"
+    src.write_text("""#include "row_halves.h"
+#include <cstdio>
+#include <cstdlib>
+int main(int argc, char** argv) {
+  for (int i = 1; i + 1 < argc; i += 2) {
+    const int64_t m = atoll(argv[i]), n = atoll(argv[i + 1]);
+    std::printf("%d\\n", gptaq::first_row_half(m, (n + 1023) / 1024, 3, false) > 0);
+  }
+}
+""")
+    exe = tmp_path / "check"
+    subprocess.run(["g++", "-std=c++17", "-O2", "-I", os.path.join(ROOT, "paper_2504_02692_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    faster = [(9216, 3072), (4352, 4096), (6144, 4096), (5120, 5120), (900, 11008), (1024, 11008), (586, 14336), (1024, 14336), (513, 16384), (1024, 28672),
+              (512, 53248), (1100, 9216), (1536, 9216), (1100, 11008), (1536, 11008), (1536, 14336), (1536, 16384)]
+    slower = [(4096, 4096), (4096, 5120), (3584, 5248), (2048, 6144), (4096, 6144), (512, 8192), (1024, 8192), (1536, 8192), (3584, 8192), (4096, 8192), (1024, 9216),
+              (1792, 9216), (820, 10240), (1792, 10240), (512, 11008), (2048, 11008), (3584, 11008), (4096, 11008), (400, 14336), (1664, 14336), (4096, 14336), (384, 16384),
+              (2048, 16384), (2048, 28672)]
+    out = subprocess.run([str(exe), *(str(x) for mn in faster + slower for x in mn)], check=True, capture_output=True, text=True).stdout.split()
+    assert out == ["1"] * len(faster) + ["0"] * len(slower)

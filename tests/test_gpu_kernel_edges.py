@@ -489,8 +489,9 @@ def test_sums_in_parts_round_the_total_once(n, tokens):
         assert call is B.gptaq_accumulate_upper or torch.equal(A, refs[1])
 
 
-# Two row halves: the lines of the rule by rows and super-blocks, with and without vector stores; the last one is just on the other side.
-@pytest.mark.parametrize("m,n,group", [(8193, 2064, 0), (4097, 3201, 0), (3585, 5248, 128), (1300, 6784, 64), (760, 10250, 0), (744, 11264, 128)])
+# Two row halves: the lines of the rule by rows and super-blocks, with and without vector stores; 3585 and 1300 rows are two chains, 744 one.
+@pytest.mark.parametrize("m,n,group", [(8193, 2064, 0), (4097, 3201, 0), (3585, 5248, 128), (1300, 6784, 64), (760, 10250, 0), (744, 11264, 128), (4097, 5248, 128),
+                                       (1025, 8208, 16), (1536, 10250, 0)])
 def test_row_halves_equal_separate_calls(m, n, group):
     """Rows are independent: the result is bit for bit that of calls on 600 rows at a time, which are too few for halves."""
     g = torch.Generator(device="cuda").manual_seed(m)
@@ -542,7 +543,8 @@ def test_few_rows_of_a_wide_matrix(m, n):
 # Two chains (1025 to 4096 rows): the fewest super-blocks and the fewest rows; both sets of the -E / V buffers taken again; each term alone; the columns left
 # where the second chain starts at once; and one row fewer, which is one chain.
 @pytest.mark.parametrize("m,n,group,terms,far_updates", [(1025, 2064, 0, 3, 3), (1024, 3088, 16, 3, 3), (1025, 3088, 16, 3, 5), (2100, 4112, 0, 1, 7), (2100, 4112, 16, 2, 7),
-                                                         (2100, 4112, 16, 3, 7), (2500, 9232, 0, 3, 17), (4096, 5120, 128, 3, 7)])
+                                                         (2100, 4112, 16, 3, 7), (2500, 9232, 0, 3, 17), (4096, 5120, 128, 3, 7), (1537, 9232, 16, 3, 17),
+                                                         (4096, 6160, 16, 3, 11)])
 def test_two_chains_equal_one(m, n, group, terms, far_updates):
     """The result is bit for bit that of calls on 700 rows at a time, which go through as one chain; columns of dead inputs are among them."""
     g = torch.Generator(device="cuda").manual_seed(m)
