@@ -236,7 +236,7 @@ static bool few_blocks(int64_t n, int64_t tokens) {
 //    896      2048  36 / 30 (35 / 32)      6144  76 / 45 (76 / 50)    16384  178 / 87 (179 / 98)   32768  347 / 159 (349 / 180)
 //   1024      1536  31 / 29 (30 / 31)      2048  35 / 29 (34 / 33)     8192  95 / 56 (94 / 75)     32768  384 / 196 (384 / 238)
 //   1152      2048  37 / 34 (36 / 36)      6144  77 / 60 (78 / 65)    16384  184 / 106 (185 / 140) 32768  442 / 239 (436 / 302)
-//   1280      4096  57 / 48 (57 / 54)      8192  97 / 76 (99 / 89)    16384  184 / 134 (183 / 163) 32768  487 / 261 (488 / 353)
+//   1280      4096  57 / 48 (57 / 54)     8192  100 / 80 (102 / 96)  16384  186 / 140 (186 / 172) 32768  487 / 261 (488 / 353)
 //   1408      6144  80 / 66 (83 / 96)     16384  190 / 148 (196 / 202) 20480  240 / 174 (248 / 240)   32768  523 / 327 (519 / 388)
 //   1536     16384  196 / 166 (214 / 230) 28672  468 / 309 (469 / 391) 32768  537 / 341 (536 / 444)
 //   1664      6144  83 / 96 (116 / 105)   12288  153 / 150 (217 / 207) 23040  348 / 292 (379 / 373) 32768  546 / 410 (557 / 530)
@@ -244,26 +244,29 @@ static bool few_blocks(int64_t n, int64_t tokens) {
 // One part stays where the best number makes one of the forms slower or gives little (in this list 1408 columns and 6144 or 16384 tokens, 1536 and
 // 16384, 1664 and 6144 or 12288, 1920); at 1792 columns two would pay from 24576 tokens on (410 / 344 and 439 /
 // 418).  Between two numbers of parts, where one form gains what the other loses (768 columns and 12288 tokens, 6 / 8 parts: 55 / 62 (73 / 64)),
-// the line is where the sum of both does not care.  Errors against 64 bits fall with the length of the sums: dXXT 8.7e-7 to 2.4e-7 at n = 1024.
+// the line is where the sum of both does not care; at 1280 columns and 7488 tokens or more 2 parts serve the full form and 4 the upper one, which is the
+// one in every solve whose columns keep their order: 8192 tokens, inputs from memory, 2 / 4 parts 94 / 90 (103 / 107), 16384 160 / 153 (173 / 182).  Errors
+// against 64 bits fall with the length of the sums: dXXT 8.7e-7 to 2.4e-7 at n = 1024.
 static int split_for(int64_t n, int64_t tokens) {
   if (sparse_remainder(n)) return 1;             // (remainder_loop takes all of K)
   if (few_blocks(n, tokens)) return 1;
   const int64_t t = (n + 127) / 128;
-  if (t <= 4) return 8;                          // (more than 4096 tokens)
+  if (t <= 3) return 8;                          // (more than 4096 tokens)
   static constexpr struct { int tokens, parts; } lines[][4] = {
-      {{1792, 4}, {3072, 6}},                                    // 5 tile rows, up to 640 columns
+      {{4160, 6}, {4736, 8}},                                    // 4 tile rows, up to 512 columns
+      {{1728, 4}, {3072, 6}},                                    // 640
       {{1792, 4}, {8192, 6}, {14080, 8}, {27008, 12}},           // 768
       {{2048, 4}, {6912, 6}},                                    // 896
-      {{2048, 4}, {16384, 8}},                                   // 1024
-      {{2048, 2}, {4096, 4}, {14336, 6}},                        // 1152
-      {{3072, 2}, {16768, 8}},                                   // 1280
+      {{2048, 4}, {16448, 8}},                                   // 1024
+      {{2048, 2}, {4096, 4}, {14400, 6}},                        // 1152
+      {{3072, 2}, {7488, 4}, {16768, 8}},                        // 1280
       {{18112, 4}, {23296, 6}},                                  // 1408
       {{28672, 8}},                                              // 1536
       {{23040, 6}},                                              // 1664
   };
   int parts = 1;
-  if (t - 5 < (int64_t)(sizeof(lines) / sizeof(lines[0])))
-    for (const auto& line : lines[t - 5])
+  if (t - 4 < (int64_t)(sizeof(lines) / sizeof(lines[0])))
+    for (const auto& line : lines[t - 4])
       if (line.parts && tokens >= line.tokens) parts = line.parts;
   return parts;
 }

@@ -62,7 +62,7 @@ def test_a_workspace_for_more_tokens_has_room_for_fewer(lib):
     16384, none where one form of the call is the slower for it."""
     size = lib.gptaq_accumulate_workspace_bytes
     operands = lambda tokens, n: 6 * -(-n // 128) * 128 * tokens
-    for n in [8, 520, *range(576, 2060, 8)]:
+    for n in [8, 400, 512, 520, *range(576, 2060, 8)]:
         sizes = [size(tokens, n) for tokens in range(64, 32769, 64)]
         assert sizes == sorted(sizes), n
         assert all(s >= operands(64 * (i + 1), n) for i, s in enumerate(sizes))
