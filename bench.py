@@ -315,7 +315,7 @@ def main() -> int:
     }
     # HBM-side bytes per launch of the dominant kernel come from two separate rocprofv3 --pmc runs of this same command
     # (FETCH_SIZE, WRITE_SIZE); they are quoted only when the committed summary is for this workload, chunk size and kernel
-    kernel = "gemm_nt_kernel<256, false, false, true>" if sparse else "gemm_nt_kernel<256, false>"
+    kernel = "gemm_nt_kernel<256, false, false, true, false>" if sparse else "gemm_nt_kernel<256, false, false, false, false>"
     traffic, traffic_src = None, None
     tpath = os.path.join(ROOT, "profiles", f"{wl.name}_block_hbm_traffic.json")
     if os.path.exists(tpath):

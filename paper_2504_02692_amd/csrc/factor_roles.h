@@ -22,7 +22,7 @@
 // all, and about 50 beside products.  As launches of their own, the factorisation in one workgroup of eight wavefronts, panel and products
 // on two streams, it was 48 + 16 and 15 to 20 of events; with a launch for each half, the rows and the update between them 16 + 7 + 6 + 16.
 // An f64 MFMA (64 clocks for 1024 products) is no faster than v_fma_f64, but its operands are one register a lane.
-// gptaq_prepare with a copy of H and dXXT in front of it, at n = 512 / 1024 / 4096 / 11008, us: 285 / 466 / 2068 / 19023 -> 183 / 325 / 1625 / 17395.
+// gptaq_prepare with a copy of H and dXXT in front of it, at n = 512 / 1024 / 4096 / 11008, us: 252 / 454 / 1992 / 18222 -> 167 / 313 / 1535 / 16965.
 #pragma once
 #include "common.h"
 #include "gemm_i8s.h"

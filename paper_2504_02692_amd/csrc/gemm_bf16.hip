@@ -802,15 +802,16 @@ __device__ __forceinline__ void gemm_tile(const GemmBatch& b, unsigned char* sme
   else store_tile<BT>(P.C, uniform(P.ldc), uniform(P.M), uniform(P.N), uniform(P.store_mode), m0, n0, acc);
 }
 
-// C[i][i] += sum_k L0[i][k]^2 over all of K, of a problem whose other sums are taken in parts: a workgroup's first wavefront per 32 rows, which takes the
-// 32 x 32 block of its tile's products in the same order as a tile that is not split.  (The diagonal of H decides the order of the columns
-// in act_order, by differences that are of the size of the rounding; the same sums keep the same order.)  A chain of K / 16 MFMAs whose
-// one operand comes straight from memory, 40 loads ahead; it ends before the parts do.
+// C[i][i] += sum_k L0[i][k]^2 over all of K, of a problem whose other sums are taken in parts or by narrow_kernel: a workgroup's first wavefront per 32
+// rows, which takes the 32 x 32 block of its tile's products in the same order as a tile that is not split.  (The diagonal of H decides the order of
+// the columns in act_order, by differences that are of the size of the rounding; the same sums keep the same order.)  A chain of K / 16 MFMAs whose
+// one operand comes straight from memory, 40 loads ahead; it ends before the parts do.  K may be as short as 64: the loads ahead of a short
+// sum stop at its last step.
 __device__ __forceinline__ void diagonal_block(const GemmProblem& P, int block) {
   const int lane = threadIdx.x & 63, rl = lane & 31, row = 32 * block + rl;
   if (32 * block >= P.M) return;
   constexpr int AHEAD = 40;                // k-steps of 16
-  const int steps = P.K / 16;              // (even; K is far more than 16 * AHEAD)
+  const int steps = P.K / 16;              // (even)
   const uint16_t* src = P.term[0].L[0] + (int64_t)row * 32 + 8 * (lane >> 5);
   auto at = [&](int step) { return *reinterpret_cast<const u32x4*>(src + (int64_t)(step >> 1) * P.term[0].ktl + (step & 1) * 16); };
   u32x4 f[AHEAD];
@@ -913,8 +914,8 @@ __global__ __launch_bounds__(256) void add_parts_kernel(GemmBatch b) {
 // C += L R^T for the two problems of a batch whose tiles are few: one workgroup per 32 x 64 block of C, its eight wavefronts take an eighth
 // of K each and add their sums up through LDS, in order, before C is rounded once.  So nothing but C is written, and a CU for every 128-tile
 // becomes one for each of its eight blocks.  Operand fragments come straight from memory, kNarrowAhead k-tiles ahead, 8 KB a k-tile for 16
-// MFMAs.  Bound by what a CU is given: a workgroup alone gets 35 bytes a clock (8 columns and 32768 tokens, 8 MB in 110 us), 200 of them 20
-// each (512 columns and 4096 tokens, full form, 1 MB in 23 us).  H's diagonal is left to diagonal_block.
+// MFMAs.  Bound by what a CU is given, some 20 bytes a clock, and by the latency in front of it: 1 MB a workgroup in 19 us at 8 columns and 4096
+// tokens, two workgroups, and in 22 at 512 columns, full form, 200 of them.  H's diagonal is left to diagonal_block.
 constexpr int kNarrowRows = 32, kNarrowCols = 64, kNarrowAhead = 4;
 template <int NL>
 __device__ __forceinline__ void narrow_loop(const GemmTerm& tm, int row0, int col0, int k0, int k1, f32x4 (&acc)[2][4]) {
