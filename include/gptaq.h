@@ -168,6 +168,10 @@ int gptaq_prepare(float* H, float* dXXT, int64_t n, int64_t ldh, float damp,
  *   ws     : >= gptaq_quantize_workspace_bytes(m, n) bytes, 256-byte aligned: the update operands (-E and V of a
  *            1024-column super-block for all rows, twice; the rows of U and P of EVERY super-block on the columns
  *            after it, as bf16 hi + lo: about 4 n^2 bytes, 0.46 GB at n = 11008, 11 GB at n = 53248).
+ * Streams: part of the updates, or half of the rows, of some matrices run on a helper stream that the
+ * library creates once per device (default priority, kept until the process ends) and ties to `stream` with events on both ends, so to the caller
+ * the call is still one asynchronous operation on `stream`.  Host-side such a call takes a library lock: concurrent calls from several host threads
+ * are serialised while they enqueue.
  * Quantiser: range [min(0,min w), max(0,max w)], scale = (max-min)/(2^bits-1),
  * zero = rint(-min/scale), q = clamp(rint(w/scale)+zero), rint = half-to-even.
  */

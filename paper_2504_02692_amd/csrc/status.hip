@@ -43,8 +43,7 @@ SideStream* side_stream(int nevents) {
   while ((int)ss.events.size() < nevents) {
     hipEvent_t e;
     // The default release.  (hipEventDisableSystemFence leaves it out altogether: that is meant for events that only take times,
-    // and what these order crosses the L2s of eight XCDs.  gptaq_prepare at n = 4096 takes 2.04 ms with it, 2.07 without;
-    // hipEventReleaseToDevice is no faster than the default.)
+    // and what these order crosses the L2s of eight XCDs.  hipEventReleaseToDevice is no faster than the default.)
     if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) return nullptr;
     ss.events.push_back(e);
   }
